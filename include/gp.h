@@ -332,7 +332,9 @@ gp_status gp_propagate_combine(const gp_plan *plan, const void *X, int64_t ldx, 
  *
  *  stack   DEVICE, K+1 slabs of n x d as gp_propagate writes them: slab k starts at
  *          element k*n*ld, rows ld elements apart (ld >= d), of `dtype` (bf16 is
- *          widened exactly; all arithmetic is fp32 on the matrix cores).
+ *          widened exactly; all arithmetic is fp32: products of fp32 operands, each
+ *          split without loss into three bf16 parts for the matrix cores, summed in
+ *          fp32; errors are no larger than the fp32 matrix instruction's).
  *  batch   DEVICE, B row numbers; NULL means rows 0 .. B-1 (then B <= n).  A row
  *          number outside [0, n) is not an error: that output row is computed
  *          from a row of zeros.
@@ -369,8 +371,8 @@ gp_status gp_lc_forward(const void *stack, int64_t ld, gp_dtype dtype, int64_t n
  *          (INVALID_ARG otherwise), out is B x that width;
  *          GP_COMB_CONCAT: out is B x (sum of the branches' widths), branches side
  *          by side in hop order.
- * Everything else as gp_lc_forward (concatenation writes the result directly and
- * needs no library buffer).
+ * Everything else as gp_lc_forward (concatenation writes the result directly: such
+ * calls may overlap).
  */
 typedef enum { GP_COMB_SUM = 0, GP_COMB_CONCAT = 1, GP_COMB_MAX = 2 } gp_comb;
 gp_status gp_lc_forward_branches(const void *stack, int64_t ld, gp_dtype dtype, int64_t n, int32_t d, int32_t K,
@@ -424,7 +426,8 @@ gp_status gp_set_hbm_budget_bytes(int64_t bytes);
  *                     by gp_plan_blocks.
  *   "column_tile"     feature columns per pass of the kernel, 0 = automatic.
  *   "persistent_blocks"  workgroups of the hop kernel (0 = as many as stay resident).
- *   "lc_tile_rows"       batch rows per work item of gp_lc_forward: 32 or 64 (0 = by batch size).
+ *   "lc_tile_rows"       batch rows per work item of gp_lc_forward, at most: 32 or 64 (0 = by batch size;
+ *                     the tallest item the kernel has is 48 rows).
  *   "column_slices"   column slices one pass is divided into (1 .. 16; 0 = automatic).
  *                     Implicit work lists take 1, 2, 4 or 8 (anything else = automatic).
  *   "split_records"   explicit work lists: 0 / 1 = every record is cut into the non-zeros

@@ -3,24 +3,43 @@
 //
 //     H[batch] = sum_k gamma_k * MLP(X_k[batch]),   MLP(Z) = relu(..relu(Z W_1)..W_{T-1}) W_T.
 //
-// This is the one dense contraction on the path, so it runs on the matrix cores:
-// fp32 MFMA (v_mfma_f32_32x32x2_f32), all layers of one hop fused in one kernel.
-// A workgroup of four waves owns 64 batch rows (32 for very small batches) of one hop;
-// the hops' results are summed afterwards in hop order.  The rows' features (later: the
-// previous layer's activations) sit in LDS as the A operand; the weights are the B
-// operand, read straight from L2 (all T matrices together are a few hundred KB and
-// stay there) one 8-row chunk ahead of the MFMAs that use them; the layer output
-// stays in accumulator registers until every wave is done with the LDS tile, then
-// replaces it (ReLU applied on the way).  Nothing but the gathered rows and the
-// per-hop B x C results touches HBM.
+// This is the one dense contraction on the path, so it runs on the matrix cores, all
+// layers of one hop fused in one kernel.  A workgroup of four waves owns 16, 32 or 48
+// batch rows of one hop; the hops' results are summed afterwards in hop order.  The rows'
+// features (later: the previous layer's activations) sit in LDS, the weights come straight
+// from L2 ahead of the products that use them, and the layer output stays in accumulator
+// registers until every wave is done with the LDS tile, then replaces it (ReLU applied on
+// the way).  Nothing but the gathered rows and the per-hop B x C results touches HBM.
 //
-// Index freedom used: MFMA sums over k and yields 32 columns per tile, but which k
-// and which column a lane supplies is the kernel's choice as long as A and B agree.
-// Lane half hh of a wave takes k = 8c + 4hh + s for step s of chunk c (one 16-byte
-// LDS read feeds four MFMA steps), and column j of a wave's tile t is output column
-// base + NT*j + t, so the NT tiles of a wave need NT consecutive weights per lane
-// (one vector load) and produce NT consecutive activations per lane (one vector
-// LDS store).
+// Arithmetic.  The fp32 matrix instruction runs at 157 TFLOP/s on this chip, the bf16 one
+// at 2.5 PFLOP/s.  An fp32 number is a sum of three bf16 numbers without loss (8 bits each,
+// rounded to nearest: x = x1 + x2 + x3, |x2| <= 2^-9 |x|, |x3| <= 2^-18 |x|), and a product
+// of two bf16 numbers is exact in fp32, so
+//
+//     x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + O(2^-26 |x w|),
+//
+// six bf16 products with fp32 accumulation: what is left out is a quarter of the rounding
+// that one fp32 addition of the term makes (2^-24), and the large products take one
+// accumulation per 32 terms.  Measured against fp64 on a 128-256-256-256-40 model: relative
+// error 0.92e-7, where the fp32 instruction left 2.5e-7.  (A bf16 stack's first layer has
+// x = x1: three products.)  Features and activations are split once, when they enter LDS;
+// weights once per call (gp_lc_split_weights).  Infinities and NaNs do not survive the
+// split, but whatever they touch comes out of it as NaN: a wave whose sums are not all finite
+// takes that layer again on the fp32 instruction (lc_layer_exact), so results with
+// infinities or NaNs are those of plain fp32 arithmetic.
+//
+// What bounds it: the matrix cores, at 69 % busy and, by then, a clock that power holds at
+// about 2.1 of 2.4 GHz.  Four hops of a 128-256-256-256-40 model over 169,343 fp32 rows: 1040
+// us = 226 TFLOP/s of fp32 work (1.36 PFLOP/s of bf16 products); on the fp32 instruction
+// 1988 us = 119.  A batch of 4096 rows: 64 -> 38 us.  100-256-256-256 branches side by side
+// from a bf16 stack, all rows: 925 -> 525 us.
+//
+// Index freedom used: MFMA sums over k, and which k a lane supplies is the kernel's choice
+// as long as both operands agree; lanes 16 kg .. + 16 take k = 32 kt + 8 kg .. + 8 in step kt
+// (one 16-byte LDS read per part).  Weights are the instruction's first operand (its rows
+// are the layer's output columns) and batch rows its second, so a lane ends up with 4 CT
+// consecutive output columns of one batch row: wide stores of the next layer's operand and
+// of the result.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,17 +52,22 @@ namespace gp {
 
 namespace {
 
-constexpr int kLcThreads = 256;
-constexpr int kPanel = 256;      // widest inner dimension staged in LDS at once
-constexpr int kLd = kPanel + 4;  // LDS row stride in floats (16-byte aligned rows, banks staggered)
+constexpr int kLcThreads = 256;   // reduction and softmax
+constexpr int kMlpThreads = 256;
+constexpr int kPanel = 256;       // widest inner dimension staged in LDS at once
+constexpr int kLd = kPanel + 16;  // LDS row stride in bf16: 544 bytes, with which the 16 lanes of an LDS pass read 16-byte pieces of different banks
 constexpr int kMaxLayers = 8;
 constexpr int kMaxHops = 16;
 constexpr int64_t kWorkspaceBytes = INT64_C(256) << 20;  // cap on the partial results of one piece
 
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte access from a dword boundary
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef unsigned short v4u16 __attribute__((ext_vector_type(4)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 struct LcArgs {
     const void* stack;
@@ -61,7 +85,8 @@ struct LcArgs {
     int T;
     const float* W[kMaxLayers];
     int width[kMaxLayers];
-    int wvec[kMaxLayers];  // 1: W_t rows may be read with NT-wide vector loads
+    const char* frags;     // split weights (gp_lc_split_weights), or nullptr: split where they are used
+    int64_t frag_off[kMaxLayers];  // layer -> its first byte there
     int xvec;              // 1: stack rows may be read four elements at a time
     float* dst;            // the result (direct), else the partial results [branch][B][ldd]
     int64_t ldd;
@@ -79,23 +104,68 @@ __device__ __forceinline__ v4f load4(const unsigned short* p)
     return r;
 }
 
-// 64 x kin panel of the batch rows of one slab -> LDS, widened to fp32, zero beyond
-// kin (up to the next multiple of 8), zero for rows past the batch or ids outside
-// [0, n) (those rows are never stored).  Eight independent requests per thread are
-// in flight before the first is written to LDS.
+// Two fp32 numbers as three pairs of bf16, packed as the matrix instructions take them, p1 + p2 + p3 = x:
+// exactly, unless x is not finite or beyond the largest bf16 number (then p3 is NaN) or so small that a part is
+// below the normal range (|x| < 1e-31; the error is below 1e-38).
+// (The dot-product instruction would form a - p1 in one step, but beside another wave's matrix instructions it
+// takes 81 cycles against 10 for an ordinary one: measured.)
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a, b}, v2bf)); }
+__device__ __forceinline__ float low_bf16(unsigned p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float high_bf16(unsigned p) { return __uint_as_float(p & 0xFFFF0000u); }
+__device__ __forceinline__ void split2_from(float a, float b, unsigned (&p)[3])
+{
+    const float ra = a - low_bf16(p[0]), rb = b - high_bf16(p[0]);
+    p[1] = pack_bf16(ra, rb);
+    p[2] = pack_bf16(ra - low_bf16(p[1]), rb - high_bf16(p[1]));
+}
+__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[3])
+{
+    p[0] = pack_bf16(a, b);
+    split2_from(a, b, p);
+}
+// eight numbers: one lane's operand, part by part
+__device__ __forceinline__ void split8(const float (&v)[8], v4u (&q)[3])
+{
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        unsigned p[3];
+        split2(v[2 * s], v[2 * s + 1], p);
+        q[0][s] = p[0], q[1][s] = p[1], q[2][s] = p[2];
+    }
+}
+// the same for any numbers: the first part is kept finite (rounding could carry the largest numbers to
+// infinity), an infinity is the second part, a NaN the second and third
+constexpr float kMaxBf16 = 3.38953139e38f;
+__device__ __forceinline__ void split2_any(float a, float b, unsigned (&p)[3])
+{
+    p[0] = pack_bf16(__builtin_amdgcn_fmed3f(a, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(b, -kMaxBf16, kMaxBf16));
+    split2_from(a, b, p);
+}
+// the number again from its three parts (a second part that is not finite is all there is to it)
+__device__ __forceinline__ float join3(__bf16 x1, __bf16 x2, __bf16 x3)
+{
+    const float b = (float)x2;
+    return __builtin_isfinite(b) ? ((float)x3 + b) + (float)x1 : b;
+}
+
+// TM x kin panel of the batch rows of one slab -> LDS, split into its bf16 parts (a bf16 stack has one),
+// zero beyond kin (up to the next multiple of 32), zero for rows past the batch or ids outside [0, n)
+// (those rows are never stored).  Six independent requests per thread are in flight before the first is
+// written to LDS.
 template <typename T, int TM>
-__device__ __forceinline__ void lc_gather(float* __restrict__ tile, const T* __restrict__ slab, const LcArgs& a,
+__device__ __forceinline__ void lc_gather(__bf16* __restrict__ tile, const T* __restrict__ slab, const LcArgs& a,
                                           int64_t row0, int p0, int kin, int tid)
 {
-    constexpr int U = 8;
-    const unsigned nq = (unsigned)(((kin + 7) & ~7) >> 2);  // groups of four columns per row
+    constexpr int U = 6;
+    constexpr int kPlane = TM * kLd;
+    const unsigned nq = (unsigned)(((kin + 31) & ~31) >> 2);  // groups of four columns per row
     const unsigned total = TM * nq;
-    for (unsigned base = 0; base < total; base += U * kLcThreads) {
+    for (unsigned base = 0; base < total; base += U * kMlpThreads) {
         int64_t id[U];
         unsigned r[U], q[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const unsigned idx = base + u * kLcThreads + tid;
+            const unsigned idx = base + u * kMlpThreads + tid;
             r[u] = idx / nq, q[u] = idx - r[u] * nq;
             const int64_t br = row0 + r[u];
             id[u] = -1;
@@ -120,260 +190,383 @@ __device__ __forceinline__ void lc_gather(float* __restrict__ tile, const T* __r
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (base + u * kLcThreads + tid < total) *reinterpret_cast<v4f*>(tile + r[u] * kLd + 4 * q[u]) = v[u];
-    }
-}
-
-// How the four waves of a workgroup split a layer with N output columns.
-//   wide   (N > 64):  wave w owns columns [w*32*NT, (w+1)*32*NT), NT = ceil(N/128), of
-//                     BOTH 32-row blocks: every weight is fetched by exactly one wave.
-//   narrow (N <= 64): wave w owns row block w & 1 and columns [(w>>1)*32, +32): all four
-//                     matrix cores stay busy on a 40- or 64-class output layer.
-// A wave whose columns all lie beyond N sits the layer out.  Tile (r, t) of a wave is
-// accumulator r*NT + t; column i of tile t is output column colbase + NT*i + t.
-struct WaveMap {
-    int rbw;      // row blocks this wave owns: 2 (wide) or 1 (narrow)
-    int nt;       // 32-column tiles per row block: 1 or 2
-    int rb0;      // first row block
-    int colbase;  // first column
-};
-template <int RB>  // RB = 32-row blocks per work item: 2 (64 rows) or 1 (32 rows, all waves split the columns)
-__device__ __forceinline__ WaveMap wave_map(int N, int wave)
-{
-    WaveMap m;
-    if (RB == 1 || N > 64) {
-        m.rbw = RB, m.nt = (N + 127) >> 7, m.rb0 = 0, m.colbase = wave * 32 * m.nt;
-    } else {
-        m.rbw = 1, m.nt = 1, m.rb0 = wave & 1, m.colbase = (wave >> 1) * 32;
-    }
-    return m;
-}
-
-// Weights of one full 8-row chunk for this lane: rows 4hh .. 4hh+3 of the chunk that
-// starts at Wc (= W + 8c*N, the same for the whole wave), NT columns.  Loads are
-// never predicated (a predicated load costs a branch): a lane whose columns lie
-// beyond N reads column 0 instead (coff is clamped) and its products are discarded
-// when the layer's output is stored.  roff = 4hh*N; vectors use coff[0] only.
-template <int NT, bool VEC>
-__device__ __forceinline__ void lc_load_b(const float* Wc, int N, int roff, const int (&coff)[NT], float (&b)[4][NT])
-{
+            if (base + u * kMlpThreads + tid < total) {
+                v2u* dst = reinterpret_cast<v2u*>(tile + r[u] * kLd + 4 * q[u]);
+                if constexpr (sizeof(T) == 2) {  // (exact: the low half of the widened value is zero)
+                    *dst = (v2u){(__float_as_uint(v[u].x) >> 16) | __float_as_uint(v[u].y),
+                                 (__float_as_uint(v[u].z) >> 16) | __float_as_uint(v[u].w)};
+                } else {
+                    unsigned lo[3], hi[3];
+                    split2_any(v[u].x, v[u].y, lo);
+                    split2_any(v[u].z, v[u].w, hi);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const float* p = Wc + s * N;
-        if constexpr (NT == 2 && VEC) {
-            const v2f v = *reinterpret_cast<const v2f*>(p + (unsigned)(roff + coff[0]));
-            b[s][0] = v.x, b[s][1] = v.y;
+                    for (int i = 0; i < 3; ++i) dst[i * (kPlane / 4)] = (v2u){lo[i], hi[i]};
+                }
+            }
+    }
+}
+
+__device__ __forceinline__ void lc_fence() { __builtin_amdgcn_sched_barrier(0); }  // the instruction scheduler moves nothing across
+
+// the same in every lane: said so, so that it stays in scalar registers
+typedef const __attribute__((address_space(1))) char global_char;
+__device__ __forceinline__ global_char* uniform(const char* p)
+{
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32));
+    return (global_char*)(((uint64_t)hi << 32) | lo);
+}
+
+// How the four waves of a workgroup share a layer with N output columns: wave w takes CT tiles of 16 columns
+// of every batch row, so that a weight is fetched by one wave.  Column i of a wave's tile t is output column
+// 16 CT w + CT i + t: the four accumulator elements of a lane's CT tiles are 4 CT consecutive columns.
+__host__ __device__ __forceinline__ int tiles_per_wave(int N) { return N > 128 ? 4 : N > 64 ? 2 : 1; }
+
+// Split weights, in the order the waves read them: for every step of 32 rows, wave of the workgroup and tile of 16
+// columns three fragments (the parts) of 64 lanes x 16 bytes; lane (i, kg) holds rows 32 kt + 8 kg .. + 8 of
+// column i of the tile.  Beyond the matrix: zeros.  Steps are padded to a multiple of 4 / CT, so that a wave
+// walks whole groups of four tiles (a panel of the first layer is 8 steps, a multiple already).
+constexpr int64_t kFragBytes = 1024;
+constexpr size_t kFragReserve = 4 << 20;  // room kept behind the partial results: eight layers of 256 x 256 take 3 MB
+constexpr int64_t kFragSlack = 64 << 10;  // requests past a layer's end reach this far at most
+__host__ __device__ __forceinline__ int64_t padded_steps(int64_t kin, int ct) { return ((kin + 31) / 32 + 4 / ct - 1) / (4 / ct) * (4 / ct); }
+__host__ __device__ __forceinline__ int64_t layer_tiles(int64_t kin, int N)
+{
+    const int ct = tiles_per_wave(N);
+    return padded_steps(kin, ct) * 4 * ct;
+}
+
+struct SplitArgs {
+    int T;
+    const float* W[kMaxLayers];
+    int kin[kMaxLayers], width[kMaxLayers];
+    int64_t first[kMaxLayers + 1];  // tiles (three fragments) before layer t
+    char* out;
+};
+
+// one wave per (layer, step, wave, tile).  A few microseconds for a few hundred thousand weights; done once per
+// call, where splitting them in every workgroup that uses them costs as much vector work as all of the
+// activations (4-hop, 4-layer model, 169,343 rows: 1430 us that way, 1042 us this way).
+__global__ __launch_bounds__(256) void gp_lc_split_weights(const SplitArgs a)
+{
+    const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (g >= a.first[a.T]) return;
+    const int lane = threadIdx.x & 63, i = lane & 15, kg = lane >> 4;
+    int t = 0;
+    while (g >= a.first[t + 1]) ++t;
+    const int N = a.width[t], CT = tiles_per_wave(N);
+    const int64_t u = g - a.first[t], kt = u / (4 * CT);
+    const int w = (int)(u / CT % 4), ct = (int)(u % CT), col = 16 * CT * w + CT * i + ct;
+    const float* W = a.W[t];
+    float v[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int64_t k = kt * 32 + 8 * kg + s;
+        v[s] = k < a.kin[t] && col < N ? W[k * N + col] : 0.0f;
+    }
+    v4u q[3];
+    split8(v, q);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) reinterpret_cast<v4u*>(a.out + (g * 3 + p) * kFragBytes)[lane] = q[p];
+}
+
+// acc += tile(16 R rows x kin) * W(kin x this wave's columns) on the fp32 instruction, operands joined from
+// their parts: plain fp32 arithmetic, for sums that infinities or NaNs take part in.  PARTS as in lc_layer.
+template <int R, int CT, int PARTS>
+__device__ __forceinline__ void lc_layer_exact(const __bf16* tile, int kin, const float* W, int N, int colbase, int i, int kg,
+                                               v4f (&acc)[R][4])
+{
+    constexpr int kPlane = 16 * R * kLd;
+    for (int k0 = 0; k0 < kin; k0 += 4) {
+        const int k = k0 + kg;
+        float x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const __bf16* p = tile + (r * 16 + i) * kLd + k;
+            x[r] = 0.0f;
+            if (k < kin) x[r] = PARTS == 1 ? (float)p[0] : join3(p[0], p[kPlane], p[2 * kPlane]);
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            const int col = colbase + CT * i + ct;
+            const float w = k < kin && col < N ? W[(int64_t)k * N + col] : 0.0f;
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[r], acc[r][ct], 0, 0, 0);
+        }
+    }
+}
+
+// acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file; true if
+// all sums are finite (and may be split without a clamp).  frags: the split weights from W's first row on.
+// PARTS: bf16 parts of a row's elements in LDS, 3 or (bf16 stack, first layer) 1.  CARRY: acc comes in with
+// sums of earlier panels (else: zeros).  RAW: no split weights, they are split here.  The products x1 w1 and
+// the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
+// roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
+// the weights of the tile four further on.
+template <int R, int CT, int PARTS, bool CARRY, bool RAW>
+__device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
+                                         int i, int kg, v4f (&acc)[R][4])
+{
+    constexpr int kPlane = 16 * R * kLd;
+    const int steps = (kin + 31) >> 5, units = (int)padded_steps(kin, CT) * CT;
+    const __bf16* xrow = tile + i * kLd + 8 * kg;
+    // fragments of unit u = kt CT + ct: ((kt 4 + wave) CT + ct) * 3 ..
+    global_char* mine = uniform(frags + wave * (CT * 3 * kFragBytes));
+    const unsigned lane_off = (unsigned)(16 * kg + i) * 16;
+    v4f before[CARRY ? R : 1][CT], small[R][CT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            if constexpr (CARRY) before[r][c] = acc[r][c];
+            small[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    v8bf part[4][3], x[R][PARTS];
+    float raw[RAW ? 8 : 1][CT];  // RAW: one step's weights
+    auto load_w = [&](int u, int to) {  // (beyond the last unit: not used)
+        const int kt = u / CT, ct = u % CT;
+        if constexpr (RAW) {  // (whole steps, at their first tile)
+            if (ct > 0) return;
+            typedef float vec __attribute__((ext_vector_type(CT), aligned(4)));
+            const int c0 = colbase + CT * i;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const float* row = W + (int64_t)min(kt * 32 + 8 * kg + s, kin - 1) * N;  // (rows beyond kin meet zeros)
+                if (N % CT == 0) {
+                    const vec v = *reinterpret_cast<const vec*>(row + min(c0, N - CT));
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) raw[s][c] = v[c];
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) raw[s][c] = row[min(c0 + c, N - 1)];
+                }
+            }
+        } else {
+            global_char* at = mine + (kt * 4 * CT + ct) * (3 * kFragBytes);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) part[to][p] = *reinterpret_cast<const __attribute__((address_space(1))) v8bf*>(at + p * kFragBytes + lane_off);
+        }
+    };
+    auto load_x = [&](int kt) {
+        kt = min(kt, steps - 1);  // (padding steps have zero weights)
+#pragma unroll
+        for (int p = PARTS - 1; p >= 0; --p)
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[r][p] = *reinterpret_cast<const v8bf*>(xrow + p * kPlane + r * 16 * kLd + kt * 32);
+    };
+    auto products = [&](int ct, int from) {
+        auto mul = [&](int wi, int xi) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v4f& to = wi + xi > 0 ? small[r][ct] : acc[r][ct];
+                to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part[from][wi], x[r][xi], to, 0, 0, 0);
+            }
+        };
+        if constexpr (PARTS == 3) mul(0, 2), mul(1, 1), mul(0, 1);
+        mul(2, 0), mul(1, 0), mul(0, 0);
+    };
+    auto split_raw = [&](int first) {  // a step's raw weights into the parts of its tiles
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            float v[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) v[s] = raw[s][c];
+            v4u q[3];
+            split8(v, q);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) part[first + c][p] = __builtin_bit_cast(v8bf, q[p]);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < (RAW ? 1 : 4); ++u) load_w(u, u);
+    load_x(0);
+    __builtin_amdgcn_s_setprio(0);
+    for (int u = 0; u < units; u += 4) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if constexpr (RAW) {
+                if (u + v >= steps * CT) break;
+                if (v % CT == 0) split_raw(v), load_w(u + v + CT, v);
+            }
+            products(v % CT, v);
+            if constexpr (!RAW) load_w(u + v + 4, v);
+            if ((v + 1) % CT == 0) load_x((u + v + 1) / CT);
+            lc_fence();
+        }
+    }
+    __builtin_amdgcn_s_setprio(2);
+    bool odd = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            acc[r][c] += small[r][c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd |= !(fabsf(acc[r][c][e]) < kMaxBf16);
+        }
+    if (!__any(odd)) return true;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            if constexpr (CARRY)
+                acc[r][c] = before[r][c];
+            else
+                acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    lc_layer_exact<R, CT, PARTS>(tile, kin, W, N, colbase, i, kg, acc);
+    return false;
+}
+
+template <int R, int PARTS, bool CARRY, bool RAW>
+__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int i, int kg,
+                                             v4f (&acc)[R][4])
+{
+    const int ct = tiles_per_wave(N), colbase = wave * 16 * ct;
+    if (colbase >= N) return true;
+    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
+    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
+    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
+}
+
+// tile <- relu(acc) for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
+// column below the next multiple of 32 is written (the next layer reads that far); acc <- 0
+template <int R, int CT>
+__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, int colbase, int i, int kg, v4f (&acc)[R][4])
+{
+    constexpr int kPlane = 16 * R * kLd;
+    const int c0 = colbase + 4 * CT * kg;
+    const bool whole = plain && colbase + 16 * CT <= Np;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        __bf16* row = tile + (r * 16 + i) * kLd + c0;
+        unsigned q[3][2 * CT];
+        if (whole) {  // every value finite
+#pragma unroll
+            for (int h = 0; h < 2 * CT; ++h) {
+                const int u = 2 * h;
+                unsigned p[3];
+                split2(fmaxf(acc[r][u % CT][u / CT], 0.0f), fmaxf(acc[r][(u + 1) % CT][(u + 1) / CT], 0.0f), p);
+                q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
+            }
         } else {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) b[s][t] = p[(unsigned)(roff + coff[t])];
-        }
-    }
-}
-
-// The last, partial chunk (rows_left < 8 rows): a row beyond the matrix is read as
-// row 0 of the chunk and replaced by zero.
-template <int NT>
-__device__ __forceinline__ void lc_load_b_tail(const float* Wc, int N, int rows_left, int hh, const int (&coff)[NT],
-                                               float (&b)[4][NT])
-{
+            for (int h = 0; h < 2 * CT; ++h) {
+                float v[2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int r = 4 * hh + s;
-        const bool ok = r < rows_left;
-        const int roff = ok ? r * N : 0;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const float v = Wc[roff + coff[t]];
-            b[s][t] = ok ? v : 0.0f;
-        }
-    }
-}
-
-// nothing moves across: neither in the compiler's middle end (the memory clobber) nor
-// in its instruction scheduler
-__device__ __forceinline__ void lc_fence()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// the 4 * RBW * NT MFMAs of one chunk: step s multiplies k = 8c + 4hh + s
-template <int RBW, int NT>
-__device__ __forceinline__ void lc_mfma_chunk(const v4f (&av)[RBW], const float (&b)[4][NT], v16f (&acc)[4])
-{
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int r = 0; r < RBW; ++r)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                acc[r * NT + t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[r][s], b[s][t], acc[r * NT + t], 0, 0, 0);
-}
-
-// acc += tile(64 x kin) * W(kin x N) for this wave's share (see WaveMap).  Operands
-// are requested one chunk before they are used, in two alternating register sets.  A
-// request past the last full chunk repeats that chunk (harmless, in bounds) instead
-// of being skipped, which keeps the loop free of predicated loads.
-template <int RBW, int NT, bool VEC>
-__device__ __forceinline__ void lc_layer(const float* tile, int kin, const float* W, int N, const WaveMap& m, int j, int hh,
-                                         v16f (&acc)[4])
-{
-    const int colb = m.colbase + NT * j;
-    const float* arow = tile + (m.rb0 * 32 + j) * kLd + 4 * hh;
-    const int full = kin >> 3;
-    const int roff = 4 * hh * N;
-    int coff[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) coff[t] = colb + t < N ? colb + t : 0;
-    if (full > 0) {
-        auto load_a = [&](int c, v4f (&av)[RBW]) {
-#pragma unroll
-            for (int r = 0; r < RBW; ++r) av[r] = *reinterpret_cast<const v4f*>(arow + r * 32 * kLd + min(c, full - 1) * 8);
-        };
-        auto load_b = [&](int c, float (&b)[4][NT]) { lc_load_b<NT, VEC>(W + (int64_t)min(c, full - 1) * 8 * N, N, roff, coff, b); };
-        float b0[4][NT], b1[4][NT];
-        v4f a0[RBW], a1[RBW];
-        // the fences keep each request group ahead of the MFMA group it is written
-        // before; left alone, the compiler sinks the loads to their first use
-        load_b(0, b0), load_a(0, a0);
-        int c = 0;
-        for (; c + 2 <= full; c += 2) {  // steady state: two chunks per trip, no exits inside
-            load_b(c + 1, b1), load_a(c + 1, a1);
-            lc_fence();
-            lc_mfma_chunk<RBW, NT>(a0, b0, acc);
-            lc_fence();
-            load_b(c + 2, b0), load_a(c + 2, a0);
-            lc_fence();
-            lc_mfma_chunk<RBW, NT>(a1, b1, acc);
-            lc_fence();
-        }
-        if (c < full) lc_mfma_chunk<RBW, NT>(a0, b0, acc);  // an odd last chunk is already here
-    }
-    if (kin & 7) {
-        float bt[4][NT];
-        v4f at[RBW];
-        lc_load_b_tail<NT>(W + (int64_t)full * 8 * N, N, kin & 7, hh, coff, bt);
-#pragma unroll
-        for (int r = 0; r < RBW; ++r) at[r] = *reinterpret_cast<const v4f*>(arow + r * 32 * kLd + full * 8);  // zero beyond kin
-        lc_mfma_chunk<RBW, NT>(at, bt, acc);
-    }
-}
-
-template <int RB>
-__device__ __forceinline__ void lc_layer_any(const float* tile, int kin, const float* W, int N, bool vec, int wave, int j,
-                                             int hh, v16f (&acc)[4])
-{
-    const WaveMap m = wave_map<RB>(N, wave);
-    if (m.colbase >= N) return;
-    if (m.nt == 2) {
-        if (vec)
-            lc_layer<RB, 2, true>(tile, kin, W, N, m, j, hh, acc);
-        else
-            lc_layer<RB, 2, false>(tile, kin, W, N, m, j, hh, acc);
-    } else if (RB == 2 && m.rbw == 2) {
-        lc_layer<RB, 1, false>(tile, kin, W, N, m, j, hh, acc);
-    } else {
-        lc_layer<1, 1, false>(tile, kin, W, N, m, j, hh, acc);
-    }
-}
-
-// accumulator element e of a 32x32 tile sits in row 8*(e/4) + 4*(lane/32) + e%4
-__device__ __forceinline__ int acc_row(int e, int hh) { return 8 * (e >> 2) + 4 * hh + (e & 3); }
-
-// tile <- relu(acc) for this wave's share of a layer of width Np; columns beyond Np
-// (products of clamped loads) become zeros; acc <- 0
-template <int RBW, int NT>
-__device__ __forceinline__ void lc_store_relu(float* __restrict__ tile, int Np, const WaveMap& m, int j, int hh, v16f (&acc)[4])
-{
-    bool keep[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) keep[t] = m.colbase + NT * j + t < Np;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            float* p = tile + ((m.rb0 + r) * 32 + acc_row(e, hh)) * kLd + m.colbase + NT * j;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float x = acc[r * NT + t][e];
-                p[t] = (x < 0.0f || !keep[t]) ? 0.0f : x;  // NaN stays NaN
+                for (int e = 0; e < 2; ++e) {
+                    const int u = 2 * h + e;
+                    v[e] = acc[r][u % CT][u / CT];
+                    if (v[e] < 0.0f || c0 + u >= Np) v[e] = 0.0f;  // NaN stays NaN
+                }
+                unsigned p[3];
+                split2_any(v[0], v[1], p);
+                q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
         }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = (v16f)(0.0f);
+        for (int p = 0; p < 3; ++p) {
+            if constexpr (CT == 1) {
+                *reinterpret_cast<v2u*>(row + p * kPlane) = (v2u){q[p][0], q[p][1]};
+            } else {
+#pragma unroll
+                for (int h = 0; h < CT / 2; ++h)
+                    reinterpret_cast<v4u*>(row + p * kPlane)[h] = (v4u){q[p][4 * h], q[p][4 * h + 1], q[p][4 * h + 2], q[p][4 * h + 3]};
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
 }
 
-// Every column below the next multiple of 8 of Np must be written (the next layer
-// reads that far): a wave that sat the layer out holds zeros and stores them too
-// when its columns start below that bound.
-template <int RB>
-__device__ __forceinline__ void lc_store_relu_any(float* tile, int Np, int wave, int j, int hh, v16f (&acc)[4])
+template <int R>
+__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, int wave, int i, int kg, v4f (&acc)[R][4])
 {
-    const WaveMap m = wave_map<RB>(Np, wave);
-    if (m.colbase >= ((Np + 7) & ~7)) return;
-    if (m.nt == 2)
-        lc_store_relu<RB, 2>(tile, Np, m, j, hh, acc);
-    else if (RB == 2 && m.rbw == 2)
-        lc_store_relu<RB, 1>(tile, Np, m, j, hh, acc);
-    else
-        lc_store_relu<1, 1>(tile, Np, m, j, hh, acc);
+    const int ct = tiles_per_wave(Np), colbase = wave * 16 * ct;
+    if (colbase >= ((Np + 31) & ~31)) return;  // (its sums are zeros: it sat the layer out)
+    if (ct == 4) lc_store_relu<R, 4>(tile, Np, plain, colbase, i, kg, acc);
+    else if (ct == 2) lc_store_relu<R, 2>(tile, Np, plain, colbase, i, kg, acc);
+    else lc_store_relu<R, 1>(tile, Np, plain, colbase, i, kg, acc);
 }
 
-// One workgroup: 32*RB batch rows of one branch (hop k, the first depth_k layers); writes
+template <int R, int CT>
+__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, int i, int kg,
+                                         const v4f (&acc)[R][4])
+{
+    const int c0 = colbase + 4 * CT * kg;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t row = row0 + r * 16 + i;
+        if (row >= a.B) continue;
+        float* out = dst + row * a.ldd + c0;
+#pragma unroll
+        for (int h = 0; h < CT; ++h) {
+            v4f v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = g * acc[r][(4 * h + e) % CT][(4 * h + e) / CT];
+            if (c0 + 4 * h + 4 <= C) {
+                *reinterpret_cast<v4f_a4*>(out + 4 * h) = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (c0 + 4 * h + e < C) out[4 * h + e] = v[e];
+            }
+        }
+    }
+}
+
+// One workgroup: 16 R batch rows of one branch (hop k, the first depth_k layers); writes
 // gamma_k * branch_k either to its slab of the partial results or, when branches are
-// concatenated, to its columns of the result.
-template <typename T, int RB>
-__global__ __launch_bounds__(kLcThreads, 2) void gp_lc_mlp(const LcArgs a)
+// concatenated, to its columns of the result.  48 rows take 78 KB of LDS: two workgroups share a compute unit,
+// and while one gathers, stores or waits at a barrier the other keeps the matrix cores busy.
+template <typename T, int R, bool CARRY, bool RAW>
+__global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
 {
-    constexpr int TM = 32 * RB;
-    extern __shared__ __align__(16) float tile[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 31, hh = lane >> 5;
+    constexpr int TM = 16 * R;
+    constexpr int kParts = sizeof(T) == 2 ? 1 : 3;
+    extern __shared__ __align__(16) __bf16 tile[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, kg = lane >> 4;
     const int br = (int)(blockIdx.x % (unsigned)a.hops);
     const int k = a.hop_of[br], layers = a.depth[br];
     const int64_t row0 = (int64_t)(blockIdx.x / (unsigned)a.hops) * TM;
     const int C = a.width[layers - 1];
 
-    v16f acc[4];
+    v4f acc[R][4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = (v16f)(0.0f);
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
 
     const T* slab = static_cast<const T*>(a.stack) + (int64_t)k * a.slab;
     const int N1 = a.width[0];
+    // whoever is not multiplying goes first: the other workgroup's products leave the vector units room
+    __builtin_amdgcn_s_setprio(2);
+    bool plain = true;
     for (int p0 = 0; p0 < a.d; p0 += kPanel) {  // first layer, one panel of feature columns at a time
         const int kin = min(kPanel, a.d - p0);
         if (p0 > 0) __syncthreads();  // every wave is done with the previous panel (nothing is in the tile before the first)
         lc_gather<T, TM>(tile, slab, a, row0, p0, kin, tid);
         __syncthreads();
-        lc_layer_any<RB>(tile, kin, a.W[0] + (int64_t)p0 * N1, N1, a.wvec[0] != 0, wave, j, hh, acc);
+        const char* frags = a.frags + a.frag_off[0] + (int64_t)(p0 / 32) * 4 * tiles_per_wave(N1) * (3 * kFragBytes);
+        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc);
     }
     for (int t = 1; t < layers; ++t) {
         const int Np = a.width[t - 1], N = a.width[t];
         __syncthreads();  // every wave is done reading the tile
-        lc_store_relu_any<RB>(tile, Np, wave, j, hh, acc);
+        lc_store_relu_any<R>(tile, Np, plain, wave, i, kg, acc);
         __syncthreads();
-        lc_layer_any<RB>(tile, Np, a.W[t], N, a.wvec[t] != 0, wave, j, hh, acc);
+        plain = lc_layer_any<R, 3, false, RAW>(tile, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc);
     }
 
     const float g = a.gamma[k];
     float* dst = a.direct ? a.dst + a.out_off[br] : a.dst + (int64_t)br * a.B * a.ldd;
-    const WaveMap m = wave_map<RB>(C, wave);
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        if (r >= m.rbw) break;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            if (t >= m.nt) break;
-            const int col = m.colbase + m.nt * j + t;
-            // (r, t) -> accumulator r*nt + t; nt is 1 or 2
-            const v16f& v = m.nt == 1 ? acc[r] : acc[r * 2 + t];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int64_t row = row0 + (m.rb0 + r) * 32 + acc_row(e, hh);
-                if (row < a.B && col < C) dst[row * a.ldd + col] = g * v[e];
-            }
-        }
-    }
+    const int ct = tiles_per_wave(C), colbase = wave * 16 * ct;
+    if (ct == 4) lc_write<R, 4>(dst, a, row0, C, colbase, g, i, kg, acc);
+    else if (ct == 2) lc_write<R, 2>(dst, a, row0, C, colbase, g, i, kg, acc);
+    else lc_write<R, 1>(dst, a, row0, C, colbase, g, i, kg, acc);
 }
 
 // out[i][c] = sum (or maximum) over the branches, in branch order, of the partial results
@@ -412,7 +605,7 @@ __global__ __launch_bounds__(kLcThreads) void gp_lc_softmax_rows(float* __restri
     }
 }
 
-// partial results of the split schedule: one grow-only buffer per device
+// partial results, and the split weights of calls that have them: one grow-only buffer per device
 struct Workspace {
     float* p = nullptr;
     size_t bytes = 0;
@@ -437,6 +630,51 @@ gp_status workspace(size_t bytes, float** out)
     return GP_OK;
 }
 
+// Split weights of direct calls (no partial results, so calls may overlap): one buffer per stream, calls on one
+// stream being ordered by it.  A stream without a buffer takes a new one, or, once there are kFragBuffers, the one
+// whose last call was longest ago, and waits for that call (an event) before it writes there.  g_frag_mu is
+// held while a call enqueues: another thread's launches on the same stream do not come in between the split
+// and the products that read it.
+constexpr int kFragBuffers = 16;
+struct FragBuffer {
+    int device = -1;
+    hipStream_t stream = nullptr;
+    char* p = nullptr;
+    size_t bytes = 0;
+    hipEvent_t done = nullptr;  // recorded behind the last call that used it
+    uint64_t last = 0;
+};
+std::mutex g_frag_mu;
+FragBuffer g_frag[kFragBuffers];
+uint64_t g_frag_calls = 0;
+
+gp_status frag_buffer(int dev, hipStream_t stream, size_t bytes, FragBuffer** out)  // (g_frag_mu held)
+{
+    FragBuffer *mine = nullptr, *oldest = nullptr;
+    for (FragBuffer& f : g_frag) {
+        if (f.device == dev && f.stream == stream) mine = &f;
+        if (f.device < 0) {
+            if (!oldest || oldest->device >= 0) oldest = &f;
+        } else if (f.device == dev && (!oldest || (oldest->device >= 0 && f.last < oldest->last))) {
+            oldest = &f;
+        }
+    }
+    *out = nullptr;
+    FragBuffer* f = mine ? mine : oldest;
+    if (!f) return GP_OK;  // (every buffer belongs to another device: the caller does without)
+    if (f->device >= 0 && f != mine) GP_HIP(hipStreamWaitEvent(stream, f->done, 0));
+    if (!f->done) GP_HIP(hipEventCreateWithFlags(&f->done, hipEventDisableTiming));
+    if (f->bytes < bytes) {
+        if (f->p) GP_HIP(hipFree(f->p));  // waits for the device
+        f->p = nullptr, f->bytes = 0;
+        GP_HIP(hipMalloc((void**)&f->p, bytes));
+        f->bytes = bytes;
+    }
+    f->device = dev, f->stream = stream, f->last = ++g_frag_calls;
+    *out = f;
+    return GP_OK;
+}
+
 int compute_units()
 {
     static int cus = [] {
@@ -449,10 +687,10 @@ int compute_units()
     return cus;
 }
 
-template <typename T, int RB>
-gp_status launch_mlp(const LcArgs& a, unsigned grid, hipStream_t stream)
+template <typename T, int R, bool CARRY, bool RAW>
+gp_status launch_mlp_t(const LcArgs& a, unsigned grid, hipStream_t stream)
 {
-    constexpr size_t lds = (size_t)32 * RB * kLd * sizeof(float);
+    constexpr size_t lds = (size_t)16 * R * kLd * 3 * sizeof(uint16_t);
     // the kernel's LDS tile is above the 64 KB a kernel gets by default: raise the limit
     // once per device (the attribute belongs to the device's copy of the kernel)
     static std::atomic<uint64_t> done{0};
@@ -460,15 +698,48 @@ gp_status launch_mlp(const LcArgs& a, unsigned grid, hipStream_t stream)
     GP_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64) return fail(GP_ERR_UNSUPPORTED, "device ordinal %d not supported", dev);
     if (!(done.load(std::memory_order_acquire) >> dev & 1)) {
-        GP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gp_lc_mlp<T, RB>),
+        GP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gp_lc_mlp<T, R, CARRY, RAW>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         done.fetch_or(UINT64_C(1) << dev, std::memory_order_release);
     }
     profile_begin("gp_lc_mlp", stream);
-    hipLaunchKernelGGL((gp_lc_mlp<T, RB>), dim3(grid), dim3(kLcThreads), lds, stream, a);
+    hipLaunchKernelGGL((gp_lc_mlp<T, R, CARRY, RAW>), dim3(grid), dim3(kMlpThreads), lds, stream, a);
     profile_end(stream);
     GP_HIP(hipGetLastError());
     return GP_OK;
+}
+
+template <typename T, bool CARRY>
+gp_status launch_mlp_c(int tile_rows, const LcArgs& a, unsigned grid, hipStream_t stream)
+{
+    if (!a.frags) return tile_rows == 16 ? launch_mlp_t<T, 1, CARRY, true>(a, grid, stream) : launch_mlp_t<T, 2, CARRY, true>(a, grid, stream);
+    if (tile_rows == 16) return launch_mlp_t<T, 1, CARRY, false>(a, grid, stream);
+    if (tile_rows == 32) return launch_mlp_t<T, 2, CARRY, false>(a, grid, stream);
+    return launch_mlp_t<T, 3, CARRY, false>(a, grid, stream);
+}
+
+template <typename T>
+gp_status launch_mlp(int tile_rows, const LcArgs& a, unsigned grid, hipStream_t stream)
+{
+    return a.d > kPanel ? launch_mlp_c<T, true>(tile_rows, a, grid, stream) : launch_mlp_c<T, false>(tile_rows, a, grid, stream);
+}
+
+// Rows of a work item.  Two items share a compute unit; a round of items lasts (measured on a 128-256-256-256-40
+// model, microseconds) 21 / 28 / 38 for 16 / 32 / 48 rows where every unit has two, 19 / 22 / 28 where none has
+// more than one: the height with the least sum over the call's rounds.  (4 hops: 512 rows 19 us with 16-row items,
+// 28 with 48; 4096 rows 38 us with 32, 56 with 16, 45 with 48; all 169,343 rows 1042 us with 48, 1157 with 32.)
+int choose_tile_rows(int64_t B, int hops)
+{
+    const int64_t both[3] = {21, 28, 38}, alone[3] = {19, 22, 28};
+    int best = 0;
+    int64_t best_cost = 0;
+    for (int r = 0; r < 3; ++r) {
+        const int64_t items = (B + 16 * (r + 1) - 1) / (16 * (r + 1)) * hops, cus = compute_units();
+        const int64_t rest = items % (2 * cus);
+        const int64_t cost = items / (2 * cus) * both[r] + (rest == 0 ? 0 : rest <= cus ? alone[r] : both[r]);
+        if (r == 0 || cost <= best_cost) best = r, best_cost = cost;
+    }
+    return 16 * (best + 1);
 }
 
 }  // namespace
@@ -514,27 +785,56 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     if (ldo < out_width) return fail(GP_ERR_INVALID_ARG, "ldo < output width %d", out_width);
     if (B == 0) return GP_OK;
     a.direct = comb == GP_COMB_CONCAT || a.hops == 1;
-    for (int t = 0; t < T; ++t) {
-        a.W[t] = W[t], a.width[t] = width[t];
-        a.wvec[t] = width[t] > 128 && width[t] % 2 == 0 && (uintptr_t)W[t] % 8 == 0;  // two tiles per wave, pairs aligned
-    }
+    for (int t = 0; t < T; ++t) a.W[t] = W[t], a.width[t] = width[t];
     const size_t esz = dtype == GP_F32 ? 4 : 2;
     a.xvec = ld % 4 == 0 && (uintptr_t)stack % (4 * esz) == 0;
 
-    // One workgroup per (row tile, branch), so that a mini-batch of a few thousand rows
-    // still fills the chip; the branches' results are then combined in hop order.
-    // Tiles are 64 rows; 32 rows when even those give no more than one workgroup per CU
-    // (the call then lasts as long as one work item, and a 32-row item is the shorter
-    // one: 37 against 56 us at the paper's model shape; from two items per CU on, 64-row
-    // items win because each weight is fetched once per 64 rows).  Large batches go
-    // through in pieces that keep the partial results within a fixed size.
-    int tm = (int)options().lc_tile_rows;
-    if (tm == 0) tm = ((B + 31) / 32) * a.hops <= (int64_t)compute_units() ? 32 : 64;
+    // One workgroup per (row tile, branch), so that a mini-batch of a few thousand rows still fills the chip; the
+    // branches' results are then combined in hop order.  Large batches go through in pieces that keep the
+    // partial results within a fixed size.
+    const int asked = (int)options().lc_tile_rows;
+    int tm = asked == 0 ? choose_tile_rows(B, a.hops) : asked >= 48 ? 48 : 32;
     const int64_t piece = a.direct ? B : std::max<int64_t>(64, kWorkspaceBytes / ((int64_t)a.hops * C * 4) / 64 * 64);
+    SplitArgs sp{};
+    sp.T = T;
+    for (int t = 0; t < T; ++t) {
+        const int in = t == 0 ? d : width[t - 1];
+        sp.W[t] = W[t], sp.kin[t] = in, sp.width[t] = width[t];
+        a.frag_off[t] = sp.first[t] * 3 * kFragBytes;
+        sp.first[t + 1] = sp.first[t] + layer_tiles(in, width[t]);
+    }
+    const int64_t frag_bytes = sp.first[T] * 3 * kFragBytes + kFragSlack, split_grid = (sp.first[T] + 3) / 4;
+    if (split_grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "d = %d is too wide", d);
+    // Where the split weights go: behind the partial results where there are any (calls with partial results do
+    // not overlap), else into the stream's own buffer.  A direct call under graph capture goes without and splits
+    // weights where it uses them: its replays may run beside other calls, which a shared buffer would not survive.
     float* part = nullptr;
+    FragBuffer* own = nullptr;
+    std::unique_lock<std::mutex> own_lock(g_frag_mu, std::defer_lock);
     if (!a.direct) {
-        gp_status st = workspace((size_t)a.hops * std::min(piece, B) * C * sizeof(float), &part);
+        const size_t part_bytes = ((size_t)a.hops * std::min(piece, B) * C * sizeof(float) + 255) / 256 * 256;
+        gp_status st = workspace(part_bytes + std::max<size_t>((size_t)frag_bytes, kFragReserve), &part);
         if (st != GP_OK) return st;
+        a.frags = sp.out = (char*)part + part_bytes;
+    } else {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        GP_HIP(hipStreamIsCapturing(stream, &capture));
+        if (capture == hipStreamCaptureStatusNone) {
+            int dev = 0;
+            GP_HIP(hipGetDevice(&dev));
+            own_lock.lock();
+            gp_status st = frag_buffer(dev, stream, (size_t)frag_bytes, &own);
+            if (st != GP_OK) return st;
+            if (own) a.frags = sp.out = own->p;
+        }
+    }
+    if (a.frags) {
+        profile_begin("gp_lc_split_weights", stream);
+        hipLaunchKernelGGL(gp_lc_split_weights, dim3((unsigned)split_grid), dim3(256), 0, stream, sp);
+        profile_end(stream);
+        GP_HIP(hipGetLastError());
+    } else {
+        tm = std::min(tm, 32);  // (raw weights take registers: 32 rows at most)
     }
     for (int64_t b0 = 0; b0 < B; b0 += piece) {
         LcArgs p = a;
@@ -547,13 +847,7 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
             p.dst = part, p.ldd = C;
         const int64_t grid = (p.B + tm - 1) / tm * a.hops;
         if (grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "batch too large for one launch");
-        gp_status st;
-        if (tm == 64)
-            st = dtype == GP_F32 ? launch_mlp<float, 2>(p, (unsigned)grid, stream)
-                                 : launch_mlp<unsigned short, 2>(p, (unsigned)grid, stream);
-        else
-            st = dtype == GP_F32 ? launch_mlp<float, 1>(p, (unsigned)grid, stream)
-                                 : launch_mlp<unsigned short, 1>(p, (unsigned)grid, stream);
+        gp_status st = dtype == GP_F32 ? launch_mlp<float>(tm, p, (unsigned)grid, stream) : launch_mlp<unsigned short>(tm, p, (unsigned)grid, stream);
         if (st != GP_OK) return st;
         if (!a.direct) {
             const unsigned rgrid = (unsigned)std::min<int64_t>((p.B * C + kLcThreads - 1) / kLcThreads, 256 * 8);
@@ -564,6 +858,7 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
             GP_HIP(hipGetLastError());
         }
     }
+    if (own) GP_HIP(hipEventRecord(own->done, stream));
     return GP_OK;
 }
 

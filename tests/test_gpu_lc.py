@@ -284,3 +284,88 @@ def test_softmax_rows(B, C, pad):
     assert np.all(np.abs(got - want) <= (C + 160) * 2.0 ** -24 * want + 1e-37)
     if pad:
         assert torch.all(buf[:, C:] == 9.0)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d,widths,B", [(31, [256, 40], 47), (300, [130, 70], 49), (64, [65], 16), (32, [129, 256], 97)])
+def test_infinities_and_nans(d, widths, B, bf16):
+    """Sums that an infinity, a NaN or a number beyond the largest bf16 one takes part in are plain fp32
+    arithmetic's: the same infinities and NaNs as the oracle, and the other elements within tolerance."""
+    rng = np.random.default_rng(77 + d)
+    n, K = 120, 1
+    stack = rng.normal(size=(K + 1, n, d)).astype(np.float32)
+    stack[0, 3, 1] = np.inf
+    stack[1, 5, 0] = -np.inf
+    stack[0, 7, d - 1] = np.nan
+    if bf16:
+        stack = gp_synth.f32_to_bf16_bits(stack)
+        stack[0, 7, d - 1] = 0x7FC0
+    else:
+        stack[0, 9, 2] = np.float32(3.4e38)  # rounds to infinity in bf16
+    Ws = make_weights(rng, d, widths)
+    Ws[0][2] *= np.float32(1e-3)
+    ids = np.concatenate([[3, 5, 7, 9, 0], rng.integers(10, n, B - 5)])
+    gamma = [0.5, 0.25]
+    got = run(stack, ids, gamma, Ws, bf16=bf16)
+    wide = gp_synth.bf16_bits_to_f32(stack) if bf16 else stack
+    with np.errstate(all="ignore"):
+        want = lc.lc_forward(wide, ids, gamma, Ws)
+        bound = lc.lc_bound(wide, ids, gamma, Ws)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want)) and not np.all(np.isfinite(want))
+    ok = np.isfinite(want)
+    assert np.all(np.abs(got - want)[ok] <= tolerance(d, widths, K) * bound[ok] + 1e-30)
+
+
+@pytest.mark.parametrize("d,widths,B,bf16", [(100, [256, 172, 41], 333, False), (270, [70, 130], 5000, True), (48, [40], 17, False)])
+def test_captured_call_that_writes_its_result_directly(d, widths, B, bf16):
+    """A concatenating call under graph capture splits its weights where it uses them (no shared buffer): every
+    replay gives the eager call's bits, with other calls of the library in between."""
+    import torch
+    rng = np.random.default_rng(5 + d)
+    n, K, T = 700, 2, len(widths)
+    stack = torch.from_numpy(rng.normal(size=(K + 1, n, d)).astype(np.float32)).cuda()
+    if bf16:
+        stack = stack.bfloat16()
+    Wd = [torch.from_numpy(W).cuda() for W in make_weights(rng, d, widths)]
+    batch = torch.from_numpy(rng.integers(0, n, B).astype(np.int32)).cuda()
+    depth, gamma = [T, 1, T], [1.0, 0.5, 0.25]
+
+    def call(out=None):
+        return gp.lc_forward_tensors(stack, batch, gamma, Wd, out=out, depth=depth, comb=gp.GP_COMB_CONCAT)
+
+    eager = call()
+    out = torch.empty_like(eager)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call(out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out)
+    for _ in range(3):
+        out.fill_(-3.0)
+        graph.replay()
+        gp.lc_forward_tensors(stack, batch[:9], gamma, Wd)
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+
+
+def test_calls_on_many_streams():
+    """Direct calls on more streams than the library keeps weight buffers for, interleaved without waiting: each
+    gives what it gives alone."""
+    import torch
+    rng = np.random.default_rng(21)
+    n, d = 4000, 96
+    stack = torch.from_numpy(rng.normal(size=(1, n, d)).astype(np.float32)).cuda()
+    models = [[torch.from_numpy(W).cuda() for W in make_weights(rng, d, [200, 64])] for _ in range(5)]
+    want = [gp.lc_forward_tensors(stack, None, [1.0], m) for m in models]
+    outs = [torch.empty_like(want[0]) for _ in range(40)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(20)]
+    for k in range(40):
+        with torch.cuda.stream(streams[k % 20]):
+            gp.lc_forward_tensors(stack, None, [1.0], models[k % 5], out=outs[k])
+    torch.cuda.synchronize()
+    for k in range(40):
+        assert torch.equal(outs[k], want[k % 5]), k
