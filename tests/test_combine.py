@@ -117,6 +117,42 @@ def test_gpu_combine_with_the_lds_pass(gpu_or_skip, dtype, d, agg, hubs):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gp.GP_F32, gp.GP_BF16])
+@pytest.mark.parametrize("d,x_pad,out_pad", [(1, 0, 0), (3, 0, 1), (4, 0, 0), (5, 1, 0), (8, 4, 0), (12, 0, 1), (31, 0, 0), (32, 1, 3),
+                                             (33, 0, 4), (64, 0, 0), (257, 0, 0), (260, 3, 1)])
+def test_gpu_combine_at_the_edges_of_the_vectors(gpu_or_skip, dtype, d, x_pad, out_pad):
+    """Rows of less than a vector, of whole vectors and with a last vector moved back, with and without gaps between
+    rows, on 16-byte boundaries and off them: every column takes every term once and nothing else is written.
+    A term is at most K + 1 roundings of fp32 (of bf16 at each hop, and once at the end) away from its value."""
+    import torch
+    K = 2
+    w = gp_synth.make_workload(2, scale=0.01, d=d)
+    X = w.X if dtype == gp.GP_F32 else gp_synth.f32_to_bf16_bits(w.X)
+    Xw = (w.X if dtype == gp.GP_F32 else gp_synth.bf16_bits_to_f32(X)).astype(np.float64)
+    coeff = [0.5, -0.75, 0.3]
+    xt = torch.from_numpy(X) if dtype == gp.GP_F32 else torch.from_numpy(X.view(np.int16)).view(torch.bfloat16)
+    xd = torch.full((w.n, d + x_pad), float("nan"), dtype=xt.dtype, device="cuda:0")
+    xd[:, :d] = xt.cuda()
+    out = torch.full((w.n, d + out_pad), 7.0, dtype=xt.dtype, device="cuda:0")
+    op = oracle.plan_blocks(w.src, w.dst, w.n, 4000, w.flags)
+    gp.gp_set_option("segment_edges", 16)                      # the fix-up adds its rows' terms too
+    try:
+        with gp.gp_plan_blocks(w.src, w.dst, w.n, 4000, w.flags) as lp:
+            assert lp.num_partial_rows > 0
+            gp.gp_propagate_combine(lp, xd.data_ptr(), d + x_pad, d, dtype, AGG_SYM, K, coeff, out.data_ptr(), d + out_pad,
+                                    torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+    finally:
+        gp.gp_set_option("segment_edges", 0)
+    assert (out[:, d:] == 7.0).all()
+    c32 = np.asarray(coeff, dtype=np.float32).astype(np.float64)
+    want, bound = oracle.combine(op, Xw, AGG_SYM, c32, threads=4)
+    err = np.abs(out[:, :d].float().cpu().numpy().astype(np.float64) - want)
+    tol = 1e-5 if dtype == gp.GP_F32 else 1e-2
+    assert np.all(err <= tol * bound + 1e-30), f"worst ratio {np.max(err / (bound + 1e-300)):.3g}"
+
+
+@pytest.mark.gpu
 def test_gpu_combine_rejects_bad_arguments(gpu_or_skip):
     import torch
     x = torch.zeros((8, 4), device="cuda:0")
