@@ -630,11 +630,13 @@ gp_status workspace(size_t bytes, float** out)
     return GP_OK;
 }
 
-// Split weights of direct calls (no partial results, so calls may overlap): one buffer per stream, calls on one
-// stream being ordered by it.  A stream without a buffer takes a new one, or, once there are kFragBuffers, the one
-// whose last call was longest ago, and waits for that call (an event) before it writes there.  g_frag_mu is
-// held while a call enqueues: another thread's launches on the same stream do not come in between the split
-// and the products that read it.
+// Split weights of direct calls (no partial results, so calls may overlap): a few buffers, handed out by stream
+// handle so that calls on different streams do not wait for one another.  Equal handles are not taken for an order: one handle
+// can be several streams (hipStreamPerThread is another one in every thread; a destroyed stream's handle
+// comes back).  Every call waits for the event recorded behind the call that used its buffer last, which
+// costs nothing where both are on one stream.  A stream without a buffer takes a new one, or, once there are
+// kFragBuffers, the one whose last call was longest ago.  g_frag_mu is held while a call enqueues: nobody takes
+// the buffer between the wait and the next record.
 constexpr int kFragBuffers = 16;
 struct FragBuffer {
     int device = -1;
@@ -642,6 +644,7 @@ struct FragBuffer {
     char* p = nullptr;
     size_t bytes = 0;
     hipEvent_t done = nullptr;  // recorded behind the last call that used it
+    bool used = false;          // it has been recorded
     uint64_t last = 0;
 };
 std::mutex g_frag_mu;
@@ -662,7 +665,7 @@ gp_status frag_buffer(int dev, hipStream_t stream, size_t bytes, FragBuffer** ou
     *out = nullptr;
     FragBuffer* f = mine ? mine : oldest;
     if (!f) return GP_OK;  // (every buffer belongs to another device: the caller does without)
-    if (f->device >= 0 && f != mine) GP_HIP(hipStreamWaitEvent(stream, f->done, 0));
+    if (f->used) GP_HIP(hipStreamWaitEvent(stream, f->done, 0));
     if (!f->done) GP_HIP(hipEventCreateWithFlags(&f->done, hipEventDisableTiming));
     if (f->bytes < bytes) {
         if (f->p) GP_HIP(hipFree(f->p));  // waits for the device
@@ -674,6 +677,20 @@ gp_status frag_buffer(int dev, hipStream_t stream, size_t bytes, FragBuffer** ou
     *out = f;
     return GP_OK;
 }
+
+// Marks the end of a call that took a buffer, however the call ends: whatever it enqueued is in front of the event.
+// A call whose event cannot be recorded waits for its stream instead.
+struct FragUse {
+    FragBuffer* f = nullptr;
+    ~FragUse()
+    {
+        if (!f) return;
+        if (hipEventRecord(f->done, f->stream) == hipSuccess)
+            f->used = true;
+        else
+            (void)hipStreamSynchronize(f->stream);
+    }
+};
 
 int compute_units()
 {
@@ -809,8 +826,8 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     // not overlap), else into the stream's own buffer.  A direct call under graph capture goes without and splits
     // weights where it uses them: its replays may run beside other calls, which a shared buffer would not survive.
     float* part = nullptr;
-    FragBuffer* own = nullptr;
     std::unique_lock<std::mutex> own_lock(g_frag_mu, std::defer_lock);
+    FragUse own;  // (after the lock: it ends before the lock does)
     if (!a.direct) {
         const size_t part_bytes = ((size_t)a.hops * std::min(piece, B) * C * sizeof(float) + 255) / 256 * 256;
         gp_status st = workspace(part_bytes + std::max<size_t>((size_t)frag_bytes, kFragReserve), &part);
@@ -823,9 +840,9 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
             int dev = 0;
             GP_HIP(hipGetDevice(&dev));
             own_lock.lock();
-            gp_status st = frag_buffer(dev, stream, (size_t)frag_bytes, &own);
+            gp_status st = frag_buffer(dev, stream, (size_t)frag_bytes, &own.f);
             if (st != GP_OK) return st;
-            if (own) a.frags = sp.out = own->p;
+            if (own.f) a.frags = sp.out = own.f->p;
         }
     }
     if (a.frags) {
@@ -858,7 +875,6 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
             GP_HIP(hipGetLastError());
         }
     }
-    if (own) GP_HIP(hipEventRecord(own->done, stream));
     return GP_OK;
 }
 

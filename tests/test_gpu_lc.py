@@ -369,3 +369,39 @@ def test_calls_on_many_streams():
     torch.cuda.synchronize()
     for k in range(40):
         assert torch.equal(outs[k], want[k % 5]), k
+
+
+def test_one_handle_that_is_a_stream_of_its_own_in_every_thread():
+    """hipStreamPerThread (handle 2) names another stream in each thread: direct calls of two threads on it, with
+    different weights and nothing that orders them, each give what they give alone."""
+    import threading
+    import torch
+    per_thread = 2
+    rng = np.random.default_rng(31)
+    n, d = 30000, 96
+    stack = torch.from_numpy(rng.normal(size=(1, n, d)).astype(np.float32)).cuda()
+    models = [[torch.from_numpy(W).cuda() for W in make_weights(rng, d, [256, 200, 64])] for _ in range(2)]
+    want = [gp.lc_forward_tensors(stack, None, [1.0], m) for m in models]
+    outs = [[torch.empty_like(want[0]) for _ in range(12)] for _ in models]
+    torch.cuda.synchronize()
+    start, failures = threading.Barrier(2), []
+
+    def work(k):
+        try:
+            torch.cuda.set_device(0)
+            start.wait(30)
+            for out in outs[k]:
+                gp.lc_forward_tensors(stack, None, [1.0], models[k], out=out, stream=per_thread)
+            torch.cuda.synchronize()   # before the thread ends and its stream with it
+        except Exception as e:  # noqa: BLE001
+            failures.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not failures, failures
+    for k in range(2):
+        for j, out in enumerate(outs[k]):
+            assert torch.equal(out, want[k]), (k, j)
