@@ -630,65 +630,74 @@ gp_status workspace(size_t bytes, float** out)
     return GP_OK;
 }
 
-// Split weights of direct calls (no partial results, so calls may overlap): a few buffers, handed out by stream
-// handle so that calls on different streams do not wait for one another.  Equal handles are not taken for an order: one handle
-// can be several streams (hipStreamPerThread is another one in every thread; a destroyed stream's handle
-// comes back).  Every call waits for the event recorded behind the call that used its buffer last, which
-// costs nothing where both are on one stream.  A stream without a buffer takes a new one, or, once there are
-// kFragBuffers, the one whose last call was longest ago.  g_frag_mu is held while a call enqueues: nobody takes
-// the buffer between the wait and the next record.
-constexpr int kFragBuffers = 16;
-struct FragBuffer {
-    int device = -1;
+// Room for split weights: a fixed array on every device, held from load to process end, so that no call
+// allocates, frees or waits for the device on their account (another thread may be capturing a graph, which
+// an allocation would break), and what is held is bounded.  Weights that do not fit their slot are split where they
+// are used: 8 MiB are 1.3 million weights, one 256-wide layer on 5,400 features.
+// Direct calls (no partial results, so calls may overlap) share the slots, handed out by stream handle so that calls on
+// different streams do not wait for one another.  Equal handles are not taken for an order: one handle can be several
+// streams (hipStreamPerThread is another one in every thread; a destroyed stream's handle comes back).  Every call
+// waits for the event recorded behind the call that used its slot last, which costs nothing where both are on
+// one stream.  A stream without a slot takes a new one, or, once all are taken, the one whose last call was longest
+// ago.  g_slot_mu is held while a call enqueues: nobody takes the slot between the wait and the next record.
+constexpr int kSlots = 8;
+constexpr size_t kSlotBytes = 8 << 20;
+static __device__ __align__(256) char split_room[kSlots * kSlotBytes];
+struct Slot {
     hipStream_t stream = nullptr;
-    char* p = nullptr;
-    size_t bytes = 0;
+    bool taken = false;
     hipEvent_t done = nullptr;  // recorded behind the last call that used it
     bool used = false;          // it has been recorded
     uint64_t last = 0;
 };
-std::mutex g_frag_mu;
-FragBuffer g_frag[kFragBuffers];
-uint64_t g_frag_calls = 0;
+std::mutex g_slot_mu;
+Slot g_slots[64][kSlots];
+char* g_room[64];
+uint64_t g_slot_calls = 0;
 
-gp_status frag_buffer(int dev, hipStream_t stream, size_t bytes, FragBuffer** out)  // (g_frag_mu held)
+gp_status room_on_current_device(int* dev, char** out)  // (g_slot_mu held)
 {
-    FragBuffer *mine = nullptr, *oldest = nullptr;
-    for (FragBuffer& f : g_frag) {
-        if (f.device == dev && f.stream == stream) mine = &f;
-        if (f.device < 0) {
-            if (!oldest || oldest->device >= 0) oldest = &f;
-        } else if (f.device == dev && (!oldest || (oldest->device >= 0 && f.last < oldest->last))) {
-            oldest = &f;
-        }
+    GP_HIP(hipGetDevice(dev));
+    if (*dev < 0 || *dev >= 64) return fail(GP_ERR_UNSUPPORTED, "device ordinal %d not supported", *dev);
+    if (!g_room[*dev]) {
+        void* p = nullptr;
+        GP_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(split_room)));
+        g_room[*dev] = (char*)p;
     }
-    *out = nullptr;
-    FragBuffer* f = mine ? mine : oldest;
-    if (!f) return GP_OK;  // (every buffer belongs to another device: the caller does without)
-    if (f->used) GP_HIP(hipStreamWaitEvent(stream, f->done, 0));
-    if (!f->done) GP_HIP(hipEventCreateWithFlags(&f->done, hipEventDisableTiming));
-    if (f->bytes < bytes) {
-        if (f->p) GP_HIP(hipFree(f->p));  // waits for the device
-        f->p = nullptr, f->bytes = 0;
-        GP_HIP(hipMalloc((void**)&f->p, bytes));
-        f->bytes = bytes;
-    }
-    f->device = dev, f->stream = stream, f->last = ++g_frag_calls;
-    *out = f;
+    *out = g_room[*dev];
     return GP_OK;
 }
 
-// Marks the end of a call that took a buffer, however the call ends: whatever it enqueued is in front of the event.
+gp_status take_slot(hipStream_t stream, Slot** out, char** where)  // (g_slot_mu held)
+{
+    int dev = 0;
+    char* room = nullptr;
+    gp_status st = room_on_current_device(&dev, &room);
+    if (st != GP_OK) return st;
+    Slot* s = nullptr;  // the stream's own, else a free one, else the one longest unused
+    for (Slot& t : g_slots[dev])
+        if (t.taken && t.stream == stream) s = &t;
+    if (!s)
+        for (Slot& t : g_slots[dev])
+            if (!s || (s->taken && (!t.taken || t.last < s->last))) s = &t;
+    if (!s->done) GP_HIP(hipEventCreateWithFlags(&s->done, hipEventDisableTiming));
+    if (s->used) GP_HIP(hipStreamWaitEvent(stream, s->done, 0));
+    s->stream = stream, s->taken = true, s->last = ++g_slot_calls;
+    *out = s, *where = room + (s - g_slots[dev]) * kSlotBytes;
+    return GP_OK;
+}
+
+// Marks the end of a call that took a slot, however the call ends: whatever it enqueued is in front of the event.
 // A call whose event cannot be recorded waits for its stream instead.
-struct FragUse {
-    FragBuffer* f = nullptr;
-    ~FragUse()
+struct SlotUse {
+    Slot* s = nullptr;
+    ~SlotUse()
     {
-        if (!f) return;
-        if (hipEventRecord(f->done, f->stream) == hipSuccess)
-            f->used = true;
+        if (!s) return;
+        if (hipEventRecord(s->done, s->stream) == hipSuccess)
+            s->used = true;
         else
-            (void)hipStreamSynchronize(f->stream);
+            (void)hipStreamSynchronize(s->stream);
     }
 };
 
@@ -823,26 +832,24 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     const int64_t frag_bytes = sp.first[T] * 3 * kFragBytes + kFragSlack, split_grid = (sp.first[T] + 3) / 4;
     if (split_grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "d = %d is too wide", d);
     // Where the split weights go: behind the partial results where there are any (calls with partial results do
-    // not overlap), else into the stream's own buffer.  A direct call under graph capture goes without and splits
-    // weights where it uses them: its replays may run beside other calls, which a shared buffer would not survive.
+    // not overlap), else into a slot.  A direct call under graph capture goes without and splits
+    // weights where it uses them: its replays may run beside other calls, which a shared slot would not survive.
     float* part = nullptr;
-    std::unique_lock<std::mutex> own_lock(g_frag_mu, std::defer_lock);
-    FragUse own;  // (after the lock: it ends before the lock does)
+    std::unique_lock<std::mutex> slot_lock(g_slot_mu, std::defer_lock);
+    SlotUse slot;  // (after the lock: it ends before the lock does)
     if (!a.direct) {
         const size_t part_bytes = ((size_t)a.hops * std::min(piece, B) * C * sizeof(float) + 255) / 256 * 256;
         gp_status st = workspace(part_bytes + std::max<size_t>((size_t)frag_bytes, kFragReserve), &part);
         if (st != GP_OK) return st;
         a.frags = sp.out = (char*)part + part_bytes;
-    } else {
+    } else if ((size_t)frag_bytes <= kSlotBytes) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         GP_HIP(hipStreamIsCapturing(stream, &capture));
         if (capture == hipStreamCaptureStatusNone) {
-            int dev = 0;
-            GP_HIP(hipGetDevice(&dev));
-            own_lock.lock();
-            gp_status st = frag_buffer(dev, stream, (size_t)frag_bytes, &own.f);
+            slot_lock.lock();
+            gp_status st = take_slot(stream, &slot.s, &sp.out);
             if (st != GP_OK) return st;
-            if (own.f) a.frags = sp.out = own.f->p;
+            a.frags = sp.out;
         }
     }
     if (a.frags) {

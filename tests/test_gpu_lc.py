@@ -405,3 +405,37 @@ def test_one_handle_that_is_a_stream_of_its_own_in_every_thread():
     for k in range(2):
         for j, out in enumerate(outs[k]):
             assert torch.equal(out, want[k]), (k, j)
+
+
+def test_direct_calls_beside_a_capture():
+    """Direct calls allocate nothing: on streams the library has not seen, while another stream is captured in the mode
+    that forbids allocations to everybody, they work and the capture survives them."""
+    import torch
+    rng = np.random.default_rng(41)
+    n, d = 30000, 64
+    stack = torch.from_numpy(rng.normal(size=(1, n, d)).astype(np.float32)).cuda()
+    Ws = [torch.from_numpy(W).cuda() for W in make_weights(rng, d, [256, 200, 40])]
+    want = gp.lc_forward_tensors(stack, None, [1.0], Ws)
+    outs = [torch.empty_like(want) for _ in range(3)]
+    streams = [torch.cuda.Stream() for _ in outs]
+    counter = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(), capture_error_mode="global"):
+        counter.add_(1.0)
+        for out, s in zip(outs, streams):
+            gp.lc_forward_tensors(stack, None, [1.0], Ws, out=out, stream=s.cuda_stream)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.all(counter == k + 1.0)
+    for out in outs:
+        assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("d,widths,K", [(5300, [256], 0), (5600, [256], 0), (5600, [250, 40], 1)])
+def test_weights_that_fill_the_room_for_split_ones(d, widths, K):
+    """The largest weights that are split beforehand, and larger ones, which are split where they are used."""
+    rng = np.random.default_rng(51 + d)
+    stack = rng.normal(size=(K + 1, 150, d)).astype(np.float32)
+    check(stack, rng.integers(0, 150, 3000), rng.normal(size=K + 1), make_weights(rng, d, widths))
