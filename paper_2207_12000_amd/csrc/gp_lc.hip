@@ -227,7 +227,6 @@ __host__ __device__ __forceinline__ int tiles_per_wave(int N) { return N > 128 ?
 // column i of the tile.  Beyond the matrix: zeros.  Steps are padded to a multiple of 4 / CT, so that a wave
 // walks whole groups of four tiles (a panel of the first layer is 8 steps, a multiple already).
 constexpr int64_t kFragBytes = 1024;
-constexpr size_t kFragReserve = 4 << 20;  // room kept behind the partial results: eight layers of 256 x 256 take 3 MB
 constexpr int64_t kFragSlack = 64 << 10;  // requests past a layer's end reach this far at most
 __host__ __device__ __forceinline__ int64_t padded_steps(int64_t kin, int ct) { return ((kin + 31) / 32 + 4 / ct - 1) / (4 / ct) * (4 / ct); }
 __host__ __device__ __forceinline__ int64_t layer_tiles(int64_t kin, int N)
@@ -605,7 +604,7 @@ __global__ __launch_bounds__(kLcThreads) void gp_lc_softmax_rows(float* __restri
     }
 }
 
-// partial results, and the split weights of calls that have them: one grow-only buffer per device
+// partial results: one grow-only buffer per device
 struct Workspace {
     float* p = nullptr;
     size_t bytes = 0;
@@ -634,8 +633,9 @@ gp_status workspace(size_t bytes, float** out)
 // allocates, frees or waits for the device on their account (another thread may be capturing a graph, which
 // an allocation would break), and what is held is bounded.  Weights that do not fit their slot are split where they
 // are used: 8 MiB are 1.3 million weights, one 256-wide layer on 5,400 features.
-// Direct calls (no partial results, so calls may overlap) share the slots, handed out by stream handle so that calls on
-// different streams do not wait for one another.  Equal handles are not taken for an order: one handle can be several
+// Slot 0 is for calls with partial results, captured ones too: they do not overlap.  Direct calls (no partial
+// results, so calls may overlap) share the other slots, handed out by stream handle so that calls on different
+// streams do not wait for one another.  Equal handles are not taken for an order: one handle can be several
 // streams (hipStreamPerThread is another one in every thread; a destroyed stream's handle comes back).  Every call
 // waits for the event recorded behind the call that used its slot last, which costs nothing where both are on
 // one stream.  A stream without a slot takes a new one, or, once all are taken, the one whose last call was longest
@@ -674,12 +674,13 @@ gp_status take_slot(hipStream_t stream, Slot** out, char** where)  // (g_slot_mu
     char* room = nullptr;
     gp_status st = room_on_current_device(&dev, &room);
     if (st != GP_OK) return st;
+    Slot *const first = g_slots[dev] + 1, *const end = g_slots[dev] + kSlots;
     Slot* s = nullptr;  // the stream's own, else a free one, else the one longest unused
-    for (Slot& t : g_slots[dev])
-        if (t.taken && t.stream == stream) s = &t;
+    for (Slot* t = first; t < end; ++t)
+        if (t->taken && t->stream == stream) s = t;
     if (!s)
-        for (Slot& t : g_slots[dev])
-            if (!s || (s->taken && (!t.taken || t.last < s->last))) s = &t;
+        for (Slot* t = first; t < end; ++t)
+            if (!s || (s->taken && (!t->taken || t->last < s->last))) s = t;
     if (!s->done) GP_HIP(hipEventCreateWithFlags(&s->done, hipEventDisableTiming));
     if (s->used) GP_HIP(hipStreamWaitEvent(stream, s->done, 0));
     s->stream = stream, s->taken = true, s->last = ++g_slot_calls;
@@ -831,27 +832,31 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     }
     const int64_t frag_bytes = sp.first[T] * 3 * kFragBytes + kFragSlack, split_grid = (sp.first[T] + 3) / 4;
     if (split_grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "d = %d is too wide", d);
-    // Where the split weights go: behind the partial results where there are any (calls with partial results do
-    // not overlap), else into a slot.  A direct call under graph capture goes without and splits
-    // weights where it uses them: its replays may run beside other calls, which a shared slot would not survive.
+    // Where the split weights go: into slot 0 where there are partial results (such calls do not overlap), else into
+    // a slot of the stream's.  A direct call under graph capture goes without and splits weights where it uses them: its
+    // replays may run beside other calls, which a shared slot would not survive.
     float* part = nullptr;
     std::unique_lock<std::mutex> slot_lock(g_slot_mu, std::defer_lock);
     SlotUse slot;  // (after the lock: it ends before the lock does)
+    const bool fits = (size_t)frag_bytes <= kSlotBytes;
     if (!a.direct) {
-        const size_t part_bytes = ((size_t)a.hops * std::min(piece, B) * C * sizeof(float) + 255) / 256 * 256;
-        gp_status st = workspace(part_bytes + std::max<size_t>((size_t)frag_bytes, kFragReserve), &part);
+        gp_status st = workspace((size_t)a.hops * std::min(piece, B) * C * sizeof(float), &part);
         if (st != GP_OK) return st;
-        a.frags = sp.out = (char*)part + part_bytes;
-    } else if ((size_t)frag_bytes <= kSlotBytes) {
+        if (fits) {
+            int dev = 0;
+            std::lock_guard<std::mutex> lk(g_slot_mu);
+            if ((st = room_on_current_device(&dev, &sp.out)) != GP_OK) return st;
+        }
+    } else if (fits) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         GP_HIP(hipStreamIsCapturing(stream, &capture));
         if (capture == hipStreamCaptureStatusNone) {
             slot_lock.lock();
             gp_status st = take_slot(stream, &slot.s, &sp.out);
             if (st != GP_OK) return st;
-            a.frags = sp.out;
         }
     }
+    a.frags = sp.out;
     if (a.frags) {
         profile_begin("gp_lc_split_weights", stream);
         hipLaunchKernelGGL(gp_lc_split_weights, dim3((unsigned)split_grid), dim3(256), 0, stream, sp);

@@ -439,3 +439,33 @@ def test_weights_that_fill_the_room_for_split_ones(d, widths, K):
     rng = np.random.default_rng(51 + d)
     stack = rng.normal(size=(K + 1, 150, d)).astype(np.float32)
     check(stack, rng.integers(0, 150, 3000), rng.normal(size=K + 1), make_weights(rng, d, widths))
+
+
+def test_captured_sum_after_a_call_with_fewer_features():
+    """The library's buffer depends on rows and output columns alone: a summing call on more features and more
+    layers than the eager calls before it can be captured, and its replays are right after eager calls on still more."""
+    import torch
+    rng = np.random.default_rng(61)
+    n, K, C, B = 300, 1, 40, 2000
+    batch = torch.from_numpy(rng.integers(0, n, B).astype(np.int32)).cuda()
+    gamma = [0.75, 0.5]
+
+    def model(d, widths):
+        stack = torch.from_numpy(rng.normal(size=(K + 1, n, d)).astype(np.float32)).cuda()
+        return stack, [torch.from_numpy(W).cuda() for W in make_weights(rng, d, widths)]
+
+    small, wide, wider = model(32, [C]), model(3000, [256, 256, C]), model(5000, [256, C])
+    out = torch.full((B, C), -1.0, device="cuda")
+    gp.lc_forward_tensors(small[0], batch, gamma, small[1])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gp.lc_forward_tensors(wide[0], batch, gamma, wide[1], out=out)
+    want = gp.lc_forward_tensors(wide[0], batch, gamma, wide[1])
+    for _ in range(3):
+        gp.lc_forward_tensors(wider[0], batch, gamma, wider[1])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        out.fill_(-1.0)
