@@ -12,21 +12,23 @@
 // the way).  Nothing but the gathered rows and the per-hop B x C results touches HBM.
 //
 // Arithmetic.  The fp32 matrix instruction runs at 157 TFLOP/s on this chip, the bf16 one
-// at 2.5 PFLOP/s.  An fp32 number is a sum of three bf16 numbers without loss (8 bits each,
-// rounded to nearest: x = x1 + x2 + x3, |x2| <= 2^-9 |x|, |x3| <= 2^-18 |x|), and a product
-// of two bf16 numbers is exact in fp32, so
+// at 2.5 PFLOP/s.  An fp32 number times 2^16 is a sum of three bf16 numbers (8 bits each,
+// rounded to nearest: 2^16 x = x1 + x2 + x3, |x2| <= 2^-8 |x1|, |x3| <= 2^-17 |x1|), without loss
+// down to the smallest subnormal: 2^-149 becomes 2^-133, bf16's own smallest, which the
+// conversions and the matrix instruction keep.  (Without the factor, the parts of numbers below
+// 2^-110 run out of exponents.)  A product of two bf16 numbers is exact in fp32, so
 //
-//     x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + O(2^-26 |x w|),
+//     2^32 x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + (x2 w3 + x3 w2 + x3 w3),
 //
-// six bf16 products with fp32 accumulation: what is left out is a quarter of the rounding
-// that one fp32 addition of the term makes (2^-24), and the large products take one
-// accumulation per 32 terms.  Measured against fp64 on a 128-256-256-256-40 model: relative
-// error 0.92e-7, where the fp32 instruction left 2.5e-7.  (A bf16 stack's first layer has
-// x = x1: three products.)  Features and activations are split once, when they enter LDS;
-// weights once per call (gp_lc_split_weights).  Infinities and NaNs do not survive the
-// split, but whatever they touch comes out of it as NaN: a wave whose sums are not all finite
-// takes that layer again on the fp32 instruction (lc_layer_exact), so results with
-// infinities or NaNs are those of plain fp32 arithmetic.
+// of which the last bracket, at most 2^-24 of the product, is left out: six bf16 products with fp32
+// accumulation, the large ones with one accumulation per 32 terms.  Measured against fp64
+// on a 128-256-256-256-40 model with normal weights and features: relative error 0.92e-7, where
+// the fp32 instruction left 2.5e-7.  (A bf16 stack's first layer has one part, x itself: three
+// products.)  Features and activations are split once, when they enter LDS; weights once per
+// call (gp_lc_split_weights).  Infinities, NaNs and numbers that the factor carries beyond
+// the largest bf16 one do not survive the split, but whatever they touch comes out of it as infinite
+// or NaN: a wave whose sums are not all finite takes that layer again on the fp32 instruction
+// (lc_layer_exact), so results with such numbers are those of plain fp32 arithmetic.
 //
 // What bounds it: the matrix cores, at 69 % busy and, by then, a clock that power holds at
 // about 2.1 of 2.4 GHz.  Four hops of a 128-256-256-256-40 model over 169,343 fp32 rows: 1040
@@ -104,48 +106,47 @@ __device__ __forceinline__ v4f load4(const unsigned short* p)
     return r;
 }
 
-// Two fp32 numbers as three pairs of bf16, packed as the matrix instructions take them, p1 + p2 + p3 = x:
-// exactly, unless x is not finite or beyond the largest bf16 number (then p3 is NaN) or so small that a part is
-// below the normal range (|x| < 1e-31; the error is below 1e-38).
+// Two fp32 numbers (times 2^16 already) as three pairs of bf16, packed as the matrix instructions take them,
+// p1 + p2 + p3 = x: exactly, for |x| < kMaxBf16 that are 2^16 times an fp32 number.
 // (The dot-product instruction would form a - p1 in one step, but beside another wave's matrix instructions it
 // takes 81 cycles against 10 for an ordinary one: measured.)
+constexpr float kUp = 0x1p16f;
+constexpr float kMaxBf16 = 3.38953139e38f;
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) { return __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a, b}, v2bf)); }
 __device__ __forceinline__ float low_bf16(unsigned p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float high_bf16(unsigned p) { return __uint_as_float(p & 0xFFFF0000u); }
-__device__ __forceinline__ void split2_from(float a, float b, unsigned (&p)[3])
+__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[3])
 {
+    p[0] = pack_bf16(a, b);
     const float ra = a - low_bf16(p[0]), rb = b - high_bf16(p[0]);
     p[1] = pack_bf16(ra, rb);
     p[2] = pack_bf16(ra - low_bf16(p[1]), rb - high_bf16(p[1]));
 }
-__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[3])
-{
-    p[0] = pack_bf16(a, b);
-    split2_from(a, b, p);
-}
-// eight numbers: one lane's operand, part by part
+// eight fp32 numbers: one lane's operand, part by part
 __device__ __forceinline__ void split8(const float (&v)[8], v4u (&q)[3])
 {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         unsigned p[3];
-        split2(v[2 * s], v[2 * s + 1], p);
+        split2(v[2 * s] * kUp, v[2 * s + 1] * kUp, p);
         q[0][s] = p[0], q[1][s] = p[1], q[2][s] = p[2];
     }
 }
-// the same for any numbers: the first part is kept finite (rounding could carry the largest numbers to
-// infinity), an infinity is the second part, a NaN the second and third
-constexpr float kMaxBf16 = 3.38953139e38f;
-__device__ __forceinline__ void split2_any(float a, float b, unsigned (&p)[3])
+// an activation that cannot be split has a NaN as its first part, so that its row's sums come out as NaN, and its
+// own bits, high and low half, as the others (low: it is the lower number of the pair)
+__device__ __forceinline__ void keep_whole(float v, bool low, unsigned (&p)[3])
 {
-    p[0] = pack_bf16(__builtin_amdgcn_fmed3f(a, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(b, -kMaxBf16, kMaxBf16));
-    split2_from(a, b, p);
+    const unsigned u = __float_as_uint(v), mask = low ? 0xFFFFu : 0xFFFF0000u;
+    p[0] = (p[0] & ~mask) | (0x7FC07FC0u & mask);
+    p[1] = (p[1] & ~mask) | (low ? u >> 16 : u & 0xFFFF0000u);
+    p[2] = (p[2] & ~mask) | (low ? u & 0xFFFFu : u << 16);
 }
-// the number again from its three parts (a second part that is not finite is all there is to it)
+// the number again from its parts
 __device__ __forceinline__ float join3(__bf16 x1, __bf16 x2, __bf16 x3)
 {
-    const float b = (float)x2;
-    return __builtin_isfinite(b) ? ((float)x3 + b) + (float)x1 : b;
+    const float a = (float)x1;
+    if (a != a) return __uint_as_float((unsigned)__builtin_bit_cast(unsigned short, x2) << 16 | __builtin_bit_cast(unsigned short, x3));
+    return (((float)x3 + (float)x2) + a) * (1.0f / kUp);
 }
 
 // TM x kin panel of the batch rows of one slab -> LDS, split into its bf16 parts (a bf16 stack has one),
@@ -197,8 +198,9 @@ __device__ __forceinline__ void lc_gather(__bf16* __restrict__ tile, const T* __
                                  (__float_as_uint(v[u].z) >> 16) | __float_as_uint(v[u].w)};
                 } else {
                     unsigned lo[3], hi[3];
-                    split2_any(v[u].x, v[u].y, lo);
-                    split2_any(v[u].z, v[u].w, hi);
+                    asm("" : "+v"(v[u]));  // (the multiplications are not moved to the loads, each of which would then be waited for)
+                    split2(v[u].x * kUp, v[u].y * kUp, lo);
+                    split2(v[u].z * kUp, v[u].w * kUp, hi);
 #pragma unroll
                     for (int i = 0; i < 3; ++i) dst[i * (kPlane / 4)] = (v2u){lo[i], hi[i]};
                 }
@@ -239,7 +241,7 @@ struct SplitArgs {
     int T;
     const float* W[kMaxLayers];
     int kin[kMaxLayers], width[kMaxLayers];
-    int64_t first[kMaxLayers + 1];  // tiles (three fragments) before layer t
+    int first[kMaxLayers + 1];  // tiles (three fragments) before layer t
     char* out;
 };
 
@@ -248,43 +250,38 @@ struct SplitArgs {
 // activations (4-hop, 4-layer model, 169,343 rows: 1430 us that way, 1042 us this way).
 __global__ __launch_bounds__(256) void gp_lc_split_weights(const SplitArgs a)
 {
-    const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int g = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (a slot holds a few thousand tiles)
     if (g >= a.first[a.T]) return;
     const int lane = threadIdx.x & 63, i = lane & 15, kg = lane >> 4;
     int t = 0;
     while (g >= a.first[t + 1]) ++t;
-    const int N = a.width[t], CT = tiles_per_wave(N);
-    const int64_t u = g - a.first[t], kt = u / (4 * CT);
+    const int N = a.width[t], kin = a.kin[t], CT = tiles_per_wave(N);
+    const unsigned u = (unsigned)(g - a.first[t]), kt = u / (4 * CT);
     const int w = (int)(u / CT % 4), ct = (int)(u % CT), col = 16 * CT * w + CT * i + ct;
-    const float* W = a.W[t];
+    // (all eight in flight: read at a clamped place and replaced beyond the matrix, not read under a condition)
+    const float* at = a.W[t] + min(col, N - 1);
     float v[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const int64_t k = kt * 32 + 8 * kg + s;
-        v[s] = k < a.kin[t] && col < N ? W[k * N + col] : 0.0f;
-    }
+    for (int s = 0; s < 8; ++s) v[s] = at[(int64_t)min((int)kt * 32 + 8 * kg + s, kin - 1) * N];
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+        if ((int)kt * 32 + 8 * kg + s >= kin || col >= N) v[s] = 0.0f;
     v4u q[3];
     split8(v, q);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) reinterpret_cast<v4u*>(a.out + (g * 3 + p) * kFragBytes)[lane] = q[p];
+    for (int p = 0; p < 3; ++p) reinterpret_cast<v4u*>(a.out + ((int64_t)g * 3 + p) * kFragBytes)[lane] = q[p];
 }
 
-// acc += tile(16 R rows x kin) * W(kin x this wave's columns) on the fp32 instruction, operands joined from
-// their parts: plain fp32 arithmetic, for sums that infinities or NaNs take part in.  PARTS as in lc_layer.
-template <int R, int CT, int PARTS>
-__device__ __forceinline__ void lc_layer_exact(const __bf16* tile, int kin, const float* W, int N, int colbase, int i, int kg,
-                                               v4f (&acc)[R][4])
+// acc += X(16 R rows x kin) * W(kin x this wave's columns) on the fp32 instruction: plain fp32 arithmetic, for sums
+// that infinities, NaNs or very large numbers take part in.  elem(row, k): X's element in row `row` of the tile, column k.
+template <int R, int CT, typename Elem>
+__device__ __forceinline__ void lc_layer_exact(Elem elem, int kin, const float* W, int N, int colbase, int i, int kg, v4f (&acc)[R][4])
 {
-    constexpr int kPlane = 16 * R * kLd;
     for (int k0 = 0; k0 < kin; k0 += 4) {
         const int k = k0 + kg;
         float x[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const __bf16* p = tile + (r * 16 + i) * kLd + k;
-            x[r] = 0.0f;
-            if (k < kin) x[r] = PARTS == 1 ? (float)p[0] : join3(p[0], p[kPlane], p[2 * kPlane]);
-        }
+        for (int r = 0; r < R; ++r) x[r] = k < kin ? elem(r * 16 + i, k) : 0.0f;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
             const int col = colbase + CT * i + ct;
@@ -295,16 +292,18 @@ __device__ __forceinline__ void lc_layer_exact(const __bf16* tile, int kin, cons
     }
 }
 
-// acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file; true if
-// all sums are finite (and may be split without a clamp).  frags: the split weights from W's first row on.
-// PARTS: bf16 parts of a row's elements in LDS, 3 or (bf16 stack, first layer) 1.  CARRY: acc comes in with
-// sums of earlier panels (else: zeros).  RAW: no split weights, they are split here.  The products x1 w1 and
+// acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file, or a multiple
+// of it: the sums are acc * factor.  (Numbers are taken up by 2^16 where they are split; the sums are taken down
+// again where they are used.  Sums on the fp32 instruction have the factor one.)  Returns true if all of the wave's
+// sums may be split.  frags: the split weights from W's first row on.  elem: as in lc_layer_exact.
+// PARTS: bf16 parts of a row's elements in LDS, 3 (of 2^16 x) or (bf16 stack, first layer) 1 (x itself).  CARRY: acc
+// comes in with sums of earlier panels (else: zeros), and leaves with the factor one.  RAW: no split weights, they are split here.  The products x1 w1 and
 // the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
 // roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
 // the weights of the tile four further on.
-template <int R, int CT, int PARTS, bool CARRY, bool RAW>
-__device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
-                                         int i, int kg, v4f (&acc)[R][4])
+template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Elem>
+__device__ __forceinline__ bool lc_layer(const __bf16* tile, Elem elem, int kin, const float* W, int N, const char* frags, int wave,
+                                         int colbase, int i, int kg, v4f (&acc)[R][4], float& factor)
 {
     constexpr int kPlane = 16 * R * kLd;
     const int steps = (kin + 31) >> 5, units = (int)padded_steps(kin, CT) * CT;
@@ -317,7 +316,10 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const floa
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            if constexpr (CARRY) before[r][c] = acc[r][c];
+            if constexpr (CARRY) {
+                before[r][c] = acc[r][c];
+                acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            }
             small[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
         }
     v8bf part[4][3], x[R][PARTS];
@@ -394,6 +396,7 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const floa
         }
     }
     __builtin_amdgcn_s_setprio(2);
+    constexpr float kSumDown = 1.0f / (PARTS == 1 ? kUp : kUp * kUp), kMost = CARRY ? kMaxBf16 / kUp : kMaxBf16;
     bool odd = false;
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -401,9 +404,14 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const floa
         for (int c = 0; c < CT; ++c) {
             acc[r][c] += small[r][c];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) odd |= !(fabsf(acc[r][c][e]) < kMaxBf16);
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (CARRY) acc[r][c][e] = fmaf(acc[r][c][e], kSumDown, before[r][c][e]);
+                odd |= !(fabsf(acc[r][c][e]) < kMost);
+            }
         }
+    factor = CARRY ? 1.0f : kSumDown;
     if (!__any(odd)) return true;
+    factor = 1.0f;
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -413,39 +421,41 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, int kin, const floa
             else
                 acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
         }
-    lc_layer_exact<R, CT, PARTS>(tile, kin, W, N, colbase, i, kg, acc);
+    asm volatile("" : "+v"(i), "+v"(kg));  // (so that no part of this way's addresses is worked out ahead of the branch, in registers the other way needs)
+    lc_layer_exact<R, CT>(elem, kin, W, N, colbase, i, kg, acc);
     return false;
 }
 
-template <int R, int PARTS, bool CARRY, bool RAW>
-__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int i, int kg,
-                                             v4f (&acc)[R][4])
+template <int R, int PARTS, bool CARRY, bool RAW, typename Elem>
+__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, Elem elem, int kin, const float* W, int N, const char* frags, int wave, int i,
+                                             int kg, v4f (&acc)[R][4], float& factor)
 {
     const int ct = tiles_per_wave(N), colbase = wave * 16 * ct;
     if (colbase >= N) return true;
-    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
-    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
-    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc);
+    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
+    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
+    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
 }
 
-// tile <- relu(acc) for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
+// tile <- relu(acc * factor) for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
 // column below the next multiple of 32 is written (the next layer reads that far); acc <- 0
 template <int R, int CT>
-__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, int colbase, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, float factor, int colbase, int i, int kg, v4f (&acc)[R][4])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int c0 = colbase + 4 * CT * kg;
+    const float up = factor * kUp;
     const bool whole = plain && colbase + 16 * CT <= Np;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         __bf16* row = tile + (r * 16 + i) * kLd + c0;
         unsigned q[3][2 * CT];
-        if (whole) {  // every value finite
+        if (whole) {  // every value may be split
 #pragma unroll
             for (int h = 0; h < 2 * CT; ++h) {
                 const int u = 2 * h;
                 unsigned p[3];
-                split2(fmaxf(acc[r][u % CT][u / CT], 0.0f), fmaxf(acc[r][(u + 1) % CT][(u + 1) / CT], 0.0f), p);
+                split2(fmaxf(acc[r][u % CT][u / CT], 0.0f) * up, fmaxf(acc[r][(u + 1) % CT][(u + 1) / CT], 0.0f) * up, p);
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
         } else {
@@ -459,7 +469,9 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
                     if (v[e] < 0.0f || c0 + u >= Np) v[e] = 0.0f;  // NaN stays NaN
                 }
                 unsigned p[3];
-                split2_any(v[0], v[1], p);
+                split2(v[0] * up, v[1] * up, p);
+                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the factor is one if that happens)
+                if (!(v[1] * up < kMaxBf16)) keep_whole(v[1], false, p);
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
         }
@@ -481,17 +493,17 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
 }
 
 template <int R>
-__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, int wave, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, float factor, int wave, int i, int kg, v4f (&acc)[R][4])
 {
     const int ct = tiles_per_wave(Np), colbase = wave * 16 * ct;
     if (colbase >= ((Np + 31) & ~31)) return;  // (its sums are zeros: it sat the layer out)
-    if (ct == 4) lc_store_relu<R, 4>(tile, Np, plain, colbase, i, kg, acc);
-    else if (ct == 2) lc_store_relu<R, 2>(tile, Np, plain, colbase, i, kg, acc);
-    else lc_store_relu<R, 1>(tile, Np, plain, colbase, i, kg, acc);
+    if (ct == 4) lc_store_relu<R, 4>(tile, Np, plain, factor, colbase, i, kg, acc);
+    else if (ct == 2) lc_store_relu<R, 2>(tile, Np, plain, factor, colbase, i, kg, acc);
+    else lc_store_relu<R, 1>(tile, Np, plain, factor, colbase, i, kg, acc);
 }
 
 template <int R, int CT>
-__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, int i, int kg,
+__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, float factor, int i, int kg,
                                          const v4f (&acc)[R][4])
 {
     const int c0 = colbase + 4 * CT * kg;
@@ -504,7 +516,7 @@ __device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& 
         for (int h = 0; h < CT; ++h) {
             v4f v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = g * acc[r][(4 * h + e) % CT][(4 * h + e) / CT];
+            for (int e = 0; e < 4; ++e) v[e] = g * (factor * acc[r][(4 * h + e) % CT][(4 * h + e) / CT]);
             if (c0 + 4 * h + 4 <= C) {
                 *reinterpret_cast<v4f_a4*>(out + 4 * h) = v;
             } else {
@@ -544,28 +556,39 @@ __global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
     // whoever is not multiplying goes first: the other workgroup's products leave the vector units room
     __builtin_amdgcn_s_setprio(2);
     bool plain = true;
+    float factor = 1.0f;
     for (int p0 = 0; p0 < a.d; p0 += kPanel) {  // first layer, one panel of feature columns at a time
         const int kin = min(kPanel, a.d - p0);
         if (p0 > 0) __syncthreads();  // every wave is done with the previous panel (nothing is in the tile before the first)
         lc_gather<T, TM>(tile, slab, a, row0, p0, kin, tid);
         __syncthreads();
         const char* frags = a.frags + a.frag_off[0] + (int64_t)(p0 / 32) * 4 * tiles_per_wave(N1) * (3 * kFragBytes);
-        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc);
+        // (an element that cannot be split is not in the tile: for the sums that need it the row is read again)
+        auto elem = [&](int r, int c) {
+            const int64_t row = row0 + r;
+            const int64_t id = row >= a.B ? -1 : a.batch ? (int64_t)a.batch[row] : row;
+            return id >= 0 && id < a.n ? widen(slab[id * a.ld + p0 + c]) : 0.0f;
+        };
+        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, elem, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc, factor);
     }
     for (int t = 1; t < layers; ++t) {
         const int Np = a.width[t - 1], N = a.width[t];
         __syncthreads();  // every wave is done reading the tile
-        lc_store_relu_any<R>(tile, Np, plain, wave, i, kg, acc);
+        lc_store_relu_any<R>(tile, Np, plain, factor, wave, i, kg, acc);
         __syncthreads();
-        plain = lc_layer_any<R, 3, false, RAW>(tile, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc);
+        auto elem = [&](int r, int c) {
+            const __bf16* x = tile + r * kLd + c;
+            return join3(x[0], x[TM * kLd], x[2 * TM * kLd]);
+        };
+        plain = lc_layer_any<R, 3, false, RAW>(tile, elem, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc, factor);
     }
 
     const float g = a.gamma[k];
     float* dst = a.direct ? a.dst + a.out_off[br] : a.dst + (int64_t)br * a.B * a.ldd;
     const int ct = tiles_per_wave(C), colbase = wave * 16 * ct;
-    if (ct == 4) lc_write<R, 4>(dst, a, row0, C, colbase, g, i, kg, acc);
-    else if (ct == 2) lc_write<R, 2>(dst, a, row0, C, colbase, g, i, kg, acc);
-    else lc_write<R, 1>(dst, a, row0, C, colbase, g, i, kg, acc);
+    if (ct == 4) lc_write<R, 4>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
+    else if (ct == 2) lc_write<R, 2>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
+    else lc_write<R, 1>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
 }
 
 // out[i][c] = sum (or maximum) over the branches, in branch order, of the partial results
@@ -827,11 +850,10 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     for (int t = 0; t < T; ++t) {
         const int in = t == 0 ? d : width[t - 1];
         sp.W[t] = W[t], sp.kin[t] = in, sp.width[t] = width[t];
-        a.frag_off[t] = sp.first[t] * 3 * kFragBytes;
-        sp.first[t + 1] = sp.first[t] + layer_tiles(in, width[t]);
+        a.frag_off[t] = (int64_t)sp.first[t] * 3 * kFragBytes;
+        sp.first[t + 1] = sp.first[t] + (int)layer_tiles(in, width[t]);  // (at most 2^30, of the widest first layer)
     }
-    const int64_t frag_bytes = sp.first[T] * 3 * kFragBytes + kFragSlack, split_grid = (sp.first[T] + 3) / 4;
-    if (split_grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "d = %d is too wide", d);
+    const int64_t frag_bytes = (int64_t)sp.first[T] * 3 * kFragBytes + kFragSlack;
     // Where the split weights go: into slot 0 where there are partial results (such calls do not overlap), else into
     // a slot of the stream's.  A direct call under graph capture goes without and splits weights where it uses them: its
     // replays may run beside other calls, which a shared slot would not survive.
@@ -859,7 +881,7 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     a.frags = sp.out;
     if (a.frags) {
         profile_begin("gp_lc_split_weights", stream);
-        hipLaunchKernelGGL(gp_lc_split_weights, dim3((unsigned)split_grid), dim3(256), 0, stream, sp);
+        hipLaunchKernelGGL(gp_lc_split_weights, dim3((unsigned)(sp.first[T] + 3) / 4), dim3(256), 0, stream, sp);
         profile_end(stream);
         GP_HIP(hipGetLastError());
     } else {

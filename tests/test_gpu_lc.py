@@ -469,3 +469,39 @@ def test_captured_sum_after_a_call_with_fewer_features():
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         out.fill_(-1.0)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("x_exp,w_exps", [
+    (-118, [100, 0]),      # features whose last bits lie below the normal range
+    (-124, [110, 4]),
+    (-90, [-20, 100]),     # the first layer's activations are as small
+    (60, [-122, 30]),      # weights as small
+    (0, [-118, 118]),
+    (112, [-112, 0]),      # features, activations, weights around and beyond the largest that is split
+    (20, [95, -110]),
+    (-100, [113, -20]),
+    (120, [-120, 4]),
+])
+def test_operands_of_any_magnitude(x_exp, w_exps, bf16):
+    """Powers of two on features and weights, down to subnormal numbers and up to the largest: plain fp32 arithmetic's
+    tolerance holds at every magnitude (results and intermediates are normal numbers)."""
+    rng = np.random.default_rng(71)
+    d, widths, B, K = 96, [256, 40], 60, 1
+    stack = rng.normal(size=(K + 1, 80, d)).astype(np.float32) * np.float32(2.0 ** x_exp)
+    if bf16:
+        stack = gp_synth.f32_to_bf16_bits(stack)
+    Ws = [(W * 2.0 ** e).astype(np.float32) for W, e in zip(make_weights(rng, d, widths), w_exps)]
+    check(stack, rng.integers(0, 80, B), [0.5, 0.25], Ws, bf16=bf16)
+
+
+def test_small_operands_beside_large_ones():
+    """Half of the features are tiny and meet large weights, the other half the other way round: both halves count alike."""
+    rng = np.random.default_rng(72)
+    d, widths, B, K = 128, [256, 40], 60, 0
+    stack = rng.normal(size=(K + 1, 80, d)).astype(np.float32)
+    Ws = make_weights(rng, d, widths)
+    stack[:, :, ::2] *= np.float32(2.0 ** -120)
+    Ws[0][::2] *= np.float32(2.0 ** 60)
+    Ws[0][1::2] *= np.float32(2.0 ** -60)
+    check(stack, rng.integers(0, 80, B), [1.0], Ws)
