@@ -332,9 +332,12 @@ gp_status gp_propagate_combine(const gp_plan *plan, const void *X, int64_t ldx, 
  *
  *  stack   DEVICE, K+1 slabs of n x d as gp_propagate writes them: slab k starts at
  *          element k*n*ld, rows ld elements apart (ld >= d), of `dtype` (bf16 is
- *          widened exactly; all arithmetic is fp32: products of fp32 operands, each
- *          split without loss into three bf16 parts for the matrix cores, summed in
- *          fp32; errors are no larger than the fp32 matrix instruction's).
+ *          widened exactly).  Operands, sums and results are fp32.  A sum of more than
+ *          16 terms runs on the bf16 matrix cores: both operands of a product are split
+ *          into three bf16 parts, without loss at any magnitude, and at most 2^-24 of
+ *          the product is left out; against fp64 such sums were measured to be closer
+ *          than those of the fp32 matrix instruction (128-256-256-256-40 model, random
+ *          normal weights: 0.92e-7 of the result, and 2.5e-7).
  *  batch   DEVICE, B row numbers; NULL means rows 0 .. B-1 (then B <= n).  A row
  *          number outside [0, n) is not an error: that output row is computed
  *          from a row of zeros.

@@ -23,8 +23,9 @@
 // of which the last bracket, at most 2^-24 of the product, is left out: six bf16 products with fp32
 // accumulation, the large ones with one accumulation per 32 terms.  Measured against fp64
 // on a 128-256-256-256-40 model with normal weights and features: relative error 0.92e-7, where
-// the fp32 instruction left 2.5e-7.  (A bf16 stack's first layer has one part, x itself: three
-// products.)  Features and activations are split once, when they enter LDS; weights once per
+// the fp32 instruction left 2.5e-7.  That is a matter of long sums, whose own roundings outweigh
+// the part left out: sums of at most kShortSum terms are taken on the fp32 instruction.  (A bf16
+// stack's first layer has one part, x itself: three products.)  Features and activations are split once, when they enter LDS; weights once per
 // call (gp_lc_split_weights).  Infinities, NaNs and numbers that the factor carries beyond
 // the largest bf16 one do not survive the split, but whatever they touch comes out of it as infinite
 // or NaN: a wave whose sums are not all finite takes that layer again on the fp32 instruction
@@ -272,38 +273,79 @@ __global__ __launch_bounds__(256) void gp_lc_split_weights(const SplitArgs a)
     for (int p = 0; p < 3; ++p) reinterpret_cast<v4u*>(a.out + ((int64_t)g * 3 + p) * kFragBytes)[lane] = q[p];
 }
 
-// acc += X(16 R rows x kin) * W(kin x this wave's columns) on the fp32 instruction: plain fp32 arithmetic, for sums
-// that infinities, NaNs or very large numbers take part in.  elem(row, k): X's element in row `row` of the tile, column k.
-template <int R, int CT, typename Elem>
-__device__ __forceinline__ void lc_layer_exact(Elem elem, int kin, const float* W, int N, int colbase, int i, int kg, v4f (&acc)[R][4])
+// One term of a sum is off by up to 2^-23 of itself in six products (2^-24 left out, 2^-24 for the fp32 result), by half of
+// that on the fp32 instruction; n terms of like size by about sqrt(n) 2^-25 in either way from their additions.
+constexpr int kShortSum = 16;
+
+// The elements that sums on the fp32 instruction are taken of: a row of the stack (an element that cannot be split is not
+// in the tile), or of the tile.
+template <typename T>
+struct StackRows {
+    const T* panel;  // row 0 of the slab, from the panel's first column on
+    const int32_t* batch;
+    int64_t ld, n, row0, B;
+    struct Row {
+        const T* p;
+        bool in;
+    };
+    __device__ __forceinline__ Row row(int r) const
+    {
+        const int64_t br = row0 + r, id = br >= B ? -1 : batch ? (int64_t)batch[br] : br;
+        const bool in = id >= 0 && id < n;
+        return {panel + (in ? id * ld : 0), in};
+    }
+    __device__ __forceinline__ float at(const Row& r, int k) const { return r.in ? widen(r.p[k]) : 0.0f; }
+};
+template <int TM>
+struct TileRows {
+    const __bf16* tile;
+    typedef const __bf16* Row;
+    __device__ __forceinline__ Row row(int r) const { return tile + r * kLd; }
+    __device__ __forceinline__ float at(Row p, int k) const { return join3(p[k], p[TM * kLd + k], p[2 * TM * kLd + k]); }
+};
+
+// acc += X(16 R rows x kin) * W(kin x the 16 CT columns from colbase on) on the fp32 instruction: plain fp32
+// arithmetic, for short sums and for those that infinities, NaNs or very large numbers take part in.  (Elements are
+// read at clamped places and replaced beyond the matrix, so that those of a step are in flight together.)
+template <int R, int CT, typename Rows>
+__device__ __forceinline__ void lc_layer_exact(const Rows& rows, int kin, const float* W, int N, int colbase, int i, int kg, v4f (&acc)[R][4])
 {
+    // (so that no part of this is worked out ahead of the branch to it, in registers that the other way needs)
+    asm volatile("" : "+v"(i), "+v"(kg));
+    typename Rows::Row row[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) row[r] = rows.row(r * 16 + i);
     for (int k0 = 0; k0 < kin; k0 += 4) {
-        const int k = k0 + kg;
-        float x[R];
+        const int k = min(k0 + kg, kin - 1);
+        const bool in = k0 + kg < kin;
+        float x[R], w[CT];
 #pragma unroll
-        for (int r = 0; r < R; ++r) x[r] = k < kin ? elem(r * 16 + i, k) : 0.0f;
+        for (int r = 0; r < R; ++r) x[r] = rows.at(row[r], k);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const int col = colbase + CT * i + ct;
-            const float w = k < kin && col < N ? W[(int64_t)k * N + col] : 0.0f;
+        for (int c = 0; c < CT; ++c) w[c] = W[(int64_t)k * N + min(colbase + CT * i + c, N - 1)];
 #pragma unroll
-            for (int r = 0; r < R; ++r) acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[r], acc[r][ct], 0, 0, 0);
+        for (int r = 0; r < R; ++r) x[r] = in ? x[r] : 0.0f;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const float v = in && colbase + CT * i + c < N ? w[c] : 0.0f;
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, x[r], acc[r][c], 0, 0, 0);
         }
     }
 }
 
 // acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file, or a multiple
 // of it: the sums are acc * factor.  (Numbers are taken up by 2^16 where they are split; the sums are taken down
-// again where they are used.  Sums on the fp32 instruction have the factor one.)  Returns true if all of the wave's
-// sums may be split.  frags: the split weights from W's first row on.  elem: as in lc_layer_exact.
+// again where they are used.)  Returns true if all of the wave's sums are finite (and may be split); if not, acc is
+// left as it came.  frags: the split weights from W's first row on.
 // PARTS: bf16 parts of a row's elements in LDS, 3 (of 2^16 x) or (bf16 stack, first layer) 1 (x itself).  CARRY: acc
 // comes in with sums of earlier panels (else: zeros), and leaves with the factor one.  RAW: no split weights, they are split here.  The products x1 w1 and
 // the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
 // roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
 // the weights of the tile four further on.
-template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Elem>
-__device__ __forceinline__ bool lc_layer(const __bf16* tile, Elem elem, int kin, const float* W, int N, const char* frags, int wave,
-                                         int colbase, int i, int kg, v4f (&acc)[R][4], float& factor)
+template <int R, int CT, int PARTS, bool CARRY, bool RAW>
+__device__ __forceinline__ bool lc_layer_six(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
+                                             int i, int kg, v4f (&acc)[R][4], float& factor)
 {
     constexpr int kPlane = 16 * R * kLd;
     const int steps = (kin + 31) >> 5, units = (int)padded_steps(kin, CT) * CT;
@@ -411,7 +453,6 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, Elem elem, int kin,
         }
     factor = CARRY ? 1.0f : kSumDown;
     if (!__any(odd)) return true;
-    factor = 1.0f;
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -421,20 +462,31 @@ __device__ __forceinline__ bool lc_layer(const __bf16* tile, Elem elem, int kin,
             else
                 acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
         }
-    asm volatile("" : "+v"(i), "+v"(kg));  // (so that no part of this way's addresses is worked out ahead of the branch, in registers the other way needs)
-    lc_layer_exact<R, CT>(elem, kin, W, N, colbase, i, kg, acc);
     return false;
 }
 
-template <int R, int PARTS, bool CARRY, bool RAW, typename Elem>
-__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, Elem elem, int kin, const float* W, int N, const char* frags, int wave, int i,
+// a layer for this wave, the way its sums need; true: by six products, so that all of them may be split.  Sums on the
+// fp32 instruction have the factor one.
+template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Rows>
+__device__ __forceinline__ bool lc_layer(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
+                                         int kg, v4f (&acc)[R][4], float& factor)
+{
+    const int colbase = wave * 16 * CT;
+    if (kin > kShortSum && lc_layer_six<R, CT, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc, factor)) return true;
+    factor = 1.0f;
+    lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, acc);
+    return false;
+}
+
+template <int R, int PARTS, bool CARRY, bool RAW, typename Rows>
+__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
                                              int kg, v4f (&acc)[R][4], float& factor)
 {
-    const int ct = tiles_per_wave(N), colbase = wave * 16 * ct;
-    if (colbase >= N) return true;
-    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
-    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
-    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, elem, kin, W, N, frags, wave, colbase, i, kg, acc, factor);
+    const int ct = tiles_per_wave(N);
+    if (wave * 16 * ct >= N) return true;
+    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
+    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
+    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
 }
 
 // tile <- relu(acc * factor) for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
@@ -563,24 +615,16 @@ __global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
         lc_gather<T, TM>(tile, slab, a, row0, p0, kin, tid);
         __syncthreads();
         const char* frags = a.frags + a.frag_off[0] + (int64_t)(p0 / 32) * 4 * tiles_per_wave(N1) * (3 * kFragBytes);
-        // (an element that cannot be split is not in the tile: for the sums that need it the row is read again)
-        auto elem = [&](int r, int c) {
-            const int64_t row = row0 + r;
-            const int64_t id = row >= a.B ? -1 : a.batch ? (int64_t)a.batch[row] : row;
-            return id >= 0 && id < a.n ? widen(slab[id * a.ld + p0 + c]) : 0.0f;
-        };
-        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, elem, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc, factor);
+        const StackRows<T> rows{slab + p0, a.batch, a.ld, a.n, row0, a.B};
+        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, rows, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc, factor);
     }
     for (int t = 1; t < layers; ++t) {
         const int Np = a.width[t - 1], N = a.width[t];
         __syncthreads();  // every wave is done reading the tile
         lc_store_relu_any<R>(tile, Np, plain, factor, wave, i, kg, acc);
         __syncthreads();
-        auto elem = [&](int r, int c) {
-            const __bf16* x = tile + r * kLd + c;
-            return join3(x[0], x[TM * kLd], x[2 * TM * kLd]);
-        };
-        plain = lc_layer_any<R, 3, false, RAW>(tile, elem, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc, factor);
+        const TileRows<TM> rows{tile};
+        plain = lc_layer_any<R, 3, false, RAW>(tile, rows, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc, factor);
     }
 
     const float g = a.gamma[k];

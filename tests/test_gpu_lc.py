@@ -6,7 +6,9 @@ order, so its error is at most gamma_{in_l} = in_l * u (u = 2^-24, first order)
 times sum |a||w|; later layers pass that on through |W| (ReLU is 1-Lipschitz) and
 add their own.  With the scaling by gamma_k and the K+1-term sum the total is at most
 (sum_l in_l + T + K + 2) * u * bound, bound = sum_k |gamma_k| |X_k| |W_1| ... |W_T|;
-the tests allow 1.5 times that for the higher-order terms.
+the tests allow 1.5 times that for the higher-order terms.  (Where an fp32 product is taken as six bf16 products, at
+most u of each term is left out and the two partial sums are added once more: 2 u more for such a layer, whose
+sums have more than 16 terms, so that half of in_l covers it.)
 """
 import numpy as np
 import pytest
@@ -505,3 +507,24 @@ def test_small_operands_beside_large_ones():
     Ws[0][::2] *= np.float32(2.0 ** 60)
     Ws[0][1::2] *= np.float32(2.0 ** -60)
     check(stack, rng.integers(0, 80, B), [1.0], Ws)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d", [1, 2, 15, 16, 17, 257, 272])
+def test_short_sums_are_plain_fp32(d, bf16):
+    """A first layer (or its last panel) of few terms, numbers just above a power of two, where the parts that six bf16
+    products leave out are largest.  The second layer picks single columns, which changes nothing, so the result is
+    the first layer's: one term is a product rounded once, and n terms keep n roundings."""
+    rng = np.random.default_rng(81 + d)
+    n, N, C = 100, 256, 64
+    stack = (1.0 + rng.uniform(0.0, 2.0 ** -7, size=(1, n, d))).astype(np.float32)
+    if bf16:
+        stack = gp_synth.f32_to_bf16_bits(stack)
+    W1 = (1.0 + rng.uniform(0.0, 2.0 ** -7, size=(d, N))).astype(np.float32)
+    W2 = np.zeros((N, C), np.float32)
+    cols = rng.permutation(N)[:C]
+    W2[cols, np.arange(C)] = 1.0
+    got = run(stack, np.arange(n), [1.0], [W1, W2], bf16=bf16)
+    wide = (gp_synth.bf16_bits_to_f32(stack) if bf16 else stack)[0].astype(np.float64)
+    want = wide @ W1.astype(np.float64)[:, cols]
+    assert np.all(np.abs(got - want) <= d * 2.0 ** -24 * (1 + 1e-6) * want)
