@@ -29,7 +29,8 @@
 // call (gp_lc_split_weights).  Infinities, NaNs and numbers that the factor carries beyond
 // the largest bf16 one do not survive the split, but whatever they touch comes out of it as infinite
 // or NaN: a wave whose sums are not all finite takes that layer again on the fp32 instruction
-// (lc_layer_exact), so results with such numbers are those of plain fp32 arithmetic.
+// (lc_layer_exact) and keeps these sums for the rows concerned, so results with such numbers are
+// those of plain fp32 arithmetic, and a row's bits do not depend on the rows beside it.
 //
 // What bounds it: the matrix cores, at 69 % busy and, by then, a clock that power holds at
 // about 2.1 of 2.4 GHz.  Four hops of a 128-256-256-256-40 model over 169,343 fp32 rows: 1040
@@ -336,16 +337,16 @@ __device__ __forceinline__ void lc_layer_exact(const Rows& rows, int kin, const 
 
 // acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file, or a multiple
 // of it: the sums are acc * factor.  (Numbers are taken up by 2^16 where they are split; the sums are taken down
-// again where they are used.)  Returns true if all of the wave's sums are finite (and may be split); if not, acc is
-// left as it came.  frags: the split weights from W's first row on.
+// again where they are used.)  Returns a bit for each row 16 r + i whose sums in this lane are not all finite (or
+// cannot be split).  frags: the split weights from W's first row on.
 // PARTS: bf16 parts of a row's elements in LDS, 3 (of 2^16 x) or (bf16 stack, first layer) 1 (x itself).  CARRY: acc
-// comes in with sums of earlier panels (else: zeros), and leaves with the factor one.  RAW: no split weights, they are split here.  The products x1 w1 and
+// comes in with sums of earlier panels, which are also put aside in `before`, (else: zeros) and leaves with the factor one.  RAW: no split weights, they are split here.  The products x1 w1 and
 // the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
 // roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
 // the weights of the tile four further on.
 template <int R, int CT, int PARTS, bool CARRY, bool RAW>
-__device__ __forceinline__ bool lc_layer_six(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
-                                             int i, int kg, v4f (&acc)[R][4], float& factor)
+__device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
+                                                 int i, int kg, v4f (&acc)[R][4], v4f (&before)[R][CT], float (&factor)[R])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int steps = (kin + 31) >> 5, units = (int)padded_steps(kin, CT) * CT;
@@ -353,7 +354,7 @@ __device__ __forceinline__ bool lc_layer_six(const __bf16* tile, int kin, const 
     // fragments of unit u = kt CT + ct: ((kt 4 + wave) CT + ct) * 3 ..
     global_char* mine = uniform(frags + wave * (CT * 3 * kFragBytes));
     const unsigned lane_off = (unsigned)(16 * kg + i) * 16;
-    v4f before[CARRY ? R : 1][CT], small[R][CT];
+    v4f small[R][CT];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -439,48 +440,65 @@ __device__ __forceinline__ bool lc_layer_six(const __bf16* tile, int kin, const 
     }
     __builtin_amdgcn_s_setprio(2);
     constexpr float kSumDown = 1.0f / (PARTS == 1 ? kUp : kUp * kUp), kMost = CARRY ? kMaxBf16 / kUp : kMaxBf16;
-    bool odd = false;
+    unsigned odd = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int r = 0; r < R; ++r) {
+        factor[r] = CARRY ? 1.0f : kSumDown;
+        bool finite = true;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             acc[r][c] += small[r][c];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if constexpr (CARRY) acc[r][c][e] = fmaf(acc[r][c][e], kSumDown, before[r][c][e]);
-                odd |= !(fabsf(acc[r][c][e]) < kMost);
+                finite &= fabsf(acc[r][c][e]) < kMost;
             }
         }
-    factor = CARRY ? 1.0f : kSumDown;
+        if (!finite) odd |= 1u << r;
+    }
+    return odd;
+}
+
+// a layer for this wave, each row the way its sums need; true: by six products, so that all of them may be split.
+// Sums on the fp32 instruction have the factor one.
+template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Rows>
+__device__ __forceinline__ bool lc_layer(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
+                                         int kg, v4f (&acc)[R][4], float (&factor)[R])
+{
+    const int colbase = wave * 16 * CT;
+    if (kin <= kShortSum) {
+        lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, acc);
+#pragma unroll
+        for (int r = 0; r < R; ++r) factor[r] = 1.0f;
+        return false;
+    }
+    v4f before[R][CT];
+    const unsigned odd = lc_layer_six<R, CT, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc, before, factor);
     if (!__any(odd)) return true;
+    v4f exact[R][4];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             if constexpr (CARRY)
-                acc[r][c] = before[r][c];
+                exact[r][c] = before[r][c];
             else
-                acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+                exact[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
         }
-    return false;
-}
-
-// a layer for this wave, the way its sums need; true: by six products, so that all of them may be split.  Sums on the
-// fp32 instruction have the factor one.
-template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Rows>
-__device__ __forceinline__ bool lc_layer(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
-                                         int kg, v4f (&acc)[R][4], float& factor)
-{
-    const int colbase = wave * 16 * CT;
-    if (kin > kShortSum && lc_layer_six<R, CT, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc, factor)) return true;
-    factor = 1.0f;
-    lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, acc);
+    lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, exact);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (odd >> r & 1) {
+            factor[r] = 1.0f;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[r][c] = exact[r][c];
+        }
     return false;
 }
 
 template <int R, int PARTS, bool CARRY, bool RAW, typename Rows>
 __device__ __forceinline__ bool lc_layer_any(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
-                                             int kg, v4f (&acc)[R][4], float& factor)
+                                             int kg, v4f (&acc)[R][4], float (&factor)[R])
 {
     const int ct = tiles_per_wave(N);
     if (wave * 16 * ct >= N) return true;
@@ -489,18 +507,18 @@ __device__ __forceinline__ bool lc_layer_any(const __bf16* tile, const Rows& row
     return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
 }
 
-// tile <- relu(acc * factor) for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
+// tile <- relu(acc * factor), row by row, for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
 // column below the next multiple of 32 is written (the next layer reads that far); acc <- 0
 template <int R, int CT>
-__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, float factor, int colbase, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, const float (&factor)[R], int colbase, int i, int kg, v4f (&acc)[R][4])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int c0 = colbase + 4 * CT * kg;
-    const float up = factor * kUp;
     const bool whole = plain && colbase + 16 * CT <= Np;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         __bf16* row = tile + (r * 16 + i) * kLd + c0;
+        const float up = factor[r] * kUp;
         unsigned q[3][2 * CT];
         if (whole) {  // every value may be split
 #pragma unroll
@@ -522,7 +540,7 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
                 }
                 unsigned p[3];
                 split2(v[0] * up, v[1] * up, p);
-                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the factor is one if that happens)
+                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the row's factor is one if that happens)
                 if (!(v[1] * up < kMaxBf16)) keep_whole(v[1], false, p);
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
@@ -545,7 +563,7 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
 }
 
 template <int R>
-__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, float factor, int wave, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, const float (&factor)[R], int wave, int i, int kg, v4f (&acc)[R][4])
 {
     const int ct = tiles_per_wave(Np), colbase = wave * 16 * ct;
     if (colbase >= ((Np + 31) & ~31)) return;  // (its sums are zeros: it sat the layer out)
@@ -555,7 +573,7 @@ __device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool pla
 }
 
 template <int R, int CT>
-__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, float factor, int i, int kg,
+__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, const float (&factor)[R], int i, int kg,
                                          const v4f (&acc)[R][4])
 {
     const int c0 = colbase + 4 * CT * kg;
@@ -568,7 +586,7 @@ __device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& 
         for (int h = 0; h < CT; ++h) {
             v4f v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = g * (factor * acc[r][(4 * h + e) % CT][(4 * h + e) / CT]);
+            for (int e = 0; e < 4; ++e) v[e] = g * (factor[r] * acc[r][(4 * h + e) % CT][(4 * h + e) / CT]);
             if (c0 + 4 * h + 4 <= C) {
                 *reinterpret_cast<v4f_a4*>(out + 4 * h) = v;
             } else {
@@ -608,7 +626,9 @@ __global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
     // whoever is not multiplying goes first: the other workgroup's products leave the vector units room
     __builtin_amdgcn_s_setprio(2);
     bool plain = true;
-    float factor = 1.0f;
+    float factor[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) factor[r] = 1.0f;
     for (int p0 = 0; p0 < a.d; p0 += kPanel) {  // first layer, one panel of feature columns at a time
         const int kin = min(kPanel, a.d - p0);
         if (p0 > 0) __syncthreads();  // every wave is done with the previous panel (nothing is in the tile before the first)

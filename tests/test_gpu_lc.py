@@ -528,3 +528,38 @@ def test_short_sums_are_plain_fp32(d, bf16):
     wide = (gp_synth.bf16_bits_to_f32(stack) if bf16 else stack)[0].astype(np.float64)
     want = wide @ W1.astype(np.float64)[:, cols]
     assert np.all(np.abs(got - want) <= d * 2.0 ** -24 * (1 + 1e-6) * want)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d,widths", [(40, [256, 200, 41]), (300, [100, 250, 64]), (128, [256, 256, 40])])
+def test_a_row_does_not_depend_on_the_rows_beside_it(d, widths, bf16):
+    """Rows with an infinity, a NaN or a very large number change nothing in the other rows, bit for bit; nor do the
+    number of rows in the batch and the height of the work items."""
+    rng = np.random.default_rng(91 + d)
+    n, K, B = 400, 1, 333
+    stack = rng.normal(size=(K + 1, n, d)).astype(np.float32)
+    Ws = make_weights(rng, d, widths)
+    gamma = [0.5, 0.25]
+    odd = stack.copy()
+    odd[0, 1, 3], odd[1, 1, 7], odd[0, 2, 5], odd[1, 3, 0], odd[0, 3, 1] = np.inf, -np.inf, np.nan, 3e38, -2e35
+    odd[1, 4] *= np.float32(1e30)     # finite sums beyond those that may be split
+    if bf16:
+        stack, odd = gp_synth.f32_to_bf16_bits(stack), gp_synth.f32_to_bf16_bits(odd)
+        odd[0, 2, 5] = 0x7FC0
+    ids = rng.integers(5, n, B)
+    plain = run(stack, ids, gamma, Ws, bf16=bf16)
+    mixed = ids.copy()
+    at = rng.permutation(B)[:40]
+    mixed[at] = 1 + np.arange(40) % 4
+    rest = np.setdiff1d(np.arange(B), at)
+    with np.errstate(all="ignore"):
+        got = run(odd, mixed, gamma, Ws, bf16=bf16)
+    assert not np.all(np.isfinite(got[at])) and np.array_equal(got[rest], plain[rest])
+    assert np.array_equal(run(stack, ids[:7], gamma, Ws, bf16=bf16), plain[:7])
+    assert np.array_equal(run(stack, np.tile(ids, 20), gamma, Ws, bf16=bf16)[-B:], plain)
+    for rows in (32, 64):
+        gp.gp_set_option("lc_tile_rows", rows)
+        try:
+            assert np.array_equal(run(stack, ids, gamma, Ws, bf16=bf16), plain)
+        finally:
+            gp.gp_set_option("lc_tile_rows", 0)
