@@ -335,18 +335,29 @@ __device__ __forceinline__ void lc_layer_exact(const Rows& rows, int kin, const 
     }
 }
 
-// acc += tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file, or a multiple
-// of it: the sums are acc * factor.  (Numbers are taken up by 2^16 where they are split; the sums are taken down
-// again where they are used.)  Returns a bit for each row 16 r + i whose sums in this lane are not all finite (or
+// Numbers are taken up by 2^16 where they are split, sums are taken down again where they are used (CARRY: at once).
+__host__ __device__ constexpr float sum_down(int parts, bool carry) { return carry ? 1.0f : 1.0f / (parts == 1 ? kUp : kUp * kUp); }
+
+template <int R, int C>
+__device__ __forceinline__ void lc_zero(v4f (&acc)[R][C])
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+}
+
+// acc = tile(16 R rows x kin) * W(kin x the 16 CT columns from colbase on), see the head of the file, or a multiple
+// of it: the sums are acc * sum_down().  Returns a bit for each row 16 r + i whose sums in this lane are not all finite (or
 // cannot be split).  frags: the split weights from W's first row on.
 // PARTS: bf16 parts of a row's elements in LDS, 3 (of 2^16 x) or (bf16 stack, first layer) 1 (x itself).  CARRY: acc
-// comes in with sums of earlier panels, which are also put aside in `before`, (else: zeros) and leaves with the factor one.  RAW: no split weights, they are split here.  The products x1 w1 and
+// comes in with sums of earlier panels, to which these are added (and which are put aside in `before`).  RAW: no split weights, they are split here.  The products x1 w1 and
 // the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
 // roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
 // the weights of the tile four further on.
 template <int R, int CT, int PARTS, bool CARRY, bool RAW>
 __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, const float* W, int N, const char* frags, int wave, int colbase,
-                                                 int i, int kg, v4f (&acc)[R][4], v4f (&before)[R][CT], float (&factor)[R])
+                                                 int i, int kg, v4f (&acc)[R][4], v4f (&before)[R][CT])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int steps = (kin + 31) >> 5, units = (int)padded_steps(kin, CT) * CT;
@@ -354,17 +365,14 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
     // fragments of unit u = kt CT + ct: ((kt 4 + wave) CT + ct) * 3 ..
     global_char* mine = uniform(frags + wave * (CT * 3 * kFragBytes));
     const unsigned lane_off = (unsigned)(16 * kg + i) * 16;
-    v4f small[R][CT];
+    v4f big[R][CT], small[R][CT];
+    lc_zero(big), lc_zero(small);
+    if constexpr (CARRY) {
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            if constexpr (CARRY) {
-                before[r][c] = acc[r][c];
-                acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-            }
-            small[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        }
+            for (int c = 0; c < CT; ++c) before[r][c] = acc[r][c];
+    }
     v8bf part[4][3], x[R][PARTS];
     float raw[RAW ? 8 : 1][CT];  // RAW: one step's weights
     auto load_w = [&](int u, int to) {  // (beyond the last unit: not used)
@@ -402,7 +410,7 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
         auto mul = [&](int wi, int xi) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                v4f& to = wi + xi > 0 ? small[r][ct] : acc[r][ct];
+                v4f& to = wi + xi > 0 ? small[r][ct] : big[r][ct];
                 to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part[from][wi], x[r][xi], to, 0, 0, 0);
             }
         };
@@ -439,18 +447,17 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
         }
     }
     __builtin_amdgcn_s_setprio(2);
-    constexpr float kSumDown = 1.0f / (PARTS == 1 ? kUp : kUp * kUp), kMost = CARRY ? kMaxBf16 / kUp : kMaxBf16;
+    constexpr float kDown = sum_down(PARTS, false), kMost = CARRY ? kMaxBf16 / kUp : kMaxBf16;
     unsigned odd = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        factor[r] = CARRY ? 1.0f : kSumDown;
         bool finite = true;
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            acc[r][c] += small[r][c];
+            acc[r][c] = big[r][c] + small[r][c];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if constexpr (CARRY) acc[r][c][e] = fmaf(acc[r][c][e], kSumDown, before[r][c][e]);
+                if constexpr (CARRY) acc[r][c][e] = fmaf(acc[r][c][e], kDown, before[r][c][e]);
                 finite &= fabsf(acc[r][c][e]) < kMost;
             }
         }
@@ -459,68 +466,68 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
     return odd;
 }
 
-// a layer for this wave, each row the way its sums need; true: by six products, so that all of them may be split.
-// Sums on the fp32 instruction have the factor one.
+// a layer for this wave, each row the way its sums need.  Returns a bit for each row 16 r + i whose sums come from the
+// fp32 instruction: these are acc itself, the others acc * sum_down().
 template <int R, int CT, int PARTS, bool CARRY, bool RAW, typename Rows>
-__device__ __forceinline__ bool lc_layer(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
-                                         int kg, v4f (&acc)[R][4], float (&factor)[R])
+__device__ __forceinline__ unsigned lc_layer(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave,
+                                             int i, int kg, v4f (&acc)[R][4])
 {
     const int colbase = wave * 16 * CT;
-    if (kin <= kShortSum) {
+    if (__builtin_expect(kin <= kShortSum, 0)) {
+        if constexpr (!CARRY) lc_zero(acc);
         lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, acc);
-#pragma unroll
-        for (int r = 0; r < R; ++r) factor[r] = 1.0f;
-        return false;
+        return ~0u;
     }
     v4f before[R][CT];
-    const unsigned odd = lc_layer_six<R, CT, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc, before, factor);
-    if (!__any(odd)) return true;
+    const unsigned odd = lc_layer_six<R, CT, PARTS, CARRY, RAW>(tile, kin, W, N, frags, wave, colbase, i, kg, acc, before);
+    if (__builtin_expect(!__any(odd), 1)) return 0;
     v4f exact[R][4];
+    lc_zero(exact);
+    if constexpr (CARRY) {
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            if constexpr (CARRY)
-                exact[r][c] = before[r][c];
-            else
-                exact[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        }
+            for (int c = 0; c < CT; ++c) exact[r][c] = before[r][c];
+    }
     lc_layer_exact<R, CT>(rows, kin, W, N, colbase, i, kg, exact);
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (odd >> r & 1) {
-            factor[r] = 1.0f;
 #pragma unroll
             for (int c = 0; c < CT; ++c) acc[r][c] = exact[r][c];
         }
-    return false;
+    return odd;
 }
 
 template <int R, int PARTS, bool CARRY, bool RAW, typename Rows>
-__device__ __forceinline__ bool lc_layer_any(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave, int i,
-                                             int kg, v4f (&acc)[R][4], float (&factor)[R])
+__device__ __forceinline__ unsigned lc_layer_any(const __bf16* tile, const Rows& rows, int kin, const float* W, int N, const char* frags, int wave,
+                                                 int i, int kg, v4f (&acc)[R][4])
 {
     const int ct = tiles_per_wave(N);
-    if (wave * 16 * ct >= N) return true;
-    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
-    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
-    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc, factor);
+    if (wave * 16 * ct >= N) {
+        lc_zero(acc);
+        return 0;
+    }
+    if (ct == 4) return lc_layer<R, 4, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc);
+    if (ct == 2) return lc_layer<R, 2, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc);
+    return lc_layer<R, 1, PARTS, CARRY, RAW>(tile, rows, kin, W, N, frags, wave, i, kg, acc);
 }
 
-// tile <- relu(acc * factor), row by row, for this wave's share of a layer of width Np; columns beyond Np become zeros, and every
-// column below the next multiple of 32 is written (the next layer reads that far); acc <- 0
+// tile <- relu(sums) for this wave's share of a layer of width Np (odd, down: how the sums stand in acc, see lc_layer);
+// columns beyond Np become zeros, and every column below the next multiple of 32 is written (the next layer reads
+// that far)
 template <int R, int CT>
-__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, bool plain, const float (&factor)[R], int colbase, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, unsigned odd, float down, int colbase, int i, int kg, const v4f (&acc)[R][4])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int c0 = colbase + 4 * CT * kg;
-    const bool whole = plain && colbase + 16 * CT <= Np;
+    const bool whole = !__any(odd) && colbase + 16 * CT <= Np;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         __bf16* row = tile + (r * 16 + i) * kLd + c0;
-        const float up = factor[r] * kUp;
         unsigned q[3][2 * CT];
         if (whole) {  // every value may be split
+            const float up = down * kUp;
 #pragma unroll
             for (int h = 0; h < 2 * CT; ++h) {
                 const int u = 2 * h;
@@ -529,6 +536,7 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
         } else {
+            const float up = (odd >> r & 1 ? 1.0f : down) * kUp;
 #pragma unroll
             for (int h = 0; h < 2 * CT; ++h) {
                 float v[2];
@@ -540,7 +548,7 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
                 }
                 unsigned p[3];
                 split2(v[0] * up, v[1] * up, p);
-                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the row's factor is one if that happens)
+                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the row's sums are v itself if that happens)
                 if (!(v[1] * up < kMaxBf16)) keep_whole(v[1], false, p);
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
@@ -556,24 +564,20 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
             }
         }
     }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
 }
 
 template <int R>
-__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, bool plain, const float (&factor)[R], int wave, int i, int kg, v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, unsigned odd, float down, int wave, int i, int kg, const v4f (&acc)[R][4])
 {
     const int ct = tiles_per_wave(Np), colbase = wave * 16 * ct;
     if (colbase >= ((Np + 31) & ~31)) return;  // (its sums are zeros: it sat the layer out)
-    if (ct == 4) lc_store_relu<R, 4>(tile, Np, plain, factor, colbase, i, kg, acc);
-    else if (ct == 2) lc_store_relu<R, 2>(tile, Np, plain, factor, colbase, i, kg, acc);
-    else lc_store_relu<R, 1>(tile, Np, plain, factor, colbase, i, kg, acc);
+    if (ct == 4) lc_store_relu<R, 4>(tile, Np, odd, down, colbase, i, kg, acc);
+    else if (ct == 2) lc_store_relu<R, 2>(tile, Np, odd, down, colbase, i, kg, acc);
+    else lc_store_relu<R, 1>(tile, Np, odd, down, colbase, i, kg, acc);
 }
 
 template <int R, int CT>
-__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, const float (&factor)[R], int i, int kg,
+__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, unsigned odd, float down, int i, int kg,
                                          const v4f (&acc)[R][4])
 {
     const int c0 = colbase + 4 * CT * kg;
@@ -582,11 +586,12 @@ __device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& 
         const int64_t row = row0 + r * 16 + i;
         if (row >= a.B) continue;
         float* out = dst + row * a.ldd + c0;
+        const float f = odd >> r & 1 ? 1.0f : down;
 #pragma unroll
         for (int h = 0; h < CT; ++h) {
             v4f v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = g * (factor[r] * acc[r][(4 * h + e) % CT][(4 * h + e) / CT]);
+            for (int e = 0; e < 4; ++e) v[e] = g * (f * acc[r][(4 * h + e) % CT][(4 * h + e) / CT]);
             if (c0 + 4 * h + 4 <= C) {
                 *reinterpret_cast<v4f_a4*>(out + 4 * h) = v;
             } else {
@@ -616,19 +621,14 @@ __global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
     const int C = a.width[layers - 1];
 
     v4f acc[R][4];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    lc_zero(acc);
 
     const T* slab = static_cast<const T*>(a.stack) + (int64_t)k * a.slab;
     const int N1 = a.width[0];
     // whoever is not multiplying goes first: the other workgroup's products leave the vector units room
     __builtin_amdgcn_s_setprio(2);
-    bool plain = true;
-    float factor[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) factor[r] = 1.0f;
+    unsigned odd = 0;
+    float down = sum_down(kParts, CARRY);
     for (int p0 = 0; p0 < a.d; p0 += kPanel) {  // first layer, one panel of feature columns at a time
         const int kin = min(kPanel, a.d - p0);
         if (p0 > 0) __syncthreads();  // every wave is done with the previous panel (nothing is in the tile before the first)
@@ -636,23 +636,24 @@ __global__ __launch_bounds__(kMlpThreads, 2) void gp_lc_mlp(const LcArgs a)
         __syncthreads();
         const char* frags = a.frags + a.frag_off[0] + (int64_t)(p0 / 32) * 4 * tiles_per_wave(N1) * (3 * kFragBytes);
         const StackRows<T> rows{slab + p0, a.batch, a.ld, a.n, row0, a.B};
-        plain = lc_layer_any<R, kParts, CARRY, RAW>(tile, rows, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc, factor);
+        odd = lc_layer_any<R, kParts, CARRY, RAW>(tile, rows, kin, a.W[0] + (int64_t)p0 * N1, N1, frags, wave, i, kg, acc);
     }
     for (int t = 1; t < layers; ++t) {
         const int Np = a.width[t - 1], N = a.width[t];
         __syncthreads();  // every wave is done reading the tile
-        lc_store_relu_any<R>(tile, Np, plain, factor, wave, i, kg, acc);
+        lc_store_relu_any<R>(tile, Np, odd, down, wave, i, kg, acc);
+        down = sum_down(3, false);
         __syncthreads();
         const TileRows<TM> rows{tile};
-        plain = lc_layer_any<R, 3, false, RAW>(tile, rows, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc, factor);
+        odd = lc_layer_any<R, 3, false, RAW>(tile, rows, Np, a.W[t], N, a.frags + a.frag_off[t], wave, i, kg, acc);
     }
 
     const float g = a.gamma[k];
     float* dst = a.direct ? a.dst + a.out_off[br] : a.dst + (int64_t)br * a.B * a.ldd;
     const int ct = tiles_per_wave(C), colbase = wave * 16 * ct;
-    if (ct == 4) lc_write<R, 4>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
-    else if (ct == 2) lc_write<R, 2>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
-    else lc_write<R, 1>(dst, a, row0, C, colbase, g, factor, i, kg, acc);
+    if (ct == 4) lc_write<R, 4>(dst, a, row0, C, colbase, g, odd, down, i, kg, acc);
+    else if (ct == 2) lc_write<R, 2>(dst, a, row0, C, colbase, g, odd, down, i, kg, acc);
+    else lc_write<R, 1>(dst, a, row0, C, colbase, g, odd, down, i, kg, acc);
 }
 
 // out[i][c] = sum (or maximum) over the branches, in branch order, of the partial results
