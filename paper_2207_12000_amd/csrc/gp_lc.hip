@@ -44,13 +44,11 @@
 // are the layer's output columns) and batch rows its second, so a lane ends up with 4 CT
 // consecutive output columns of one batch row: wide stores of the next layer's operand and
 // of the result.
-#include <hip/hip_runtime.h>
-
 #include <algorithm>
 #include <atomic>
 #include <mutex>
 
-#include "gp_internal.h"
+#include "gp_lc.h"
 
 namespace gp {
 
@@ -58,55 +56,15 @@ namespace {
 
 constexpr int kLcThreads = 256;   // reduction and softmax
 constexpr int kMlpThreads = 256;
-constexpr int kPanel = 256;       // widest inner dimension staged in LDS at once
 constexpr int kLd = kPanel + 16;  // LDS row stride in bf16: 544 bytes, with which the 16 lanes of an LDS pass read 16-byte pieces of different banks
-constexpr int kMaxLayers = 8;
-constexpr int kMaxHops = 16;
 constexpr int64_t kWorkspaceBytes = INT64_C(256) << 20;  // cap on the partial results of one piece
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte access from a dword boundary
 typedef float v2f __attribute__((ext_vector_type(2)));
-typedef unsigned short v4u16 __attribute__((ext_vector_type(4)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
-
-struct LcArgs {
-    const void* stack;
-    int64_t ld, slab;  // elements: row stride, distance between hop slabs
-    int64_t n;
-    int d;
-    int hops;                 // branches in use: work item = tile * hops + branch
-    int hop_of[kMaxHops];     // branch -> slab of the stack it reads
-    int depth[kMaxHops];      // branch -> number of weight matrices it applies
-    int out_off[kMaxHops];    // branch -> first output column when branches are written side by side
-    int direct;               // 1: branches write the final result (side by side, or there is just one)
-    const int32_t* batch;
-    int64_t B;
-    float gamma[kMaxHops];
-    int T;
-    const float* W[kMaxLayers];
-    int width[kMaxLayers];
-    const char* frags;     // split weights (gp_lc_split_weights), or nullptr: split where they are used
-    int64_t frag_off[kMaxLayers];  // layer -> its first byte there
-    int xvec;              // 1: stack rows may be read four elements at a time
-    float* dst;            // the result (direct), else the partial results [branch][B][ldd]
-    int64_t ldd;
-};
-
-__device__ __forceinline__ float widen(float v) { return v; }
-__device__ __forceinline__ float widen(unsigned short v) { return __uint_as_float((unsigned)v << 16); }
-
-__device__ __forceinline__ v4f load4(const float* p) { return *reinterpret_cast<const v4f*>(p); }
-__device__ __forceinline__ v4f load4(const unsigned short* p)
-{
-    const v4u16 b = *reinterpret_cast<const v4u16*>(p);
-    v4f r;
-    r.x = widen(b.x), r.y = widen(b.y), r.z = widen(b.z), r.w = widen(b.w);
-    return r;
-}
 
 // Two fp32 numbers (times 2^16 already) as three pairs of bf16, packed as the matrix instructions take them,
 // p1 + p2 + p3 = x: exactly, for |x| < kMaxBf16 that are 2^16 times an fp32 number.
@@ -521,7 +479,7 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
 {
     constexpr int kPlane = 16 * R * kLd;
     const int c0 = colbase + 4 * CT * kg;
-    const bool whole = !__any(odd) && colbase + 16 * CT <= Np;
+    const bool some_odd = __any(odd), whole = !some_odd && colbase + 16 * CT <= Np;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         __bf16* row = tile + (r * 16 + i) * kLd + c0;
@@ -548,8 +506,10 @@ __device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np,
                 }
                 unsigned p[3];
                 split2(v[0] * up, v[1] * up, p);
-                if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);  // (the row's sums are v itself if that happens)
-                if (!(v[1] * up < kMaxBf16)) keep_whole(v[1], false, p);
+                if (some_odd) {  // (where that cannot be split the row's sums are v itself)
+                    if (!(v[0] * up < kMaxBf16)) keep_whole(v[0], true, p);
+                    if (!(v[1] * up < kMaxBf16)) keep_whole(v[1], false, p);
+                }
                 q[0][h] = p[0], q[1][h] = p[1], q[2][h] = p[2];
             }
         }
@@ -857,6 +817,46 @@ int choose_tile_rows(int64_t B, int hops)
     return 16 * (best + 1);
 }
 
+// Which models run on the fp32 instruction (gp_lc_f32.hip): those of few products per row, whatever the batch, so that a
+// row's bits do not depend on it.  Products of a layer at most 64 wide on fewer than 128 inputs do not count: its steps
+// are padded to 128.  us per call, fp32 instruction / six products, 4 hops side by side:
+//   model               counted   1024 rows     60,000 rows     60,000 rows of a bf16 stack
+//   16-16                     0   12.0 / 12.8     33 /  56        34 /  51
+//   64-64-64-40               0   12.7 / 13.2    100 / 115       109 / 111
+//   16-256                4,096   12.5 / 12.9    103 / 125       102 / 111
+//   128-40                5,120   12.4 / 12.6     77 /  73        92 /  78
+//   32-200-16             9,600   12.7 / 13.4    122 / 106       125 / 101
+//   300-40               12,000   13.9 / 12.5    189 / 185       197 / 158
+//   128-128-40           21,504   12.6 / 12.7    145 / 110       159 / 108
+//   100-256-40           35,840   15.5 / 13.2    231 / 168       232 / 142
+//   128-128-128-40       37,888   14.2 / 16.1    214 / 146       217 / 140
+//   128-256-256-256-40  174,080   33.8 / 25      723 / 389       731 / 367
+constexpr int64_t kSmallModel = 5000;
+bool small_model(int T, int d, const int32_t* width)
+{
+    int64_t products = 0;
+    for (int t = 0; t < T; ++t) {
+        const int64_t in = t == 0 ? d : width[t - 1];
+        if (width[t] > 64 || in >= 128) products += in * width[t];
+    }
+    return products < kSmallModel;
+}
+
+// Where a call's work items are few, splitting the weights in each of them costs less than the launch that splits them
+// once: the launch takes 2 to 3 us, with the event of a direct call 4 to 5 (host time, where the queue runs dry), and a step
+// of 32 weight rows takes 0.3 to 0.6 us longer in a layer wider than 64, twice that where two items share a unit.
+// us, 4 hops, split beforehand / where used: 32-256-40 summed, 1024 rows 17.1 / 14.4; 100-256-40 summed, 256 rows 15.7 / 15.6,
+// 2048 rows 18.4 / 19.3, side by side, 1024 rows 16.3 / 13.2; 32-256-256 summed, 256 rows 17.4 / 19.4, side by side
+// 17.9 / 16.3; 128-256-256-256-40 side by side 25.1 / 31.4.  Every workgroup of the call is resident at once: a second
+// round would pay again, except in models without a wider layer on one panel of features (128-40 side by side, 16,384
+// rows 31.5 / 26.0 in four rounds of 32-row items, 60,000 rows 73 / 81; 602-64-40, 16,384 rows 120 / 129).
+bool split_where_used(int wide_steps, int d, bool direct, int64_t items)
+{
+    const int cus = compute_units();
+    if (wide_steps == 0 && d <= kPanel) return items <= 8 * cus;
+    return items <= 2 * cus && (direct ? wide_steps <= 9 : wide_steps * (items > cus ? 2 : 1) <= 5);
+}
+
 }  // namespace
 
 gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, int32_t d, int32_t K, const int32_t* batch,
@@ -907,8 +907,17 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     // One workgroup per (row tile, branch), so that a mini-batch of a few thousand rows still fills the chip; the
     // branches' results are then combined in hop order.  Large batches go through in pieces that keep the
     // partial results within a fixed size.
+    for (int t = 0; t < T; ++t) a.wvec[t] = width[t] > 128 && width[t] % 2 == 0 && (uintptr_t)W[t] % 8 == 0;  // two tiles per wave, pairs aligned
+    const bool small = small_model(T, d, width);
     const int asked = (int)options().lc_tile_rows;
-    int tm = asked == 0 ? choose_tile_rows(B, a.hops) : asked >= 48 ? 48 : 32;
+    int tm, wide_steps = 0;  // (wide_steps: of 32 weight rows, in layers wider than 64)
+    for (int t = 0; t < T; ++t)
+        if (width[t] > 64) wide_steps += ((t == 0 ? d : width[t - 1]) + 31) / 32;
+    if (small)  // 32 rows where even these give no more than one workgroup per CU: the call lasts as long as one item
+        tm = asked != 0 ? asked : (B + 31) / 32 * a.hops <= compute_units() ? 32 : 64;
+    else
+        tm = asked == 0 ? choose_tile_rows(B, a.hops) : asked >= 48 ? 48 : 32;
+    if (!small && asked == 0 && tm > 32 && wide_steps == 0 && split_where_used(0, d, a.direct, (B + 31) / 32 * a.hops)) tm = 32;
     const int64_t piece = a.direct ? B : std::max<int64_t>(64, kWorkspaceBytes / ((int64_t)a.hops * C * 4) / 64 * 64);
     SplitArgs sp{};
     sp.T = T;
@@ -925,16 +934,17 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
     float* part = nullptr;
     std::unique_lock<std::mutex> slot_lock(g_slot_mu, std::defer_lock);
     SlotUse slot;  // (after the lock: it ends before the lock does)
-    const bool fits = (size_t)frag_bytes <= kSlotBytes;
+    const bool split = !small && (size_t)frag_bytes <= kSlotBytes &&
+                       !(tm <= 32 && split_where_used(wide_steps, d, a.direct, (B + tm - 1) / tm * a.hops));
     if (!a.direct) {
         gp_status st = workspace((size_t)a.hops * std::min(piece, B) * C * sizeof(float), &part);
         if (st != GP_OK) return st;
-        if (fits) {
+        if (split) {
             int dev = 0;
             std::lock_guard<std::mutex> lk(g_slot_mu);
             if ((st = room_on_current_device(&dev, &sp.out)) != GP_OK) return st;
         }
-    } else if (fits) {
+    } else if (split) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         GP_HIP(hipStreamIsCapturing(stream, &capture));
         if (capture == hipStreamCaptureStatusNone) {
@@ -949,7 +959,7 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
         hipLaunchKernelGGL(gp_lc_split_weights, dim3((unsigned)(sp.first[T] + 3) / 4), dim3(256), 0, stream, sp);
         profile_end(stream);
         GP_HIP(hipGetLastError());
-    } else {
+    } else if (!small) {
         tm = std::min(tm, 32);  // (raw weights take registers: 32 rows at most)
     }
     for (int64_t b0 = 0; b0 < B; b0 += piece) {
@@ -963,7 +973,9 @@ gp_status lc_forward(const void* stack, int64_t ld, gp_dtype dtype, int64_t n, i
             p.dst = part, p.ldd = C;
         const int64_t grid = (p.B + tm - 1) / tm * a.hops;
         if (grid > 0x7fffffffLL) return fail(GP_ERR_UNSUPPORTED, "batch too large for one launch");
-        gp_status st = dtype == GP_F32 ? launch_mlp<float>(tm, p, (unsigned)grid, stream) : launch_mlp<unsigned short>(tm, p, (unsigned)grid, stream);
+        gp_status st = small             ? launch_lc_f32(dtype, tm, p, (unsigned)grid, stream)
+                       : dtype == GP_F32 ? launch_mlp<float>(tm, p, (unsigned)grid, stream)
+                                         : launch_mlp<unsigned short>(tm, p, (unsigned)grid, stream);
         if (st != GP_OK) return st;
         if (!a.direct) {
             const unsigned rgrid = (unsigned)std::min<int64_t>((p.B * C + kLcThreads - 1) / kLcThreads, 256 * 8);

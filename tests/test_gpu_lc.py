@@ -73,8 +73,8 @@ CASES = [
     (100, [256, 41], 3, 2000, 4096),              # d not a multiple of 8, duplicates in the batch
     (602, [256, 256, 41], 2, 700, 130),           # three feature panels
     (7, [5], 2, 50, 33),                          # one layer: a linear model on the filtered features
-    (64, [192, 172], 5, 500, 64),                 # three tiles per wave
-    (33, [37, 130, 3], 1, 300, 1),                # odd widths: scalar weight loads, a single row
+    (64, [192, 172], 5, 500, 64),                 # layers that end inside a wave's columns
+    (33, [37, 130, 3], 1, 300, 1),                # odd widths, a single row
     (16, [64] * 7 + [10], 0, 200, 77),            # K = 0, eight layers
     (256, [128, 128], 4, 400, 191),
 ]
@@ -84,7 +84,8 @@ CASES = [
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("tile_rows", [32, 64])
 def test_parity(d, widths, K, n, B, bf16, tile_rows):
-    """Both work-item heights (the library picks 32 rows for small batches, 64 otherwise)."""
+    """Both work-item heights that can be asked for (64 stands for 48, the tallest there is, where fp32 products are
+    taken as six bf16 products); the library's own choice, 16 rows among them, is in the tests at the end."""
     rng = np.random.default_rng(1000 + d + B)
     stack = rng.normal(size=(K + 1, n, d)).astype(np.float32)
     if bf16:
@@ -181,8 +182,8 @@ def test_on_the_propagated_stack_of_config_2():
 
 def test_random_shapes():
     """Forty seeded random shapes: feature widths 1 .. 300 (one or two panels), one to
-    four layers of widths 1 .. 256, 1 .. 5 hops, 1 .. 300 rows, both work-item heights,
-    batch lists with out-of-range entries mixed in."""
+    four layers of widths 1 .. 256, 1 .. 5 hops, 1 .. 300 rows, work-item heights asked for and
+    chosen, batch lists with out-of-range entries mixed in."""
     rng = np.random.default_rng(4242)
     try:
         for case in range(40):
@@ -319,10 +320,11 @@ def test_infinities_and_nans(d, widths, B, bf16):
     assert np.all(np.abs(got - want)[ok] <= tolerance(d, widths, K) * bound[ok] + 1e-30)
 
 
-@pytest.mark.parametrize("d,widths,B,bf16", [(100, [256, 172, 41], 333, False), (270, [70, 130], 5000, True), (48, [40], 17, False)])
+@pytest.mark.parametrize("d,widths,B,bf16", [(100, [256, 172, 41], 333, False), (270, [70, 130], 5000, True), (48, [40], 17, False),
+                                             (128, [256, 256, 256, 40], 600, False)])
 def test_captured_call_that_writes_its_result_directly(d, widths, B, bf16):
-    """A concatenating call under graph capture splits its weights where it uses them (no shared buffer): every
-    replay gives the eager call's bits, with other calls of the library in between."""
+    """A concatenating call under graph capture splits its weights where it uses them (no shared slot), or needs none
+    split (the last model): every replay gives the eager call's bits, with other calls of the library in between."""
     import torch
     rng = np.random.default_rng(5 + d)
     n, K, T = 700, 2, len(widths)
@@ -354,13 +356,13 @@ def test_captured_call_that_writes_its_result_directly(d, widths, B, bf16):
 
 
 def test_calls_on_many_streams():
-    """Direct calls on more streams than the library keeps weight buffers for, interleaved without waiting: each
-    gives what it gives alone."""
+    """Direct calls on more streams than the library has slots for split weights, interleaved without waiting: each
+    gives what it gives alone.  (A model deep enough that its weights are split beforehand.)"""
     import torch
     rng = np.random.default_rng(21)
     n, d = 4000, 96
     stack = torch.from_numpy(rng.normal(size=(1, n, d)).astype(np.float32)).cuda()
-    models = [[torch.from_numpy(W).cuda() for W in make_weights(rng, d, [200, 64])] for _ in range(5)]
+    models = [[torch.from_numpy(W).cuda() for W in make_weights(rng, d, [256, 256, 256, 64])] for _ in range(5)]
     want = [gp.lc_forward_tensors(stack, None, [1.0], m) for m in models]
     outs = [torch.empty_like(want[0]) for _ in range(40)]
     torch.cuda.synchronize()
@@ -531,7 +533,7 @@ def test_short_sums_are_plain_fp32(d, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("d,widths", [(40, [256, 200, 41]), (300, [100, 250, 64]), (128, [256, 256, 40])])
+@pytest.mark.parametrize("d,widths", [(40, [256, 200, 41]), (300, [100, 250, 64]), (128, [256, 256, 40]), (128, [256, 40]), (60, [130, 40])])
 def test_a_row_does_not_depend_on_the_rows_beside_it(d, widths, bf16):
     """Rows with an infinity, a NaN or a very large number change nothing in the other rows, bit for bit; nor do the
     number of rows in the batch and the height of the work items."""
@@ -563,3 +565,24 @@ def test_a_row_does_not_depend_on_the_rows_beside_it(d, widths, bf16):
             assert np.array_equal(run(stack, ids, gamma, Ws, bf16=bf16), plain)
         finally:
             gp.gp_set_option("lc_tile_rows", 0)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d,widths,K,B", [
+    (39, [128], 3, 700), (40, [128], 3, 700),                # the last model on the fp32 instruction, the first in six products
+    (124, [40], 1, 90), (128, [40], 1, 90), (127, [64, 64], 1, 40),
+    (128, [128, 40], 0, 512 * 16), (128, [128, 40], 0, 512 * 32), (128, [128, 40], 0, 512 * 32 + 1),  # weights split where they are used
+    (32, [256, 250], 1, 100), (33, [256, 250], 1, 100), (160, [256, 40], 3, 64 * 16), (160, [256, 40], 3, 64 * 16 + 1),  # .. or beforehand
+    (150, [64, 40], 0, 2048 * 32), (150, [64, 40], 0, 2048 * 32 + 1), (257, [64, 40], 0, 512 * 32 + 1),
+    (600, [64, 16], 3, 40), (600, [64, 16], 0, 16),          # 16 rows to an item, three panels
+    (100, [256, 172, 41], 3, 1), (256, [65] * 7 + [10], 0, 17), (270, [70, 130], 2, 600),
+])
+def test_edges_of_the_rules(d, widths, K, B, bf16):
+    """Both sides of every line at which another kernel, or another way for the weights, is taken, with the work items'
+    height left to the library: 16 rows in the small batches."""
+    rng = np.random.default_rng(101 + d + B)
+    n = 300
+    stack = rng.normal(size=(K + 1, n, d)).astype(np.float32)
+    if bf16:
+        stack = gp_synth.f32_to_bf16_bits(stack)
+    check(stack, rng.integers(0, n, B), rng.normal(size=K + 1), make_weights(rng, d, widths), bf16=bf16, ldo_pad=1)
