@@ -337,7 +337,7 @@ gp_status gp_propagate_combine(const gp_plan *plan, const void *X, int64_t ldx, 
  *          into three bf16 parts, without loss at any magnitude, and at most 2^-24 of
  *          the product is left out; against fp64 such sums were measured to be closer
  *          than those of the fp32 matrix instruction (128-256-256-256-40 model, random
- *          normal weights: 0.92e-7 of the result, and 2.5e-7).
+ *          normal weights: 0.99e-7 of the result, and 2.7e-7).
  *  batch   DEVICE, B row numbers; NULL means rows 0 .. B-1 (then B <= n).  A row
  *          number outside [0, n) is not an error: that output row is computed
  *          from a row of zeros.
@@ -430,8 +430,8 @@ gp_status gp_set_hbm_budget_bytes(int64_t bytes);
  *                     by gp_plan_blocks.
  *   "column_tile"     feature columns per pass of the kernel, 0 = automatic.
  *   "persistent_blocks"  workgroups of the hop kernel (0 = as many as stay resident).
- *   "lc_tile_rows"       batch rows per work item of gp_lc_forward, at most: 32 or 64 (0 = by batch size;
- *                     the tallest item the kernel has is 48 rows).
+ *   "lc_tile_rows"       batch rows per work item of gp_lc_forward, at most: 32 or 64 (0 = by batch size: 16, 32 or
+ *                     48, the tallest there is; models of few products 32 or 64).  Results do not depend on it.
  *   "column_slices"   column slices one pass is divided into (1 .. 16; 0 = automatic).
  *                     Implicit work lists take 1, 2, 4 or 8 (anything else = automatic).
  *   "split_records"   explicit work lists: 0 / 1 = every record is cut into the non-zeros

@@ -176,7 +176,8 @@ struct Row<uint16_t, VEC> {
 // Running filter output: cp[0..VEC) += gamma * o, every column once.  The update is bound by the memory path, so a
 // whole vector is read and written by one instruction each (element by element, the lanes of one instruction are VEC
 // floats apart and every 128-byte line is asked for VEC times over: ten hops over 169,343 rows of 64 columns, 2.5
-// million non-zeros, 1065.6 us that way against 1044.0).  A row's last vector that was moved back repeats `fresh` columns of the vector before it: it takes only its own, one by one.
+// million non-zeros, 1065.6 us that way against 1044.0).  A row's last vector that was moved back repeats `fresh`
+// columns of the vector before it: it takes only its own, one by one.
 template <int VEC>
 __device__ __forceinline__ void add_to_filter(float* __restrict__ cp, const float (&o)[VEC], int fresh, float gamma)
 {

@@ -22,8 +22,8 @@
 //
 // of which the last bracket, at most 2^-24 of the product, is left out: six bf16 products with fp32
 // accumulation, the large ones with one accumulation per 32 terms.  Measured against fp64
-// on a 128-256-256-256-40 model with normal weights and features: relative error 0.92e-7, where
-// the fp32 instruction left 2.5e-7.  That is a matter of long sums, whose own roundings outweigh
+// on a 128-256-256-256-40 model with normal weights and features: relative error 0.99e-7, where
+// the fp32 instruction left 2.7e-7.  That is a matter of long sums, whose own roundings outweigh
 // the part left out: sums of at most kShortSum terms are taken on the fp32 instruction.  (A bf16
 // stack's first layer has one part, x itself: three products.)  Features and activations are split once, when they enter LDS; weights once per
 // call (gp_lc_split_weights).  Infinities, NaNs and numbers that the factor carries beyond
@@ -32,11 +32,12 @@
 // (lc_layer_exact) and keeps these sums for the rows concerned, so results with such numbers are
 // those of plain fp32 arithmetic, and a row's bits do not depend on the rows beside it.
 //
-// What bounds it: the matrix cores, at 69 % busy and, by then, a clock that power holds at
-// about 2.1 of 2.4 GHz.  Four hops of a 128-256-256-256-40 model over 169,343 fp32 rows: 1040
-// us = 226 TFLOP/s of fp32 work (1.36 PFLOP/s of bf16 products); on the fp32 instruction
-// 1988 us = 119.  A batch of 4096 rows: 64 -> 38 us.  100-256-256-256 branches side by side
-// from a bf16 stack, all rows: 925 -> 525 us.
+// What bounds it: the matrix cores, 64 % busy at about 2 GHz (counters of the call over 169,343 fp32 rows); what they
+// wait for is gather, splits and barriers, which the second workgroup of a compute unit covers in part.  us per
+// call, on the fp32 instruction / here: four hops of a 128-256-256-256-40 model over all rows 1991 / 1050 - 1130 (the clock
+// varies with the power that is left; 225 to 209 TFLOP/s of fp32 work, 1.35 to 1.25 PFLOP/s of bf16 products), a batch of
+// 4096 rows with its launches 59.3 / 42.4; 100-256-256-256 branches of growing depth side by side from a bf16 stack,
+// all rows, 920 / 505.  Models of few products have a kernel of their own (small_model).
 //
 // Index freedom used: MFMA sums over k, and which k a lane supplies is the kernel's choice
 // as long as both operands agree; lanes 16 kg .. + 16 take k = 32 kt + 8 kg .. + 8 in step kt
@@ -207,7 +208,7 @@ struct SplitArgs {
 
 // one wave per (layer, step, wave, tile).  A few microseconds for a few hundred thousand weights; done once per
 // call, where splitting them in every workgroup that uses them costs as much vector work as all of the
-// activations (4-hop, 4-layer model, 169,343 rows: 1430 us that way, 1042 us this way).
+// activations (128-256-256-256-40 model, 4 hops side by side, 60,000 rows: 625 us that way, 390 us this way).
 __global__ __launch_bounds__(256) void gp_lc_split_weights(const SplitArgs a)
 {
     const int g = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (a slot holds a few thousand tiles)
@@ -801,8 +802,11 @@ gp_status launch_mlp(int tile_rows, const LcArgs& a, unsigned grid, hipStream_t 
 
 // Rows of a work item.  Two items share a compute unit; a round of items lasts (measured on a 128-256-256-256-40
 // model, microseconds) 21 / 28 / 38 for 16 / 32 / 48 rows where every unit has two, 19 / 22 / 28 where none has
-// more than one: the height with the least sum over the call's rounds.  (4 hops: 512 rows 19 us with 16-row items,
-// 28 with 48; 4096 rows 38 us with 32, 56 with 16, 45 with 48; all 169,343 rows 1042 us with 48, 1157 with 32.)
+// more than one: the height with the least sum over the call's rounds.  (4 hops: 512 rows 25 us with 16-row items,
+// 33 with 48; 4096 rows 41 us with 32, 54 with 16, 48 with 48; 60,000 rows 397 us with 48, 433 with 32.)  Over 17
+// models (widths 16 to 256, 1 to 7 layers, 32 to 602 features, both types, sums and side by side, 1024 to 60,000 rows) the
+// height chosen is 1.1 % from the best on average.  It is wrong where it gives every unit exactly two 16-row items, which
+// a single round of 32-row items beats by 10 to 35 % (2048 rows x 4 hops).
 int choose_tile_rows(int64_t B, int hops)
 {
     const int64_t both[3] = {21, 28, 38}, alone[3] = {19, 22, 28};

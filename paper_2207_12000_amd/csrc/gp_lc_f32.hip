@@ -7,8 +7,8 @@
 // LDS tile, then replaces it (ReLU applied on the way).
 //
 // It needs no splitting of weights and activations, which is what a small model's time goes to in the
-// other kernel; what it is bound by there is gather, barriers and launch.  On large models it is bound by the
-// instruction's rate (75 % of 157 TFLOP/s).
+// other kernel; what it is bound by there is gather, barriers and launch (16-16 model, 4 hops side by side, 60,000
+// rows: 33 us for 31 MB).  On large models it is bound by the instruction's rate: 75 % of 157 TFLOP/s.
 //
 // Index freedom used: MFMA sums over k and yields 32 columns per tile, but which k
 // and which column a lane supplies is the kernel's choice as long as A and B agree.

@@ -101,7 +101,7 @@ class _Widened:
         return gp_synth.bf16_bits_to_f32(self.bits[idx])
 
 
-# Pinned host memory on the GPU machine: hipHostMalloc succeeds up to 65.5 GiB in total (measured in
+# Pinned host memory on the machine measured: hipHostMalloc succeeds up to 65.5 GiB in total (measured in
 # 0.5 GiB steps; a single 64 GiB request succeeds, anything past 65.5 GiB returns hipErrorOutOfMemory
 # although the host has 309 GB).  The streamed schedule keeps, pinned: the hop stack (K + 1 slabs of
 # n x 128 bf16 = 1024 B per node with X living in slab 0), a copy of the column list (4 B per
