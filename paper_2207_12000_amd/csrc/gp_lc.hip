@@ -208,7 +208,7 @@ struct SplitArgs {
 
 // one wave per (layer, step, wave, tile).  A few microseconds for a few hundred thousand weights; done once per
 // call, where splitting them in every workgroup that uses them costs as much vector work as all of the
-// activations (128-256-256-256-40 model, 4 hops side by side, 60,000 rows: 625 us that way, 390 us this way).
+// activations (128-256-256-256-40 model, 4 hops side by side, 60,000 rows: 572 us that way, 390 us this way).
 __global__ __launch_bounds__(256) void gp_lc_split_weights(const SplitArgs a)
 {
     const int g = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (a slot holds a few thousand tiles)
@@ -333,30 +333,22 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
             for (int c = 0; c < CT; ++c) before[r][c] = acc[r][c];
     }
     v8bf part[4][3], x[R][PARTS];
-    float raw[RAW ? 8 : 1][CT];  // RAW: one step's weights
+    // RAW: weights of the steps ahead, as loaded: two where the accumulators leave the room.  (One load for all widths of
+    // rows: with a way of its own for widths that are no multiple of CT, every load was waited for at the end of its
+    // branch: 600-100 model, 60,000 rows, captured, 904 us that way, 469 this way; 128-256-256-256-40 632, 572.)
+    typedef float vec __attribute__((ext_vector_type(CT), aligned(4)));
+    constexpr int kAhead = CT == 4 ? 1 : 2;
+    vec raw[RAW ? kAhead : 1][RAW ? 8 : 1];
+    const int rawcol = min(colbase + CT * i, N - CT), shift = colbase + CT * i - rawcol;  // (columns beyond N: not used)
+    auto load_raw = [&](int kt, int to) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s)  // (rows beyond kin meet zeros)
+            raw[to][s] = *reinterpret_cast<const vec*>(W + (int64_t)min(kt * 32 + 8 * kg + s, kin - 1) * N + rawcol);
+    };
     auto load_w = [&](int u, int to) {  // (beyond the last unit: not used)
-        const int kt = u / CT, ct = u % CT;
-        if constexpr (RAW) {  // (whole steps, at their first tile)
-            if (ct > 0) return;
-            typedef float vec __attribute__((ext_vector_type(CT), aligned(4)));
-            const int c0 = colbase + CT * i;
+        global_char* at = mine + ((u / CT) * 4 * CT + u % CT) * (3 * kFragBytes);
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const float* row = W + (int64_t)min(kt * 32 + 8 * kg + s, kin - 1) * N;  // (rows beyond kin meet zeros)
-                if (N % CT == 0) {
-                    const vec v = *reinterpret_cast<const vec*>(row + min(c0, N - CT));
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) raw[s][c] = v[c];
-                } else {
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) raw[s][c] = row[min(c0 + c, N - 1)];
-                }
-            }
-        } else {
-            global_char* at = mine + (kt * 4 * CT + ct) * (3 * kFragBytes);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) part[to][p] = *reinterpret_cast<const __attribute__((address_space(1))) v8bf*>(at + p * kFragBytes + lane_off);
-        }
+        for (int p = 0; p < 3; ++p) part[to][p] = *reinterpret_cast<const __attribute__((address_space(1))) v8bf*>(at + p * kFragBytes + lane_off);
     };
     auto load_x = [&](int kt) {
         kt = min(kt, steps - 1);  // (padding steps have zero weights)
@@ -376,20 +368,38 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
         if constexpr (PARTS == 3) mul(0, 2), mul(1, 1), mul(0, 1);
         mul(2, 0), mul(1, 0), mul(0, 0);
     };
-    auto split_raw = [&](int first) {  // a step's raw weights into the parts of its tiles
+    auto split_raw = [&](int from, int first) {  // a step's raw weights into the parts of its tiles
+        if (CT > 1 && N % CT != 0) {  // a lane whose last columns lie beyond N has read its first ones further right
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int k = 0; k < CT - 1; ++k)  // one to the left, `shift` times at most
+                    if (k < shift) {
+#pragma unroll
+                        for (int c = 0; c + 1 < CT; ++c) raw[from][s][c] = raw[from][s][c + 1];
+                    }
+        }
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             float v[8];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) v[s] = raw[s][c];
+            for (int s = 0; s < 8; ++s) {
+                if constexpr (CT == 1) v[s] = raw[from][s][0];
+                else v[s] = raw[from][s][c];
+            }
             v4u q[3];
             split8(v, q);
 #pragma unroll
             for (int p = 0; p < 3; ++p) part[first + c][p] = __builtin_bit_cast(v8bf, q[p]);
         }
     };
+    if constexpr (RAW) {
 #pragma unroll
-    for (int u = 0; u < (RAW ? 1 : 4); ++u) load_w(u, u);
+        for (int k = 0; k < kAhead; ++k) load_raw(k, k);
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_w(u, u);
+    }
     load_x(0);
     __builtin_amdgcn_s_setprio(0);
     for (int u = 0; u < units; u += 4) {
@@ -397,7 +407,8 @@ __device__ __forceinline__ unsigned lc_layer_six(const __bf16* tile, int kin, co
         for (int v = 0; v < 4; ++v) {
             if constexpr (RAW) {
                 if (u + v >= steps * CT) break;
-                if (v % CT == 0) split_raw(v), load_w(u + v + CT, v);
+                constexpr int kMask = kAhead - 1;
+                if (v % CT == 0) split_raw((v / CT) & kMask, v), load_raw((u + v) / CT + kAhead, (v / CT) & kMask);
             }
             products(v % CT, v);
             if constexpr (!RAW) load_w(u + v + 4, v);
@@ -828,12 +839,12 @@ int choose_tile_rows(int64_t B, int hops)
 //   16-16                     0   12.0 / 12.8     33 /  56        34 /  51
 //   64-64-64-40               0   12.7 / 13.2    100 / 115       109 / 111
 //   16-256                4,096   12.5 / 12.9    103 / 125       102 / 111
-//   128-40                5,120   12.4 / 12.6     77 /  73        92 /  78
-//   32-200-16             9,600   12.7 / 13.4    122 / 106       125 / 101
+//   128-40                5,120   12.4 / 12.5     77 /  73        92 /  78
+//   32-200-16             9,600   12.7 / 13.1    122 / 106       125 / 101
 //   300-40               12,000   13.9 / 12.5    189 / 185       197 / 158
-//   128-128-40           21,504   12.6 / 12.7    145 / 110       159 / 108
-//   100-256-40           35,840   15.5 / 13.2    231 / 168       232 / 142
-//   128-128-128-40       37,888   14.2 / 16.1    214 / 146       217 / 140
+//   128-128-40           21,504   12.6 / 12.5    145 / 110       159 / 108
+//   100-256-40           35,840   15.5 / 12.3    231 / 168       232 / 142
+//   128-128-128-40       37,888   14.2 / 13.3    214 / 146       217 / 140
 //   128-256-256-256-40  174,080   33.8 / 25      723 / 389       731 / 367
 constexpr int64_t kSmallModel = 5000;
 bool small_model(int T, int d, const int32_t* width)
@@ -848,17 +859,25 @@ bool small_model(int T, int d, const int32_t* width)
 
 // Where a call's work items are few, splitting the weights in each of them costs less than the launch that splits them
 // once: the launch takes 2 to 3 us, with the event of a direct call 4 to 5 (host time, where the queue runs dry), and a step
-// of 32 weight rows takes 0.3 to 0.6 us longer in a layer wider than 64, twice that where two items share a unit.
-// us, 4 hops, split beforehand / where used: 32-256-40 summed, 1024 rows 17.1 / 14.4; 100-256-40 summed, 256 rows 15.7 / 15.6,
-// 2048 rows 18.4 / 19.3, side by side, 1024 rows 16.3 / 13.2; 32-256-256 summed, 256 rows 17.4 / 19.4, side by side
-// 17.9 / 16.3; 128-256-256-256-40 side by side 25.1 / 31.4.  Every workgroup of the call is resident at once: a second
-// round would pay again, except in models without a wider layer on one panel of features (128-40 side by side, 16,384
-// rows 31.5 / 26.0 in four rounds of 32-row items, 60,000 rows 73 / 81; 602-64-40, 16,384 rows 120 / 129).
+// of 32 weight rows takes 0.1 to 0.2 us longer in a layer wider than 64, twice that where two items share a unit.
+// us, 4 hops, split beforehand / where used:
+//                                       items alone (1024 rows)      two to a unit (2048)
+//   steps  model                 side by side   summed         side by side   summed
+//       4  100-256-40               18.0 / 12.3    17.0 / 15.0     19.0 / 15.0    18.6 / 18.7
+//       8  128-128-128-40           16.3 / 13.3    15.8 / 15.4     18.2 / 15.1    17.7 / 18.7
+//      12  128-128-128-128-40       18.6 / 14.5    18.0 / 18.0     21.5 / 18.9    20.9 / 22.6
+//      20  128-256-256-256-40       25.8 / 24.6    25.7 / 28.3     33.6 / 35.3    34.5 / 39.3
+//      24  128, six times 128, 40   24.3 / 22.5    23.4 / 26.0     28.4 / 30.9    28.3 / 35.1
+// Every workgroup of the call is resident at once: a second round would pay again, except in models without a wider layer
+// on one panel of features (128-40 side by side, 16,384 rows 31.5 / 26.0 in four rounds of 32-row items, 60,000 rows
+// 73 / 81; 602-64-40, 16,384 rows 120 / 129).
 bool split_where_used(int wide_steps, int d, bool direct, int64_t items)
 {
     const int cus = compute_units();
     if (wide_steps == 0 && d <= kPanel) return items <= 8 * cus;
-    return items <= 2 * cus && (direct ? wide_steps <= 9 : wide_steps * (items > cus ? 2 : 1) <= 5);
+    if (items > 2 * cus) return false;
+    const bool alone = items <= cus;
+    return wide_steps <= (direct ? (alone ? 30 : 15) : (alone ? 12 : 4));
 }
 
 }  // namespace

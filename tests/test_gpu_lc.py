@@ -321,7 +321,8 @@ def test_infinities_and_nans(d, widths, B, bf16):
 
 
 @pytest.mark.parametrize("d,widths,B,bf16", [(100, [256, 172, 41], 333, False), (270, [70, 130], 5000, True), (48, [40], 17, False),
-                                             (128, [256, 256, 256, 40], 600, False)])
+                                             (128, [256, 256, 256, 40], 9000, False),
+                                             (90, [131, 77, 40], 3000, False)])
 def test_captured_call_that_writes_its_result_directly(d, widths, B, bf16):
     """A concatenating call under graph capture splits its weights where it uses them (no shared slot), or needs none
     split (the last model): every replay gives the eager call's bits, with other calls of the library in between."""
@@ -357,10 +358,10 @@ def test_captured_call_that_writes_its_result_directly(d, widths, B, bf16):
 
 def test_calls_on_many_streams():
     """Direct calls on more streams than the library has slots for split weights, interleaved without waiting: each
-    gives what it gives alone.  (A model deep enough that its weights are split beforehand.)"""
+    gives what it gives alone.  (A model and a batch large enough that the weights are split beforehand.)"""
     import torch
     rng = np.random.default_rng(21)
-    n, d = 4000, 96
+    n, d = 9000, 96
     stack = torch.from_numpy(rng.normal(size=(1, n, d)).astype(np.float32)).cuda()
     models = [[torch.from_numpy(W).cuda() for W in make_weights(rng, d, [256, 256, 256, 64])] for _ in range(5)]
     want = [gp.lc_forward_tensors(stack, None, [1.0], m) for m in models]
@@ -572,7 +573,9 @@ def test_a_row_does_not_depend_on_the_rows_beside_it(d, widths, bf16):
     (39, [128], 3, 700), (40, [128], 3, 700),                # the last model on the fp32 instruction, the first in six products
     (124, [40], 1, 90), (128, [40], 1, 90), (127, [64, 64], 1, 40),
     (128, [128, 40], 0, 512 * 16), (128, [128, 40], 0, 512 * 32), (128, [128, 40], 0, 512 * 32 + 1),  # weights split where they are used
-    (32, [256, 250], 1, 100), (33, [256, 250], 1, 100), (160, [256, 40], 3, 64 * 16), (160, [256, 40], 3, 64 * 16 + 1),  # .. or beforehand
+    (128, [256, 250], 1, 100), (129, [256, 250], 1, 100), (160, [256, 40], 3, 64 * 16), (160, [256, 40], 3, 64 * 16 + 1),  # .. or beforehand
+    (192, [256] * 4, 0, 60), (193, [256] * 4, 0, 60), (224, [256, 256], 0, 6000), (225, [256, 256], 0, 6000),
+    (100, [131, 77, 40], 0, 50), (64, [253, 66, 129], 1, 50),  # .. lanes whose last columns lie beyond the layer
     (150, [64, 40], 0, 2048 * 32), (150, [64, 40], 0, 2048 * 32 + 1), (257, [64, 40], 0, 512 * 32 + 1),
     (600, [64, 16], 3, 40), (600, [64, 16], 0, 16),          # 16 rows to an item, three panels
     (100, [256, 172, 41], 3, 1), (256, [65] * 7 + [10], 0, 17), (270, [70, 130], 2, 600),
