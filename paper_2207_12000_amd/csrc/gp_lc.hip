@@ -25,12 +25,15 @@
 // on a 128-256-256-256-40 model with normal weights and features: relative error 0.99e-7, where
 // the fp32 instruction left 2.7e-7.  That is a matter of long sums, whose own roundings outweigh
 // the part left out: sums of at most kShortSum terms are taken on the fp32 instruction.  (A bf16
-// stack's first layer has one part, x itself: three products.)  Features and activations are split once, when they enter LDS; weights once per
-// call (gp_lc_split_weights).  Infinities, NaNs and numbers that the factor carries beyond
-// the largest bf16 one do not survive the split, but whatever they touch comes out of it as infinite
-// or NaN: a wave whose sums are not all finite takes that layer again on the fp32 instruction
-// (lc_layer_exact) and keeps these sums for the rows concerned, so results with such numbers are
-// those of plain fp32 arithmetic, and a row's bits do not depend on the rows beside it.
+// stack's first layer has one part, x itself: three products.  Splitting fp32 operands into bf16 parts is
+// due to Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for
+// higher-precision computations", 2019.)  Features and activations are split once, when they enter
+// LDS; weights once per call (gp_lc_split_weights) or, in calls of few work items, in each of them.
+// Infinities, NaNs and numbers that the factor carries beyond the largest bf16 one do not survive the
+// split, but whatever they touch comes out of it as infinite or NaN: a wave whose sums are not all
+// finite takes that layer again on the fp32 instruction (lc_layer_exact) and keeps these sums for
+// the rows concerned, so results with such numbers are those of plain fp32 arithmetic, and a row's
+// bits do not depend on the rows beside it.
 //
 // What bounds it: the matrix cores, 64 % busy at about 2 GHz (counters of the call over 169,343 fp32 rows); what they
 // wait for is gather, splits and barriers, which the second workgroup of a compute unit covers in part.  us per
@@ -310,7 +313,8 @@ __device__ __forceinline__ void lc_zero(v4f (&acc)[R][C])
 // of it: the sums are acc * sum_down().  Returns a bit for each row 16 r + i whose sums in this lane are not all finite (or
 // cannot be split).  frags: the split weights from W's first row on.
 // PARTS: bf16 parts of a row's elements in LDS, 3 (of 2^16 x) or (bf16 stack, first layer) 1 (x itself).  CARRY: acc
-// comes in with sums of earlier panels, to which these are added (and which are put aside in `before`).  RAW: no split weights, they are split here.  The products x1 w1 and
+// comes in with sums of earlier panels, to which these are added (and which are put aside in `before`).
+// RAW: no split weights, they are split here.  The products x1 w1 and
 // the small ones have accumulators of their own, added at the end: the small ones then cost the large sum no
 // roundings.  Four tiles' weights are in registers at any time: a tile's products done, its registers take
 // the weights of the tile four further on.
@@ -487,7 +491,8 @@ __device__ __forceinline__ unsigned lc_layer_any(const __bf16* tile, const Rows&
 // columns beyond Np become zeros, and every column below the next multiple of 32 is written (the next layer reads
 // that far)
 template <int R, int CT>
-__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, unsigned odd, float down, int colbase, int i, int kg, const v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_store_relu(__bf16* __restrict__ tile, int Np, unsigned odd, float down, int colbase, int i, int kg,
+                                              const v4f (&acc)[R][4])
 {
     constexpr int kPlane = 16 * R * kLd;
     const int c0 = colbase + 4 * CT * kg;
@@ -549,8 +554,8 @@ __device__ __forceinline__ void lc_store_relu_any(__bf16* tile, int Np, unsigned
 }
 
 template <int R, int CT>
-__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g, unsigned odd, float down, int i, int kg,
-                                         const v4f (&acc)[R][4])
+__device__ __forceinline__ void lc_write(float* __restrict__ dst, const LcArgs& a, int64_t row0, int C, int colbase, float g,
+                                         unsigned odd, float down, int i, int kg, const v4f (&acc)[R][4])
 {
     const int c0 = colbase + 4 * CT * kg;
 #pragma unroll
@@ -862,7 +867,7 @@ bool small_model(int T, int d, const int32_t* width)
 // of 32 weight rows takes 0.1 to 0.2 us longer in a layer wider than 64, twice that where two items share a unit.
 // us, 4 hops, split beforehand / where used:
 //                                       items alone (1024 rows)      two to a unit (2048)
-//   steps  model                 side by side   summed         side by side   summed
+//   steps  model                 side by side   summed          side by side   summed
 //       4  100-256-40               18.0 / 12.3    17.0 / 15.0     19.0 / 15.0    18.6 / 18.7
 //       8  128-128-128-40           16.3 / 13.3    15.8 / 15.4     18.2 / 15.1    17.7 / 18.7
 //      12  128-128-128-128-40       18.6 / 14.5    18.0 / 18.0     21.5 / 18.9    20.9 / 22.6
