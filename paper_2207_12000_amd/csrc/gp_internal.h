@@ -117,7 +117,13 @@ struct DevicePlan {
     float* dinv = nullptr;
     Segment* segs = nullptr;
     SplitRow* split = nullptr;
-    float* edge_ws = nullptr;   // nnz: dinv_sqrt[col[e]], built on first use of the sym operator
+    float* edge_ws = nullptr;   // nnz: dinv_sqrt[col[e]], for launches of the sym operator that read `col`
+    // the implicit lists' records with their ids in the order they are walked: 0 = not made, 1 = there, 2 = no room for them
+    int ord_state = 0;
+    Segment* ord_segs = nullptr;   // the allocation; ids (and weights) lie behind the records
+    int32_t* ord_col = nullptr;
+    float* ord_ws = nullptr;       // dinv_sqrt[ord_col[e]] (sym operator)
+    float* ord_ws_late = nullptr;  // allocated apart when the list was made by a call without weights
     float* carry = nullptr;     // num_slots x carry_ld fp32
     int64_t carry_ld = 0;
     unsigned long long* ctrl = nullptr;  // kHopCtrlWords words, zero between launches
@@ -370,6 +376,7 @@ struct HopArgs {
     int num_slices = 1;
     int slice_elems = 0;
     int64_t column_slices = 0;
+    int run_log2 = 0;  // implicit lists: an XCD takes runs of 2^run_log2 consecutive records
     int64_t persistent_blocks = 0;  // workgroups of the launch, 0 = as many as stay resident
     int64_t column_tile = 0;        // feature columns per kernel pass, 0 = automatic
     // optional plane entries (vectors of 4 columns, or of 8 bf16 columns with d a multiple of 4; implicit lists): a
@@ -408,6 +415,10 @@ gp_status launch_fixup(const FixupArgs& a, hipStream_t stream);
 gp_status launch_scale_convert(const void* src, int64_t lds, gp_dtype src_type, void* dst, int64_t ldd, gp_dtype dst_type,
                                int64_t n, int32_t d, float gamma, hipStream_t stream);
 gp_status launch_zero_words(unsigned long long* p, int count, hipStream_t stream);
+// the records' ids copied record after record (out_col, nnz < 2^32 of them) and the records with their new starts; starts:
+// num_segs words, scan_scratch: device_scan_scratch_words(num_segs) words
+gp_status launch_order_columns(const Segment* segs, int64_t num_segs, const int32_t* col, uint32_t* starts, uint32_t* scan_scratch,
+                               int32_t* out_col, Segment* out_segs, hipStream_t stream);
 gp_status launch_fill_edge_weights(const int32_t* col, const float* by_col, float* w, int64_t nnz, hipStream_t stream);
 // max_blocks > 0 caps the grid (copies over the host link need few workgroups and
 // must leave the compute units to the kernels running beside them)

@@ -266,9 +266,9 @@ __global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __res
     const int lane = threadIdx.x % G;
     const int xcd = blockIdx.x & 7;
     // This XCD's list: the record of position p < count is segs[place_of(p)].  Implicit lists: the
-    // XCDs that share a slice take the records interleaved, in runs of 2^run_log2 consecutive records
-    // (1 as a rule; 8 where records add plane entries: the entries of 8 consecutive records share their lines, which then
-    // only one XCD asks for).
+    // XCDs that share a slice take the records interleaved, in runs of 2^run_log2 consecutive records: what consecutive
+    // records read side by side (ids and weights of an ordered column list, plane entries) shares lines, which then
+    // one XCD asks for.
     int64_t base, count;
     int rstep, xcd_slice;
     if (lists.explicit_lists) {
@@ -599,6 +599,33 @@ __global__ __launch_bounds__(kThreads) void gp_fill_edge_weights(const int32_t* 
         w[e] = by_col[col[e]];
 }
 
+// The column list in the order in which the records are walked: record i's ids from out_start[i] (the sum of the lengths
+// before it) on, and the record itself with its new start.  Sixteen lanes per record (a record has a few tens of ids).
+__global__ __launch_bounds__(kThreads) void gp_record_lengths(const Segment* __restrict__ segs, int64_t num_segs, uint32_t* __restrict__ len)
+{
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < num_segs; i += (int64_t)gridDim.x * kThreads)
+        len[i] = segs[i].len;
+}
+
+__global__ __launch_bounds__(kThreads) void gp_order_columns(const Segment* __restrict__ segs, int64_t num_segs,
+                                                             const uint32_t* __restrict__ out_start, const int32_t* __restrict__ col,
+                                                             int32_t* __restrict__ out_col, Segment* __restrict__ out_segs)
+{
+    constexpr int G = 16, GPB = kThreads / G;
+    const int lane = threadIdx.x % G;
+    for (int64_t i = (int64_t)blockIdx.x * GPB + threadIdx.x / G; i < num_segs; i += (int64_t)gridDim.x * GPB) {
+        Segment s = segs[i];
+        const int64_t from = ((int64_t)s.start_hi << 32) | s.start_lo;
+        const uint32_t to = out_start[i];
+        for (int j = lane; j < s.len; j += G) out_col[(int64_t)to + j] = col[from + j];
+        if (lane == 0) {
+            s.start_lo = to;
+            s.start_hi = 0;
+            out_segs[i] = s;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // rows that were cut: add their partial rows in list order, scale, store
 // ---------------------------------------------------------------------------
@@ -716,6 +743,7 @@ template <typename T, int VEC, int G, int VPL>
 gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
 {
     constexpr int GPB = kThreads / G;
+    const int run_log2 = a.planes ? std::max(3, a.run_log2) : a.run_log2;
     XcdLists lists;
     int64_t longest = 0;  // records in the longest per-XCD list
     if (a.xcd_off) {
@@ -725,7 +753,8 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     } else {
         for (int x = 0; x <= 8; ++x) lists.off[x] = 0;
         const int reps = 8 / a.num_slices;  // XCDs that share one slice
-        longest = (a.num_segs + reps - 1) / reps;
+        const int64_t runs = (a.num_segs + ((int64_t)1 << run_log2) - 1) >> run_log2;
+        longest = std::min(a.num_segs, ((runs + reps - 1) / reps) << run_log2);
         lists.explicit_lists = 0;
     }
     const int64_t chunks = (longest + GPB - 1) / GPB;  // workgroups per XCD that find work
@@ -750,15 +779,15 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     if (a.edge_w && a.edge_w_per_edge)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 2>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, a.planes ? 3 : 0, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
     else if (a.edge_w)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 1>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, a.planes ? 3 : 0, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
     else
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 0>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, a.planes ? 3 : 0, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -915,6 +944,21 @@ gp_status launch_fill_edge_weights(const int32_t* col, const float* by_col, floa
     if (nnz == 0) return GP_OK;
     const int64_t blocks = std::min<int64_t>((nnz + kThreads - 1) / kThreads, 256 * 32);
     hipLaunchKernelGGL(gp_fill_edge_weights, dim3((unsigned)blocks), dim3(kThreads), 0, stream, col, by_col, w, nnz);
+    GP_HIP(hipGetLastError());
+    return GP_OK;
+}
+
+gp_status launch_order_columns(const Segment* segs, int64_t num_segs, const int32_t* col, uint32_t* starts, uint32_t* scan_scratch,
+                               int32_t* out_col, Segment* out_segs, hipStream_t stream)
+{
+    if (num_segs == 0) return GP_OK;
+    const int64_t flat = std::min<int64_t>((num_segs + kThreads - 1) / kThreads, 256 * 32);
+    hipLaunchKernelGGL(gp_record_lengths, dim3((unsigned)flat), dim3(kThreads), 0, stream, segs, num_segs, starts);
+    GP_HIP(hipGetLastError());
+    gp_status st = device_exclusive_scan(starts, num_segs, scan_scratch, stream);
+    if (st != GP_OK) return st;
+    const int64_t blocks = std::min<int64_t>((num_segs + kThreads / 16 - 1) / (kThreads / 16), 256 * 32);
+    hipLaunchKernelGGL(gp_order_columns, dim3((unsigned)blocks), dim3(kThreads), 0, stream, segs, num_segs, starts, col, out_col, out_segs);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }

@@ -28,6 +28,8 @@ void release(DevicePlan& D)
     (void)hipFree(D.split);
     (void)hipFree(D.carry);
     (void)hipFree(D.edge_ws);
+    (void)hipFree(D.ord_segs);
+    (void)hipFree(D.ord_ws_late);
     (void)hipFree(D.ctrl);
     (void)hipFree(D.ping[0]);
     (void)hipFree(D.ping[1]);
@@ -48,7 +50,7 @@ void release(DevicePlan& D)
 
 // Uploads the plan once per plan (to the device that is current at that time)
 // and (re)sizes the partial-row buffer for d columns.
-gp_status ensure_device(const gp_plan* plan, int32_t d, bool want_edge_weights, hipStream_t stream)
+gp_status ensure_device(const gp_plan* plan, int32_t d, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lk(plan->mu);
     DevicePlan& D = plan->dev;
@@ -73,13 +75,6 @@ gp_status ensure_device(const gp_plan* plan, int32_t d, bool want_edge_weights, 
         // so the host vectors may be touched freely afterwards
         GP_HIP(hipStreamSynchronize(stream));
         D.device = cur;
-    }
-    if (want_edge_weights && !D.edge_ws && plan->nnz > 0) {
-        // one coalesced fp32 per non-zero instead of one random 4-byte gather per non-zero and hop
-        GP_HIP(hipMalloc((void**)&D.edge_ws, (size_t)plan->nnz * sizeof(float)));
-        gp_status st = launch_fill_edge_weights(D.col, D.dinv_sqrt, D.edge_ws, plan->nnz, stream);
-        if (st != GP_OK) return st;
-        GP_HIP(hipStreamSynchronize(stream));  // once per plan: later calls may come on other streams
     }
     const int64_t need_ld = ((int64_t)d + 3) / 4 * 4;
     if (plan->num_slots > 0 && need_ld > D.carry_ld) {
@@ -314,6 +309,104 @@ gp_status ensure_lds(const gp_plan* plan, int32_t d, hipStream_t stream)
     return GP_OK;
 }
 
+// dinv_sqrt[col[e]] for every entry of a device column list, made once (plan->mu held): one coalesced fp32 per
+// non-zero instead of one random 4-byte gather per non-zero and hop.  *w stays nullptr when there is no room.
+gp_status ensure_edge_weights(const gp_plan* plan, const int32_t* col, float** w, hipStream_t stream)
+{
+    if (*w || plan->nnz == 0) return GP_OK;
+    float* p = nullptr;
+    if (hipMalloc((void**)&p, (size_t)plan->nnz * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        return GP_OK;
+    }
+    gp_status st = launch_fill_edge_weights(col, plan->dev.dinv_sqrt, p, plan->nnz, stream);
+    if (st == GP_OK && hipStreamSynchronize(stream) != hipSuccess)  // once per plan: later calls may come on other streams
+        st = fail(GP_ERR_DEVICE, "edge weights");
+    if (st != GP_OK) {
+        (void)hipFree(p);
+        return st;
+    }
+    *w = p;
+    return GP_OK;
+}
+
+// The implicit lists' records with their ids in the order they are walked (plan->mu held).  Records are walked longest
+// first, so in the plan's own order the ids and weights of neighbouring records lie apart: a record of 13 ids reads
+// 1.4 lines of each where 0.4 hold them, and records handed out one by one have every XCD read the lines of all of them.
+// The hop is bound by the lines that the L2s miss (about 57 lines per ns, all XCDs together; 47.5 were measured), and a
+// fourth of the misses of a hop of 64 columns in two slices were these.
+// One allocation holds records, ids, weights (if this call wants them) and the scan's scratch: allocating is most of what
+// the list costs.
+gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t stream)
+{
+    DevicePlan& D = plan->dev;
+    if (D.ord_state != 0) return GP_OK;
+    const size_t nsegs = plan->segs.size(), nnz = (size_t)plan->nnz;
+    D.ord_state = 2;
+    if (nsegs == 0 || nnz == 0 || plan->nnz > (int64_t)UINT32_MAX) return GP_OK;
+    const size_t words = nnz * (want_weights ? 2 : 1) + nsegs + device_scan_scratch_words((int64_t)nsegs);
+    if (hipMalloc((void**)&D.ord_segs, nsegs * sizeof(Segment) + words * 4) != hipSuccess) {
+        (void)hipGetLastError();  // no room: the records as the plan has them do
+        D.ord_segs = nullptr;
+        return GP_OK;
+    }
+    int32_t* col = (int32_t*)(D.ord_segs + nsegs);
+    float* ws = want_weights ? (float*)(col + nnz) : nullptr;
+    uint32_t* starts = (uint32_t*)(col + nnz * (want_weights ? 2 : 1));
+    gp_status st = launch_order_columns(D.segs, (int64_t)nsegs, D.col, starts, starts + nsegs, col, D.ord_segs, stream);
+    if (st == GP_OK && ws) st = launch_fill_edge_weights(col, D.dinv_sqrt, ws, plan->nnz, stream);
+    if (hipStreamSynchronize(stream) != hipSuccess && st == GP_OK)  // once per plan: later calls may come on other streams
+        st = fail(GP_ERR_DEVICE, "ordering the column list");
+    if (st != GP_OK) return st;  // (the memory goes with the plan)
+    D.ord_col = col;
+    D.ord_ws = ws;
+    D.ord_state = 1;
+    return GP_OK;
+}
+
+// An XCD takes runs of 32 records of an ordered list: their ids and weights (one to two KB of each) share all lines but
+// the outer two.  Runs of 1 / 8 / 16 / 32 / 128 records, us: three hops of 169,343 rows x 128 fp32 columns, 2.5 million
+// non-zeros, 506 / 486 / 477 / 478 / 474 (517 in the plan's own order); 507,001 rows x 128 bf16, 10.3 million, 1121 / 1054 /
+// 1048 / 1052 / 1044 (1144); ten filter hops of 169,343 x 64 fp32 1009 / 939 / 933 / 924 / 927 (1027).  Longer runs gain
+// nothing more, and in a small graph they deal the work to the XCDs less evenly.
+constexpr int kOrderedRunLog2 = 5;
+
+// Records, ids and weights of a launch on the implicit lists, or on explicit ones over the plan's own column list
+// (plan->mu held).  may_build = false, and a stream that is being captured: only what is there.
+gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build)
+{
+    DevicePlan& D = plan->dev;
+    const bool weighted = a.edge_w != nullptr, own_col = a.xcd_off != nullptr;
+    gp_status st;
+    if (may_build && ((!own_col && D.ord_state == 0) || (weighted && !(own_col || D.ord_state == 2 ? D.edge_ws : D.ord_ws)))) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+            (void)hipGetLastError();
+            cs = hipStreamCaptureStatusActive;
+        }
+        if (cs == hipStreamCaptureStatusNone) {
+            if (!own_col && (st = ensure_ordered(plan, weighted, stream)) != GP_OK) return st;
+            if (weighted && !own_col && D.ord_state == 1 && !D.ord_ws) {  // made by a call without weights
+                if ((st = ensure_edge_weights(plan, D.ord_col, &D.ord_ws_late, stream)) != GP_OK) return st;
+                D.ord_ws = D.ord_ws_late;
+            }
+            if (weighted && (own_col || D.ord_state != 1) && (st = ensure_edge_weights(plan, D.col, &D.edge_ws, stream)) != GP_OK) return st;
+        }
+    }
+    const bool ordered = !own_col && D.ord_state == 1;
+    if (ordered) {
+        a.segs = D.ord_segs;
+        a.col = D.ord_col;
+        a.run_log2 = kOrderedRunLog2;
+    }
+    const float* w = ordered ? D.ord_ws : D.edge_ws;
+    if (weighted) {
+        a.edge_w = w ? w : D.dinv_sqrt;
+        a.edge_w_per_edge = w != nullptr;
+    }
+    return GP_OK;
+}
+
 // Gives the launch explicit work lists if the plan's cache schedule applies to it
 // (building and uploading them on first use of a slice shape).  *split comes back true
 // when the lists hold the hot pieces of the split schedule: the caller then runs the cold
@@ -323,14 +416,14 @@ gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream,
 {
     if (split) *split = false;
     if (lds) *lds = false;
+    std::lock_guard<std::mutex> lk(plan->mu);
     const int es = a.dtype == GP_F32 ? 4 : 2;
     const int vec = hop_vector_width(a);
     // several column passes: implicit lists (explicit ones are cut for the whole row)
     if (pass_width(a.column_tile, a.dtype, a.d, a.ldin, a.xout ? a.ldout : a.ldin, a.xin, a.xout ? a.xout : a.xin) < a.d)
-        return GP_OK;
-    std::lock_guard<std::mutex> lk(plan->mu);
+        return attach_columns(plan, a, stream, may_build);
     int S = 0, elems = 0;
-    if (!may_build && plan->hot_mode == 0) return GP_OK;  // nothing built yet: implicit lists
+    if (!may_build && plan->hot_mode == 0) return attach_columns(plan, a, stream, false);  // nothing built yet: implicit lists
     decide_hot_mode(plan, a.d);
     DevicePlan& D = plan->dev;
     // the hot non-zeros can come out of LDS where the segment kernel's vectors are whole strips of four columns:
@@ -350,7 +443,7 @@ gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream,
         }
     }
     // no clusters: nothing an L2 could be made to hold
-    if (plan->hot_mode != 1 || !choose_cache_schedule(plan, a.d, es, vec, S, elems)) return GP_OK;
+    if (plan->hot_mode != 1 || !choose_cache_schedule(plan, a.d, es, vec, S, elems)) return attach_columns(plan, a, stream, may_build);
     // hot and cold pieces in phases of their own need buffers of their own: only where the caller may allocate
     // (not worth it when hardly anything leaves the clusters: every row then pays two partial rows for nothing)
     const bool want_split = split && may_build && plan->opt.split_records != 2 &&
@@ -362,7 +455,7 @@ gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream,
     const XcdWork* found = nullptr;
     for (const XcdWork& w : D.work)
         if (w.num_slices == S && w.slice_elems == elems && w.split == want_split) found = &w;
-    if (!found && !may_build) return GP_OK;
+    if (!found && !may_build) return attach_columns(plan, a, stream, false);
     if (!found) {
         std::vector<Segment> recs;
         XcdWork w;
@@ -390,7 +483,7 @@ gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream,
     a.num_slices = found->num_slices;
     a.slice_elems = found->slice_elems;
     if (split) *split = found->split;
-    return GP_OK;
+    return found->split ? GP_OK : attach_columns(plan, a, stream, may_build);
 }
 
 }  // namespace
@@ -439,7 +532,7 @@ gp_status fixup_passes(const FixupArgs& f0, hipStream_t stream)
 gp_status propagate_resident(const gp_plan* plan, const void* X, int64_t ldx, int32_t d, gp_dtype dtype, gp_agg agg,
                              int32_t K, void* out, int64_t ldo, hipStream_t stream)
 {
-    gp_status st = ensure_device(plan, d, agg == GP_AGG_SYM, stream);
+    gp_status st = ensure_device(plan, d, stream);
     if (st != GP_OK) return st;
     const DevicePlan& D = plan->dev;
     return resident_hops(plan, X, ldx, d, dtype, agg, K, out, ldo, stream, D.carry, D.carry_ld, D.ctrl, true);
@@ -526,8 +619,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         if (st != GP_OK) return st;
     }
 
-    const bool per_edge = D.edge_ws != nullptr;
-    const float* edge_w = agg == GP_AGG_SYM ? (per_edge ? D.edge_ws : D.dinv_sqrt) : nullptr;
+    const float* edge_w = agg == GP_AGG_SYM ? D.dinv_sqrt : nullptr;  // (attach_work_lists has one per non-zero where it can)
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
 
     for (int32_t k = 1; k <= K; ++k) {
@@ -537,7 +629,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         a.col = D.col;
         a.col_base = 0;
         a.edge_w = edge_w;
-        a.edge_w_per_edge = per_edge;
+        a.edge_w_per_edge = false;
         a.row_scale = row_scale;
         a.xin = base + (int64_t)(k - 1) * slab;
         a.ldin = ldo;
@@ -599,7 +691,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
 gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int32_t d, gp_dtype dtype, gp_agg agg,
                             int32_t K, const float* coeff, void* out, int64_t ldo, hipStream_t stream)
 {
-    gp_status st = ensure_device(plan, d, agg == GP_AGG_SYM, stream);
+    gp_status st = ensure_device(plan, d, stream);
     if (st != GP_OK) return st;
     DevicePlan& D = plan->dev;
     const int64_t n = plan->n;
@@ -635,7 +727,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
     profile_end(stream);
     if (st != GP_OK) return st;
 
-    const float* edge_w = agg == GP_AGG_SYM ? D.edge_ws : nullptr;
+    const float* edge_w = agg == GP_AGG_SYM ? D.dinv_sqrt : nullptr;  // (attach_work_lists has one per non-zero where it can)
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
     for (int32_t k = 1; k <= K; ++k) {
         HopArgs a;
@@ -644,7 +736,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         a.col = D.col;
         a.col_base = 0;
         a.edge_w = edge_w;
-        a.edge_w_per_edge = true;
+        a.edge_w_per_edge = false;
         a.row_scale = row_scale;
         a.xin = k == 1 ? X : D.ping[(k - 1) & 1];
         a.ldin = k == 1 ? ldx : ldp;

@@ -1,0 +1,73 @@
+"""Implicit lists on ids in walking order, an XCD taking runs of 32 records: sizes around a run and around the runs
+that the XCDs share, against the fp64 oracle at 1e-5 * (A^^k |X|); and calls that may not build the ordered list."""
+import numpy as np
+import pytest
+
+import gp_synth
+import oracle
+import paper_2207_12000_amd as gp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _defaults(gpu_or_skip):
+    yield
+    for name in ("column_slices", "segment_edges", "cache_schedule", "hub_pass"):
+        gp.gp_set_option(name, 0)
+
+
+def graph(n, m, seed):
+    rng = np.random.default_rng(seed)
+    return rng.integers(0, n, m).astype(np.int32), (rng.integers(0, n, m) ** 2 // max(1, n)).astype(np.int32)
+
+
+def hops(plan, x, agg, K):
+    import torch
+    out = gp.propagate_tensors(plan, x, agg, K)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 1025, 4099])   # rows = records where no row is cut
+@pytest.mark.parametrize("slices", [1, 4, 8])
+@pytest.mark.parametrize("agg", [gp.GP_AGG_SYM, gp.GP_AGG_MEAN])
+def test_runs_of_records_match_the_oracle(n, slices, agg):
+    import torch
+    gp.gp_set_option("column_slices", slices)
+    gp.gp_set_option("cache_schedule", 2)          # no clusters: implicit lists
+    gp.gp_set_option("segment_edges", 16)          # hubs are cut: more records than rows
+    src, dst = graph(n, 6 * n, n)
+    d, K, budget = 40, 2, max(64, 3 * n)
+    X = gp_synth.features(n, d, "normal", gp_synth.rng_for(7, n))
+    op = oracle.plan_blocks(src, dst, n, budget, gp.GP_SYMMETRISE)
+    with gp.gp_plan_blocks(src, dst, n, budget, gp.GP_SYMMETRISE) as plan:
+        got = hops(plan, torch.from_numpy(X).cuda(), agg, K).cpu().numpy().astype(np.float64)
+    Xw = X.astype(np.float64)
+    want, bound = oracle.propagate(op, Xw, agg, K), oracle.bound_stack(op, Xw, agg, K)
+    for k in range(K + 1):
+        assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
+
+
+def test_captured_calls_that_find_no_ordered_list():
+    """A plan whose calls so far took the LDS pass has no ordered list; a captured call of another width may not make
+    one and runs on the plan's own order, with the same bits."""
+    import torch
+    w = gp_synth.make_workload(2, scale=0.2, d=36)
+    gp.gp_set_option("hub_pass", 1)
+    n, K = w.n, 2
+    with gp.gp_plan_blocks(w.src, w.dst, n, max(20_000, w.m // 3), w.flags) as plan:
+        hops(plan, torch.from_numpy(w.X).cuda(), gp.GP_AGG_SYM, K)
+        x = torch.from_numpy(np.ascontiguousarray(w.X[:, :3])).cuda()
+        out = torch.zeros((K + 1, n, 3), device="cuda:0")
+        g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(g, stream=side):
+            gp.gp_propagate(plan, x.data_ptr(), 3, 3, gp.GP_F32, gp.GP_AGG_SYM, K, out.data_ptr(), 3,
+                            torch.cuda.current_stream().cuda_stream)
+        for rep in range(3):
+            x.copy_(torch.from_numpy(gp_synth.features(n, 3, "normal", gp_synth.rng_for(5, rep))))
+            out.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, hops(plan, x, gp.GP_AGG_SYM, K))     # eager: the ordered list
