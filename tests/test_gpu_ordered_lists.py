@@ -71,3 +71,33 @@ def test_captured_calls_that_find_no_ordered_list():
             g.replay()
             torch.cuda.synchronize()
             assert torch.equal(out, hops(plan, x, gp.GP_AGG_SYM, K))     # eager: the ordered list
+
+
+@pytest.mark.parametrize("d", [7, 40, 128])
+def test_rows_of_few_and_many_partial_rows(d):
+    """Rows cut into 2 .. 18 segments: the fix-up's partial rows in flight (four and four more) and its remainders, and the
+    filter sum, which takes the very rows of the stack: at most one rounding per term of sum_k |c_k| |A^^k X|."""
+    import torch
+    gp.gp_set_option("cache_schedule", 2)
+    gp.gp_set_option("segment_edges", 8)
+    n, K, coeff = 400, 3, [0.5, -0.25, 2.0, 0.125]
+    lengths = [9, 16, 17, 24, 25, 32, 33, 40, 41, 64, 65, 72, 73, 129, 137, 140]
+    rng = np.random.default_rng(d)
+    src = np.repeat(np.arange(len(lengths)), lengths).astype(np.int32)
+    dst = np.concatenate([rng.choice(np.arange(20, n), c, replace=False) for c in lengths]).astype(np.int32)
+    X = gp_synth.features(n, d, "normal", gp_synth.rng_for(3, d))
+    op = oracle.plan_blocks(src, dst, n, 1 << 20, gp.GP_SYMMETRISE)
+    with gp.gp_plan_blocks(src, dst, n, 1 << 20, gp.GP_SYMMETRISE) as plan:
+        x = torch.from_numpy(X).cuda()
+        stack = hops(plan, x, gp.GP_AGG_SYM, K).cpu().numpy().astype(np.float64)
+        out = torch.empty_like(x)
+        gp.gp_propagate_combine(plan, x.data_ptr(), d, d, gp.GP_F32, gp.GP_AGG_SYM, K, coeff, out.data_ptr(), d,
+                                torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    Xw = X.astype(np.float64)
+    want, bound = oracle.propagate(op, Xw, gp.GP_AGG_SYM, K), oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, K)
+    for k in range(K + 1):
+        assert np.all(np.abs(stack[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
+    total = sum(abs(c) * np.abs(s) for c, s in zip(coeff, stack))
+    exact = sum(c * s for c, s in zip(coeff, stack))
+    assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - exact) <= (K + 1) * 2.0 ** -24 * 1.01 * total + 1e-30)
