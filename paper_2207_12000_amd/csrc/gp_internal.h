@@ -390,6 +390,8 @@ struct HopArgs {
     float* comb = nullptr;
     int64_t ldc = 0;
     float gamma = 0.0f;
+    bool comb_starts = false;  // the first hop, X = xin: comb[row] = gamma0 * X[row] + gamma * result row
+    float gamma0 = 0.0f;
 };
 gp_status launch_hop(const HopArgs& a, hipStream_t stream);
 // widest vector (in elements) the operands of this launch are aligned for
@@ -408,6 +410,9 @@ struct FixupArgs {
     float* comb = nullptr;  // as in HopArgs
     int64_t ldc = 0;
     float gamma = 0.0f;
+    const void* x0 = nullptr;  // the first hop's X (leading dimension ldx0): comb[row] = gamma0 * X[row] + gamma * result row
+    int64_t ldx0 = 0;
+    float gamma0 = 0.0f;
     int64_t column_tile = 0;
 };
 gp_status launch_fixup(const FixupArgs& a, hipStream_t stream);

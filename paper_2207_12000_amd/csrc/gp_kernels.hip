@@ -194,6 +194,33 @@ __device__ __forceinline__ void add_to_filter(float* __restrict__ cp, const floa
     }
 }
 
+// x[0..VEC) = gamma0 * X's vector: the k = 0 term
+template <typename T, int VEC>
+__device__ __forceinline__ void first_term(const T* __restrict__ xp, float gamma0, float (&x)[VEC])
+{
+    Row<T, VEC>::load(xp, x);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) x[i] *= gamma0;
+}
+
+// the filter output's first two terms at once: cp[0..VEC) = gamma0 * X + gamma * o
+template <typename T, int VEC>
+__device__ __forceinline__ void start_filter(const T* __restrict__ xp, float gamma0, float* __restrict__ cp, const float (&o)[VEC],
+                                             int fresh, float gamma)
+{
+    float c[VEC];
+    first_term<T, VEC>(xp, gamma0, c);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) c[i] = fmaf(gamma, o[i], c[i]);
+    if (fresh == 0) {
+        Row<float, VEC>::store(cp, c);
+    } else {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+            if (i >= fresh) cp[i] = c[i];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // one hop over a list of segments
 // ---------------------------------------------------------------------------
@@ -253,7 +280,8 @@ __global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __res
                                                             T* __restrict__ xout, int64_t ldout,
                                                             float* __restrict__ carry, int64_t carry_ld, int d,
                                                             int num_slices, int slice_elems, float* __restrict__ comb,
-                                                            int64_t ldc, float gamma, const float* __restrict__ planes,
+                                                            int64_t ldc, float gamma, int comb_starts, float gamma0,
+                                                            const float* __restrict__ planes,
                                                             int64_t num_pos, int run_log2, int plane_log2)
 {
     constexpr int GPB = kThreads / G;
@@ -390,7 +418,12 @@ __global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __res
         if constexpr (kFiltAhead) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) filt[i] = 0.0f;
-            if (filt_ahead) Row<float, VEC>::load(comb + (int64_t)r.row * ldc + coff[0], filt);
+            if (filt_ahead) {
+                if (comb_starts)
+                    first_term<T, VEC>(xin + (int64_t)r.row * ldin + coff[0], gamma0, filt);
+                else
+                    Row<float, VEC>::load(comb + (int64_t)r.row * ldc + coff[0], filt);
+            }
         }
         float acc[NACC][VPL][VEC];
 #pragma unroll
@@ -571,6 +604,8 @@ __global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __res
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) filt[i] = fmaf(gamma, o[i], filt[i]);
                     Row<float, VEC>::store(comb + (int64_t)r.row * ldc + coff[v], filt);
+                } else if (comb && comb_starts) {
+                    start_filter<T, VEC>(xin + (int64_t)r.row * ldin + coff[v], gamma0, comb + (int64_t)r.row * ldc + coff[v], o, fresh[v], gamma);
                 } else if (comb) {
                     add_to_filter<VEC>(comb + (int64_t)r.row * ldc + coff[v], o, fresh[v], gamma);
                 }
@@ -651,7 +686,7 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
                                                           const float* __restrict__ carry, int64_t carry_ld,
                                                           const float* __restrict__ row_scale, T* __restrict__ xout,
                                                           int64_t ldout, int d, float* __restrict__ comb, int64_t ldc,
-                                                          float gamma)
+                                                          float gamma, const T* __restrict__ x0, int64_t ldx0, float gamma0)
 {
     constexpr int GPB = kThreads / G;
     const int lane = threadIdx.x % G;
@@ -674,7 +709,12 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
 #pragma unroll
         for (int i = 0; i < VEC; ++i) filt[i] = 0.0f;
         const bool filt_ahead = comb && fresh == 0;
-        if (filt_ahead) Row<float, VEC>::load(comb + (int64_t)sr.row * ldc + c0, filt);
+        if (filt_ahead) {
+            if (x0)
+                first_term<T, VEC>(x0 + (int64_t)sr.row * ldx0 + c0, gamma0, filt);
+            else
+                Row<float, VEC>::load(comb + (int64_t)sr.row * ldc + c0, filt);
+        }
         float acc[4][VEC];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -715,6 +755,8 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
 #pragma unroll
             for (int i = 0; i < VEC; ++i) filt[i] = fmaf(gamma, r[i], filt[i]);
             Row<float, VEC>::store(comb + (int64_t)sr.row * ldc + c0, filt);
+        } else if (comb && x0) {
+            start_filter<T, VEC>(x0 + (int64_t)sr.row * ldx0 + c0, gamma0, comb + (int64_t)sr.row * ldc + c0, r, fresh, gamma);
         } else if (comb) {
             add_to_filter<VEC>(comb + (int64_t)sr.row * ldc + c0, r, fresh, gamma);
         }
@@ -825,15 +867,15 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     if (a.edge_w && a.edge_w_per_edge)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 2>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
     else if (a.edge_w)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 1>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
     else
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 0>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -846,7 +888,8 @@ gp_status launch_fixup_t(const FixupArgs& a, hipStream_t stream)
     if (blocks == 0) return GP_OK;
     if (blocks > INT32_MAX) return fail(GP_ERR_UNSUPPORTED, "%lld workgroups exceed the grid limit", (long long)blocks);
     hipLaunchKernelGGL((gp_fixup_rows<T, VEC, G, VPL>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.split,
-                       a.num_split, a.carry, a.carry_ld, a.row_scale, (T*)a.xout, a.ldout, a.d, a.comb, a.ldc, a.gamma);
+                       a.num_split, a.carry, a.carry_ld, a.row_scale, (T*)a.xout, a.ldout, a.d, a.comb, a.ldc, a.gamma,
+                       (const T*)a.x0, a.ldx0, a.gamma0);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -945,6 +988,7 @@ gp_status launch_fixup(const FixupArgs& a, hipStream_t stream)
 {
     // the fix-up reads fp32 carry rows and writes T rows: use the vector width both allow
     int vec = a.xout ? vector_width(a.dtype, a.d, a.ldout, a.ldout, a.xout, a.xout) : 4;
+    if (a.x0) vec = std::min(vec, vector_width(a.dtype, a.d, a.ldx0, a.ldx0, a.x0, a.x0));
     if (a.comb) vec = std::min(vec, vector_width(GP_F32, a.d, a.ldc, a.ldc, a.comb, a.comb));
     if (vec > 4) vec = 4;
     while (vec > 1 && (a.carry_ld % vec != 0)) vec /= 2;

@@ -101,3 +101,30 @@ def test_rows_of_few_and_many_partial_rows(d):
     total = sum(abs(c) * np.abs(s) for c, s in zip(coeff, stack))
     exact = sum(c * s for c, s in zip(coeff, stack))
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - exact) <= (K + 1) * 2.0 ** -24 * 1.01 * total + 1e-30)
+
+
+@pytest.mark.parametrize("dtype,d,pad", [(gp.GP_F32, 64, 0), (gp.GP_F32, 47, 2), (gp.GP_F32, 1100, 1), (gp.GP_BF16, 72, 0), (gp.GP_BF16, 601, 1),
+                                         (gp.GP_BF16, 600, 1)])
+def test_first_hop_writes_the_filters_two_terms(dtype, d, pad):
+    """c0 X + c1 A^ X in one hop, X's rows aligned less well than the output's (the fix-up then takes X's vectors and
+    column passes): fp32 sums to 1e-5 of the magnitudes, and one rounding of the result for bf16 storage."""
+    import torch
+    gp.gp_set_option("cache_schedule", 2)
+    gp.gp_set_option("segment_edges", 8)
+    n, c0, c1 = 300, 0.75, -1.5
+    src, dst = graph(n, 4000, d)
+    X = torch.randn(n, d + pad, generator=torch.Generator().manual_seed(d)).to(torch.float32 if dtype == gp.GP_F32 else torch.bfloat16)
+    x = X.cuda()
+    out = torch.full((n, d), float("nan"), dtype=x.dtype, device="cuda")
+    Xw = X[:, :d].double().numpy()
+    op = oracle.plan_blocks(src, dst, n, 900, gp.GP_SYMMETRISE)
+    with gp.gp_plan_blocks(src, dst, n, 900, gp.GP_SYMMETRISE) as plan:
+        assert plan.num_partial_rows > 0
+        gp.gp_propagate_combine(plan, x.data_ptr(), d + pad, d, dtype, gp.GP_AGG_SYM, 1, [c0, c1], out.data_ptr(), d,
+                                torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    hop = oracle.propagate(op, Xw, gp.GP_AGG_SYM, 1)[1]
+    want = c0 * Xw + c1 * hop
+    err = np.abs(out.double().cpu().numpy() - want)
+    sums = 1e-5 * (c0 * np.abs(Xw) + abs(c1) * oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, 1)[1])
+    assert np.all(err <= sums + (2.0 ** -8 * np.abs(want) + sums * 2.0 ** -8 if dtype == gp.GP_BF16 else 0.0) + 1e-30)
