@@ -118,6 +118,7 @@ struct DevicePlan {
     Segment* segs = nullptr;
     SplitRow* split = nullptr;
     float* edge_ws = nullptr;   // nnz: dinv_sqrt[col[e]], for launches of the sym operator that read `col`
+    bool weighted_calls = false;  // a call of the sym operator that could allocate has been made: every list that a launch may take has its weights
     // the implicit lists' records with their ids in the order they are walked: 0 = not made, 1 = there, 2 = no room for them
     int ord_state = 0;
     Segment* ord_segs = nullptr;   // the allocation; ids (and weights) lie behind the records

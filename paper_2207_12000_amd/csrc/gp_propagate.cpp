@@ -371,38 +371,46 @@ gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t str
 // nothing more, and in a small graph they deal the work to the XCDs less evenly.
 constexpr int kOrderedRunLog2 = 5;
 
-// Records, ids and weights of a launch on the implicit lists, or on explicit ones over the plan's own column list
-// (plan->mu held).  may_build = false, and a stream that is being captured: only what is there.
+bool may_allocate_on(hipStream_t stream)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
+}
+
+// Weights per non-zero for every list that an implicit or an explicit launch may be given (plan->mu held): the ordered
+// list if there is one, else the plan's own, which the explicit lists are written over too.
+gp_status ensure_weights(const gp_plan* plan, hipStream_t stream)
+{
+    DevicePlan& D = plan->dev;
+    const bool ordered = D.ord_state == 1;
+    const bool own = !ordered || std::any_of(D.work.begin(), D.work.end(), [](const XcdWork& w) { return !w.split; });
+    if (plan->nnz == 0 || ((!own || D.edge_ws) && (!ordered || D.ord_ws)) || !may_allocate_on(stream)) return GP_OK;
+    gp_status st;
+    if (ordered && !D.ord_ws) {  // made by a call without weights
+        if ((st = ensure_edge_weights(plan, D.ord_col, &D.ord_ws_late, stream)) != GP_OK) return st;
+        D.ord_ws = D.ord_ws_late;
+    }
+    return own ? ensure_edge_weights(plan, D.col, &D.edge_ws, stream) : GP_OK;
+}
+
+// Records and ids of a launch on the implicit lists, or on explicit ones over the plan's own column list (plan->mu
+// held).  may_build = false, and a stream that is being captured: only what is there.
 gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build)
 {
     DevicePlan& D = plan->dev;
-    const bool weighted = a.edge_w != nullptr, own_col = a.xcd_off != nullptr;
-    gp_status st;
-    if (may_build && ((!own_col && D.ord_state == 0) || (weighted && !(own_col || D.ord_state == 2 ? D.edge_ws : D.ord_ws)))) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusActive;
-        }
-        if (cs == hipStreamCaptureStatusNone) {
-            if (!own_col && (st = ensure_ordered(plan, weighted, stream)) != GP_OK) return st;
-            if (weighted && !own_col && D.ord_state == 1 && !D.ord_ws) {  // made by a call without weights
-                if ((st = ensure_edge_weights(plan, D.ord_col, &D.ord_ws_late, stream)) != GP_OK) return st;
-                D.ord_ws = D.ord_ws_late;
-            }
-            if (weighted && (own_col || D.ord_state != 1) && (st = ensure_edge_weights(plan, D.col, &D.edge_ws, stream)) != GP_OK) return st;
-        }
+    if (a.xcd_off) return GP_OK;
+    if (may_build && D.ord_state == 0 && may_allocate_on(stream)) {
+        gp_status st = ensure_ordered(plan, D.weighted_calls, stream);
+        if (st != GP_OK) return st;
     }
-    const bool ordered = !own_col && D.ord_state == 1;
-    if (ordered) {
+    if (D.ord_state == 1) {
         a.segs = D.ord_segs;
         a.col = D.ord_col;
         a.run_log2 = kOrderedRunLog2;
-    }
-    const float* w = ordered ? D.ord_ws : D.edge_ws;
-    if (weighted) {
-        a.edge_w = w ? w : D.dinv_sqrt;
-        a.edge_w_per_edge = w != nullptr;
     }
     return GP_OK;
 }
@@ -411,12 +419,11 @@ gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bo
 // (building and uploading them on first use of a slice shape).  *split comes back true
 // when the lists hold the hot pieces of the split schedule: the caller then runs the cold
 // records first and reads column ids, weights and partial rows from the split schedule.
-gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build = true, bool* split = nullptr,
-                            bool* lds = nullptr)
+// (plan->mu held)
+gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, bool* split, bool* lds)
 {
     if (split) *split = false;
     if (lds) *lds = false;
-    std::lock_guard<std::mutex> lk(plan->mu);
     const int es = a.dtype == GP_F32 ? 4 : 2;
     const int vec = hop_vector_width(a);
     // several column passes: implicit lists (explicit ones are cut for the whole row)
@@ -483,7 +490,36 @@ gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream,
     a.num_slices = found->num_slices;
     a.slice_elems = found->slice_elems;
     if (split) *split = found->split;
-    return found->split ? GP_OK : attach_columns(plan, a, stream, may_build);
+    return GP_OK;
+}
+
+// The lists of a launch, and their weights per non-zero for the sym operator.  Whatever lists its own hops take (the LDS
+// pass and split records bring their own weights), a sym call that may allocate leaves weights for those that a later
+// call may take that may not: with d = 16 of 100,000 rows and 20 million non-zeros, the launches that a captured graph keeps
+// took 493 us with them and 637 gathering every weight from the n-vector.
+gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build = true, bool* split = nullptr,
+                            bool* lds = nullptr)
+{
+    std::lock_guard<std::mutex> lk(plan->mu);
+    DevicePlan& D = plan->dev;
+    if (may_build && a.edge_w) D.weighted_calls = true;
+    gp_status st = choose_lists(plan, a, stream, may_build, split, lds);
+    if (st != GP_OK) return st;
+    if (may_build && D.weighted_calls && (st = ensure_weights(plan, stream)) != GP_OK) return st;
+    if (a.edge_w && !(split && *split) && !(lds && *lds)) {
+        const float* w = a.col == D.col ? D.edge_ws : D.ord_ws;
+        a.edge_w = w ? w : D.dinv_sqrt;
+        a.edge_w_per_edge = w != nullptr;
+    }
+    return GP_OK;
+}
+
+// A sym call without hops: as attach_work_lists does for those with hops.
+gp_status weights_without_hops(const gp_plan* plan, hipStream_t stream)
+{
+    std::lock_guard<std::mutex> lk(plan->mu);
+    plan->dev.weighted_calls = true;
+    return ensure_weights(plan, stream);
 }
 
 }  // namespace
@@ -535,6 +571,7 @@ gp_status propagate_resident(const gp_plan* plan, const void* X, int64_t ldx, in
                              int32_t K, void* out, int64_t ldo, hipStream_t stream)
 {
     gp_status st = ensure_device(plan, d, stream);
+    if (st == GP_OK && K == 0 && agg == GP_AGG_SYM) st = weights_without_hops(plan, stream);
     if (st != GP_OK) return st;
     const DevicePlan& D = plan->dev;
     return resident_hops(plan, X, ldx, d, dtype, agg, K, out, ldo, stream, D.carry, D.carry_ld, D.ctrl, true);
@@ -694,6 +731,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
                             int32_t K, const float* coeff, void* out, int64_t ldo, hipStream_t stream)
 {
     gp_status st = ensure_device(plan, d, stream);
+    if (st == GP_OK && K == 0 && agg == GP_AGG_SYM) st = weights_without_hops(plan, stream);
     if (st != GP_OK) return st;
     DevicePlan& D = plan->dev;
     const int64_t n = plan->n;

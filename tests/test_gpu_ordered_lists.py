@@ -1,5 +1,7 @@
 """Implicit lists on ids in walking order, an XCD taking runs of 32 records: sizes around a run and around the runs
 that the XCDs share, against the fp64 oracle at 1e-5 * (A^^k |X|); and calls that may not build the ordered list."""
+import re
+
 import numpy as np
 import pytest
 
@@ -13,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(autouse=True)
 def _defaults(gpu_or_skip):
     yield
-    for name in ("column_slices", "segment_edges", "cache_schedule", "hub_pass"):
+    for name in ("column_slices", "segment_edges", "cache_schedule", "hub_pass", "lds_pass", "split_records"):
         gp.gp_set_option(name, 0)
 
 
@@ -128,3 +130,62 @@ def test_first_hop_writes_the_filters_two_terms(dtype, d, pad):
     err = np.abs(out.double().cpu().numpy() - want)
     sums = 1e-5 * (c0 * np.abs(Xw) + abs(c1) * oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, 1)[1])
     assert np.all(err <= sums + (2.0 ** -8 * np.abs(want) + sums * 2.0 ** -8 if dtype == gp.GP_BF16 else 0.0) + 1e-30)
+
+
+def noalloc(plan, x, agg, K):
+    import torch
+    n, d = x.shape
+    out = torch.empty((K + 1, n, d), device="cuda:0")
+    gp.gp_propagate_noalloc(plan, x.data_ptr(), d, d, gp.GP_F32, agg, K, out.data_ptr(), d, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return out
+
+
+def kernels(call):
+    """The names of the kernels that a call launches, in order."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+    return [e.name for e in p.events() if "gp::" in e.name]
+
+
+def weights_read(names):
+    """How the hop launches among them get their weights (the kernel's last parameter): 1 = from the n-vector, by column
+    id, 2 = one per non-zero."""
+    return [int(m.group(1)) for m in (re.search(r"gp_hop_segments<.*?, (\d)>", x) for x in names) if m]
+
+
+@pytest.mark.parametrize("earlier", ["hubs in LDS", "split records", "no hops", "sum's list after sym", "mean's lists after sym"])
+def test_calls_that_may_not_allocate_have_weights_per_nonzero(earlier):
+    """After any allocating call of the sym operator, whatever its own hops ran on, a call that may not allocate finds
+    weights for the list that it walks."""
+    import torch
+    K, communities = 2, earlier in ("split records", "mean's lists after sym")
+    w = gp_synth.make_workload(4, scale=0.01, d=52) if communities else gp_synth.make_workload(2, scale=0.2, d=36)
+    gp.gp_set_option("hub_pass", 1)
+    if communities:
+        gp.gp_set_option("lds_pass", 2)
+        gp.gp_set_option("cache_schedule", 1)
+        gp.gp_set_option("split_records", 1 if earlier == "split records" else 2)
+    op = oracle.plan_blocks(w.src, w.dst, w.n, w.m, w.flags)
+    X = np.ascontiguousarray(w.X[:, :52 if communities else 3])
+    x = torch.from_numpy(X).cuda()
+    with gp.gp_plan_blocks(w.src, w.dst, w.n, w.m, w.flags) as plan:
+        wide = torch.randn(w.n, 1100 if communities else 36, device="cuda")
+        if earlier == "no hops":
+            hops(plan, wide, gp.GP_AGG_SYM, 0)
+        elif earlier == "split records":
+            assert len(weights_read(kernels(lambda: hops(plan, x, gp.GP_AGG_SYM, K)))) == 2 * K   # cold records, hot records
+        elif earlier == "mean's lists after sym":
+            hops(plan, wide, gp.GP_AGG_SYM, 1)       # several column passes: implicit lists
+            hops(plan, x, gp.GP_AGG_MEAN, 1)         # explicit lists
+        else:
+            assert sum("gp_hop_cluster_lds" in k for k in kernels(lambda: hops(plan, wide, gp.GP_AGG_SYM, K))) == K
+            if earlier == "sum's list after sym":
+                assert any("gp_order_columns" in k for k in kernels(lambda: hops(plan, x, gp.GP_AGG_SUM, 1)))
+        assert weights_read(kernels(lambda: noalloc(plan, x, gp.GP_AGG_SYM, K))) == [2] * K
+        got = noalloc(plan, x, gp.GP_AGG_SYM, K).cpu().numpy().astype(np.float64)
+    Xw = X.astype(np.float64)
+    want, bound = oracle.propagate(op, Xw, gp.GP_AGG_SYM, K), oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, K)
+    for k in range(K + 1):
+        assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
