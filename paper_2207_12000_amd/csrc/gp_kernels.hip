@@ -269,8 +269,14 @@ struct XcdLists {
 // intended size.  Every group starts with the chunk of its own number and asks for the
 // next one while it works; ctrl[8] counts the groups that are done and the last one puts
 // all nine words back to zero, so the buffer is zero between launches.
+//
+// The kernel waits for memory, so wavefronts count.  Rows of two or three fp32 columns are held to the 96 registers that
+// let five stay on a SIMD (the weighted instance, which sizes the grid for all three, takes 98 by itself): three hops of
+// 490,000 rows and 12 million non-zeros, 2 columns, sum 321 -> 280 us, sym 358 -> 320.
+constexpr int resident_wavefronts(size_t element, int vec, int group) { return element == 4 && vec == 2 && group == 8 ? 5 : 1; }
+
 template <typename T, int VEC, int G, int VPL, int EDGE_W>
-__global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
+__global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
                                                             const XcdLists lists, unsigned long long* __restrict__ ctrl,
                                                             int chunk_records, const int32_t* __restrict__ col,
                                                             int64_t col_base,
@@ -412,7 +418,9 @@ __global__ __launch_bounds__(kThreads) void gp_hop_segments(const Segment* __res
         // filter hops of 169,343 x 64 954 -> 939).
         const bool partial = r.slot >= 0;
         const float rs = (!partial && row_scale) ? row_scale[r.row] : 1.0f;
-        constexpr bool kFiltAhead = VPL == 1 && VEC <= 4 && G < 64;  // where the registers cost no resident wavefront
+        // The filter's vector only where one short vector is all a lane has: its registers then cost the weighted instances no
+        // resident wavefront (unweighted ones lose one here and there, of more than the grid, sized by the weighted, has).
+        constexpr bool kFiltAhead = VPL == 1 && VEC <= 4 && G < 64;
         float filt[VEC];  // the filter sum's vector
         const bool filt_ahead = kFiltAhead && comb && !partial && live[0] && fresh[0] == 0;
         if constexpr (kFiltAhead) {
