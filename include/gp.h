@@ -242,7 +242,13 @@ gp_status gp_plan_work_lists(const gp_plan *plan, int32_t d, gp_dtype dtype, int
  * buffers are kept with the plan and reused by later calls of the same shape; edge
  * blocks that all fit the budget are sent once per plan).  The first call on a plan
  * uploads the plan to the current device and allocates scratch (partial-row
- * buffer); later calls with the same d reuse both.  Calls on ONE plan must not
+ * buffer); later calls with the same d reuse both.  What hops read beside the plan is made by
+ * the first call whose hops read it, which allocates and waits for the stream, and stays until the
+ * plan is destroyed: for hops on implicit lists a copy of records and ids in walking order (4 bytes
+ * per non-zero, about 20 per record); after a call of GP_AGG_SYM one weight per non-zero (4 bytes)
+ * for that copy, and for the plan's own list where hops read it; these only where there is room
+ * (option "list_bytes").  The lists of the LDS pass and of the cache schedule come the same way,
+ * but not without room.  Calls on ONE plan must not
  * overlap in time (they share that scratch); different plans are independent.
  * Results are deterministic: the same inputs and options give the same bits on every
  * call (how a row's partial sums are grouped depends on the schedule, so the streamed and
@@ -415,8 +421,8 @@ gp_status gp_solve_aggregation_blocks(double B_S, double B_X, double B_GPU, doub
 /* ---------------------------------------------------------------------------
  * Library-wide knobs.  gp_set_option changes the process-wide defaults;
  * gp_plan_blocks copies them into the plan it makes, and every later call on that
- * plan uses the plan's copy ("lc_tile_rows" and the HBM budget, which belong to
- * calls without a plan or to the machine, are read when the call is made).
+ * plan uses the plan's copy ("lc_tile_rows", "list_bytes" and the HBM budget, which belong
+ * to calls without a plan or to the machine, are read when the call is made).
  */
 
 /* Upper limit of HBM bytes the streamed schedule may use for its staging buffers
@@ -454,6 +460,10 @@ gp_status gp_set_hbm_budget_bytes(int64_t bytes);
  *                     for the launch that writes them).  0 = 8 with row clusters (long segments,
  *                     few stores), 4 with hubs (short segments: the stores weigh as much as the
  *                     reads).  The results do not depend on it.
+ *   "list_bytes"      device memory, in bytes, that a list which calls can do without may take: the copy of
+ *                     records and ids in walking order, and weights per non-zero (see gp_propagate).  0 = a
+ *                     fourth of what is free for the copy, whatever is free for weights.  A call that
+ *                     finds no room runs without, with the same bits; the next call asks again.
  *   "device_plan_chunk"  GP_PLAN_ON_DEVICE: most candidate entries sorted at once
  *                     (1 .. 2^31 - 1; 0 = 2^31 - 1).  Read by gp_plan_blocks.
  *   "cache_schedule"  0 = explicit per-XCD work lists where the plan's row clusters

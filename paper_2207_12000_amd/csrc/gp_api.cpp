@@ -162,6 +162,11 @@ gp_status gp_set_option(const char* name, int64_t value)
         options().plane_strips = value;
         return GP_OK;
     }
+    if (!strcmp(name, "list_bytes")) {
+        if (value < 0) return fail(GP_ERR_INVALID_ARG, "list_bytes must be >= 0");
+        options().list_bytes = value;
+        return GP_OK;
+    }
     if (!strcmp(name, "device_plan_chunk")) {
         if (value < 0 || value > (INT64_C(1) << 31) - 1) return fail(GP_ERR_INVALID_ARG, "device_plan_chunk must be 0 .. 2^31 - 1");
         options().device_plan_chunk = value;
@@ -188,6 +193,7 @@ int64_t gp_get_option(const char* name)
     if (!strcmp(name, "column_slices")) return options().column_slices;
     if (!strcmp(name, "persistent_blocks")) return options().persistent_blocks;
     if (!strcmp(name, "cache_schedule")) return options().cache_schedule;
+    if (!strcmp(name, "list_bytes")) return options().list_bytes;
     if (!strcmp(name, "device_plan_chunk")) return options().device_plan_chunk;
     if (!strcmp(name, "split_records")) return options().split_records;
     if (!strcmp(name, "lds_pass")) return options().lds_pass;

@@ -39,6 +39,7 @@ struct Options {
     int64_t hub_pass = 0;        // graphs without row clusters: the most popular rows served from LDS: 0 = where it pays, 1 = always, 2 = never
     int64_t hub_sets = 0;        // hub pass: row sets the rows are cut into, 0 = automatic
     int64_t plane_strips = 0;    // LDS pass: strips of one position that lie together in the planes (1, 2, 4, 8), 0 = automatic
+    int64_t list_bytes = 0;      // most device memory of a list that calls can do without (copy in walking order, weights), 0 = automatic
     int64_t device_plan_chunk = 0;  // GP_PLAN_ON_DEVICE: most candidate entries sorted at once, 0 = 2^31 - 1
 };
 Options& options();
@@ -119,10 +120,9 @@ struct DevicePlan {
     SplitRow* split = nullptr;
     float* edge_ws = nullptr;   // nnz: dinv_sqrt[col[e]], for launches of the sym operator that read `col`
     bool weighted_calls = false;  // a call of the sym operator that could allocate has been made: every list that a launch may take has its weights
-    // the implicit lists' records with their ids in the order they are walked: 0 = not made, 1 = there, 2 = no room for them
-    int ord_state = 0;
+    // the implicit lists' records with their ids in the order they are walked (a copy that calls can do without)
     Segment* ord_segs = nullptr;   // the allocation; ids (and weights) lie behind the records
-    int32_t* ord_col = nullptr;
+    int32_t* ord_col = nullptr;    // not nullptr: the copy is there
     float* ord_ws = nullptr;       // dinv_sqrt[ord_col[e]] (sym operator)
     float* ord_ws_late = nullptr;  // allocated apart when the list was made by a call without weights
     float* carry = nullptr;     // num_slots x carry_ld fp32

@@ -309,14 +309,36 @@ gp_status ensure_lds(const gp_plan* plan, int32_t d, hipStream_t stream)
     return GP_OK;
 }
 
+// Lists that a call found no room for: its other hops do without them and do not ask again, the next call does.
+struct NoRoom {
+    bool copy = false, weights = false;
+};
+
+// Whether device memory has room for a list that calls can do without.  The copy in walking order takes at most a fourth
+// of what is free: what later calls and the caller cannot do without comes after it.
+bool room_for_list(size_t bytes, bool copy)
+{
+    const int64_t most = options().list_bytes;
+    if (most > 0) return bytes <= (size_t)most;
+    size_t free = 0, total = 0;
+    if (!copy) return true;
+    if (hipMemGetInfo(&free, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return bytes <= free / 4;
+}
+
 // dinv_sqrt[col[e]] for every entry of a device column list, made once (plan->mu held): one coalesced fp32 per
 // non-zero instead of one random 4-byte gather per non-zero and hop.  *w stays nullptr when there is no room.
-gp_status ensure_edge_weights(const gp_plan* plan, const int32_t* col, float** w, hipStream_t stream)
+gp_status ensure_edge_weights(const gp_plan* plan, const int32_t* col, float** w, hipStream_t stream, NoRoom& no_room)
 {
-    if (*w || plan->nnz == 0) return GP_OK;
+    if (*w || plan->nnz == 0 || no_room.weights) return GP_OK;
     float* p = nullptr;
-    if (hipMalloc((void**)&p, (size_t)plan->nnz * sizeof(float)) != hipSuccess) {
+    const size_t bytes = (size_t)plan->nnz * sizeof(float);
+    if (!room_for_list(bytes, false) || hipMalloc((void**)&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
+        no_room.weights = true;
         return GP_OK;
     }
     gp_status st = launch_fill_edge_weights(col, plan->dev.dinv_sqrt, p, plan->nnz, stream);
@@ -337,17 +359,17 @@ gp_status ensure_edge_weights(const gp_plan* plan, const int32_t* col, float** w
 // fourth of the misses of a hop of 64 columns in two slices were these.
 // One allocation holds records, ids, weights (if this call wants them) and the scan's scratch: allocating is most of what
 // the list costs.
-gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t stream)
+bool can_be_ordered(const gp_plan* plan) { return !plan->segs.empty() && plan->nnz > 0 && plan->nnz <= (int64_t)UINT32_MAX; }
+
+gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t stream, NoRoom& no_room)
 {
     DevicePlan& D = plan->dev;
-    if (D.ord_state != 0) return GP_OK;
     const size_t nsegs = plan->segs.size(), nnz = (size_t)plan->nnz;
-    D.ord_state = 2;
-    if (nsegs == 0 || nnz == 0 || plan->nnz > (int64_t)UINT32_MAX) return GP_OK;
-    const size_t words = nnz * (want_weights ? 2 : 1) + nsegs + device_scan_scratch_words((int64_t)nsegs);
-    if (hipMalloc((void**)&D.ord_segs, nsegs * sizeof(Segment) + words * 4) != hipSuccess) {
+    const size_t bytes = nsegs * sizeof(Segment) + (nnz * (want_weights ? 2 : 1) + nsegs + device_scan_scratch_words((int64_t)nsegs)) * 4;
+    if (!room_for_list(bytes, true) || hipMalloc((void**)&D.ord_segs, bytes) != hipSuccess) {
         (void)hipGetLastError();  // no room: the records as the plan has them do
         D.ord_segs = nullptr;
+        no_room.copy = true;
         return GP_OK;
     }
     int32_t* col = (int32_t*)(D.ord_segs + nsegs);
@@ -357,10 +379,13 @@ gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t str
     if (st == GP_OK && ws) st = launch_fill_edge_weights(col, D.dinv_sqrt, ws, plan->nnz, stream);
     if (hipStreamSynchronize(stream) != hipSuccess && st == GP_OK)  // once per plan: later calls may come on other streams
         st = fail(GP_ERR_DEVICE, "ordering the column list");
-    if (st != GP_OK) return st;  // (the memory goes with the plan)
+    if (st != GP_OK) {
+        (void)hipFree(D.ord_segs);
+        D.ord_segs = nullptr;
+        return st;
+    }
     D.ord_col = col;
     D.ord_ws = ws;
-    D.ord_state = 1;
     return GP_OK;
 }
 
@@ -383,31 +408,30 @@ bool may_allocate_on(hipStream_t stream)
 
 // Weights per non-zero for every list that an implicit or an explicit launch may be given (plan->mu held): the ordered
 // list if there is one, else the plan's own, which the explicit lists are written over too.
-gp_status ensure_weights(const gp_plan* plan, hipStream_t stream)
+gp_status ensure_weights(const gp_plan* plan, hipStream_t stream, NoRoom& no_room)
 {
     DevicePlan& D = plan->dev;
-    const bool ordered = D.ord_state == 1;
+    const bool ordered = D.ord_col != nullptr;
     const bool own = !ordered || std::any_of(D.work.begin(), D.work.end(), [](const XcdWork& w) { return !w.split; });
-    if (plan->nnz == 0 || ((!own || D.edge_ws) && (!ordered || D.ord_ws)) || !may_allocate_on(stream)) return GP_OK;
+    if (plan->nnz == 0 || no_room.weights || ((!own || D.edge_ws) && (!ordered || D.ord_ws)) || !may_allocate_on(stream)) return GP_OK;
     gp_status st;
     if (ordered && !D.ord_ws) {  // made by a call without weights
-        if ((st = ensure_edge_weights(plan, D.ord_col, &D.ord_ws_late, stream)) != GP_OK) return st;
+        if ((st = ensure_edge_weights(plan, D.ord_col, &D.ord_ws_late, stream, no_room)) != GP_OK) return st;
         D.ord_ws = D.ord_ws_late;
     }
-    return own ? ensure_edge_weights(plan, D.col, &D.edge_ws, stream) : GP_OK;
+    return own ? ensure_edge_weights(plan, D.col, &D.edge_ws, stream, no_room) : GP_OK;
 }
 
-// Records and ids of a launch on the implicit lists, or on explicit ones over the plan's own column list (plan->mu
-// held).  may_build = false, and a stream that is being captured: only what is there.
-gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build)
+// Records and ids of a launch on the implicit lists (plan->mu held).  may_build = false, and a stream that is being
+// captured: only what is there.
+gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, NoRoom& no_room)
 {
     DevicePlan& D = plan->dev;
-    if (a.xcd_off) return GP_OK;
-    if (may_build && D.ord_state == 0 && may_allocate_on(stream)) {
-        gp_status st = ensure_ordered(plan, D.weighted_calls, stream);
+    if (may_build && !D.ord_col && !no_room.copy && can_be_ordered(plan) && may_allocate_on(stream)) {
+        gp_status st = ensure_ordered(plan, D.weighted_calls, stream, no_room);
         if (st != GP_OK) return st;
     }
-    if (D.ord_state == 1) {
+    if (D.ord_col) {
         a.segs = D.ord_segs;
         a.col = D.ord_col;
         a.run_log2 = kOrderedRunLog2;
@@ -420,7 +444,7 @@ gp_status attach_columns(const gp_plan* plan, HopArgs& a, hipStream_t stream, bo
 // when the lists hold the hot pieces of the split schedule: the caller then runs the cold
 // records first and reads column ids, weights and partial rows from the split schedule.
 // (plan->mu held)
-gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, bool* split, bool* lds)
+gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, bool* split, bool* lds, NoRoom& no_room)
 {
     if (split) *split = false;
     if (lds) *lds = false;
@@ -428,9 +452,9 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
     const int vec = hop_vector_width(a);
     // several column passes: implicit lists (explicit ones are cut for the whole row)
     if (pass_width(a.column_tile, a.dtype, a.d, a.ldin, a.xout ? a.ldout : a.ldin, a.xin, a.xout ? a.xout : a.xin) < a.d)
-        return attach_columns(plan, a, stream, may_build);
+        return attach_columns(plan, a, stream, may_build, no_room);
     int S = 0, elems = 0;
-    if (!may_build && plan->hot_mode == 0) return attach_columns(plan, a, stream, false);  // nothing built yet: implicit lists
+    if (!may_build && plan->hot_mode == 0) return attach_columns(plan, a, stream, false, no_room);  // nothing built yet: implicit lists
     decide_hot_mode(plan, a.d);
     DevicePlan& D = plan->dev;
     // the hot non-zeros can come out of LDS where the segment kernel's vectors are whole strips of four columns:
@@ -450,7 +474,7 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
         }
     }
     // no clusters: nothing an L2 could be made to hold
-    if (plan->hot_mode != 1 || !choose_cache_schedule(plan, a.d, es, vec, S, elems)) return attach_columns(plan, a, stream, may_build);
+    if (plan->hot_mode != 1 || !choose_cache_schedule(plan, a.d, es, vec, S, elems)) return attach_columns(plan, a, stream, may_build, no_room);
     // hot and cold pieces in phases of their own need buffers of their own: only where the caller may allocate
     // (not worth it when hardly anything leaves the clusters: every row then pays two partial rows for nothing)
     const bool want_split = split && may_build && plan->opt.split_records != 2 &&
@@ -462,7 +486,7 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
     const XcdWork* found = nullptr;
     for (const XcdWork& w : D.work)
         if (w.num_slices == S && w.slice_elems == elems && w.split == want_split) found = &w;
-    if (!found && !may_build) return attach_columns(plan, a, stream, false);
+    if (!found && !may_build) return attach_columns(plan, a, stream, false, no_room);
     if (!found) {
         std::vector<Segment> recs;
         XcdWork w;
@@ -497,15 +521,14 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
 // pass and split records bring their own weights), a sym call that may allocate leaves weights for those that a later
 // call may take that may not: with d = 16 of 100,000 rows and 20 million non-zeros, the launches that a captured graph keeps
 // took 493 us with them and 637 gathering every weight from the n-vector.
-gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build = true, bool* split = nullptr,
-                            bool* lds = nullptr)
+gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, bool* split, bool* lds, NoRoom& no_room)
 {
     std::lock_guard<std::mutex> lk(plan->mu);
     DevicePlan& D = plan->dev;
     if (may_build && a.edge_w) D.weighted_calls = true;
-    gp_status st = choose_lists(plan, a, stream, may_build, split, lds);
+    gp_status st = choose_lists(plan, a, stream, may_build, split, lds, no_room);
     if (st != GP_OK) return st;
-    if (may_build && D.weighted_calls && (st = ensure_weights(plan, stream)) != GP_OK) return st;
+    if (may_build && D.weighted_calls && (st = ensure_weights(plan, stream, no_room)) != GP_OK) return st;
     if (a.edge_w && !(split && *split) && !(lds && *lds)) {
         const float* w = a.col == D.col ? D.edge_ws : D.ord_ws;
         a.edge_w = w ? w : D.dinv_sqrt;
@@ -519,7 +542,8 @@ gp_status weights_without_hops(const gp_plan* plan, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lk(plan->mu);
     plan->dev.weighted_calls = true;
-    return ensure_weights(plan, stream);
+    NoRoom no_room;
+    return ensure_weights(plan, stream, no_room);
 }
 
 }  // namespace
@@ -660,6 +684,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
 
     const float* edge_w = agg == GP_AGG_SYM ? D.dinv_sqrt : nullptr;  // (attach_work_lists has one per non-zero where it can)
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
+    NoRoom no_room;
 
     for (int32_t k = 1; k <= K; ++k) {
         HopArgs a;
@@ -684,7 +709,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         a.column_tile = plan->opt.column_tile;
         bool split = false, lds = false;
         HopArgs cold = a;  // as it stands: implicit lists
-        if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds)) != GP_OK) return st;
+        if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds, no_room)) != GP_OK) return st;
         if (split) {
             // Records that gather outside their row's cluster first, whole rows wide: nothing of
             // theirs is worth keeping in a cache, and run on their own they evict nothing that is.
@@ -772,6 +797,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
 
     const float* edge_w = agg == GP_AGG_SYM ? D.dinv_sqrt : nullptr;  // (attach_work_lists has one per non-zero where it can)
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
+    NoRoom no_room;
     for (int32_t k = 1; k <= K; ++k) {
         HopArgs a;
         a.segs = D.segs;
@@ -799,7 +825,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         a.comb_starts = k == 1;
         a.gamma0 = coeff[0];
         bool lds = false;
-        if ((st = attach_work_lists(plan, a, stream, true, nullptr, &lds)) != GP_OK) return st;
+        if ((st = attach_work_lists(plan, a, stream, true, nullptr, &lds, no_room)) != GP_OK) return st;
         if (lds) {
             if ((st = lds_hop(plan, a, agg, stream)) != GP_OK) return st;
         } else if ((st = hop_passes(a, stream)) != GP_OK) {

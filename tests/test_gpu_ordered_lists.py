@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(autouse=True)
 def _defaults(gpu_or_skip):
     yield
-    for name in ("column_slices", "segment_edges", "cache_schedule", "hub_pass", "lds_pass", "split_records"):
+    for name in ("column_slices", "segment_edges", "cache_schedule", "hub_pass", "lds_pass", "split_records", "list_bytes"):
         gp.gp_set_option(name, 0)
 
 
@@ -187,5 +187,40 @@ def test_calls_that_may_not_allocate_have_weights_per_nonzero(earlier):
         got = noalloc(plan, x, gp.GP_AGG_SYM, K).cpu().numpy().astype(np.float64)
     Xw = X.astype(np.float64)
     want, bound = oracle.propagate(op, Xw, gp.GP_AGG_SYM, K), oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, K)
+    for k in range(K + 1):
+        assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
+
+
+@pytest.mark.parametrize("agg", [gp.GP_AGG_SYM, gp.GP_AGG_MEAN])
+@pytest.mark.parametrize("room", ["none", "weights"])
+def test_calls_without_room_run_on_the_plans_order_and_the_next_call_asks_again(agg, room):
+    """Device memory is short while the first calls run: they do without the copy in walking order (and without
+    weights per non-zero), with the same bits; the copy is made by the first call that finds room, and only by it."""
+    import torch
+    K = 3
+    w = gp_synth.make_workload(2, scale=0.2, d=40)
+    gp.gp_set_option("cache_schedule", 2)
+    x = torch.from_numpy(w.X).cuda()
+    op = oracle.plan_blocks(w.src, w.dst, w.n, w.m, w.flags)
+    sym = agg == gp.GP_AGG_SYM
+    with gp.gp_plan_blocks(w.src, w.dst, w.n, w.m, w.flags) as plan:
+        gp.gp_set_option("list_bytes", 1 if room == "none" else 4 * plan.nnz)
+        out = {}
+
+        def call(name):
+            names = kernels(lambda: out.update({name: hops(plan, x, agg, K)}))
+            return [sum(part in k for k in names) for part in ("gp_order_columns", "gp_fill_edge_weights")], weights_read(names)
+
+        for i in range(2):
+            made, read = call(f"short{i}")
+            assert made == [0, int(sym and room == "weights" and i == 0)]
+            assert read == [(1 if room == "none" else 2) if sym else 0] * K
+        gp.gp_set_option("list_bytes", 0)
+        assert call("room") == ([1, int(sym)], [2 if sym else 0] * K)
+        assert call("again") == ([0, 0], [2 if sym else 0] * K)
+    for name in ("short1", "room", "again"):
+        assert torch.equal(out[name], out["short0"]), name
+    got, Xw = out["short0"].cpu().numpy().astype(np.float64), w.X.astype(np.float64)
+    want, bound = oracle.propagate(op, Xw, agg, K), oracle.bound_stack(op, Xw, agg, K)
     for k in range(K + 1):
         assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
