@@ -57,9 +57,11 @@ def test_captured_calls_that_find_no_ordered_list():
     import torch
     w = gp_synth.make_workload(2, scale=0.2, d=36)
     gp.gp_set_option("hub_pass", 1)
-    n, K = w.n, 2
-    with gp.gp_plan_blocks(w.src, w.dst, n, max(20_000, w.m // 3), w.flags) as plan:
-        hops(plan, torch.from_numpy(w.X).cuda(), gp.GP_AGG_SYM, K)
+    n, K, budget = w.n, 2, max(20_000, w.m // 3)
+    op = oracle.plan_blocks(w.src, w.dst, n, budget, w.flags)
+    with gp.gp_plan_blocks(w.src, w.dst, n, budget, w.flags) as plan:
+        first = kernels(lambda: hops(plan, torch.from_numpy(w.X).cuda(), gp.GP_AGG_SYM, K))
+        assert sum("gp_hop_cluster_lds" in k for k in first) == K and not any("gp_order_columns" in k for k in first)
         x = torch.from_numpy(np.ascontiguousarray(w.X[:, :3])).cuda()
         out = torch.zeros((K + 1, n, 3), device="cuda:0")
         g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
@@ -68,11 +70,19 @@ def test_captured_calls_that_find_no_ordered_list():
             gp.gp_propagate(plan, x.data_ptr(), 3, 3, gp.GP_F32, gp.GP_AGG_SYM, K, out.data_ptr(), 3,
                             torch.cuda.current_stream().cuda_stream)
         for rep in range(3):
-            x.copy_(torch.from_numpy(gp_synth.features(n, 3, "normal", gp_synth.rng_for(5, rep))))
+            X = gp_synth.features(n, 3, "normal", gp_synth.rng_for(5, rep))
+            x.copy_(torch.from_numpy(X))
             out.fill_(float("nan"))
             g.replay()
             torch.cuda.synchronize()
-            assert torch.equal(out, hops(plan, x, gp.GP_AGG_SYM, K))     # eager: the ordered list
+            eager = {}
+            made = kernels(lambda: eager.update(out=hops(plan, x, gp.GP_AGG_SYM, K)))
+            assert any("gp_order_columns" in k for k in made) == (rep == 0)  # the captured call had made none
+            assert torch.equal(out, eager["out"])
+            got, Xw = out.cpu().numpy().astype(np.float64), X.astype(np.float64)
+            want, bound = oracle.propagate(op, Xw, gp.GP_AGG_SYM, K), oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, K)
+            for k in range(K + 1):
+                assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
 
 
 @pytest.mark.parametrize("d", [7, 40, 128])
@@ -224,3 +234,33 @@ def test_calls_without_room_run_on_the_plans_order_and_the_next_call_asks_again(
     want, bound = oracle.propagate(op, Xw, agg, K), oracle.bound_stack(op, Xw, agg, K)
     for k in range(K + 1):
         assert np.all(np.abs(got[k] - want[k]) <= 1e-5 * bound[k] + 1e-30), f"hop {k}"
+
+
+@pytest.mark.parametrize("dtype,d,K", [(gp.GP_F32, 52, 1), (gp.GP_F32, 52, 3), (gp.GP_F32, 7, 1), (gp.GP_BF16, 72, 1)])
+def test_first_hop_on_explicit_lists_writes_the_filters_two_terms(dtype, d, K):
+    """The same sums from the per-XCD lists of a community graph: fp32 to 1e-5 of the magnitudes, and one rounding of
+    the result for bf16 storage."""
+    import torch
+    gp.gp_set_option("cache_schedule", 1)
+    gp.gp_set_option("lds_pass", 2)
+    gp.gp_set_option("segment_edges", 16)
+    w = gp_synth.make_workload(4, scale=0.01, d=d)
+    coeff = [0.75, -1.5, 0.5, 0.25][:K + 1]
+    X = torch.from_numpy(w.X).to(torch.float32 if dtype == gp.GP_F32 else torch.bfloat16)
+    x, out = X.cuda(), torch.full((w.n, d), float("nan"), dtype=X.dtype, device="cuda")
+    Xw = X.double().numpy()
+    op = oracle.plan_blocks(w.src, w.dst, w.n, w.m // 3, w.flags)
+    with gp.gp_plan_blocks(w.src, w.dst, w.n, w.m // 3, w.flags) as plan:
+        assert plan.num_partial_rows > 0
+
+        def call():
+            gp.gp_propagate_combine(plan, x.data_ptr(), d, d, dtype, gp.GP_AGG_SYM, K, coeff, out.data_ptr(), d,
+                                    torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+
+        names = kernels(call)
+        assert len(weights_read(names)) == K and not any("gp_order_columns" in k or "gp_hop_cluster_lds" in k for k in names)
+    want = sum(c * h for c, h in zip(coeff, oracle.propagate(op, Xw, gp.GP_AGG_SYM, K)))
+    err = np.abs(out.double().cpu().numpy() - want)
+    sums = 1e-5 * sum(abs(c) * b for c, b in zip(coeff, oracle.bound_stack(op, Xw, gp.GP_AGG_SYM, K)))
+    assert np.all(err <= sums + (2.0 ** -8 * (np.abs(want) + sums) if dtype == gp.GP_BF16 else 0.0) + 1e-30)
