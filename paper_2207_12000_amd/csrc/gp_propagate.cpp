@@ -355,10 +355,12 @@ gp_status ensure_edge_weights(const gp_plan* plan, const int32_t* col, float** w
 // The implicit lists' records with their ids in the order they are walked (plan->mu held).  Records are walked longest
 // first, so in the plan's own order the ids and weights of neighbouring records lie apart: a record of 13 ids reads
 // 1.4 lines of each where 0.4 hold them, and records handed out one by one have every XCD read the lines of all of them.
-// The hop is bound by the lines that the L2s miss (about 57 lines per ns, all XCDs together; 47.5 were measured), and a
-// fourth of the misses of a hop of 64 columns in two slices were these.
-// One allocation holds records, ids, weights (if this call wants them) and the scan's scratch: allocating is most of what
-// the list costs.
+// The hop is bound by the reads that the L2s miss (about 57 lines per ns, all XCDs together, in a probe that gathers;
+// 46 - 53 here).  Such reads per hop, in the plan's own order and in this one: 169,343 rows and 2.5 million non-zeros x
+// 64 fp32 columns 4.47 / 3.93 million, x 128 7.85 / 7.03; 507,001 rows and 10.3 million non-zeros x 128 bf16 columns
+// 18.6 / 17.0.
+// One allocation holds records, ids, weights (if the plan's calls want them) and the scan's scratch, 4 bytes per record
+// and some: allocating is most of what the list costs.
 bool can_be_ordered(const gp_plan* plan) { return !plan->segs.empty() && plan->nnz > 0 && plan->nnz <= (int64_t)UINT32_MAX; }
 
 gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t stream, NoRoom& no_room)
@@ -389,11 +391,12 @@ gp_status ensure_ordered(const gp_plan* plan, bool want_weights, hipStream_t str
     return GP_OK;
 }
 
-// An XCD takes runs of 32 records of an ordered list: their ids and weights (one to two KB of each) share all lines but
-// the outer two.  Runs of 1 / 8 / 16 / 32 / 128 records, us: three hops of 169,343 rows x 128 fp32 columns, 2.5 million
-// non-zeros, 506 / 486 / 477 / 478 / 474 (517 in the plan's own order); 507,001 rows x 128 bf16, 10.3 million, 1121 / 1054 /
-// 1048 / 1052 / 1044 (1144); ten filter hops of 169,343 x 64 fp32 1009 / 939 / 933 / 924 / 927 (1027).  Longer runs gain
-// nothing more, and in a small graph they deal the work to the XCDs less evenly.
+// An XCD takes runs of 32 records of an ordered list: their ids and weights (one to two KB of each for records of 8 to 16
+// non-zeros, more for longer ones) share all lines but the outer two.  Runs of 1 / 8 / 16 / 32 / 128 records, us: three
+// hops of 169,343 rows x 128 fp32 columns, 2.5 million non-zeros, 506 / 486 / 477 / 478 / 474 (517 in the plan's own order);
+// 507,001 rows x 128 bf16, 10.3 million, 1121 / 1054 / 1048 / 1052 / 1044 (1144); ten filter hops of 169,343 x 64 fp32
+// 1009 / 939 / 933 / 924 / 927 (1027).  Longer runs gain less than 1 % more, and in a small graph they deal the work to
+// the XCDs less evenly.
 constexpr int kOrderedRunLog2 = 5;
 
 bool may_allocate_on(hipStream_t stream)
@@ -519,8 +522,9 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
 
 // The lists of a launch, and their weights per non-zero for the sym operator.  Whatever lists its own hops take (the LDS
 // pass and split records bring their own weights), a sym call that may allocate leaves weights for those that a later
-// call may take that may not: with d = 16 of 100,000 rows and 20 million non-zeros, the launches that a captured graph keeps
-// took 493 us with them and 637 gathering every weight from the n-vector.
+// call may take that may not.  Three hops of 100,000 rows and 20 million non-zeros on the plan's own order, us with them
+// and gathering every weight from the n-vector: 16 fp32 columns 492 / 637, 64 bf16 columns 579 / 697 (wide rows hide the
+// gathers: 64 fp32 columns 1595 / 1522).
 gp_status attach_work_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool may_build, bool* split, bool* lds, NoRoom& no_room)
 {
     std::lock_guard<std::mutex> lk(plan->mu);
