@@ -96,8 +96,7 @@ void cluster_rows(const gp_plan& P, RowClusters& C)
     std::vector<int32_t> lab((size_t)n), nxt((size_t)n);
     std::iota(lab.begin(), lab.end(), 0);
 
-    const int max_iter = 10;
-    for (int it = 0; it < max_iter; ++it) {
+    for (int it = 0; it < kClusterRounds; ++it) {
         std::atomic<int64_t> changed{0};
         parallel_run(nt, [&](int t, int) {
             std::vector<int32_t> key, cnt, near;

@@ -207,7 +207,11 @@ gp_status build_schedule(gp_plan* plan);
 // (block p = [block_off[p], block_off[p+1])): the plan's own blocks, or another cut of the same list
 gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_off, std::vector<Segment>& segs,
                        std::vector<int64_t>& seg_off, std::vector<SplitRow>& split, int64_t& num_slots);
+constexpr int kClusterRounds = 10;
 void cluster_rows(const gp_plan& P, RowClusters& C);
+// gp_cluster_device.hip: the same clusters made on the GPU that holds the plan's column list (which is current), on a
+// stream that is not being captured; false, and C untouched but for its capacity, where that is not possible.
+bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream);
 void build_xcd_lists(const gp_plan& P, const std::vector<Segment>& segs, const RowClusters& C, int S, int slice_elems, int d,
                      std::vector<Segment>& recs, int64_t off[9]);
 HotSets hot_sets_from_clusters(const RowClusters& C);
@@ -329,7 +333,8 @@ gp_status launch_pack_strips(const HotLdsArgs& a, hipStream_t stream);  // fills
 gp_status launch_hot_lds(const HotLdsArgs& a, hipStream_t stream);
 // Slice shape of the explicit work lists for rows of d elements in vectors of `vec`
 // (element size es), or false if this plan keeps the implicit lists.
-bool choose_cache_schedule(const gp_plan* plan, int32_t d, int es, int vec, int& num_slices, int& slice_elems);
+// (stream: row clusters that are not there yet are made on it; nullptr: on the host)
+bool choose_cache_schedule(const gp_plan* plan, int32_t d, int es, int vec, int& num_slices, int& slice_elems, const hipStream_t* stream);
 // fills plan->nnz, rowptr, col, deg from validated input pairs, on the current GPU
 gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan);
 // fills block_row_lo / block_row_hi from rowptr and block_off, on the current GPU
