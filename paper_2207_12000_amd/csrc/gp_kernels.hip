@@ -870,6 +870,15 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
         return per_cu * prop.multiProcessorCount;
     }();
     int64_t persist = a.persistent_blocks > 0 ? a.persistent_blocks : resident;
+    // Long implicit lists get several times as many workgroups as stay resident, so that most of the list is dealt out as
+    // workgroups finish: with one round of fixed shares the launch waits for the slowest compute unit.  Whole multiples
+    // (a last round that is nearly empty costs more than it gains: 1.25 rounds are 5 - 14 % slower than one), up to six,
+    // and two records per group left for the pipeline.  One / two / three / six rounds, us: three hops of 169,343 rows x 128
+    // fp32 columns 474 / 462 / 471 / 461, x 256 1135 / 1051 / 1040 / 1032; 507,001 x 128 bf16 1045 / 1029 / 1026 / 1029;
+    // ten filter hops of 169,343 x 64 892 / 899 / 867 / 860; 2,450,000 x 100 22600 / 22570 / 22850 / 22350.  Lists of
+    // less than eight records per group lose: 37,123 rows x 128 (five records) 148 / 151 / 151 / 161.
+    const int64_t per_group = chunks * 8 / resident;
+    if (a.persistent_blocks <= 0 && !a.xcd_off && per_group >= 8) persist *= std::min<int64_t>(6, per_group / 2);
     persist = (persist + 7) / 8 * 8;
     const int64_t blocks = std::min<int64_t>(persist, 8 * chunks);
     const dim3 grid((unsigned)blocks), block(kThreads);
