@@ -179,8 +179,8 @@ void cluster_rows(const gp_plan& P, RowClusters& C)
 // (chunk, slice) pair goes, in that order, to the XCD with the least work so far, so
 // the slices of one chunk run on different XCDs at about the same time and every XCD
 // moves through the clusters at the same pace.
-void build_xcd_lists(const gp_plan& P, const std::vector<Segment>& segs, const RowClusters& C, int S, int slice_elems, int d,
-                     std::vector<Segment>& recs, int64_t off[9])
+void build_xcd_lists(const gp_plan& P, const HostArray<Segment>& segs, const RowClusters& C, int S, int slice_elems, int d,
+                     HostArray<Segment>& recs, int64_t off[9])
 {
     const int64_t n = P.n, nsegs = (int64_t)segs.size();
     // rows in (cluster, row) order

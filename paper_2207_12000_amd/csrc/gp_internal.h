@@ -3,11 +3,16 @@
 
 #include <hip/hip_runtime.h>
 
+#include <sys/mman.h>
+
 #include <cstdarg>
 #include <cstdint>
+#include <cstdlib>
 #include <functional>
 #include <mutex>
+#include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "gp.h"
@@ -43,6 +48,54 @@ struct Options {
     int64_t device_plan_chunk = 0;  // GP_PLAN_ON_DEVICE: most candidate entries sorted at once, 0 = 2^31 - 1
 };
 Options& options();
+
+// Host arrays of a plan: resize() leaves new entries of plain types unwritten (whoever makes an array fills it, on all
+// threads), and large arrays lie on pages of 2 MiB.  Filling 50 MB with zeros first, on one thread and 4 KiB pages, took
+// 6 - 7 ms of page faults, and giving them back 0.8; on large pages 1.7 and 0.07, and four threads touch them in 0.8.
+template <class T>
+struct PlainAllocator {
+    using value_type = T;
+    static constexpr size_t kHuge = (size_t)2 << 20;
+    PlainAllocator() = default;
+    template <class U>
+    PlainAllocator(const PlainAllocator<U>&) noexcept
+    {
+    }
+    T* allocate(size_t count)
+    {
+        if (count > (SIZE_MAX - kHuge) / sizeof(T)) throw std::bad_alloc();
+        const size_t bytes = count * sizeof(T);
+        void* p = nullptr;
+        if (bytes < 2 * kHuge) {
+            p = std::malloc(bytes);
+        } else if ((p = std::aligned_alloc(kHuge, (bytes + kHuge - 1) / kHuge * kHuge))) {
+            (void)madvise(p, bytes, MADV_HUGEPAGE);  // (refused: pages of the usual size)
+        }
+        if (!p) throw std::bad_alloc();
+        return (T*)p;
+    }
+    void deallocate(T* p, size_t) noexcept { std::free(p); }
+    template <class U, class... A>
+    void construct(U* p, A&&... a)
+    {
+        if constexpr (sizeof...(A) == 0)
+            ::new ((void*)p) U;
+        else
+            ::new ((void*)p) U(std::forward<A>(a)...);
+    }
+    template <class U>
+    bool operator==(const PlainAllocator<U>&) const noexcept
+    {
+        return true;
+    }
+    template <class U>
+    bool operator!=(const PlainAllocator<U>&) const noexcept
+    {
+        return false;
+    }
+};
+template <class T>
+using HostArray = std::vector<T, PlainAllocator<T>>;
 
 int host_threads();
 // Runs fn(t, nthreads) on nthreads host threads (t = 0 .. nthreads-1) and joins.
@@ -143,7 +196,7 @@ struct DevicePlan {
     int64_t split_num_rows = 0, split_num_slots = 0;
     float* split_carry = nullptr;
     int64_t split_carry_ld = 0;
-    std::vector<Segment> split_hot_host;  // hot records in plan order (source of the per-XCD lists)
+    HostArray<Segment> split_hot_host;  // hot records in plan order (source of the per-XCD lists)
     // LDS pass over the hot pieces: 0 = not looked at yet, 1 = ready, 2 = does not apply to this plan
     int lds_state = 0;
     int32_t *lds_members = nullptr, *lds_group_off = nullptr, *lds_list_of_set = nullptr, *lds_col = nullptr, *lds_wave_cut = nullptr;
@@ -173,14 +226,14 @@ struct gp_plan {
     int32_t num_blocks = 0;
     std::vector<int64_t> block_off;
     std::vector<int32_t> block_row_lo, block_row_hi;
-    std::vector<int64_t> rowptr;
-    std::vector<int32_t> col;
-    std::vector<int32_t> deg;
-    std::vector<float> dinv_sqrt, dinv;
+    gp::HostArray<int64_t> rowptr;
+    gp::HostArray<int32_t> col;
+    gp::HostArray<int32_t> deg;
+    gp::HostArray<float> dinv_sqrt, dinv;
 
     // kernel schedule (library's own; not part of the checked plan)
     int64_t segment_edges = 0;
-    std::vector<gp::Segment> segs;       // grouped by block, longest first inside a block
+    gp::HostArray<gp::Segment> segs;       // grouped by block, longest first inside a block
     std::vector<int64_t> seg_off;        // b+1: block p owns segs [seg_off[p], seg_off[p+1])
     std::vector<gp::SplitRow> split;     // ascending row
     int64_t num_slots = 0;
@@ -205,15 +258,15 @@ namespace gp {
 gp_status build_schedule(gp_plan* plan);
 // segments, split rows and partial-row slots for the sorted list of `plan` cut at block_off
 // (block p = [block_off[p], block_off[p+1])): the plan's own blocks, or another cut of the same list
-gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_off, std::vector<Segment>& segs,
+gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_off, HostArray<Segment>& segs,
                        std::vector<int64_t>& seg_off, std::vector<SplitRow>& split, int64_t& num_slots);
 constexpr int kClusterRounds = 10;
 void cluster_rows(const gp_plan& P, RowClusters& C);
 // gp_cluster_device.hip: the same clusters made on the GPU that holds the plan's column list (which is current), on a
 // stream that is not being captured; false, and C untouched but for its capacity, where that is not possible.
 bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream);
-void build_xcd_lists(const gp_plan& P, const std::vector<Segment>& segs, const RowClusters& C, int S, int slice_elems, int d,
-                     std::vector<Segment>& recs, int64_t off[9]);
+void build_xcd_lists(const gp_plan& P, const HostArray<Segment>& segs, const RowClusters& C, int S, int slice_elems, int d,
+                     HostArray<Segment>& recs, int64_t off[9]);
 HotSets hot_sets_from_clusters(const RowClusters& C);
 // the `hubs` most popular source rows; sets of about rows_per_set consecutive rows
 HotSets hot_sets_from_hubs(const gp_plan& P, int32_t hubs, int64_t rows_per_set);
@@ -222,7 +275,7 @@ HotSets hot_sets_from_hubs(const gp_plan& P, int32_t hubs, int64_t rows_per_set)
 // from the others (cold), with a column list reordered to match (gp_cluster.cpp).
 struct SplitSchedule {
     std::vector<int32_t> col;
-    std::vector<Segment> hot, cold;
+    HostArray<Segment> hot, cold;
     std::vector<SplitRow> split;
     int64_t num_slots = 0;
 };
@@ -251,7 +304,7 @@ struct LdsOctet {
 };
 struct LdsSchedule {
     std::vector<int32_t> col;         // the column list, every segment's hot non-zeros first
-    std::vector<Segment> cold;        // every segment's other non-zeros, in position order; slice = kAddPlaneEntry where it has hot ones
+    HostArray<Segment> cold;        // every segment's other non-zeros, in position order; slice = kAddPlaneEntry where it has hot ones
     std::vector<int32_t> members;     // rows of list l, ascending: members[member_off[l] .. member_off[l+1])
     std::vector<int64_t> member_off;  // num_lists + 1
     std::vector<int32_t> list_of_set; // num_sets
@@ -335,8 +388,12 @@ gp_status launch_hot_lds(const HotLdsArgs& a, hipStream_t stream);
 // (element size es), or false if this plan keeps the implicit lists.
 // (stream: row clusters that are not there yet are made on it; nullptr: on the host)
 bool choose_cache_schedule(const gp_plan* plan, int32_t d, int es, int vec, int& num_slices, int& slice_elems, const hipStream_t* stream);
-// fills plan->nnz, rowptr, col, deg from validated input pairs, on the current GPU
-gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan);
+// fills plan->nnz, rowptr, deg and col from input pairs, on the current GPU (leave_columns: not col, which
+// columns_to_host then does); pairs_valid is asked once the pairs are on their way (m > 0), before anything reads them: false ends the call with GP_ERR_INDEX_RANGE
+gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan,
+                        const std::function<bool()>& pairs_valid, bool leave_columns);
+// fills plan->col from the column list that csr_on_device left on the GPU
+gp_status columns_to_host(gp_plan* plan);
 // fills block_row_lo / block_row_hi from rowptr and block_off, on the current GPU
 gp_status block_rows_on_device(gp_plan* plan);
 

@@ -50,6 +50,33 @@ void parallel_run(int nthreads, const std::function<void(int, int)>& fn)
         if (e) std::rethrow_exception(e);
 }
 
+// Host work on a thread of its own beside the caller's; finish() waits for it and passes on what it threw.
+struct Beside {
+    std::thread th;
+    std::exception_ptr err;
+    template <class F>
+    void start(F fn)
+    {
+        th = std::thread([this, fn]() mutable {
+            try {
+                fn();
+            } catch (...) {
+                err = std::current_exception();
+            }
+        });
+    }
+    void finish()
+    {
+        if (th.joinable()) th.join();
+        if (err) std::rethrow_exception(std::exchange(err, nullptr));
+    }
+    ~Beside()
+    {
+        if (th.joinable()) th.join();
+    }
+};
+constexpr int64_t kPairsBeside = 1 << 18;  // pairs from which that is worth a thread
+
 static inline void chunk_of(int64_t total, int t, int nt, int64_t& lo, int64_t& hi)
 {
     lo = total * t / nt;
@@ -83,9 +110,9 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
         plan->flags = flags;
         plan->opt = options();
 
-        // 1. validate
+        // 1. validate (a plan made on the GPU has its list on the way there meanwhile)
         std::atomic<int64_t> bad{-1};
-        parallel_run(nt, [&](int t, int k) {
+        auto find_bad_pair = [&] { parallel_run(nt, [&](int t, int k) {
             int64_t lo, hi;
             chunk_of(m, t, k, lo, hi);
             for (int64_t e = lo; e < hi; ++e) {
@@ -96,17 +123,29 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
                     return;
                 }
             }
-        });
-        if (bad.load() >= 0) {
+        }); };
+        auto refuse_bad_pair = [&] {
             const int64_t e = bad.load();
             gp_plan_destroy(plan);
             return fail(GP_ERR_INDEX_RANGE, "pair %lld = (%d, %d) has a node id outside [0, %lld)", (long long)e,
                         src[e], dst[e], (long long)n);
-        }
+        };
+        const bool beside = (flags & GP_PLAN_ON_DEVICE) && m >= kPairsBeside;
+        Beside validation;
+        if (beside)
+            validation.start([&] { find_bad_pair(); });
+        else
+            find_bad_pair();
+        if (!beside && bad.load() >= 0) return refuse_bad_pair();
 
         if (flags & GP_PLAN_ON_DEVICE) {
             // sort / unique / row pointers on the current GPU; same arrays, bit for bit
-            gp_status st = csr_on_device(src, dst, m, n, sym, loops, plan);
+            gp_status st = csr_on_device(src, dst, m, n, sym, loops, plan, [&] {
+                validation.finish();
+                return bad.load() < 0;
+            }, /*leave_columns=*/beside);
+            validation.finish();
+            if (bad.load() >= 0) return refuse_bad_pair();
             if (st != GP_OK) {
                 gp_plan_destroy(plan);
                 return st;
@@ -133,7 +172,7 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
             const int64_t ncand = cand_ptr[n];
 
             // 3. bucket the column ids by row
-            std::vector<int32_t> cand((size_t)ncand);
+            HostArray<int32_t> cand((size_t)ncand);
             {
                 std::vector<int64_t> cursor(cand_ptr.begin(), cand_ptr.end() - 1);
                 if (loops)
@@ -151,7 +190,7 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
             }
 
             // 4. sort + unique inside each row; threads own row ranges of similar candidate count
-            plan->deg.assign((size_t)n, 0);
+            plan->deg.resize((size_t)n);
             std::vector<int64_t> row_cut((size_t)nt + 1);
             for (int t = 0; t <= nt; ++t) {
                 const int64_t target = ncand / nt * t + std::min<int64_t>(t, ncand % nt);
@@ -170,7 +209,8 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
             });
 
             // 5. rowptr and the compacted column list
-            plan->rowptr.assign((size_t)n + 1, 0);
+            plan->rowptr.resize((size_t)n + 1);
+            plan->rowptr[0] = 0;
             for (int64_t i = 0; i < n; ++i) plan->rowptr[i + 1] = plan->rowptr[i] + plan->deg[i];
             const int64_t nnz = plan->rowptr[n];
             if (nnz >= (INT64_C(1) << 40)) {
@@ -185,7 +225,7 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
                         std::memcpy(plan->col.data() + plan->rowptr[i], cand.data() + cand_ptr[i],
                                     sizeof(int32_t) * (size_t)plan->deg[i]);
             });
-            std::vector<int32_t>().swap(cand);
+            HostArray<int32_t>().swap(cand);
             std::vector<int64_t>().swap(cand_ptr);
 
         }
@@ -249,10 +289,24 @@ extern "C" gp_status gp_plan_blocks(const int32_t* src, const int32_t* dst, int6
             while (L < 1024 && L * 2 <= nnz / 65536) L *= 2;
         }
         plan->segment_edges = L;
-        gp_status st = build_schedule(plan);
-        if (st != GP_OK) {
+        // (a plan made on the GPU: its column list comes to the host meanwhile)
+        gp_status st = GP_OK, copied = GP_OK;
+        std::string why;
+        {
+            Beside schedule;
+            auto cut = [&] {
+                if ((st = build_schedule(plan)) != GP_OK) why = gp_last_error();
+            };
+            if (beside)
+                schedule.start(cut);
+            else
+                cut();
+            if (beside) copied = columns_to_host(plan);
+            schedule.finish();
+        }
+        if (st != GP_OK || copied != GP_OK) {
             gp_plan_destroy(plan);
-            return st;
+            return copied != GP_OK ? copied : fail(st, "%s", why.c_str());
         }
     } catch (const std::bad_alloc&) {
         gp_plan_destroy(plan);

@@ -191,7 +191,8 @@ struct DeviceBuffers {
 
 }  // namespace
 
-gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan)
+gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan,
+                        const std::function<bool()>& pairs_valid, bool leave_columns)
 {
     hipStream_t stream = nullptr;
     DeviceBuffers B;
@@ -209,6 +210,10 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
     if (m) {
         GP_HIP(hipMemcpyAsync(d_src, src, (size_t)m * 4, hipMemcpyHostToDevice, stream));
         GP_HIP(hipMemcpyAsync(d_dst, dst, (size_t)m * 4, hipMemcpyHostToDevice, stream));
+        if (!pairs_valid()) {
+            GP_HIP(hipStreamSynchronize(stream));
+            return GP_ERR_INDEX_RANGE;  // (the caller names the pair)
+        }
         hipLaunchKernelGGL(gp_count_candidates, dim3(grid_for(m)), dim3(kThreads), 0, stream, d_src, d_dst, m, sym ? 1 : 0, d_cnt);
         GP_HIP(hipGetLastError());
     }
@@ -316,13 +321,14 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
 
     plan->nnz = nnz;
     plan->rowptr.resize((size_t)n + 1);
-    plan->col.resize((size_t)nnz);
+    if (!leave_columns) plan->col.resize((size_t)nnz);
     plan->deg.resize((size_t)n);
     plan->dinv_sqrt.resize((size_t)n);
     plan->dinv.resize((size_t)n);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(plan->rowptr.data(), d_rowptr, ((size_t)n + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess && nnz) e = hipMemcpyAsync(plan->col.data(), d_col, (size_t)nnz * sizeof(int32_t), hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess && nnz && !leave_columns)
+        e = hipMemcpyAsync(plan->col.data(), d_col, (size_t)nnz * sizeof(int32_t), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(plan->deg.data(), d_deg, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(plan->dinv_sqrt.data(), d_dinv_sqrt, (size_t)n * sizeof(float), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(plan->dinv.data(), d_dinv, (size_t)n * sizeof(float), hipMemcpyDeviceToHost, stream);
@@ -341,6 +347,13 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
     plan->dev.dinv_sqrt = d_dinv_sqrt;
     plan->dev.dinv = d_dinv;
     plan->norms_on_device = true;
+    return GP_OK;
+}
+
+gp_status columns_to_host(gp_plan* plan)
+{
+    plan->col.resize((size_t)plan->nnz);
+    if (plan->nnz) GP_HIP(hipMemcpy(plan->col.data(), plan->dev.col, (size_t)plan->nnz * sizeof(int32_t), hipMemcpyDeviceToHost));
     return GP_OK;
 }
 

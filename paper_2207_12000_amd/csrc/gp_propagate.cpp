@@ -10,8 +10,8 @@ namespace gp {
 
 namespace {
 
-template <class T>
-gp_status upload(T*& dptr, const std::vector<T>& h, hipStream_t stream)
+template <class T, class A>
+gp_status upload(T*& dptr, const std::vector<T, A>& h, hipStream_t stream)
 {
     if (dptr || h.empty()) return GP_OK;  // already there (the device planner leaves its results), or nothing to send
     GP_HIP(hipMalloc((void**)&dptr, h.size() * sizeof(T)));
@@ -182,8 +182,8 @@ bool choose_cache_schedule(const gp_plan* plan, int32_t d, int es, int vec, int&
 
 namespace {
 
-template <class T>
-gp_status upload_now(T*& dptr, const std::vector<T>& h, hipStream_t stream)
+template <class T, class A>
+gp_status upload_now(T*& dptr, const std::vector<T, A>& h, hipStream_t stream)
 {
     dptr = nullptr;
     if (h.empty()) return GP_OK;
@@ -504,7 +504,7 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
         if (w.num_slices == S && w.slice_elems == elems && w.split == want_split) found = &w;
     if (!found && !may_build) return attach_columns(plan, a, stream, false, no_room);
     if (!found) {
-        std::vector<Segment> recs;
+        HostArray<Segment> recs;
         XcdWork w;
         w.num_slices = S;
         w.slice_elems = elems;
@@ -914,7 +914,7 @@ extern "C" gp_status gp_plan_work_lists(const gp_plan* plan, int32_t d, gp_dtype
         *slice_elems = 0;
         for (int x = 0; x <= 8; ++x) xcd_off[x] = 0;
         if (!choose_cache_schedule(plan, d, es, vec, S, elems, nullptr)) return GP_OK;  // implicit lists
-        std::vector<Segment> recs;
+        HostArray<Segment> recs;
         build_xcd_lists(*plan, plan->segs, plan->clusters, S, elems, d, recs, xcd_off);
         *num_slices = S;
         *slice_elems = elems;

@@ -20,7 +20,7 @@ namespace {
 struct CutPlan {
     const gp_plan& plan;
     const std::vector<int64_t>& block_off;
-    const std::vector<int64_t>& rowptr;
+    const HostArray<int64_t>& rowptr;
     int64_t nnz, n;
     int32_t num_blocks;
     CutPlan(const gp_plan& p, const std::vector<int64_t>& off)
@@ -83,13 +83,11 @@ struct Cutter {
         else
             r1 = std::lower_bound(P.rowptr.begin(), P.rowptr.end() - 1, hi) - P.rowptr.begin();
     }
-    // calls emit(row, start, len, piece_index) for every segment of block p
+    // calls emit(row, start, len, piece_index) for every segment of block p that lies in rows [r0, r1) of its rows_of_block
     template <class F>
-    void walk(int32_t p, F&& emit) const
+    void walk(int32_t p, int64_t r0, int64_t r1, F&& emit) const
     {
         const int64_t lo = P.block_off[p], hi = P.block_off[p + 1];
-        int64_t r0, r1;
-        rows_of_block(p, r0, r1);
         for (int64_t r = r0; r < r1; ++r) {
             const int64_t rs = P.rowptr[r], re = P.rowptr[r + 1];
             if (rs == re) {
@@ -114,7 +112,7 @@ gp_status build_schedule(gp_plan* plan)
     return cut_schedule(*plan, plan->block_off, plan->segs, plan->seg_off, plan->split, plan->num_slots);
 }
 
-gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_off, std::vector<Segment>& out_segs,
+gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_off, HostArray<Segment>& out_segs,
                        std::vector<int64_t>& out_seg_off, std::vector<SplitRow>& out_split, int64_t& out_num_slots)
 {
     const int64_t L = plan.segment_edges;
@@ -123,9 +121,9 @@ gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_of
     Cutter cut(plan, block_off);
     // the names the body below uses
     struct Out {
-        const std::vector<int64_t>& rowptr;
+        const HostArray<int64_t>& rowptr;
         int64_t n, nnz;
-        std::vector<Segment>& segs;
+        HostArray<Segment>& segs;
         std::vector<int64_t>& seg_off;
         std::vector<SplitRow>& split;
         int64_t& num_slots;
@@ -163,40 +161,108 @@ gp_status cut_schedule(const gp_plan& plan, const std::vector<int64_t>& block_of
     };
     if (P.num_slots > INT32_MAX) return fail(GP_ERR_OVERFLOW, "%lld partial rows exceed int32", (long long)P.num_slots);
 
-    // segments per block
+    auto record = [&](int64_t r, int64_t s, int64_t len, int64_t idx) {
+        Segment g;
+        g.start_lo = (uint32_t)(s & 0xFFFFFFFF);
+        g.start_hi = (uint8_t)(s >> 32);
+        g.slice = 0;
+        g.len = (uint16_t)len;
+        g.row = (int32_t)r;
+        const int64_t fs = len == P.rowptr[r + 1] - P.rowptr[r] ? -1 : first_slot_of((int32_t)r);
+        g.slot = fs < 0 ? -1 : (int32_t)(fs + idx);
+        return g;
+    };
+
+    // Segments per block, by a stable counting sort, longest first.  A block's rows are walked by several threads where there
+    // are fewer blocks than threads (two blocks of 12.5 million non-zeros on two threads: 7.7 ms): every part of a block
+    // counts its lengths, and writes its records behind those of the parts before it of the same length.
+    // A thread gets 16,384 rows or segments at least: a block of 10,000 rows is walked in 0.2 ms, sixteen threads start in 0.4.
+    const int64_t walkers = std::min<int64_t>(nt, std::max<int64_t>(1, (P.n + P.nnz / L) >> 14));
+    const int64_t parts = b < walkers ? (walkers + b - 1) / b : 1;
+    const int64_t lengths = L + 1;
+    struct Part {
+        int64_t r0, r1;
+        std::vector<int64_t> at;  // segments of each length, then the next one's place
+    };
+    std::vector<Part> part((size_t)(b * parts));
+    auto cut_block = [&](int32_t p) {
+        int64_t r0, r1;
+        cut.rows_of_block(p, r0, r1);
+        const int64_t lo = P.rowptr[r0] + r0, hi = r1 > r0 ? P.rowptr[r1] + r1 : lo;
+        int64_t at = r0;
+        for (int64_t q = 0; q < parts; ++q) {
+            Part& t = part[(size_t)(p * parts + q)];
+            t.r0 = at;
+            if (q + 1 == parts) {
+                at = r1;
+            } else {  // as many rows and non-zeros in every part
+                const int64_t target = lo + (hi - lo) / parts * (q + 1);
+                int64_t a = at, z = r1;
+                while (a < z) {
+                    const int64_t mid = a + (z - a) / 2;
+                    if (P.rowptr[mid] + mid < target)
+                        a = mid + 1;
+                    else
+                        z = mid;
+                }
+                at = a;
+            }
+            t.r1 = std::max(at, t.r0);
+        }
+    };
+    auto count_part = [&](int32_t p, Part& t) {
+        t.at.assign((size_t)lengths, 0);
+        cut.walk(p, t.r0, t.r1, [&](int64_t, int64_t, int64_t len, int64_t) { ++t.at[(size_t)len]; });
+    };
+    auto place_block = [&](int32_t p, int64_t first) {  // counts become places
+        int64_t at = first;
+        for (int64_t len = L; len >= 0; --len)
+            for (int64_t q = 0; q < parts; ++q) {
+                int64_t& c = part[(size_t)(p * parts + q)].at[(size_t)len];
+                const int64_t here = c;
+                c = at;
+                at += here;
+            }
+        return at;
+    };
+    auto write_part = [&](int32_t p, Part& t) {
+        cut.walk(p, t.r0, t.r1, [&](int64_t r, int64_t s, int64_t len, int64_t idx) {
+            P.segs[(size_t)t.at[(size_t)len]++] = record(r, s, len, idx);
+        });
+        std::vector<int64_t>().swap(t.at);
+    };
+
     P.seg_off.assign((size_t)b + 1, 0);
+    if (parts > 1) {
+        for (int32_t p = 0; p < b; ++p) cut_block(p);
+        const int all = (int)(b * parts);
+        parallel_run(std::min(nt, all), [&](int t, int k) {
+            for (int i = t; i < all; i += k) count_part((int32_t)(i / parts), part[(size_t)i]);
+        });
+        for (int32_t p = 0; p < b; ++p) P.seg_off[p + 1] = place_block(p, P.seg_off[p]);
+        P.segs.resize((size_t)P.seg_off[b]);
+        parallel_run(std::min(nt, all), [&](int t, int k) {
+            for (int i = t; i < all; i += k) write_part((int32_t)(i / parts), part[(size_t)i]);
+        });
+        return GP_OK;
+    }
     parallel_run(std::min<int>(nt, b), [&](int t, int k) {
         for (int32_t p = t; p < b; p += k) {
             int64_t c = 0;
-            cut.walk(p, [&](int64_t, int64_t, int64_t, int64_t) { ++c; });
+            cut_block(p);
+            const Part& all = part[(size_t)p];
+            cut.walk(p, all.r0, all.r1, [&](int64_t, int64_t, int64_t, int64_t) { ++c; });
             P.seg_off[(size_t)p + 1] = c;
         }
     });
     for (int32_t p = 0; p < b; ++p) P.seg_off[p + 1] += P.seg_off[p];
     P.segs.resize((size_t)P.seg_off[b]);
-
     parallel_run(std::min<int>(nt, b), [&](int t, int k) {
-        std::vector<Segment> tmp;
-        std::vector<int64_t> hist;
         for (int32_t p = t; p < b; p += k) {
-            tmp.clear();
-            cut.walk(p, [&](int64_t r, int64_t s, int64_t len, int64_t idx) {
-                Segment g;
-                g.start_lo = (uint32_t)(s & 0xFFFFFFFF);
-                g.start_hi = (uint8_t)(s >> 32);
-                g.slice = 0;
-                g.len = (uint16_t)len;
-                g.row = (int32_t)r;
-                const int64_t fs = first_slot_of((int32_t)r);
-                g.slot = fs < 0 ? -1 : (int32_t)(fs + idx);
-                tmp.push_back(g);
-            });
-            // stable counting sort, longest first
-            hist.assign((size_t)L + 2, 0);
-            for (const Segment& g : tmp) ++hist[(size_t)(L - g.len) + 1];
-            for (int64_t i = 0; i <= L; ++i) hist[i + 1] += hist[i];
-            Segment* out = P.segs.data() + P.seg_off[p];
-            for (const Segment& g : tmp) out[hist[(size_t)(L - g.len)]++] = g;
+            Part& all = part[(size_t)p];
+            count_part(p, all);
+            place_block(p, P.seg_off[p]);
+            write_part(p, all);
         }
     });
     return GP_OK;

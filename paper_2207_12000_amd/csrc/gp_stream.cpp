@@ -32,12 +32,12 @@ namespace {
 struct StreamSchedule {
     bool own = false;
     std::vector<int64_t> own_block_off, own_seg_off;
-    std::vector<Segment> own_segs;
+    HostArray<Segment> own_segs;
     std::vector<SplitRow> own_split;
     int64_t own_slots = 0;
     const std::vector<int64_t>* block_off = nullptr;
     const std::vector<int64_t>* seg_off = nullptr;
-    const std::vector<Segment>* segs = nullptr;
+    const HostArray<Segment>* segs = nullptr;
     const std::vector<SplitRow>* split = nullptr;
     int64_t num_slots = 0;
     int32_t b = 0;
