@@ -66,7 +66,7 @@ struct PlainAllocator {
         if (count > (SIZE_MAX - kHuge) / sizeof(T)) throw std::bad_alloc();
         const size_t bytes = count * sizeof(T);
         void* p = nullptr;
-        if (bytes < 2 * kHuge) {
+        if (bytes < kHuge) {
             p = std::malloc(bytes);
         } else if ((p = std::aligned_alloc(kHuge, (bytes + kHuge - 1) / kHuge * kHuge))) {
             (void)madvise(p, bytes, MADV_HUGEPAGE);  // (refused: pages of the usual size)
@@ -392,10 +392,8 @@ bool choose_cache_schedule(const gp_plan* plan, int32_t d, int es, int vec, int&
 // columns_to_host then does); pairs_valid is asked once the pairs are on their way (m > 0), before anything reads them: false ends the call with GP_ERR_INDEX_RANGE
 gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64_t n, bool sym, bool loops, gp_plan* plan,
                         const std::function<bool()>& pairs_valid, bool leave_columns);
-// fills plan->col from the column list that csr_on_device left on the GPU
+// fills plan->col (nnz entries) from the column list that csr_on_device left on the GPU
 gp_status columns_to_host(gp_plan* plan);
-// fills block_row_lo / block_row_hi from rowptr and block_off, on the current GPU
-gp_status block_rows_on_device(gp_plan* plan);
 
 // resident schedule: everything already in HBM
 gp_status propagate_resident(const gp_plan* plan, const void* X, int64_t ldx, int32_t d, gp_dtype dtype,

@@ -3,12 +3,11 @@
 // normalisation vectors of Eq. 1 computed there.  The paper runs its adjacency
 // normalisation block-wise on the GPU (Section 3.2, Section 4.2); here the
 // normalisation needs no matrix at all, only the sorted set and its row counts, so the
-// GPU's share is: count the candidate entries of every row, cut the rows into ranges
-// whose candidates fit one sort, and per range emit one 64-bit key (row << 32 | col)
+// GPU's share is: where the candidate entries may not fit one sort, count them row by row and cut the rows into
+// ranges that do, and per range emit one 64-bit key (row << 32 | col)
 // per candidate, radix-sort the keys, drop duplicates, split them back into columns and
 // find every row's first entry by binary search; then degrees, 1/sqrt(deg) and 1/deg
-// (in fp64, narrowed once: the host planner's recipe) and the rows at the block
-// boundaries.  Integers and correctly rounded operations only, so the result is the host
+// (in fp64, narrowed once: the host planner's recipe).  Integers and correctly rounded operations only, so the result is the host
 // planner's bit for bit.  The sort and the duplicate removal are gp_device_sort.hip's.
 // The column list and the two norm vectors stay on the device for gp_propagate.
 #include <hip/hip_runtime.h>
@@ -142,49 +141,32 @@ __global__ __launch_bounds__(kThreads) void gp_degrees_and_norms(const int64_t* 
     }
 }
 
-// rows of the first and last entry of every block (0 and -1 for an empty block)
-__global__ void gp_block_rows(const int64_t* __restrict__ rowptr, int64_t n, const int64_t* __restrict__ block_off, int32_t b,
-                              int32_t* __restrict__ row_lo, int32_t* __restrict__ row_hi)
-{
-    const int32_t p = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (p >= b) return;
-    const int64_t lo = block_off[p], hi = block_off[p + 1];
-    int32_t rl = 0, rh = -1;
-    if (hi > lo) {
-        auto row_of = [&](int64_t e) {  // the i with rowptr[i] <= e < rowptr[i + 1]
-            int64_t a = 0, z = n;       // invariant: rowptr[a] <= e, rowptr[z] > e
-            while (z - a > 1) {
-                const int64_t mid = a + (z - a) / 2;
-                if (rowptr[mid] <= e)
-                    a = mid;
-                else
-                    z = mid;
-            }
-            return (int32_t)a;
-        };
-        rl = row_of(lo);
-        rh = row_of(hi - 1);
-    }
-    row_lo[p] = rl;
-    row_hi[p] = rh;
-}
-
 inline unsigned grid_for(int64_t items) { return (unsigned)std::min<int64_t>((items + kThreads - 1) / kThreads, 256 * 32); }
 
+// Device scratch, freed at the end of the scope.  Arrays that are needed together share an allocation (each hipMalloc and
+// hipFree of tens of megabytes takes 0.1 - 0.3 ms): ask() for each, then one alloc().
 struct DeviceBuffers {
     std::vector<void*> ptrs;
+    std::vector<std::function<void(char*)>> asked;
+    size_t bytes = 0;
     ~DeviceBuffers()
     {
         for (void* p : ptrs) (void)hipFree(p);
     }
     template <class T>
-    gp_status alloc(T*& p, size_t count)
+    void ask(T*& p, size_t count)
     {
-        p = nullptr;
+        asked.push_back([&p, at = bytes](char* base) { p = (T*)(base + at); });
+        bytes += (count * sizeof(T) + 255) / 256 * 256;
+    }
+    gp_status alloc()
+    {
         void* q = nullptr;
-        GP_HIP(hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T)));
+        GP_HIP(hipMalloc(&q, std::max<size_t>(bytes, 256)));
         ptrs.push_back(q);
-        p = (T*)q;
+        for (auto& a : asked) a((char*)q);
+        asked.clear();
+        bytes = 0;
         return GP_OK;
     }
 };
@@ -196,17 +178,21 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
 {
     hipStream_t stream = nullptr;
     DeviceBuffers B;
-    int32_t *d_src, *d_dst;
-    unsigned long long* d_cnt;
+    int32_t *d_src, *d_dst, *d_deg;
+    unsigned long long* d_cnt = nullptr;
     int64_t* d_rowptr;
     gp_status st;
-    if ((st = B.alloc(d_src, (size_t)m)) != GP_OK || (st = B.alloc(d_dst, (size_t)m)) != GP_OK ||
-        (st = B.alloc(d_cnt, (size_t)n)) != GP_OK ||
-        (st = B.alloc(d_rowptr, (size_t)n + 1)) != GP_OK)
-        return st;
-    // ---- candidates per row, and row ranges whose candidates fit one sort ------------
-    hipLaunchKernelGGL(gp_fill_words, dim3(grid_for(n)), dim3(kThreads), 0, stream, d_cnt, n, loops ? 1ULL : 0ULL);
-    GP_HIP(hipGetLastError());
+    const int64_t limit = options().device_plan_chunk > 0 ? options().device_plan_chunk : (INT64_C(1) << 31) - 1;
+    // Candidates at most (a pair of a node with itself gives none).  Where one sort takes that many the rows need not be
+    // counted: 12.5 million candidates, 0.6 ms of atomics and 1.5 of copies and host work.
+    const int64_t most = (sym ? 2 : 1) * m + (loops ? n : 0);
+    const bool one_range = most <= limit;
+    B.ask(d_src, (size_t)m);
+    B.ask(d_dst, (size_t)m);
+    B.ask(d_rowptr, (size_t)n + 1);
+    B.ask(d_deg, (size_t)n);
+    if (!one_range) B.ask(d_cnt, (size_t)n);
+    if ((st = B.alloc()) != GP_OK) return st;
     if (m) {
         GP_HIP(hipMemcpyAsync(d_src, src, (size_t)m * 4, hipMemcpyHostToDevice, stream));
         GP_HIP(hipMemcpyAsync(d_dst, dst, (size_t)m * 4, hipMemcpyHostToDevice, stream));
@@ -214,16 +200,24 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
             GP_HIP(hipStreamSynchronize(stream));
             return GP_ERR_INDEX_RANGE;  // (the caller names the pair)
         }
-        hipLaunchKernelGGL(gp_count_candidates, dim3(grid_for(m)), dim3(kThreads), 0, stream, d_src, d_dst, m, sym ? 1 : 0, d_cnt);
-        GP_HIP(hipGetLastError());
     }
-    std::vector<unsigned long long> cnt((size_t)n);
-    GP_HIP(hipMemcpyAsync(cnt.data(), d_cnt, (size_t)n * sizeof(unsigned long long), hipMemcpyDeviceToHost, stream));
-    GP_HIP(hipStreamSynchronize(stream));
-    int64_t limit = options().device_plan_chunk > 0 ? options().device_plan_chunk : (INT64_C(1) << 31) - 1;
-    std::vector<int64_t> range_lo, range_cnt;  // row ranges [range_lo[k], range_lo[k+1]) and their candidate counts
+    // ---- row ranges [range_lo[k], range_lo[k+1]) whose candidates fit one sort, and their candidate counts ------------
+    std::vector<int64_t> range_lo, range_cnt;
     int64_t total = 0, largest = 0;
-    {
+    if (one_range) {
+        range_lo = {0, n};
+        range_cnt = {most};  // (no less than there are)
+        total = largest = most;
+    } else {
+        hipLaunchKernelGGL(gp_fill_words, dim3(grid_for(n)), dim3(kThreads), 0, stream, d_cnt, n, loops ? 1ULL : 0ULL);
+        GP_HIP(hipGetLastError());
+        if (m) {
+            hipLaunchKernelGGL(gp_count_candidates, dim3(grid_for(m)), dim3(kThreads), 0, stream, d_src, d_dst, m, sym ? 1 : 0, d_cnt);
+            GP_HIP(hipGetLastError());
+        }
+        std::vector<unsigned long long> cnt((size_t)n);
+        GP_HIP(hipMemcpyAsync(cnt.data(), d_cnt, (size_t)n * sizeof(unsigned long long), hipMemcpyDeviceToHost, stream));
+        GP_HIP(hipStreamSynchronize(stream));
         int64_t acc = 0;
         range_lo.push_back(0);
         for (int64_t i = 0; i < n; ++i) {
@@ -242,11 +236,16 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
         range_lo.push_back(n);
         for (int64_t c : range_cnt) largest = std::max(largest, c);
     }
-    std::vector<unsigned long long>().swap(cnt);
 
     uint64_t *d_keys, *d_sorted;
+    uint32_t *d_scratch, *d_emit;  // the sort's digit tables and the duplicate removal's tile counts; the key emission's tile counts
+    const int64_t most_tiles = (m + n + kEmitTile - 1) / kEmitTile + 1;  // (+ 1: the total)
+    B.ask(d_keys, (size_t)largest);
+    B.ask(d_sorted, (size_t)largest);
+    B.ask(d_scratch, device_sort_scratch_words(largest));
+    B.ask(d_emit, (size_t)most_tiles + device_scan_scratch_words(most_tiles));
+    if ((st = B.alloc()) != GP_OK) return st;
     int32_t* d_col = nullptr;  // stays with the plan
-    if ((st = B.alloc(d_keys, (size_t)largest)) != GP_OK || (st = B.alloc(d_sorted, (size_t)largest)) != GP_OK) return st;
     GP_HIP(hipMalloc((void**)&d_col, (size_t)std::max<int64_t>(total, 1) * sizeof(int32_t)));
     struct ColGuard {
         int32_t*& p;
@@ -259,12 +258,6 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
             }
         }
     } col_guard{d_col};
-    uint32_t *d_scratch, *d_emit;  // the sort's digit tables and the duplicate removal's tile counts; the key emission's tile counts
-    if ((st = B.alloc(d_scratch, device_sort_scratch_words(largest))) != GP_OK) return st;
-    {
-        const int64_t most_tiles = (m + n + kEmitTile - 1) / kEmitTile + 1;  // (+ 1: the total)
-        if ((st = B.alloc(d_emit, (size_t)most_tiles + device_scan_scratch_words(most_tiles))) != GP_OK) return st;
-    }
     // bits in which keys can differ: a column is below n, a row of the range below its end
     auto bits_of = [](int64_t values) {
         int b = 0;
@@ -274,7 +267,8 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
 
     int64_t nnz = 0;
     for (size_t k = 0; k < range_cnt.size(); ++k) {
-        const int64_t r0 = range_lo[k], r1 = range_lo[k + 1], cand = range_cnt[k];
+        const int64_t r0 = range_lo[k], r1 = range_lo[k + 1];
+        int64_t cand = range_cnt[k];
         int64_t uniq = 0;
         uint64_t* d_distinct = d_keys;  // (no candidates: nothing is read from it)
         if (cand > 0) {
@@ -286,6 +280,14 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
             hipLaunchKernelGGL(gp_emit_keys_range, dim3((unsigned)emit_tiles), dim3(kThreads), 0, stream, d_src, d_dst, m, sym ? 1 : 0,
                                loops ? 1 : 0, r0, r1, d_emit, d_keys, cand);
             GP_HIP(hipGetLastError());
+            if (one_range) {  // the keys there are
+                uint32_t keys = 0;
+                GP_HIP(hipMemcpyAsync(&keys, d_emit + emit_tiles, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+                GP_HIP(hipStreamSynchronize(stream));
+                cand = (int64_t)keys;
+            }
+        }
+        if (cand > 0) {
             uint64_t* sorted = nullptr;
             if ((st = device_sort_keys(d_keys, d_sorted, cand, bits_of(n), bits_of(r1), d_scratch, stream, &sorted)) != GP_OK) return st;
             // the distinct keys go into the buffer the sorted ones are not in
@@ -308,9 +310,7 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
     }
 
     // ---- degrees and the normalisation vectors of Eq. 1 -------------------------------
-    int32_t* d_deg;
     float *d_dinv_sqrt = nullptr, *d_dinv = nullptr;  // stay with the plan
-    if ((st = B.alloc(d_deg, (size_t)n)) != GP_OK) return st;
     if (hipMalloc((void**)&d_dinv_sqrt, (size_t)n * sizeof(float)) != hipSuccess ||
         hipMalloc((void**)&d_dinv, (size_t)n * sizeof(float)) != hipSuccess) {
         (void)hipFree(d_dinv_sqrt);
@@ -352,30 +352,7 @@ gp_status csr_on_device(const int32_t* src, const int32_t* dst, int64_t m, int64
 
 gp_status columns_to_host(gp_plan* plan)
 {
-    plan->col.resize((size_t)plan->nnz);
     if (plan->nnz) GP_HIP(hipMemcpy(plan->col.data(), plan->dev.col, (size_t)plan->nnz * sizeof(int32_t), hipMemcpyDeviceToHost));
-    return GP_OK;
-}
-
-// rows at the block boundaries, found on the device from the row pointers
-gp_status block_rows_on_device(gp_plan* plan)
-{
-    const int32_t b = plan->num_blocks;
-    const int64_t n = plan->n;
-    DeviceBuffers B;
-    int64_t *d_rowptr, *d_off;
-    int32_t *d_lo, *d_hi;
-    gp_status st;
-    if ((st = B.alloc(d_rowptr, (size_t)n + 1)) != GP_OK || (st = B.alloc(d_off, (size_t)b + 1)) != GP_OK ||
-        (st = B.alloc(d_lo, (size_t)b)) != GP_OK || (st = B.alloc(d_hi, (size_t)b)) != GP_OK)
-        return st;
-    GP_HIP(hipMemcpy(d_rowptr, plan->rowptr.data(), ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    GP_HIP(hipMemcpy(d_off, plan->block_off.data(), ((size_t)b + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-    hipLaunchKernelGGL(gp_block_rows, dim3((unsigned)((b + kThreads - 1) / kThreads)), dim3(kThreads), 0, nullptr, d_rowptr, n, d_off, b,
-                       d_lo, d_hi);
-    GP_HIP(hipGetLastError());
-    GP_HIP(hipMemcpy(plan->block_row_lo.data(), d_lo, (size_t)b * sizeof(int32_t), hipMemcpyDeviceToHost));
-    GP_HIP(hipMemcpy(plan->block_row_hi.data(), d_hi, (size_t)b * sizeof(int32_t), hipMemcpyDeviceToHost));
     return GP_OK;
 }
 
