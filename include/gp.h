@@ -246,8 +246,9 @@ gp_status gp_plan_work_lists(const gp_plan *plan, int32_t d, gp_dtype dtype, int
  * the first call whose hops read it, which allocates and waits for the stream, and stays until the
  * plan is destroyed: for hops on implicit lists a copy of records and ids in walking order (4 bytes
  * per non-zero, about 20 per record); after a call of GP_AGG_SYM one weight per non-zero (4 bytes)
- * for that copy, and for the plan's own list where hops read it; these only where there is room
- * (option "list_bytes").  The lists of the LDS pass and of the cache schedule come the same way,
+ * for that copy, and for the plan's own list where hops read it; where rows start off 128-byte lines
+ * and hops gain by reading them from lines of their own, two slabs of n rows (a row's bytes rounded up
+ * to 64 or 128); these only where there is room (option "list_bytes").  The lists of the LDS pass and of the cache schedule come the same way,
  * but not without room.  Calls on ONE plan must not
  * overlap in time (they share that scratch); different plans are independent.
  * Results are deterministic: the same inputs and options give the same bits on every
@@ -461,8 +462,9 @@ gp_status gp_set_hbm_budget_bytes(int64_t bytes);
  *                     few stores), 4 with hubs (short segments: the stores weigh as much as the
  *                     reads).  The results do not depend on it.
  *   "list_bytes"      device memory, in bytes, that a list which calls can do without may take: the copy of
- *                     records and ids in walking order, and weights per non-zero (see gp_propagate).  0 = a
- *                     fourth of what is free for the copy, whatever is free for weights.  A call that
+ *                     records and ids in walking order, the slabs of rows on lines of their own, and weights per
+ *                     non-zero (see gp_propagate).  0 = a fourth of what is free for copy and slabs,
+ *                     whatever is free for weights.  A call that
  *                     finds no room runs without, with the same bits; the next call asks again.
  *   "device_plan_chunk"  GP_PLAN_ON_DEVICE: most candidate entries sorted at once
  *                     (1 .. 2^31 - 1; 0 = 2^31 - 1).  Read by gp_plan_blocks.

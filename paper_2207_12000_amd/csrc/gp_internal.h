@@ -420,6 +420,9 @@ struct HopArgs {
     int64_t ldin;
     void* xout;             // DEVICE n x d, leading dimension ldout
     int64_t ldout;
+    // optional: finished rows once more (beside xout), laid out as xin is: the next hop's xin
+    void* xnext = nullptr;
+    bool xout_apart = false;  // xout may lie worse than xin: it does not bound the vector width (bf16 rows off a dword are stored by element)
     float* carry;           // DEVICE num_slots x carry_ld
     int64_t carry_ld;
     int32_t d;
@@ -466,6 +469,8 @@ struct FixupArgs {
     const float* row_scale;
     void* xout;
     int64_t ldout;
+    void* xnext = nullptr;  // as in HopArgs
+    int64_t ldnext = 0;
     int32_t d;
     gp_dtype dtype;
     float* comb = nullptr;  // as in HopArgs

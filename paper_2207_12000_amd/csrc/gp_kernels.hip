@@ -275,6 +275,9 @@ struct XcdLists {
 // 490,000 rows and 12 million non-zeros, 2 columns, sum 321 -> 280 us, sym 358 -> 320.
 constexpr int resident_wavefronts(size_t element, int vec, int group) { return element == 4 && vec == 2 && group == 8 ? 5 : 1; }
 
+constexpr int kCombStarts = 1;    // comb[row] = gamma0 * xin[row] + gamma * result
+constexpr int kOutByElement = 2;  // rows of xout may start off a dword (bf16)
+
 template <typename T, int VEC, int G, int VPL, int EDGE_W>
 __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
                                                             const XcdLists lists, unsigned long long* __restrict__ ctrl,
@@ -286,9 +289,10 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
                                                             T* __restrict__ xout, int64_t ldout,
                                                             float* __restrict__ carry, int64_t carry_ld, int d,
                                                             int num_slices, int slice_elems, float* __restrict__ comb,
-                                                            int64_t ldc, float gamma, int comb_starts, float gamma0,
+                                                            int64_t ldc, float gamma, int flags, float gamma0,
                                                             const float* __restrict__ planes,
-                                                            int64_t num_pos, int run_log2, int plane_log2)
+                                                            int64_t num_pos, int run_log2, int plane_log2,
+                                                            T* __restrict__ xnext)
 {
     constexpr int GPB = kThreads / G;
     constexpr int PF = G >= 32 ? 1 : 32 / G;  // column ids each lane prefetches per segment
@@ -299,6 +303,7 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
     constexpr int NACC = sizeof(T) == 2 ? 2 : 4;
     const int lane = threadIdx.x % G;
     const int xcd = blockIdx.x & 7;
+    const bool comb_starts = flags & kCombStarts;
     // This XCD's list: the record of position p < count is segs[place_of(p)].  Implicit lists: the
     // XCDs that share a slice take the records interleaved, in runs of 2^run_log2 consecutive records: what consecutive
     // records read side by side (ids and weights of an ordered column list, plane entries) shares lines, which then
@@ -606,7 +611,17 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
             if (partial) {
                 Row<float, VEC>::store(carry + (int64_t)r.slot * carry_ld + coff[v], o);
             } else {
-                if (xout) Row<T, VEC>::store_stream(xout + (int64_t)r.row * ldout + coff[v], o);
+                T* op = xout + (int64_t)r.row * ldout + coff[v];
+                if (sizeof(T) == 2 && VEC > 1 && (flags & kOutByElement)) {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        const float one[1] = {o[i]};
+                        Row<T, 1>::store_stream(op + i, one);
+                    }
+                } else if (xout) {
+                    Row<T, VEC>::store_stream(op, o);
+                }
+                if (xnext) Row<T, VEC>::store(xnext + (int64_t)r.row * ldin + coff[v], o);
                 // running filter output: comb[row] += gamma * (A^^k X)[row]
                 if (kFiltAhead && filt_ahead) {
 #pragma unroll
@@ -694,7 +709,8 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
                                                           const float* __restrict__ carry, int64_t carry_ld,
                                                           const float* __restrict__ row_scale, T* __restrict__ xout,
                                                           int64_t ldout, int d, float* __restrict__ comb, int64_t ldc,
-                                                          float gamma, const T* __restrict__ x0, int64_t ldx0, float gamma0)
+                                                          float gamma, const T* __restrict__ x0, int64_t ldx0, float gamma0,
+                                                          T* __restrict__ xnext, int64_t ldnext)
 {
     constexpr int GPB = kThreads / G;
     const int lane = threadIdx.x % G;
@@ -760,6 +776,7 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
 #pragma unroll
         for (int i = 0; i < VEC; ++i) r[i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * rs;
         if (xout) Row<T, VEC>::store_stream(xout + (int64_t)sr.row * ldout + c0, r);
+        if (xnext) Row<T, VEC>::store(xnext + (int64_t)sr.row * ldnext + c0, r);
         if (filt_ahead) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) filt[i] = fmaf(gamma, r[i], filt[i]);
@@ -816,6 +833,22 @@ __global__ __launch_bounds__(kThreads) void gp_copy_rows(const U* __restrict__ s
     }
 }
 
+// The same for rows of at least four dwords that are no whole number of 16-byte units, or do not start on them: 16 bytes per
+// lane from any dword on, the row's last vector moved back to end with it (what it repeats is written twice, identically).
+// I: 32-bit numbers where they hold every vector's.
+template <typename I>
+__global__ __launch_bounds__(kThreads) void gp_copy_rows_dwords(const uint32_t* __restrict__ src, int64_t lds, uint32_t* __restrict__ dst,
+                                                                int64_t ldd, I total, I nvec, int w)
+{
+    using V = VecOf<uint32_t, 4>::type;
+    const I step = (I)gridDim.x * kThreads;
+    for (I i = (I)blockIdx.x * kThreads + threadIdx.x; i < total; i += step) {
+        const I r = i / nvec;
+        const int c = min((int)(i - r * nvec) * 4, w - 4);
+        *reinterpret_cast<V*>(dst + (int64_t)r * ldd + c) = *reinterpret_cast<const V*>(src + (int64_t)r * lds + c);
+    }
+}
+
 // ---- dispatch ---------------------------------------------------------------
 
 }  // namespace
@@ -835,6 +868,8 @@ int vector_width(gp_dtype dtype, int32_t d, int64_t ld_a, int64_t ld_b, const vo
 }
 
 namespace {
+
+constexpr int64_t kManyRecords = 1 << 17;
 
 template <typename T, int VEC, int G, int VPL>
 gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
@@ -875,25 +910,28 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     // (a last round that is nearly empty costs more than it gains: 1.25 rounds are 5 - 14 % slower than one), up to six,
     // and two records per group left for the pipeline.  One / two / three / six rounds, us: three hops of 169,343 rows x 128
     // fp32 columns 474 / 462 / 471 / 461, x 256 1135 / 1051 / 1040 / 1032; 507,001 x 128 bf16 1045 / 1029 / 1026 / 1029;
-    // ten filter hops of 169,343 x 64 892 / 899 / 867 / 860; 2,450,000 x 100 22600 / 22570 / 22850 / 22350.  Lists of
-    // less than eight records per group lose: 37,123 rows x 128 (five records) 148 / 151 / 151 / 161.
+    // ten filter hops of 169,343 x 64 892 / 899 / 867 / 860; 2,450,000 x 100 22600 / 22570 / 22850 / 22350.  Short lists lose
+    // by it, a group's first record waiting for memory three times over: four hops of 37,123 rows x 152 (42 thousand
+    // records, ten per group) 235 / 236 / 241 / 247; 74,000 x 152 520 / 520 / 523 / 528; 150,000 x 152 1251 / 1246 / 1231 / 1223.
     const int64_t per_group = chunks * 8 / resident;
-    if (a.persistent_blocks <= 0 && !a.xcd_off && per_group >= 8) persist *= std::min<int64_t>(6, per_group / 2);
+    if (a.persistent_blocks <= 0 && !a.xcd_off && per_group >= 8 && a.num_segs >= kManyRecords) persist *= std::min<int64_t>(6, per_group / 2);
     persist = (persist + 7) / 8 * 8;
     const int64_t blocks = std::min<int64_t>(persist, 8 * chunks);
     const dim3 grid((unsigned)blocks), block(kThreads);
+    const bool by_element = a.xout_apart && sizeof(T) == 2 && ((a.ldout & 1) || ((uintptr_t)a.xout & 2));
+    const int flags = (a.comb_starts ? kCombStarts : 0) | (by_element ? kOutByElement : 0);
     if (a.edge_w && a.edge_w_per_edge)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 2>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
     else if (a.edge_w)
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 1>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
     else
         hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 0>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
                            a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, a.comb_starts ? 1 : 0, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2);
+                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -907,7 +945,7 @@ gp_status launch_fixup_t(const FixupArgs& a, hipStream_t stream)
     if (blocks > INT32_MAX) return fail(GP_ERR_UNSUPPORTED, "%lld workgroups exceed the grid limit", (long long)blocks);
     hipLaunchKernelGGL((gp_fixup_rows<T, VEC, G, VPL>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.split,
                        a.num_split, a.carry, a.carry_ld, a.row_scale, (T*)a.xout, a.ldout, a.d, a.comb, a.ldc, a.gamma,
-                       (const T*)a.x0, a.ldx0, a.gamma0);
+                       (const T*)a.x0, a.ldx0, a.gamma0, (T*)a.xnext, a.ldnext);
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -951,7 +989,8 @@ int max_columns_per_pass(int vec) { return 64 * max_vpl(vec) * vec; }
 int hop_vector_width(const HopArgs& a)
 {
     // carry rows are fp32 and 16-byte aligned by construction (carry_ld % 4 == 0)
-    int vec = vector_width(a.dtype, a.d, a.ldin, a.xout ? a.ldout : a.ldin, a.xin, a.xout ? a.xout : a.xin);
+    const bool out = a.xout && !a.xout_apart;
+    int vec = vector_width(a.dtype, a.d, a.ldin, out ? a.ldout : a.ldin, a.xin, out ? a.xout : a.xin);
     if (a.comb) vec = std::min(vec, vector_width(GP_F32, a.d, a.ldc, a.ldc, a.comb, a.comb));
     return vec;
 }
@@ -1084,6 +1123,21 @@ gp_status launch_copy_rows(const void* src, int64_t lds, void* dst, int64_t ldd,
             (uintptr_t)dst % unit == 0)
             break;
         unit /= 2;
+    }
+    // Rows of 47 fp32 columns, four bytes a lane and 16: 7.3 and 7.1 us for 37,123 of them, 12.5 and 10.4 for 169,343;
+    // 1,000,000 x 63 108 and 92.
+    if (unit < 16 && unit >= 4 && row_bytes >= 16) {
+        const int64_t nvec = (row_bytes + 15) / 16, total = n * nvec;
+        const int64_t blocks = std::min<int64_t>((total + kThreads - 1) / kThreads, max_blocks > 0 ? max_blocks : 256 * 32);
+        const int64_t s = lds * es / 4, t = ldd * es / 4;
+        if (total <= INT32_MAX)  // (an index past the last vector, one step on, is below 2^32)
+            hipLaunchKernelGGL(gp_copy_rows_dwords<uint32_t>, dim3((unsigned)blocks), dim3(kThreads), 0, stream, (const uint32_t*)src, s,
+                               (uint32_t*)dst, t, (uint32_t)total, (uint32_t)nvec, (int)(row_bytes / 4));
+        else
+            hipLaunchKernelGGL(gp_copy_rows_dwords<uint64_t>, dim3((unsigned)blocks), dim3(kThreads), 0, stream, (const uint32_t*)src, s,
+                               (uint32_t*)dst, t, (uint64_t)total, (uint64_t)nvec, (int)(row_bytes / 4));
+        GP_HIP(hipGetLastError());
+        return GP_OK;
     }
     const int64_t w = row_bytes / unit, total = n * w;
     const int64_t blocks = std::min<int64_t>((total + kThreads - 1) / kThreads, max_blocks > 0 ? max_blocks : 256 * 32);

@@ -563,12 +563,74 @@ gp_status weights_without_hops(const gp_plan* plan, hipStream_t stream)
     return ensure_weights(plan, stream, no_room);
 }
 
+// ---- rows that start on lines of their own ----
+// A gathered row costs the 128-byte lines it touches, and a row of w bytes that starts anywhere touches one more than it
+// fills, now and then: 188 bytes 2.44 on average, from multiples of 64 two.  Hops therefore read copies of X and of the
+// slabs between in rows `line_stride` apart, where that saves lines; the launch that makes a slab stores its rows twice.
+
+// lines of 128 bytes that a row of w bytes touches on average, rows `stride` bytes apart
+double lines_per_row(int64_t w, int64_t stride)
+{
+    int64_t step = kLineBytes;
+    while (stride % step) step /= 2;
+    int64_t lines = 0;
+    for (int64_t at = 0; at < kLineBytes; at += step) lines += (at + w + kLineBytes - 1) / kLineBytes;
+    return (double)lines * (double)step / (double)kLineBytes;
+}
+
+// the narrowest stride in bytes, a multiple of 64, at which rows of w bytes touch the fewest lines
+int64_t line_stride(int64_t w)
+{
+    const int64_t half = (w + 63) / 64 * 64, full = (w + kLineBytes - 1) / kLineBytes * kLineBytes;
+    return lines_per_row(w, half) <= lines_per_row(w, full) ? half : full;
+}
+
+// Whether K hops over rows of d elements gain by reading such a copy of them (leading dimension ld as they are): the lines
+// saved by a row's gathers against those of a row written and read once more, by half as much again, and so many rows
+// that a launch more does not count.  Rows of bf16 off a dword gain most, gathered two bytes a lane as they are; other
+// bf16 rows of a small matrix are not bound by lines.  With and without, us: 37,123 rows x 47 fp32 columns (7 MB), four hops
+// 99 / 104, one hop 33.6 / 33.7; x 100 bf16 (7 MB) 115 / 112, x 190 (14 MB) 170 / 168; 74,000 x 126 bf16 (18 MB) 212 / 246;
+// 169,343 x 63 fp32, three hops 280 / 349, x 47 bf16 273 / 411; 10,000 x 101 bf16 (2 MB) 43 / 48, x 47 (1 MB) 34 / 35.
+bool copy_pays(const gp_plan* plan, int32_t d, int es, int64_t ld, int32_t K)
+{
+    const int64_t w = (int64_t)d * es;
+    const bool off_dword = es == 2 && ld % 2 != 0;
+    const int64_t least = off_dword ? (int64_t)1 << 20 : es == 4 && K > 1 ? (int64_t)4 << 20 : (int64_t)16 << 20;
+    if (plan->n * w < least || plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return false;
+    const double saved = lines_per_row(w, ld * es) - lines_per_row(w, line_stride(w));
+    return off_dword || saved * (double)plan->nnz >= 3.0 * (double)w / (double)kLineBytes * (double)plan->n;
+}
+
+// Two slabs of n rows, `bytes` each, that hops hand rows on in (plan->mu held).  optional: they are done without where
+// there is little room, or no allocating now (*there says whether they are).
+gp_status ensure_slabs(const gp_plan* plan, int64_t bytes, hipStream_t stream, bool optional, bool* there)
+{
+    DevicePlan& D = plan->dev;
+    *there = bytes <= D.ping_bytes;
+    if (*there || (optional && (!may_allocate_on(stream) || !room_for_list((size_t)(2 * bytes), true)))) return GP_OK;
+    if (D.ping[0]) D.retired.push_back(D.ping[0]);
+    if (D.ping[1]) D.retired.push_back(D.ping[1]);
+    D.ping[0] = D.ping[1] = nullptr;
+    D.ping_bytes = 0;
+    for (void*& p : D.ping)
+        if (hipMalloc(&p, (size_t)bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            if (D.ping[0]) D.retired.push_back(D.ping[0]);
+            D.ping[0] = D.ping[1] = nullptr;
+            return optional ? GP_OK : fail(GP_ERR_OOM_DEVICE, "two slabs of %lld bytes", (long long)bytes);
+        }
+    D.ping_bytes = bytes;
+    *there = true;
+    return GP_OK;
+}
+
 }  // namespace
 
 gp_status hop_passes(const HopArgs& a0, hipStream_t stream)
 {
     const int es = a0.dtype == GP_F32 ? 4 : 2;
-    const int64_t tile = pass_width(a0.column_tile, a0.dtype, a0.d, a0.ldin, a0.xout ? a0.ldout : a0.ldin, a0.xin, a0.xout ? a0.xout : a0.xin);
+    const bool out = a0.xout && !a0.xout_apart;
+    const int64_t tile = pass_width(a0.column_tile, a0.dtype, a0.d, a0.ldin, out ? a0.ldout : a0.ldin, a0.xin, out ? a0.xout : a0.xin);
     for (int64_t c0 = 0; c0 < a0.d; c0 += tile) {
         HopArgs a = a0;
         a.d = (int32_t)std::min<int64_t>(tile, a0.d - c0);
@@ -577,6 +639,7 @@ gp_status hop_passes(const HopArgs& a0, hipStream_t stream)
         a.carry = a0.carry ? a0.carry + c0 : nullptr;
         a.xout = a0.xout ? (char*)a0.xout + c0 * es : nullptr;
         a.comb = a0.comb ? a0.comb + c0 : nullptr;
+        a.xnext = a0.xnext ? (char*)a0.xnext + c0 * es : nullptr;
         if (tile < a0.d && a0.xcd_off) return fail(GP_ERR_INVALID_ARG, "explicit work lists need a single column pass");
         profile_begin("gp_hop_segments", stream);
         gp_status st = launch_hop(a, stream);
@@ -595,8 +658,8 @@ gp_status fixup_passes(const FixupArgs& f0, hipStream_t stream)
     for (int64_t c0 = 0; c0 < f0.d; c0 += tile) {
         FixupArgs f = f0;
         f.d = (int32_t)std::min<int64_t>(tile, f0.d - c0);
-        f.xout = (char*)f0.xout + c0 * es;
         f.carry = f0.carry + c0;
+        f.xnext = f0.xnext ? (char*)f0.xnext + c0 * es : nullptr;
         f.xout = f0.xout ? (char*)f0.xout + c0 * es : nullptr;
         f.comb = f0.comb ? f0.comb + c0 : nullptr;
         f.x0 = f0.x0 ? (const char*)f0.x0 + c0 * es : nullptr;
@@ -702,6 +765,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
     const float* edge_w = agg == GP_AGG_SYM ? D.dinv_sqrt : nullptr;  // (attach_work_lists has one per non-zero where it can)
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
     NoRoom no_room;
+    int64_t ld_lines = 0;  // not 0: hops read copies of X and of the slabs between, rows that far apart
 
     for (int32_t k = 1; k <= K; ++k) {
         HopArgs a;
@@ -727,6 +791,27 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         bool split = false, lds = false;
         HopArgs cold = a;  // as it stands: implicit lists
         if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds, no_room)) != GP_OK) return st;
+        if (k == 1 && may_allocate && !split && !lds && !a.xcd_off && copy_pays(plan, d, es, ldo, K)) {
+            const int64_t stride = line_stride((int64_t)d * es);
+            bool there = false;
+            {
+                std::lock_guard<std::mutex> lk(plan->mu);
+                if ((st = ensure_slabs(plan, n * stride, stream, true, &there)) != GP_OK) return st;
+            }
+            if (there) {
+                ld_lines = stride / es;
+                profile_begin("gp_copy_rows", stream);
+                st = launch_copy_rows(X, ldx, D.ping[0], ld_lines, n, d, dtype, stream);
+                profile_end(stream);
+                if (st != GP_OK) return st;
+            }
+        }
+        if (ld_lines) {
+            a.xin = D.ping[(k - 1) & 1];
+            a.ldin = ld_lines;
+            a.xout_apart = true;
+            if (k < K) a.xnext = D.ping[k & 1];
+        }
         if (split) {
             // Records that gather outside their row's cluster first, whole rows wide: nothing of
             // theirs is worth keeping in a cache, and run on their own they evict nothing that is.
@@ -757,6 +842,8 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
             f.row_scale = row_scale;
             f.xout = a.xout;
             f.ldout = ldo;
+            f.xnext = a.xnext;
+            f.ldnext = ld_lines;
             f.d = d;
             f.dtype = dtype;
             f.column_tile = plan->opt.column_tile;
@@ -778,20 +865,17 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
     DevicePlan& D = plan->dev;
     const int64_t n = plan->n;
     const int es = dtype == GP_F32 ? 4 : 2;
-    const int64_t ldp = ((int64_t)d + 16 / es - 1) / (16 / es) * (16 / es);  // slab rows start on 16 bytes
+    int64_t ldp = ((int64_t)d + 16 / es - 1) / (16 / es) * (16 / es);  // slab rows start on 16 bytes, or so that they touch fewest lines
     const int64_t ldc_scratch = ((int64_t)d + 3) / 4 * 4;
     {
         std::lock_guard<std::mutex> lk(plan->mu);
-        const int64_t need = n * ldp * es;
-        if (K >= 2 && need > D.ping_bytes) {
-            if (D.ping[0]) D.retired.push_back(D.ping[0]);
-            if (D.ping[1]) D.retired.push_back(D.ping[1]);
-            D.ping[0] = D.ping[1] = nullptr;
-            D.ping_bytes = 0;
-            GP_HIP(hipMalloc(&D.ping[0], (size_t)need));
-            GP_HIP(hipMalloc(&D.ping[1], (size_t)need));
-            D.ping_bytes = need;
+        bool there = false;
+        const int64_t w = (int64_t)d * es, stride = line_stride(w);
+        if (K >= 2 && lines_per_row(w, stride) < lines_per_row(w, ldp * es)) {
+            if ((st = ensure_slabs(plan, n * stride, stream, true, &there)) != GP_OK) return st;
+            if (there) ldp = stride / es;
         }
+        if (K >= 2 && !there && (st = ensure_slabs(plan, n * ldp * es, stream, false, &there)) != GP_OK) return st;
         if (dtype == GP_BF16 && n * ldc_scratch > D.comb_elems) {
             if (D.comb) D.retired.push_back(D.comb);
             D.comb = nullptr;
@@ -843,6 +927,14 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         a.gamma0 = coeff[0];
         bool lds = false;
         if ((st = attach_work_lists(plan, a, stream, true, nullptr, &lds, no_room)) != GP_OK) return st;
+        if (k == 1 && K >= 2 && !lds && !a.xcd_off && copy_pays(plan, d, es, ldx, K)) {  // X too is read with rows on lines of their own
+            profile_begin("gp_copy_rows", stream);
+            st = launch_copy_rows(X, ldx, D.ping[0], ldp, n, d, dtype, stream);
+            profile_end(stream);
+            if (st != GP_OK) return st;
+            a.xin = D.ping[0];
+            a.ldin = ldp;
+        }
         if (lds) {
             if ((st = lds_hop(plan, a, agg, stream)) != GP_OK) return st;
         } else if ((st = hop_passes(a, stream)) != GP_OK) {
