@@ -169,7 +169,9 @@ struct DevicePlan {
     int32_t* col = nullptr;
     float* dinv_sqrt = nullptr;
     float* dinv = nullptr;
-    Segment* segs = nullptr;
+    Segment* segs = nullptr;  // the plan's segments, or (rows_whole) those with rows that only block boundaries cut put together
+    int64_t num_segs = 0;
+    bool rows_whole = false;
     SplitRow* split = nullptr;
     float* edge_ws = nullptr;   // nnz: dinv_sqrt[col[e]], for launches of the sym operator that read `col`
     bool weighted_calls = false;  // a call of the sym operator that could allocate has been made: every list that a launch may take has its weights
