@@ -137,7 +137,9 @@ int64_t gp_plan_segment_edges(const gp_plan *plan);           /* the segment len
  * *slice_elems elements (the last one narrower), and for each of the GPU's 8 XCDs the
  * records [xcd_off[x], xcd_off[x+1]) -- the plan's segments, each with the column slice
  * it is for, listed cluster by cluster.  Every (segment, slice) pair appears exactly
- * once over the 8 lists.  *num_slices = 0 means this plan keeps the implicit lists
+ * once over the 8 lists.  (Hops on a plan whose rows are cut by block boundaries only
+ * walk such lists of its rows instead: they put the pieces of a row together first.)
+ * *num_slices = 0 means this plan keeps the implicit lists
  * (XCD x takes slice x mod S of every segment): its rows do not gather mostly from
  * their own cluster, or no slice of at least 128 bytes makes a cluster's rows fit the
  * share of a 4 MB L2 the schedule counts on.  xcd_off: HOST, 9 entries.  records:

@@ -64,18 +64,14 @@ void release(DevicePlan& D)
     D = DevicePlan();
 }
 
-// The plan's segments on the device.  Where only block boundaries cut rows -- no row is longer than a segment may be --
-// the rows are whole again there: hops that walk this list then have no partial rows, and no launch that joins them
-// (10,000 rows of 20 sources in four blocks, two hops of 128 columns: 30.4 -> 26.5 us).
-gp_status upload_segments(const gp_plan* plan, hipStream_t stream)
+// The plan's segments with rows put together that only block boundaries cut; false where there are none to put together,
+// or where some row is longer than a segment may be (its partial rows are joined by a launch in any case).
+bool join_rows(const gp_plan* plan, HostArray<Segment>& rows)
 {
-    DevicePlan& D = plan->dev;
     const bool whole = !plan->split.empty() && std::all_of(plan->split.begin(), plan->split.end(), [&](const SplitRow& s) {
         return plan->rowptr[(size_t)s.row + 1] - plan->rowptr[(size_t)s.row] <= plan->segment_edges;
     });
-    D.num_segs = (int64_t)plan->segs.size();
-    if (!whole) return upload(D.segs, plan->segs, stream);
-    HostArray<Segment> rows;
+    if (!whole) return false;
     rows.reserve(plan->segs.size());
     for (Segment s : plan->segs) {
         const int64_t start = ((int64_t)s.start_hi << 32) | s.start_lo;
@@ -86,9 +82,20 @@ gp_status upload_segments(const gp_plan* plan, hipStream_t stream)
         }
         rows.push_back(s);
     }
-    gp_status st = upload_now(D.segs, rows, stream);
-    D.num_segs = (int64_t)rows.size();
-    D.rows_whole = st == GP_OK;
+    return true;
+}
+
+// The plan's segments on the device, rows joined where that leaves no partial row.  Hops over whole records, on implicit and
+// explicit lists alike (their sums are the same bits), then need no launch that joins partial rows (10,000 rows of 20
+// sources in four blocks, two hops of 128 columns: 30.4 -> 26.5 us).
+gp_status upload_segments(const gp_plan* plan, hipStream_t stream)
+{
+    DevicePlan& D = plan->dev;
+    HostArray<Segment> rows;
+    const bool joined = join_rows(plan, rows);
+    D.num_segs = (int64_t)(joined ? rows : plan->segs).size();
+    gp_status st = joined ? upload_now(D.segs, rows, stream) : upload(D.segs, plan->segs, stream);
+    D.rows_whole = joined && st == GP_OK;
     return st;
 }
 
@@ -537,9 +544,11 @@ gp_status choose_lists(const gp_plan* plan, HopArgs& a, hipStream_t stream, bool
         w.num_slices = S;
         w.slice_elems = elems;
         w.split = want_split;
-        build_xcd_lists(*plan, want_split ? D.split_hot_host : plan->segs, plan->clusters, S, elems, a.d, recs, w.off);
+        HostArray<Segment> rows;  // whole records: those of the implicit lists
+        if (!want_split && D.rows_whole) join_rows(plan, rows);
+        build_xcd_lists(*plan, want_split ? D.split_hot_host : rows.empty() ? plan->segs : rows, plan->clusters, S, elems, a.d, recs, w.off);
         // a request to the cursor should be worth about 64 non-zeros of gathering
-        const int64_t mean_len = std::max<int64_t>(1, plan->nnz / std::max<int64_t>(1, (int64_t)plan->segs.size()));
+        const int64_t mean_len = std::max<int64_t>(1, plan->nnz / std::max<int64_t>(1, D.num_segs));
         w.chunk_records = (int)std::min<int64_t>(32, std::max<int64_t>(1, 64 / mean_len));
         GP_HIP(hipMalloc((void**)&w.recs, recs.size() * sizeof(Segment)));
         hipError_t e = hipMemcpyAsync(w.recs, recs.data(), recs.size() * sizeof(Segment), hipMemcpyHostToDevice, stream);
@@ -652,11 +661,8 @@ gp_status ensure_slabs(const gp_plan* plan, int64_t bytes, hipStream_t stream, b
     return GP_OK;
 }
 
-// Whether a hop leaves partial rows of the plan's own cut: not on implicit lists of whole rows.
-bool leaves_partial_rows(const gp_plan* plan, const HopArgs& a, bool lds)
-{
-    return !plan->split.empty() && (lds || a.xcd_off || !plan->dev.rows_whole);
-}
+// Whether a hop over whole records, or one of the LDS pass, leaves partial rows of the plan's own cut.
+bool leaves_partial_rows(const gp_plan* plan, bool lds) { return !plan->split.empty() && (lds || !plan->dev.rows_whole); }
 
 }  // namespace
 
@@ -868,7 +874,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         } else if ((st = hop_passes(a, stream)) != GP_OK) {
             return st;
         }
-        if (split ? D.split_num_rows > 0 : leaves_partial_rows(plan, a, lds)) {
+        if (split ? D.split_num_rows > 0 : leaves_partial_rows(plan, lds)) {
             FixupArgs f;
             f.split = split ? D.split_rows : D.split;
             f.num_split = split ? D.split_num_rows : (int64_t)plan->split.size();
@@ -975,7 +981,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         } else if ((st = hop_passes(a, stream)) != GP_OK) {
             return st;
         }
-        if (leaves_partial_rows(plan, a, lds)) {
+        if (leaves_partial_rows(plan, lds)) {
             FixupArgs f;
             f.split = D.split;
             f.num_split = (int64_t)plan->split.size();

@@ -68,3 +68,35 @@ def test_schedules_with_lists_of_their_own_keep_the_plans_cut(option):
     one, cut = (stack(src, dst, n, b, X, gp.GP_AGG_SYM, option) for b in (1 << 30, 977))
     assert cut[4] > 0
     assert all(torch.allclose(a, b, rtol=0, atol=41 * 2.0 ** -23 * float(a.abs().max())) for a, b in zip(one[:3], cut[:3]))  # 41 terms, regrouped
+
+
+@pytest.mark.parametrize("agg", [gp.GP_AGG_SYM, gp.GP_AGG_SUM])
+def test_explicit_and_implicit_lists_of_whole_rows_give_the_same_bits(agg):
+    rng = np.random.default_rng(8)
+    n = 4000
+    dst = (np.arange(n * 40) // 40).astype(np.int32)
+    src = (dst // 400 * 400 + rng.integers(0, 400, dst.size)).astype(np.int32)
+    stream = torch.cuda.current_stream().cuda_stream
+    gp.gp_set_option("split_records", 2)
+    try:
+        stacks = {}
+        for schedule in (1, 2):  # explicit, implicit
+            gp.gp_set_option("cache_schedule", schedule)
+            with gp.gp_plan_blocks(src, dst, n, 977, gp.GP_ADD_SELF_LOOPS) as plan:
+                assert plan.num_partial_rows > 0 and (plan.work_lists(64, gp.GP_F32, 4)[0] > 0) == (schedule == 1)
+                for d in (64, 96):
+                    X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).cuda()
+                    out, first = torch.empty(3, n, d, device="cuda"), torch.empty(3, n, d, device="cuda")
+                    if d != 64:  # before a call has made explicit lists for this width: implicit ones
+                        gp.gp_propagate_noalloc(plan, X.data_ptr(), d, d, gp.GP_F32, agg, 2, first.data_ptr(), d, stream)
+                    gp.gp_profile_enable(True)
+                    gp.gp_propagate(plan, X.data_ptr(), d, d, gp.GP_F32, agg, 2, out.data_ptr(), d, stream)
+                    joins, _ = gp.gp_profile_read("gp_fixup_rows")
+                    gp.gp_profile_enable(False)
+                    assert joins == 0
+                    assert d == 64 or torch.equal(first, out)
+                    stacks[schedule, d] = out.cpu()
+        assert torch.equal(stacks[1, 64], stacks[2, 64]) and torch.equal(stacks[1, 96], stacks[2, 96])
+    finally:
+        gp.gp_set_option("split_records", 0)
+        gp.gp_set_option("cache_schedule", 0)
