@@ -5,9 +5,12 @@
 //
 // What bounds it: the label of every source, a random 4-byte read per non-zero and round, and what a row's counting takes
 // beside them.  490,000 rows and 12.5 million non-zeros of a power law: 1.3 ms in all kernels, 5 rounds (16 host threads:
-// 24 ms); 233,000 rows and 114 million non-zeros in 50 communities: 7.9 ms (100 ms).
+// 24 ms); 233,000 rows and 114 million non-zeros in 50 communities: 4.8 ms (100 ms).  A row is taken by one workgroup at
+// most, in time proportional to its sources: 1,200,000 rows, one of them of a million sources, 33 ms, 23 of them that row's
+// (874 with a table in LDS that goes over such a row 123 times a round).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "gp_block_scan.h"
@@ -22,13 +25,14 @@ constexpr int kTileRows = 16;          // consecutive rows a wavefront takes at 
 constexpr int kShortRow = 64;          // rows of up to as many sources: one per lane
 constexpr int kMidRow = 512;           // rows of up to as many: a workgroup of one wavefront and a table of twice as many places
 constexpr int kMidTable = 1024;
-constexpr int kBigTable = 16384;       // longer rows: a workgroup of 1024 and this table, in passes of at most half as many sources
+constexpr int kBigRow = 12288;         // rows of up to as many: a workgroup of 1024 and a table that they fill to three quarters at
+constexpr int kBigTable = 16384;       // most; longer rows ("huge"): a workgroup of 1024 and a counter in memory per label
 constexpr int kMaxRounds = kClusterRounds;
 
 // Words the rounds share.  changed[r]: rows that round r gave another label.
 struct Tally {
     uint32_t changed[kMaxRounds];
-    uint32_t mid_rows, big_rows;
+    uint32_t mid_rows, big_rows, huge_rows;
     unsigned long long inside;      // non-zeros whose source has the row's label
     unsigned long long weight_size; // sum over the rows of (their non-zeros x rows of their cluster)
 };
@@ -71,12 +75,12 @@ __global__ __launch_bounds__(kThreads) void gp_first_labels(int32_t* __restrict_
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) lab[i] = (int32_t)i;
 }
 
-// The rows of more than kShortRow sources, listed once: a workgroup takes kListRows rows and asks for its places on the two
-// lists with one atomic each (one per row queues at the counters: 490,000 rows, 407 us; 233,000 rows, all long, 2.7 ms).
+// The rows of more than kShortRow sources, listed once: a workgroup takes kListRows rows and asks for its places on the lists
+// of mid and big rows with one atomic each (one per row queues at the counters: 490,000 rows, 407 us; 233,000 rows, all long, 2.7 ms).
 constexpr int kListItems = 8;
 constexpr int64_t kListRows = (int64_t)kThreads * kListItems;
 __global__ __launch_bounds__(kThreads) void gp_list_long_rows(const int64_t* __restrict__ rowptr, int64_t n, Tally* __restrict__ tally,
-                                                              int32_t* __restrict__ mid, int32_t* __restrict__ big)
+                                                              int32_t* __restrict__ mid, int32_t* __restrict__ big, int32_t* __restrict__ huge)
 {
     __shared__ uint32_t ws[kScanWaves + 1];
     __shared__ uint32_t first[2];
@@ -85,7 +89,9 @@ __global__ __launch_bounds__(kThreads) void gp_list_long_rows(const int64_t* __r
     for (int j = 0; j < kListItems; ++j) {
         if (r0 + j >= n) break;
         const int64_t len = rowptr[r0 + j + 1] - rowptr[r0 + j];
-        if (len > kMidRow)
+        if (len > kBigRow)
+            huge[atomicAdd(&tally->huge_rows, 1u)] = (int32_t)(r0 + j);  // (few: one in kBigRow non-zeros at most)
+        else if (len > kMidRow)
             is_big |= 1u << j;
         else if (len > kShortRow)
             is_mid |= 1u << j;
@@ -178,10 +184,40 @@ __global__ __launch_bounds__(kThreads) void gp_label_short_rows(const int64_t* _
     }
 }
 
-// Longer rows, a workgroup per row: labels counted in a table in LDS (open addressing).  A row of more sources than half
-// the table holds is counted in several passes, each taking the labels of one residue of their hash: a label's count is
-// whole in its pass.  More distinct labels in a pass than there are places cannot be told beforehand, so a label that
-// finds no place within the table is counted by reading the row again.
+// The lanes whose label is the first lane's count it once together: most rows have one label for most sources.  True for
+// lanes that then have `votes` to add to the count of l (l < 0: no label).
+__device__ inline bool counts_label(int32_t l, int lane, uint32_t& votes)
+{
+    votes = 1;
+    const unsigned long long on = __ballot(l >= 0);
+    if (!on) return false;
+    const int first = __builtin_ctzll(on);
+    const int32_t one = __builtin_amdgcn_readlane(l, first);
+    const int together = __popcll(__ballot(l == one));
+    if (lane == first) votes = (uint32_t)together;
+    return l >= 0 && (l != one || lane == first);
+}
+
+// The workgroup's best candidate; thread 0 gives it to the row.  wave_best: a word per wavefront, in LDS
+template <int NT>
+__device__ inline void label_row(unsigned long long best, unsigned long long* wave_best, int32_t row, const int32_t* lab, int32_t* nxt,
+                                 uint32_t& changed)
+{
+#pragma unroll
+    for (int o = 32; o; o >>= 1) best = max(best, (unsigned long long)__shfl_xor(best, o, 64));
+    if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) best = max(best, wave_best[w]);
+        const int32_t label = (int32_t)~(uint32_t)best, before = lab[row];
+        nxt[row] = label;
+        changed += label != before;
+    }
+}
+
+// Longer rows, a workgroup per row: labels counted in a table in LDS (open addressing), which has more places than the row
+// sources.
 template <int NT, int TABLE>
 __global__ __launch_bounds__(NT) void gp_label_long_rows(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col, int64_t n,
                                                          const int32_t* __restrict__ even, const int32_t* __restrict__ odd, int round,
@@ -199,69 +235,93 @@ __global__ __launch_bounds__(NT) void gp_label_long_rows(const int64_t* __restri
     uint32_t changed = 0;
     for (uint32_t k = blockIdx.x; k < rows; k += gridDim.x) {
         const int32_t row = list[k];
-        const int64_t s = rowptr[row], len = rowptr[row + 1] - s;
+        const int64_t s = rowptr[row];
+        const int len = (int)(rowptr[row + 1] - s);
         uint32_t table = TABLE;  // no more of it than the row needs is cleared and looked through
-        while (table / 4 >= (uint64_t)len && table > 256) table /= 2;
-        const uint32_t passes = (uint32_t)((len + TABLE / 2 - 1) / (TABLE / 2));
+        while (table / 4 >= (uint32_t)len && table > 256) table /= 2;
         unsigned long long best = 0;
-        for (uint32_t pass = 0; pass < passes; ++pass) {
-            __syncthreads();
-            for (uint32_t j = threadIdx.x; j < table; j += NT) {
-                key[j] = 0xFFFFFFFFu;
-                cnt[j] = 0;
-            }
-            __syncthreads();
-            for (int64_t j0 = 0; j0 < len; j0 += NT) {
-                const int64_t j = j0 + threadIdx.x;
-                int32_t l = -1;
-                if (j < len) l = lab[col[s + j]];
-                const uint32_t h = mix((uint32_t)l);
-                bool mine = l >= 0 && h % passes == pass;
-                uint32_t votes = 1;
-                // lanes with the first lane's label count once together: most rows have one label for most sources
-                const unsigned long long on = __ballot(mine);
-                if (on) {
-                    const int first = __builtin_ctzll(on);
-                    const int32_t one = __builtin_amdgcn_readlane(l, first);
-                    const bool same = mine && l == one;
-                    const int together = __popcll(__ballot(same));
-                    if (same && lane != first) mine = false;
-                    if (lane == first) votes = (uint32_t)together;
-                }
-                if (mine) {
-                    uint32_t at = (h / passes) & (table - 1);
-                    uint32_t tries = 0;
-                    for (; tries < table; ++tries) {
-                        const uint32_t was = atomicCAS(&key[at], 0xFFFFFFFFu, (uint32_t)l);
-                        if (was == 0xFFFFFFFFu || was == (uint32_t)l) {
-                            atomicAdd(&cnt[at], votes);
-                            break;
-                        }
-                        at = (at + 1) & (table - 1);
-                    }
-                    if (tries == table) {  // the table is full of other labels
-                        uint32_t all = 0;
-                        for (int64_t q = 0; q < len; ++q) all += lab[col[s + q]] == l;
-                        best = max(best, candidate(all, l));
-                    }
-                }
-            }
-            __syncthreads();
-            for (uint32_t j = threadIdx.x; j < table; j += NT)
-                if (cnt[j]) best = max(best, candidate(cnt[j], (int32_t)key[j]));
+        __syncthreads();  // (the row before is done with table and wave_best)
+        for (uint32_t j = threadIdx.x; j < table; j += NT) {
+            key[j] = 0xFFFFFFFFu;
+            cnt[j] = 0;
         }
-#pragma unroll
-        for (int o = 32; o; o >>= 1) best = max(best, (unsigned long long)__shfl_xor(best, o, 64));
-        if (lane == 0) wave_best[threadIdx.x >> 6] = best;
         __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int w = 1; w < NT / 64; ++w) best = max(best, wave_best[w]);
-            const int32_t label = (int32_t)~(uint32_t)best, before = lab[row];
-            nxt[row] = label;
-            changed += label != before;
+        for (int j0 = 0; j0 < len; j0 += NT) {
+            const int j = j0 + (int)threadIdx.x;
+            const int32_t l = j < len ? lab[col[s + j]] : -1;
+            uint32_t votes;
+            if (counts_label(l, lane, votes)) {
+                uint32_t at = mix((uint32_t)l) & (table - 1);
+                for (;;) {
+                    const uint32_t was = atomicCAS(&key[at], 0xFFFFFFFFu, (uint32_t)l);
+                    if (was == 0xFFFFFFFFu || was == (uint32_t)l) break;
+                    at = (at + 1) & (table - 1);
+                }
+                atomicAdd(&cnt[at], votes);
+            }
         }
-        __syncthreads();  // (wave_best is written again for the next row)
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < table; j += NT)
+            if (cnt[j]) best = max(best, candidate(cnt[j], (int32_t)key[j]));
+        label_row<NT>(best, wave_best, row, lab, nxt, changed);
+    }
+    if (threadIdx.x == 0 && changed) atomicAdd(&tally->changed[round], changed);
+}
+
+// Rows longer than that table serves, a workgroup per row and a counter in memory for every label there may be: n words per
+// workgroup, zero before and after.  The last to add to a label's counter sees its whole count, so the counters are not
+// looked through; they are put back by going over the row once more.  What bounds it: two random reads and an atomic per
+// source, four of each in flight per lane.
+constexpr int kHugeThreads = 1024;
+__global__ __launch_bounds__(kHugeThreads) void gp_label_huge_rows(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col, int64_t n,
+                                                                   const int32_t* __restrict__ even, const int32_t* __restrict__ odd, int round,
+                                                                   Tally* __restrict__ tally, const int32_t* __restrict__ list,
+                                                                   uint32_t* counters)
+{
+    constexpr int U = 4;
+    __shared__ unsigned long long wave_best[kHugeThreads / 64];
+    if (over_before(tally, round, n)) return;
+    const int32_t* lab = round & 1 ? odd : even;
+    int32_t* nxt = const_cast<int32_t*>(round & 1 ? even : odd);
+    uint32_t* cnt = counters + (int64_t)blockIdx.x * n;
+    const uint32_t rows = tally->huge_rows;
+    const int lane = threadIdx.x & 63;
+    uint32_t changed = 0;
+    for (uint32_t k = blockIdx.x; k < rows; k += gridDim.x) {
+        const int32_t row = list[k];
+        const int64_t s = rowptr[row], len = rowptr[row + 1] - s;
+        auto labels_from = [&](int64_t j0, int32_t (&l)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t j = j0 + u * kHugeThreads + threadIdx.x;
+                l[u] = j < len ? col[s + j] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (l[u] >= 0) l[u] = lab[l[u]];
+        };
+        unsigned long long best = 0;
+        for (int64_t j0 = 0; j0 < len; j0 += U * kHugeThreads) {
+            int32_t l[U];
+            labels_from(j0, l);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                uint32_t votes;
+                if (counts_label(l[u], lane, votes)) best = max(best, candidate(atomicAdd(&cnt[l[u]], votes) + votes, l[u]));
+            }
+        }
+        label_row<kHugeThreads>(best, wave_best, row, lab, nxt, changed);
+        __threadfence();  // (counts first, then zeros, then the next row's counts)
+        __syncthreads();
+        for (int64_t j0 = 0; j0 < len; j0 += U * kHugeThreads) {
+            int32_t l[U];
+            labels_from(j0, l);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (l[u] >= 0) cnt[l[u]] = 0;
+        }
+        __threadfence();
+        __syncthreads();
     }
     if (threadIdx.x == 0 && changed) atomicAdd(&tally->changed[round], changed);
 }
@@ -366,9 +426,9 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
     const int64_t n = P.n;
     if (P.nnz == 0 || !P.dev.col || P.rowptr.size() != (size_t)n + 1) return false;
     // one allocation: row pointers, two label lists, ranks (and the scan's words), sizes, the lists of longer rows, the tally
-    const size_t words = (size_t)n;
+    const size_t words = (size_t)n, most_huge = (size_t)(P.nnz / kBigRow);
     const size_t rank_words = words + 1, scan_words = device_scan_scratch_words(n + 1);
-    const size_t bytes = sizeof(Tally) + (words + 1) * sizeof(int64_t) + 4 * (2 * words + rank_words + scan_words + words + 2 * words);
+    const size_t bytes = sizeof(Tally) + (words + 1) * sizeof(int64_t) + 4 * (2 * words + rank_words + scan_words + words + 2 * words + most_huge);
     char* base = nullptr;
     if (hipMalloc((void**)&base, bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -377,7 +437,7 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
     struct Guard {
         void* p;
         ~Guard() { (void)hipFree(p); }
-    } guard{base};
+    } guard{base}, guard_counters{nullptr};
     int64_t* rowptr = (int64_t*)base;
     Tally* tally = (Tally*)(rowptr + words + 1);
     uint32_t* rank = (uint32_t*)(tally + 1);  // (tally, ranks and sizes lie together: cleared in one launch)
@@ -387,6 +447,7 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
     int32_t* odd = even + words;
     int32_t* mid = odd + words;
     int32_t* big = mid + words;
+    int32_t* huge = big + words;
 
     static const bool big_table = hipFuncSetAttribute((const void*)gp_label_long_rows<1024, kBigTable>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                       2 * kBigTable * 4) == hipSuccess;
@@ -400,7 +461,19 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
     const int64_t clear = (int64_t)(sizeof(Tally) / 4 + rank_words + words);
     hipLaunchKernelGGL(gp_clear_words, grid(clear), dim3(kThreads), 0, stream, (uint32_t*)tally, clear);
     hipLaunchKernelGGL(gp_first_labels, grid(n), dim3(kThreads), 0, stream, even, n);
-    hipLaunchKernelGGL(gp_list_long_rows, dim3((unsigned)((n + kListRows - 1) / kListRows)), dim3(kThreads), 0, stream, rowptr, n, tally, mid, big);
+    hipLaunchKernelGGL(gp_list_long_rows, dim3((unsigned)((n + kListRows - 1) / kListRows)), dim3(kThreads), 0, stream, rowptr, n, tally, mid, big, huge);
+    // Huge rows, if there are any: counters for as many of them as go side by side, in up to 512 MiB or for one.
+    uint32_t huge_rows = 0;
+    ok = ok && hipMemcpyAsync(&huge_rows, &tally->huge_rows, sizeof(huge_rows), hipMemcpyDeviceToHost, stream) == hipSuccess;
+    ok = (hipStreamSynchronize(stream) == hipSuccess) && ok;
+    const int64_t side_by_side = std::min<int64_t>({(int64_t)huge_rows, 256, std::max<int64_t>(1, ((int64_t)512 << 20) / 4 / n)});
+    uint32_t* counters = nullptr;
+    if (!ok || (side_by_side > 0 && hipMalloc((void**)&counters, (size_t)(side_by_side * n) * 4) != hipSuccess)) {
+        (void)hipGetLastError();
+        return false;
+    }
+    guard_counters.p = counters;
+    if (counters) hipLaunchKernelGGL(gp_clear_words, grid(side_by_side * n), dim3(kThreads), 0, stream, counters, side_by_side * n);
     for (int round = 0; round < kMaxRounds; ++round) {
         hipLaunchKernelGGL(gp_label_short_rows, tiles, dim3(kThreads), 0, stream, rowptr, P.dev.col, n, even, odd, round, tally);
         if (round == 0) continue;  // (that round takes rows of any length)
@@ -408,6 +481,9 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
                            odd, round, tally, mid);
         hipLaunchKernelGGL((gp_label_long_rows<1024, kBigTable>), dim3(256), dim3(1024), 2 * kBigTable * 4, stream, rowptr, P.dev.col, n, even,
                            odd, round, tally, big);
+        if (counters)
+            hipLaunchKernelGGL(gp_label_huge_rows, dim3((unsigned)side_by_side), dim3(kHugeThreads), 0, stream, rowptr, P.dev.col, n, even, odd,
+                               round, tally, huge, counters);
     }
     hipLaunchKernelGGL(gp_mark_labels, grid(n), dim3(kThreads), 0, stream, even, odd, n, tally, rank);
     ok = ok && device_exclusive_scan(rank, n + 1, scan, stream) == GP_OK;  // the last word: the number of clusters
