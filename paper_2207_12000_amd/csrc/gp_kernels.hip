@@ -613,10 +613,12 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
             } else {
                 T* op = xout + (int64_t)r.row * ldout + coff[v];
                 if (sizeof(T) == 2 && VEC > 1 && (flags & kOutByElement)) {
+                    // (not streamed: elements of a line then go to memory one by one; two hops of 1,500,000 rows x 97 bf16
+                    // columns, 25 million non-zeros, 3415 us streamed, 2300 so)
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
                         const float one[1] = {o[i]};
-                        Row<T, 1>::store_stream(op + i, one);
+                        Row<T, 1>::store(op + i, one);
                     }
                 } else if (xout) {
                     Row<T, VEC>::store_stream(op, o);

@@ -615,27 +615,54 @@ double lines_per_row(int64_t w, int64_t stride)
     return (double)lines * (double)step / (double)kLineBytes;
 }
 
-// the narrowest stride in bytes, a multiple of 64, at which rows of w bytes touch the fewest lines
+// The narrowest stride in bytes at which rows of w bytes touch the fewest lines: a multiple of 64, or for rows that fit into
+// less the power of two from 16 on that holds them (two hops of 500,000 x 7 fp32 columns: where they lie 231 us, 32 bytes
+// apart 220, 64 bytes apart 248).
 int64_t line_stride(int64_t w)
 {
+    int64_t p = 16;
+    while (p < w) p *= 2;
+    if (p < 64) return p;
     const int64_t half = (w + 63) / 64 * 64, full = (w + kLineBytes - 1) / kLineBytes * kLineBytes;
     return lines_per_row(w, half) <= lines_per_row(w, full) ? half : full;
 }
 
-// Whether K hops over rows of d elements gain by reading such a copy of them (leading dimension ld as they are): the lines
-// saved by a row's gathers against those of a row written and read once more, by half as much again, and so many rows
-// that a launch more does not count.  Rows of bf16 off a dword gain most, gathered two bytes a lane as they are; other
-// bf16 rows of a small matrix are not bound by lines.  With and without, us: 37,123 rows x 47 fp32 columns (7 MB), four hops
-// 99 / 104, one hop 33.6 / 33.7; x 100 bf16 (7 MB) 115 / 112, x 190 (14 MB) 170 / 168; 74,000 x 126 bf16 (18 MB) 212 / 246;
-// 169,343 x 63 fp32, three hops 280 / 349, x 47 bf16 273 / 411; 10,000 x 101 bf16 (2 MB) 43 / 48, x 47 (1 MB) 34 / 35.
-bool copy_pays(const gp_plan* plan, int32_t d, int es, int64_t ld, int32_t K)
+// Lines that a gather of rows of w bytes saves by finding them `to` bytes apart instead of `from`, less what it loses by the
+// caches holding fewer rows of a larger slab.
+double lines_saved(int64_t w, int64_t from, int64_t to)
 {
-    const int64_t w = (int64_t)d * es;
-    const bool off_dword = es == 2 && ld % 2 != 0;
-    const int64_t least = off_dword ? (int64_t)1 << 20 : es == 4 && K > 1 ? (int64_t)4 << 20 : (int64_t)16 << 20;
-    if (plan->n * w < least || plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return false;
-    const double saved = lines_per_row(w, ld * es) - lines_per_row(w, line_stride(w));
-    return off_dword || saved * (double)plan->nnz >= 3.0 * (double)w / (double)kLineBytes * (double)plan->n;
+    const double before = lines_per_row(w, from);
+    return before - lines_per_row(w, to) - 0.17 * std::max(0.0, (double)to / (double)from - 1.0) * before;
+}
+
+// Whether K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading dimension ld as they
+// are).  The line reads that the gathers save have to make up for a launch, and for a row's lines copied once and written
+// once more per hop, some two of them each; the factors are those of a fit to 153 pairs of measurements (fp32, 3 to 119
+// columns, 37,000 to 1,500,000 rows of mean degree 5 to 41, one to three hops), all but three of which it calls right within
+// 1 %.  Slabs below 4 MiB stay in an L2 as they are.  With and without, us: two hops of mean degree 17, 1,500,000 rows x 28
+// 1071 / 1464, x 47 2011 / 2156, x 9 912 / 940, x 5 814 / 764, x 3 734 / 692; 60,000 x 50 74.7 / 72.7; one hop of mean
+// degree 5, 500,000 x 47 178 / 141; four hops of 37,123 x 47 98 / 104.  Small matrices of bf16 are not bound by lines
+// (four hops of 37,123 x 190, 14 MB, 170 / 168).
+// Rows of bf16 off a dword are gathered two bytes a lane as they are, and gain by being on one whatever their lines: three
+// hops of mean degree 5, 500,000 x 33 288 / 574, x 155 1050 / 1124; of 41, 60,000 x 73 207 / 491; 10,000 x 47 (1 MB) 34 / 35.
+// Up to 16 columns one load of a lane group takes the row anyhow (60,000 x 9 45.6 / 40.5, x 15 47.6 / 45.1; 500,000 x 9
+// 250 / 390), up to three are no wider than a dword (1,500,000 x 3 802 / 639), and one hop over few wide rows does not pay
+// for the copy (500,000 x 155, mean degree 5, 421 / 396).
+bool copy_pays(const gp_plan* plan, int32_t d, int es, int64_t ld, int64_t stride, int32_t K)
+{
+    if (plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return false;
+    const int64_t w = (int64_t)d * es, bytes = plan->n * w;
+    const double gathers = (double)plan->nnz * K, rows = (double)plan->n;
+    if (es == 2 && ld % 2 != 0) return d > 16 ? bytes >= (1 << 20) && (d < 128 || gathers >= 8.0 * rows) : d >= 5 && bytes >= (8 << 20);
+    if (bytes < (es == 4 ? 4 : 16) << 20) return false;
+    return lines_saved(w, ld * es, stride) * gathers >= 5e5 + 2.0 * (K + 1) * rows * (double)w / (double)kLineBytes;
+}
+
+// Whether the slabs that a filter's hops hand on gain by that stride: they are written either way.  (Smaller ones: four hops
+// of 60,000 x 20 110 / 108 us, 60,000 x 28 114 / 121; 170,000 x 20 208 / 232.)
+bool wide_slabs_pay(const gp_plan* plan, int64_t w, int64_t compact, int64_t stride)
+{
+    return plan->n * w >= (5 << 20) && lines_saved(w, compact, stride) > 0.0;
 }
 
 // Two slabs of n rows, `bytes` each, that hops hand rows on in (plan->mu held).  optional: they are done without where
@@ -832,8 +859,8 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         bool split = false, lds = false;
         HopArgs cold = a;  // as it stands: implicit lists
         if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds, no_room)) != GP_OK) return st;
-        if (k == 1 && may_allocate && !split && !lds && !a.xcd_off && copy_pays(plan, d, es, ldo, K)) {
-            const int64_t stride = line_stride((int64_t)d * es);
+        const int64_t stride = line_stride((int64_t)d * es);
+        if (k == 1 && may_allocate && !split && !lds && !a.xcd_off && copy_pays(plan, d, es, ldo, stride, K)) {
             bool there = false;
             {
                 std::lock_guard<std::mutex> lk(plan->mu);
@@ -912,7 +939,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         std::lock_guard<std::mutex> lk(plan->mu);
         bool there = false;
         const int64_t w = (int64_t)d * es, stride = line_stride(w);
-        if (K >= 2 && lines_per_row(w, stride) < lines_per_row(w, ldp * es)) {
+        if (K >= 2 && wide_slabs_pay(plan, w, ldp * es, stride)) {
             if ((st = ensure_slabs(plan, n * stride, stream, true, &there)) != GP_OK) return st;
             if (there) ldp = stride / es;
         }
@@ -968,7 +995,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         a.gamma0 = coeff[0];
         bool lds = false;
         if ((st = attach_work_lists(plan, a, stream, true, nullptr, &lds, no_room)) != GP_OK) return st;
-        if (k == 1 && K >= 2 && !lds && !a.xcd_off && copy_pays(plan, d, es, ldx, K)) {  // X too is read with rows on lines of their own
+        if (k == 1 && K >= 2 && !lds && !a.xcd_off && copy_pays(plan, d, es, ldx, ldp * es, 1)) {  // X too is read as the slabs are, by one hop
             profile_begin("gp_copy_rows", stream);
             st = launch_copy_rows(X, ldx, D.ping[0], ldp, n, d, dtype, stream);
             profile_end(stream);

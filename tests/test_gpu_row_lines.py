@@ -18,26 +18,25 @@ def graph(n, hub):
     return np.concatenate([src, np.full(hub, 3)]).astype(np.int32), np.concatenate([dst, rng.permutation(n)[:hub]]).astype(np.int32)
 
 
-def both(n, run):
-    """run(plan) with and without room for copies; the plan of the second has none left by the first."""
-    out = []
+def both(n, run, copied):
+    """run(plan) with and without room for copies; the plan of the second has none left by the first.  copied: whether the
+    first reads a copy of X (one launch more)."""
+    out, copies = [], []
     for room in (0, 1):
         gp.gp_set_option("list_bytes", room)
+        gp.gp_profile_enable(True)
         try:
             with gp.gp_plan_blocks(*graph(n, n // 10), n, 1 << 17, gp.GP_SYMMETRISE) as plan:
                 out.append(run(plan).cpu())
+                copies.append(gp.gp_profile_read("gp_copy_rows")[0])
         finally:
+            gp.gp_profile_enable(False)
             gp.gp_set_option("list_bytes", 0)
     assert out[0].isfinite().all() and torch.equal(*(o.view(BITS[o.dtype]) for o in out))
+    assert copies[0] - copies[1] == copied
 
 
-# widths on either side of a line, off 16, 8 and 4 bytes; one wide enough for column slices, one of several vectors a lane
-@pytest.mark.parametrize("n,d,dtype,agg,K", [(40_000, 33, "float32", gp.GP_AGG_SYM, 3), (40_000, 63, "float32", gp.GP_AGG_SUM, 2),
-                                             (60_000, 66, "float32", gp.GP_AGG_MEAN, 1), (20_000, 150, "float32", gp.GP_AGG_SYM, 2),
-                                             (20_000, 47, "bfloat16", gp.GP_AGG_MEAN, 3), (9_000, 301, "bfloat16", gp.GP_AGG_SYM, 2),
-                                             (60_000, 126, "bfloat16", gp.GP_AGG_SUM, 2), (7_000, 599, "bfloat16", gp.GP_AGG_SUM, 1)])
-@pytest.mark.parametrize("where", ["tensor", "in place", "padded"])
-def test_hop_stack(n, d, dtype, agg, K, where):
+def hop_stack(n, d, dtype, agg, K, where, copied):
     dtype = getattr(torch, dtype)
     ld = d + (d % 2 * 2 if where == "padded" else 0)  # an odd stride stays odd
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
@@ -55,21 +54,49 @@ def test_hop_stack(n, d, dtype, agg, K, where):
         assert torch.equal(stack[0, :, :d], X) and not stack[:, :, d:].any()  # nothing is written past a row
         return stack
 
-    both(n, run)
+    both(n, run, 2 * copied)
 
 
-@pytest.mark.parametrize("n,d,dtype", [(40_000, 20, "float32"), (40_000, 63, "float32"), (20_000, 47, "bfloat16"), (60_000, 100, "bfloat16")])
-def test_filter(n, d, dtype):
+# widths on either side of a line, off 16, 8 and 4 bytes; rows that several to a line hold; one wide enough for column
+# slices, one of several vectors a lane; one hop and more
+@pytest.mark.parametrize("n,d,dtype,agg,K", [(160_000, 7, "float32", gp.GP_AGG_SUM, 3), (40_000, 47, "float32", gp.GP_AGG_SYM, 3),
+                                             (40_000, 63, "float32", gp.GP_AGG_SUM, 2), (70_000, 58, "float32", gp.GP_AGG_MEAN, 1),
+                                             (40_000, 159, "float32", gp.GP_AGG_SYM, 2), (280_000, 15, "bfloat16", gp.GP_AGG_SUM, 2),
+                                             (20_000, 47, "bfloat16", gp.GP_AGG_MEAN, 3), (9_000, 301, "bfloat16", gp.GP_AGG_SYM, 2),
+                                             (70_000, 126, "bfloat16", gp.GP_AGG_SUM, 2), (7_000, 599, "bfloat16", gp.GP_AGG_SUM, 1)])
+@pytest.mark.parametrize("where", ["tensor", "in place", "padded"])
+def test_hop_stack(n, d, dtype, agg, K, where):
+    hop_stack(n, d, dtype, agg, K, where, True)
+
+
+# rows of a few elements, which a copy would only spread out; rows that touch no fewer lines; small matrices
+@pytest.mark.parametrize("n,d,dtype", [(600_000, 1, "bfloat16"), (400_000, 3, "bfloat16"), (360_000, 3, "float32"), (250_000, 5, "float32"),
+                                       (60_000, 9, "bfloat16"), (40_000, 33, "float32"), (20_000, 47, "float32"), (60_000, 100, "bfloat16")])
+def test_rows_that_are_read_where_they_lie(n, d, dtype):
+    hop_stack(n, d, dtype, gp.GP_AGG_SUM, 2, "tensor", False)
+
+
+@pytest.mark.parametrize("n,d,dtype,copied", [(80_000, 20, "float32", False), (40_000, 63, "float32", True), (20_000, 47, "bfloat16", True),
+                                              (60_000, 100, "bfloat16", False), (10_000, 20, "float32", False)])
+def test_filter(n, d, dtype, copied):
+    """Slabs as wide as there is room for, and X from a copy, or as its rows lie on lines already."""
     dtype = getattr(torch, dtype)
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
+    ld = -(-d * X.element_size() // 128) * 128 // X.element_size()
+    on_lines = torch.zeros(n, ld, dtype=dtype, device="cuda")
+    on_lines[:, :d] = X
 
     def run(plan):
-        out = torch.empty_like(X)
-        gp.gp_propagate_combine(plan, X.data_ptr(), d, d, gp.GP_F32 if dtype == torch.float32 else gp.GP_BF16, gp.GP_AGG_SYM, 3,
-                                [0.5, 0.25, 0.125, 0.125], out.data_ptr(), d, torch.cuda.current_stream().cuda_stream)
+        out = torch.empty(2, n, d, dtype=dtype, device="cuda")
+        for x, o, copies in ((X, out[0], copied), (on_lines, out[1], False)):
+            before = gp.gp_profile_read("gp_copy_rows")[0]
+            gp.gp_propagate_combine(plan, x.data_ptr(), x.stride(0), d, gp.GP_F32 if dtype == torch.float32 else gp.GP_BF16, gp.GP_AGG_SYM, 3,
+                                    [0.5, 0.25, 0.125, 0.125], o.data_ptr(), d, torch.cuda.current_stream().cuda_stream)
+            assert gp.gp_profile_read("gp_copy_rows")[0] - before == copies
+        assert torch.equal(*(o.view(BITS[o.dtype]) for o in out))
         return out
 
-    both(n, run)
+    both(n, run, False)  # (the slabs that a filter needs take the copy in any case)
 
 
 @pytest.mark.parametrize("n,d", [(1, 5), (3, 47), (37_123, 47), (1000, 4), (5, 1023)])
