@@ -16,6 +16,8 @@
 // needed: lanes own columns, not edges.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "gp_internal.h"
 
 namespace gp {
@@ -256,6 +258,9 @@ __device__ __forceinline__ SegRegs unpack_segment(const v4i raw, int64_t col_bas
 // next one are requested while the current one is gathered.
 // EDGE_W: 0 = every weight is 1; 1 = weight gathered from an n-vector by column id;
 // 2 = weight read from a per-edge array laid out like the column list.
+// LINES: finished rows go to xnext too, laid out as xin is, and where kOutByElement is set to xout element by element.
+// Launches without either keep their code, and their wavefronts: as branches of one instance the two cost three hops of
+// 37,000 rows x 128 bf16 columns, 0.9 million non-zeros, 93.0 us for 91.2, of 60,000 x 128 fp32 209.5 for 209.1.
 struct XcdLists {
     int64_t off[9];
     int explicit_lists;
@@ -278,7 +283,7 @@ constexpr int resident_wavefronts(size_t element, int vec, int group) { return e
 constexpr int kCombStarts = 1;    // comb[row] = gamma0 * xin[row] + gamma * result
 constexpr int kOutByElement = 2;  // rows of xout may start off a dword (bf16)
 
-template <typename T, int VEC, int G, int VPL, int EDGE_W>
+template <typename T, int VEC, int G, int VPL, int EDGE_W, bool LINES>
 __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
                                                             const XcdLists lists, unsigned long long* __restrict__ ctrl,
                                                             int chunk_records, const int32_t* __restrict__ col,
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
     constexpr int NACC = sizeof(T) == 2 ? 2 : 4;
     const int lane = threadIdx.x % G;
     const int xcd = blockIdx.x & 7;
-    const bool comb_starts = flags & kCombStarts;
+    const int comb_starts = LINES ? flags & kCombStarts : flags;  // (the only flag: not waited for before it is needed)
     // This XCD's list: the record of position p < count is segs[place_of(p)].  Implicit lists: the
     // XCDs that share a slice take the records interleaved, in runs of 2^run_log2 consecutive records: what consecutive
     // records read side by side (ids and weights of an ordered column list, plane entries) shares lines, which then
@@ -612,7 +617,7 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
                 Row<float, VEC>::store(carry + (int64_t)r.slot * carry_ld + coff[v], o);
             } else {
                 T* op = xout + (int64_t)r.row * ldout + coff[v];
-                if (sizeof(T) == 2 && VEC > 1 && (flags & kOutByElement)) {
+                if (LINES && sizeof(T) == 2 && (flags & kOutByElement)) {
                     // (not streamed: elements of a line then go to memory one by one; two hops of 1,500,000 rows x 97 bf16
                     // columns, 25 million non-zeros, 3415 us streamed, 2300 so)
 #pragma unroll
@@ -623,7 +628,7 @@ __global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) v
                 } else if (xout) {
                     Row<T, VEC>::store_stream(op, o);
                 }
-                if (xnext) Row<T, VEC>::store(xnext + (int64_t)r.row * ldin + coff[v], o);
+                if (LINES && xnext) Row<T, VEC>::store(xnext + (int64_t)r.row * ldin + coff[v], o);
                 // running filter output: comb[row] += gamma * (A^^k X)[row]
                 if (kFiltAhead && filt_ahead) {
 #pragma unroll
@@ -704,9 +709,9 @@ __global__ __launch_bounds__(kThreads) void gp_order_columns(const Segment* __re
 }
 
 // ---------------------------------------------------------------------------
-// rows that were cut: add their partial rows in list order, scale, store
+// rows that were cut: add their partial rows in list order, scale, store (LINES: to xnext too)
 // ---------------------------------------------------------------------------
-template <typename T, int VEC, int G, int VPL>
+template <typename T, int VEC, int G, int VPL, bool LINES>
 __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __restrict__ split, int64_t num_split,
                                                           const float* __restrict__ carry, int64_t carry_ld,
                                                           const float* __restrict__ row_scale, T* __restrict__ xout,
@@ -778,7 +783,7 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
 #pragma unroll
         for (int i = 0; i < VEC; ++i) r[i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * rs;
         if (xout) Row<T, VEC>::store_stream(xout + (int64_t)sr.row * ldout + c0, r);
-        if (xnext) Row<T, VEC>::store(xnext + (int64_t)sr.row * ldnext + c0, r);
+        if (LINES) Row<T, VEC>::store(xnext + (int64_t)sr.row * ldnext + c0, r);
         if (filt_ahead) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) filt[i] = fmaf(gamma, r[i], filt[i]);
@@ -900,7 +905,7 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     static const int resident = [] {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gp_hop_segments<T, VEC, G, VPL, 2>, kThreads, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gp_hop_segments<T, VEC, G, VPL, 2, false>, kThreads, 0) !=
                 hipSuccess ||
             hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess || per_cu <= 0)
             return 2048;
@@ -922,18 +927,29 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     const dim3 grid((unsigned)blocks), block(kThreads);
     const bool by_element = a.xout_apart && sizeof(T) == 2 && ((a.ldout & 1) || ((uintptr_t)a.xout & 2));
     const int flags = (a.comb_starts ? kCombStarts : 0) | (by_element ? kOutByElement : 0);
-    if (a.edge_w && a.edge_w_per_edge)
-        hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 2>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
-                           a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
-    else if (a.edge_w)
-        hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 1>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
-                           a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
-    else
-        hipLaunchKernelGGL((gp_hop_segments<T, VEC, G, VPL, 0>), grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col,
-                           a.col_base, a.edge_w, a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry,
-                           a.carry_ld, a.d, a.num_slices, a.slice_elems, a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.segs, a.num_segs, lists, a.ctrl, chunk_records, a.col, a.col_base, a.edge_w,
+                           a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry, a.carry_ld, a.d, a.num_slices, a.slice_elems,
+                           a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
+    };
+    auto launch_weighted = [&](auto lines) {
+        constexpr bool L = decltype(lines)::value;
+        if (a.edge_w && a.edge_w_per_edge)
+            launch(gp_hop_segments<T, VEC, G, VPL, 2, L>);
+        else if (a.edge_w)
+            launch(gp_hop_segments<T, VEC, G, VPL, 1, L>);
+        else
+            launch(gp_hop_segments<T, VEC, G, VPL, 0, L>);
+    };
+    if (a.xnext || by_element) {
+        // rows on lines of their own are read 16 bytes a lane, or where they are bf16 and shorter, eight
+        if constexpr (VEC * sizeof(T) == 16 || (VEC == 4 && G == 8 && VPL == 1))
+            launch_weighted(std::true_type{});
+        else
+            return fail(GP_ERR_UNSUPPORTED, "no kernel that copies rows of %d elements in vectors of %d", a.d, VEC);
+    } else {
+        launch_weighted(std::false_type{});
+    }
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
@@ -945,9 +961,18 @@ gp_status launch_fixup_t(const FixupArgs& a, hipStream_t stream)
     const int64_t blocks = (a.num_split + GPB - 1) / GPB;
     if (blocks == 0) return GP_OK;
     if (blocks > INT32_MAX) return fail(GP_ERR_UNSUPPORTED, "%lld workgroups exceed the grid limit", (long long)blocks);
-    hipLaunchKernelGGL((gp_fixup_rows<T, VEC, G, VPL>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.split,
-                       a.num_split, a.carry, a.carry_ld, a.row_scale, (T*)a.xout, a.ldout, a.d, a.comb, a.ldc, a.gamma,
-                       (const T*)a.x0, a.ldx0, a.gamma0, (T*)a.xnext, a.ldnext);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.split, a.num_split, a.carry, a.carry_ld, a.row_scale,
+                           (T*)a.xout, a.ldout, a.d, a.comb, a.ldc, a.gamma, (const T*)a.x0, a.ldx0, a.gamma0, (T*)a.xnext, a.ldnext);
+    };
+    if (a.xnext) {
+        if constexpr (VEC == 4 || (VEC == 1 && sizeof(T) == 2))  // (bf16 rows of xout off a dword: one by one)
+            launch(gp_fixup_rows<T, VEC, G, VPL, true>);
+        else
+            return fail(GP_ERR_UNSUPPORTED, "no fix-up kernel that copies rows of %d elements in vectors of %d", a.d, VEC);
+    } else {
+        launch(gp_fixup_rows<T, VEC, G, VPL, false>);
+    }
     GP_HIP(hipGetLastError());
     return GP_OK;
 }
