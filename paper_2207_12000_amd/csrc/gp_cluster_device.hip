@@ -449,9 +449,9 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
     int32_t* big = mid + words;
     int32_t* huge = big + words;
 
-    static const bool big_table = hipFuncSetAttribute((const void*)gp_label_long_rows<1024, kBigTable>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      2 * kBigTable * 4) == hipSuccess;
-    if (!big_table) {
+    // (a setting of the current device's copy of the kernel: asked for by every call)
+    if (hipFuncSetAttribute((const void*)gp_label_long_rows<1024, kBigTable>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kBigTable * 4) !=
+        hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
