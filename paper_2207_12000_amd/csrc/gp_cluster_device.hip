@@ -425,6 +425,7 @@ bool cluster_rows_on_device(const gp_plan& P, RowClusters& C, hipStream_t stream
 {
     const int64_t n = P.n;
     if (P.nnz == 0 || !P.dev.col || P.rowptr.size() != (size_t)n + 1) return false;
+    if ((double)P.nnz * (double)n >= 18e18) return false;  // (weight_size may reach their product, and holds less than 2^64)
     // one allocation: row pointers, two label lists, ranks (and the scan's words), sizes, the lists of longer rows, the tally
     const size_t words = (size_t)n, most_huge = (size_t)(P.nnz / kBigRow);
     const size_t rank_words = words + 1, scan_words = device_scan_scratch_words(n + 1);
