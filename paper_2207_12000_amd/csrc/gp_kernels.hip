@@ -16,8 +16,6 @@
 // needed: lanes own columns, not edges.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "gp_internal.h"
 
 namespace gp {
@@ -258,9 +256,24 @@ __device__ __forceinline__ SegRegs unpack_segment(const v4i raw, int64_t col_bas
 // next one are requested while the current one is gathered.
 // EDGE_W: 0 = every weight is 1; 1 = weight gathered from an n-vector by column id;
 // 2 = weight read from a per-edge array laid out like the column list.
-// LINES: finished rows go to xnext too, laid out as xin is, and where kOutByElement is set to xout element by element.
+// E = Lines<T>: finished rows go to xnext too, laid out as xin is, and where kOutByElement is set to xout element by element.
 // Launches without either keep their code, and their wavefronts: as branches of one instance the two cost three hops of
 // 37,000 rows x 128 bf16 columns, 0.9 million non-zeros, 93.0 us for 91.2, of 60,000 x 128 fp32 209.5 for 209.1.
+template <typename T>
+struct Lines {};
+template <typename E>
+struct Element {
+    using type = E;
+    static constexpr bool lines = false;
+};
+template <typename T>
+struct Element<Lines<T>> {
+    using type = T;
+    static constexpr bool lines = true;
+};
+template <typename E>
+using ElementOf = typename Element<E>::type;
+
 struct XcdLists {
     int64_t off[9];
     int explicit_lists;
@@ -283,22 +296,24 @@ constexpr int resident_wavefronts(size_t element, int vec, int group) { return e
 constexpr int kCombStarts = 1;    // comb[row] = gamma0 * xin[row] + gamma * result
 constexpr int kOutByElement = 2;  // rows of xout may start off a dword (bf16)
 
-template <typename T, int VEC, int G, int VPL, int EDGE_W, bool LINES>
-__global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(T), VEC, G)) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
+template <typename E, int VEC, int G, int VPL, int EDGE_W>
+__global__ __launch_bounds__(kThreads, resident_wavefronts(sizeof(ElementOf<E>), VEC, G)) void gp_hop_segments(const Segment* __restrict__ segs, int64_t num_segs,
                                                             const XcdLists lists, unsigned long long* __restrict__ ctrl,
                                                             int chunk_records, const int32_t* __restrict__ col,
                                                             int64_t col_base,
                                                             const float* __restrict__ edge_w,
                                                             const float* __restrict__ row_scale,
-                                                            const T* __restrict__ xin, int64_t ldin,
-                                                            T* __restrict__ xout, int64_t ldout,
+                                                            const ElementOf<E>* __restrict__ xin, int64_t ldin,
+                                                            ElementOf<E>* __restrict__ xout, int64_t ldout,
                                                             float* __restrict__ carry, int64_t carry_ld, int d,
                                                             int num_slices, int slice_elems, float* __restrict__ comb,
                                                             int64_t ldc, float gamma, int flags, float gamma0,
                                                             const float* __restrict__ planes,
                                                             int64_t num_pos, int run_log2, int plane_log2,
-                                                            T* __restrict__ xnext)
+                                                            ElementOf<E>* __restrict__ xnext)
 {
+    using T = ElementOf<E>;
+    constexpr bool LINES = Element<E>::lines;
     constexpr int GPB = kThreads / G;
     constexpr int PF = G >= 32 ? 1 : 32 / G;  // column ids each lane prefetches per segment
     constexpr int WIN = PF * G;               // edges of a segment covered by the prefetch
@@ -709,16 +724,17 @@ __global__ __launch_bounds__(kThreads) void gp_order_columns(const Segment* __re
 }
 
 // ---------------------------------------------------------------------------
-// rows that were cut: add their partial rows in list order, scale, store (LINES: to xnext too)
+// rows that were cut: add their partial rows in list order, scale, store (E = Lines<T>: to xnext too)
 // ---------------------------------------------------------------------------
-template <typename T, int VEC, int G, int VPL, bool LINES>
+template <typename E, int VEC, int G, int VPL>
 __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __restrict__ split, int64_t num_split,
                                                           const float* __restrict__ carry, int64_t carry_ld,
-                                                          const float* __restrict__ row_scale, T* __restrict__ xout,
+                                                          const float* __restrict__ row_scale, ElementOf<E>* __restrict__ xout,
                                                           int64_t ldout, int d, float* __restrict__ comb, int64_t ldc,
-                                                          float gamma, const T* __restrict__ x0, int64_t ldx0, float gamma0,
-                                                          T* __restrict__ xnext, int64_t ldnext)
+                                                          float gamma, const ElementOf<E>* __restrict__ x0, int64_t ldx0, float gamma0,
+                                                          ElementOf<E>* __restrict__ xnext, int64_t ldnext)
 {
+    using T = ElementOf<E>;
     constexpr int GPB = kThreads / G;
     const int lane = threadIdx.x % G;
     const int64_t rid = (int64_t)blockIdx.x * GPB + threadIdx.x / G;
@@ -783,7 +799,7 @@ __global__ __launch_bounds__(kThreads) void gp_fixup_rows(const SplitRow* __rest
 #pragma unroll
         for (int i = 0; i < VEC; ++i) r[i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * rs;
         if (xout) Row<T, VEC>::store_stream(xout + (int64_t)sr.row * ldout + c0, r);
-        if (LINES) Row<T, VEC>::store(xnext + (int64_t)sr.row * ldnext + c0, r);
+        if (Element<E>::lines) Row<T, VEC>::store(xnext + (int64_t)sr.row * ldnext + c0, r);
         if (filt_ahead) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) filt[i] = fmaf(gamma, r[i], filt[i]);
@@ -905,7 +921,7 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     static const int resident = [] {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gp_hop_segments<T, VEC, G, VPL, 2, false>, kThreads, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gp_hop_segments<T, VEC, G, VPL, 2>, kThreads, 0) !=
                 hipSuccess ||
             hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess || per_cu <= 0)
             return 2048;
@@ -932,23 +948,23 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
                            a.row_scale, (const T*)a.xin, a.ldin, (T*)a.xout, a.ldout, a.carry, a.carry_ld, a.d, a.num_slices, a.slice_elems,
                            a.comb, a.ldc, a.gamma, flags, a.gamma0, a.planes, a.num_pos, run_log2, a.plane_log2, (T*)a.xnext);
     };
-    auto launch_weighted = [&](auto lines) {
-        constexpr bool L = decltype(lines)::value;
+    auto launch_weighted = [&](auto element) {
+        using E = decltype(element);
         if (a.edge_w && a.edge_w_per_edge)
-            launch(gp_hop_segments<T, VEC, G, VPL, 2, L>);
+            launch(gp_hop_segments<E, VEC, G, VPL, 2>);
         else if (a.edge_w)
-            launch(gp_hop_segments<T, VEC, G, VPL, 1, L>);
+            launch(gp_hop_segments<E, VEC, G, VPL, 1>);
         else
-            launch(gp_hop_segments<T, VEC, G, VPL, 0, L>);
+            launch(gp_hop_segments<E, VEC, G, VPL, 0>);
     };
     if (a.xnext || by_element) {
         // rows on lines of their own are read 16 bytes a lane, or where they are bf16 and shorter, eight
         if constexpr (VEC * sizeof(T) == 16 || (VEC == 4 && G == 8 && VPL == 1))
-            launch_weighted(std::true_type{});
+            launch_weighted(Lines<T>{});
         else
             return fail(GP_ERR_UNSUPPORTED, "no kernel that copies rows of %d elements in vectors of %d", a.d, VEC);
     } else {
-        launch_weighted(std::false_type{});
+        launch_weighted(T{});
     }
     GP_HIP(hipGetLastError());
     return GP_OK;
@@ -967,11 +983,11 @@ gp_status launch_fixup_t(const FixupArgs& a, hipStream_t stream)
     };
     if (a.xnext) {
         if constexpr (VEC == 4 || (VEC == 1 && sizeof(T) == 2))  // (bf16 rows of xout off a dword: one by one)
-            launch(gp_fixup_rows<T, VEC, G, VPL, true>);
+            launch(gp_fixup_rows<Lines<T>, VEC, G, VPL>);
         else
             return fail(GP_ERR_UNSUPPORTED, "no fix-up kernel that copies rows of %d elements in vectors of %d", a.d, VEC);
     } else {
-        launch(gp_fixup_rows<T, VEC, G, VPL, false>);
+        launch(gp_fixup_rows<T, VEC, G, VPL>);
     }
     GP_HIP(hipGetLastError());
     return GP_OK;
