@@ -183,10 +183,12 @@ struct DevicePlan {
     float* carry = nullptr;     // num_slots x carry_ld fp32
     int64_t carry_ld = 0;
     unsigned long long* ctrl = nullptr;  // kHopCtrlWords words, zero between launches
-    // scratch of gp_propagate_combine: two hop slabs and (bf16 storage) an fp32 accumulator
+    // two slabs that hops hand rows on in (gp_propagate_combine, and gp_propagate where rows are read from lines of their
+    // own), and gp_propagate_combine's fp32 accumulator for bf16 storage
     void* ping[2] = {nullptr, nullptr};
+    int64_t ping_bytes[2] = {0, 0};
     float* comb = nullptr;
-    int64_t ping_bytes = 0, comb_elems = 0;
+    int64_t comb_elems = 0;
     std::vector<XcdWork> work;  // explicit work lists built so far (one per slice shape)
     // split schedule (hot / cold pieces of every segment), made on first use
     bool split_ready = false;

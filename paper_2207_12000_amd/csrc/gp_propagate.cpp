@@ -665,27 +665,45 @@ bool wide_slabs_pay(const gp_plan* plan, int64_t w, int64_t compact, int64_t str
     return plan->n * w >= (5 << 20) && lines_saved(w, compact, stride) > 0.0;
 }
 
-// Two slabs of n rows, `bytes` each, that hops hand rows on in (plan->mu held).  optional: they are done without where
-// there is little room, or no allocating now (*there says whether they are).
-gp_status ensure_slabs(const gp_plan* plan, int64_t bytes, hipStream_t stream, bool optional, bool* there)
+// The first `count` of two slabs of n rows, `bytes` each, that hops hand rows on in (plan->mu held).  optional: they are done
+// without where there is little room, or no allocating now (*there says whether they are).  Outgrown slabs stay until the plan
+// goes, as work enqueued earlier or a captured graph may use them: a slab grows to twice its size at least, where there is
+// room, so that those are no larger in sum than the ones in use.
+gp_status ensure_slabs(const gp_plan* plan, int64_t bytes, int count, hipStream_t stream, bool optional, bool* there)
 {
     DevicePlan& D = plan->dev;
-    *there = bytes <= D.ping_bytes;
-    if (*there || (optional && (!may_allocate_on(stream) || !room_for_list((size_t)(2 * bytes), true)))) return GP_OK;
-    if (D.ping[0]) D.retired.push_back(D.ping[0]);
-    if (D.ping[1]) D.retired.push_back(D.ping[1]);
-    D.ping[0] = D.ping[1] = nullptr;
-    D.ping_bytes = 0;
-    for (void*& p : D.ping)
-        if (hipMalloc(&p, (size_t)bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            if (D.ping[0]) D.retired.push_back(D.ping[0]);
-            D.ping[0] = D.ping[1] = nullptr;
-            return optional ? GP_OK : fail(GP_ERR_OOM_DEVICE, "two slabs of %lld bytes", (long long)bytes);
-        }
-    D.ping_bytes = bytes;
     *there = true;
-    return GP_OK;
+    for (int i = 0; i < count; ++i) *there = *there && bytes <= D.ping_bytes[i];
+    if (*there || (optional && !may_allocate_on(stream))) return GP_OK;
+    for (int64_t factor : {2, 1}) {
+        int64_t size[2] = {0, 0};  // of those to be made
+        for (int i = 0; i < count; ++i)
+            if (bytes > D.ping_bytes[i]) size[i] = std::max(bytes, factor * D.ping_bytes[i]);
+        if (optional && !room_for_list((size_t)(size[0] + size[1]), true)) continue;
+        void* fresh[2] = {nullptr, nullptr};
+        bool ok = true;
+        for (int i = 0; i < count; ++i)
+            if (ok && size[i] && hipMalloc(&fresh[i], (size_t)size[i]) != hipSuccess) {
+                (void)hipGetLastError();
+                fresh[i] = nullptr;
+                ok = false;
+            }
+        for (int i = 0; i < count; ++i) {
+            if (!fresh[i]) continue;
+            if (!ok) {
+                (void)hipFree(fresh[i]);  // (nothing uses it)
+                continue;
+            }
+            if (D.ping[i]) D.retired.push_back(D.ping[i]);
+            D.ping[i] = fresh[i];
+            D.ping_bytes[i] = size[i];
+        }
+        if (ok) {
+            *there = true;
+            return GP_OK;
+        }
+    }
+    return optional ? GP_OK : fail(GP_ERR_OOM_DEVICE, "two slabs of %lld bytes", (long long)bytes);
 }
 
 // Whether a hop over whole records, or one of the LDS pass, leaves partial rows of the plan's own cut.
@@ -864,7 +882,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
             bool there = false;
             {
                 std::lock_guard<std::mutex> lk(plan->mu);
-                if ((st = ensure_slabs(plan, n * stride, stream, true, &there)) != GP_OK) return st;
+                if ((st = ensure_slabs(plan, n * stride, K > 1 ? 2 : 1, stream, true, &there)) != GP_OK) return st;
             }
             if (there) {
                 ld_lines = stride / es;
@@ -940,10 +958,10 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         bool there = false;
         const int64_t w = (int64_t)d * es, stride = line_stride(w);
         if (K >= 2 && wide_slabs_pay(plan, w, ldp * es, stride)) {
-            if ((st = ensure_slabs(plan, n * stride, stream, true, &there)) != GP_OK) return st;
+            if ((st = ensure_slabs(plan, n * stride, 2, stream, true, &there)) != GP_OK) return st;
             if (there) ldp = stride / es;
         }
-        if (K >= 2 && !there && (st = ensure_slabs(plan, n * ldp * es, stream, false, &there)) != GP_OK) return st;
+        if (K >= 2 && !there && (st = ensure_slabs(plan, n * ldp * es, 2, stream, false, &there)) != GP_OK) return st;
         if (dtype == GP_BF16 && n * ldc_scratch > D.comb_elems) {
             if (D.comb) D.retired.push_back(D.comb);
             D.comb = nullptr;

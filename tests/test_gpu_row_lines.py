@@ -108,3 +108,35 @@ def test_slot_0_of_ragged_rows(n, d, ld_in, ld_out):
         gp.gp_propagate(plan, X.data_ptr(), d + ld_in, d, gp.GP_F32, gp.GP_AGG_SUM, 0, out.data_ptr(), d + ld_out,
                         torch.cuda.current_stream().cuda_stream)
     assert torch.equal(out[:, :d], X[:, :d]) and not out[:, d:].any()
+
+
+def test_slabs_of_a_plan_used_at_growing_widths_stay_bounded():
+    n, widths = 100_000, range(41, 127, 5)
+    src = np.random.default_rng(1).integers(0, n, 32 * n).astype(np.int32)
+    dst = np.repeat(np.arange(n, dtype=np.int32), 32)  # rows of 32: no partial rows, whose buffer grows too
+    X, out = torch.zeros(n, 128, device="cuda"), torch.empty(4 * n * 128, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    gp.gp_set_option("cache_schedule", 2)
+    gp.gp_profile_enable(True)
+    try:
+        with gp.gp_plan_blocks(src, dst, n, 1 << 23, 0) as plan:
+            def call(d, K):
+                """Bytes of device memory that the call took."""
+                free = torch.cuda.mem_get_info()[0]
+                gp.gp_propagate(plan, X.data_ptr(), d, d, gp.GP_F32, gp.GP_AGG_SUM, K, out.data_ptr(), d, stream)
+                torch.cuda.synchronize()
+                return free - torch.cuda.mem_get_info()[0]
+
+            assert plan.num_partial_rows == 0
+            call(32, 3)  # plan and lists; rows on lines as they are
+            assert gp.gp_profile_read("gp_copy_rows")[0] == 1
+            slab = n * 256
+            assert 0.9 * slab < call(63, 1) < 1.5 * slab  # one slab for one hop (memory comes in pages of 2 MiB)
+            assert 0.9 * slab < call(63, 3) < 1.5 * slab  # the other
+            copies = gp.gp_profile_read("gp_copy_rows")[0]
+            taken = sum(call(d, 3) for d in widths)
+            assert gp.gp_profile_read("gp_copy_rows")[0] - copies > len(widths) + 8
+            assert taken <= 2 * 2 * n * 512  # at most twice the widest row's two slabs (2.6 times, each as large as its call needs)
+    finally:
+        gp.gp_profile_enable(False)
+        gp.gp_set_option("cache_schedule", 0)
