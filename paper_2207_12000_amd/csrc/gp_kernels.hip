@@ -1168,8 +1168,10 @@ gp_status launch_copy_rows(const void* src, int64_t lds, void* dst, int64_t ldd,
         unit /= 2;
     }
     // Rows of 47 fp32 columns, four bytes a lane and 16: 7.3 and 7.1 us for 37,123 of them, 12.5 and 10.4 for 169,343;
-    // 1,000,000 x 63 108 and 92.
-    if (unit < 16 && unit >= 4 && row_bytes >= 16) {
+    // 1,000,000 x 63 108 and 92.  Over the host link (max_blocks) rows that start on 8 bytes keep to these: streamed calls in
+    // column slabs, ms on 4 or 8 bytes a lane and 16: 200,000 x 602 fp32 17.6 / 18.4, 400,000 x 300 bf16 12.5 / 12.1;
+    // 300,000 x 203 fp32 (two hops) 21.9 / 19.6, 400,000 x 150 bf16 (two) 13.5 / 12.6, 400,000 x 99 fp32 10.1 / 10.1.
+    if (row_bytes >= 16 && (unit == 4 || (unit == 8 && max_blocks == 0))) {
         const int64_t nvec = (row_bytes + 15) / 16, total = n * nvec;
         const int64_t blocks = std::min<int64_t>((total + kThreads - 1) / kThreads, max_blocks > 0 ? max_blocks : 256 * 32);
         const int64_t s = lds * es / 4, t = ldd * es / 4;
