@@ -250,9 +250,10 @@ gp_status gp_plan_work_lists(const gp_plan *plan, int32_t d, gp_dtype dtype, int
  * per non-zero, about 20 per record); after a call of GP_AGG_SYM one weight per non-zero (4 bytes)
  * for that copy, and for the plan's own list where hops read it; where rows start off 128-byte lines
  * and hops gain by reading them from lines of their own, two slabs of n rows (a row's bytes rounded up
- * to a multiple of 64, or below that to a power of two; one slab for one hop; a plan that is used
- * at growing widths keeps outgrown slabs, up to the size of those in use); these only where there is
- * room (option "list_bytes").  The lists of the LDS pass and of the cache schedule come the same way,
+ * to a multiple of 64, or below that to a power of two; one slab for one hop; made by a plan's second
+ * call with hops unless the first gains more by them than they cost; a plan that is used at growing
+ * widths keeps outgrown slabs, up to the size of those in use); these only where there is room
+ * (option "list_bytes").  The lists of the LDS pass and of the cache schedule come the same way,
  * but not without room.  Calls on ONE plan must not
  * overlap in time (they share that scratch); different plans are independent.
  * Results are deterministic: the same inputs and options give the same bits on every

@@ -187,6 +187,7 @@ struct DevicePlan {
     // own), and gp_propagate_combine's fp32 accumulator for bf16 storage
     void* ping[2] = {nullptr, nullptr};
     int64_t ping_bytes[2] = {0, 0};
+    bool hops_made = false;  // by a stack call that could allocate
     float* comb = nullptr;
     int64_t comb_elems = 0;
     std::vector<XcdWork> work;  // explicit work lists built so far (one per slice shape)

@@ -635,8 +635,8 @@ double lines_saved(int64_t w, int64_t from, int64_t to)
     return before - lines_per_row(w, to) - 0.17 * std::max(0.0, (double)to / (double)from - 1.0) * before;
 }
 
-// Whether K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading dimension ld as they
-// are).  The line reads that the gathers save have to make up for a launch, and for a row's lines copied once and written
+// Line reads (some 57 a ns) that K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading
+// dimension ld as they are); none or less: they do not.  The line reads that the gathers save have to make up for a launch, and for a row's lines copied once and written
 // once more per hop, some two of them each; the factors are those of a fit to 153 pairs of measurements (fp32, 3 to 119
 // columns, 37,000 to 1,500,000 rows of mean degree 5 to 41, one to three hops), all but three of which it calls right within
 // 1 %.  Slabs below 4 MiB stay in an L2 as they are.  With and without, us: two hops of mean degree 17, 1,500,000 rows x 28
@@ -648,15 +648,22 @@ double lines_saved(int64_t w, int64_t from, int64_t to)
 // Up to 16 columns one load of a lane group takes the row anyhow (60,000 x 9 45.6 / 40.5, x 15 47.6 / 45.1; 500,000 x 9
 // 250 / 390), up to three are no wider than a dword (1,500,000 x 3 802 / 639), and one hop over few wide rows does not pay
 // for the copy (500,000 x 155, mean degree 5, 421 / 396).
-bool copy_pays(const gp_plan* plan, int32_t d, int es, int64_t ld, int64_t stride, int32_t K)
+double copy_gains(const gp_plan* plan, int32_t d, int es, int64_t ld, int64_t stride, int32_t K)
 {
-    if (plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return false;
+    if (plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return 0.0;
     const int64_t w = (int64_t)d * es, bytes = plan->n * w;
     const double gathers = (double)plan->nnz * K, rows = (double)plan->n;
-    if (es == 2 && ld % 2 != 0) return d > 16 ? bytes >= (1 << 20) && (d < 128 || gathers >= 8.0 * rows) : d >= 5 && bytes >= (8 << 20);
-    if (bytes < (es == 4 ? 4 : 16) << 20) return false;
-    return lines_saved(w, ld * es, stride) * gathers >= 5e5 + 2.0 * (K + 1) * rows * (double)w / (double)kLineBytes;
+    if (es == 2 && ld % 2 != 0) {
+        const bool pays = d > 16 ? bytes >= (1 << 20) && (d < 128 || gathers >= 8.0 * rows) : d >= 5 && bytes >= (8 << 20);
+        return pays ? 0.3 * lines_per_row(w, ld * es) * gathers : 0.0;  // (500,000 x 97, mean degree 41: 2840 -> 1996 us)
+    }
+    if (bytes < (es == 4 ? 4 : 16) << 20) return 0.0;
+    return lines_saved(w, ld * es, stride) * gathers - 5e5 - 2.0 * (K + 1) * rows * (double)w / (double)kLineBytes;
 }
+// What making slabs costs the one call that does, about a ms for two, in such line reads: a plan's first call leaves them
+// to the next unless it gains more by itself (plan, three hops, plan dropped, 60,000 x 47 fp32: 4.1 ms with and 3.2 without;
+// 490,000 x 47 13.4 and 13.1).
+constexpr double kSlabsCost = 5.7e7;
 
 // Whether the slabs that a filter's hops hand on gain by that stride: they are written either way.  (Smaller ones: four hops
 // of 60,000 x 20 110 / 108 us, 60,000 x 28 114 / 121; 170,000 x 20 208 / 232.)
@@ -852,6 +859,11 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
     const float* row_scale = agg == GP_AGG_SYM ? D.dinv_sqrt : agg == GP_AGG_MEAN ? D.dinv : nullptr;
     NoRoom no_room;
     int64_t ld_lines = 0;  // not 0: hops read copies of X and of the slabs between, rows that far apart
+    bool first_hops = false;
+    if (may_allocate && K > 0) {
+        std::lock_guard<std::mutex> lk(plan->mu);
+        first_hops = !std::exchange(plan->dev.hops_made, true);
+    }
 
     for (int32_t k = 1; k <= K; ++k) {
         HopArgs a;
@@ -878,11 +890,15 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         HopArgs cold = a;  // as it stands: implicit lists
         if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds, no_room)) != GP_OK) return st;
         const int64_t stride = line_stride((int64_t)d * es);
-        if (k == 1 && may_allocate && !split && !lds && !a.xcd_off && copy_pays(plan, d, es, ldo, stride, K)) {
+        const double gain = k == 1 && may_allocate && !split && !lds && !a.xcd_off ? copy_gains(plan, d, es, ldo, stride, K) : 0.0;
+        if (gain > 0.0) {
             bool there = false;
             {
                 std::lock_guard<std::mutex> lk(plan->mu);
-                if ((st = ensure_slabs(plan, n * stride, K > 1 ? 2 : 1, stream, true, &there)) != GP_OK) return st;
+                const int slabs = K > 1 ? 2 : 1;
+                if (!first_hops || gain > kSlabsCost || D.ping_bytes[slabs - 1] >= n * stride)
+                    st = ensure_slabs(plan, n * stride, slabs, stream, true, &there);
+                if (st != GP_OK) return st;
             }
             if (there) {
                 ld_lines = stride / es;
@@ -1013,7 +1029,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         a.gamma0 = coeff[0];
         bool lds = false;
         if ((st = attach_work_lists(plan, a, stream, true, nullptr, &lds, no_room)) != GP_OK) return st;
-        if (k == 1 && K >= 2 && !lds && !a.xcd_off && copy_pays(plan, d, es, ldx, ldp * es, 1)) {  // X too is read as the slabs are, by one hop
+        if (k == 1 && K >= 2 && !lds && !a.xcd_off && copy_gains(plan, d, es, ldx, ldp * es, 1) > 0.0) {  // X too is read as the slabs are, by one hop
             profile_begin("gp_copy_rows", stream);
             st = launch_copy_rows(X, ldx, D.ping[0], ldp, n, d, dtype, stream);
             profile_end(stream);

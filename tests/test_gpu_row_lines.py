@@ -48,13 +48,13 @@ def hop_stack(n, d, dtype, agg, K, where, copied):
             stack[0, :, :d] = X
             src = stack
         code = gp.GP_F32 if dtype == torch.float32 else gp.GP_BF16
-        for _ in range(2):  # a plan's first call, and one on what that left
+        for _ in range(2):  # a plan's first call, which makes no slabs (unless it gains a ms by them), and the next
             gp.gp_propagate(plan, src.data_ptr(), src.stride(-2), d, code, agg, K, stack.data_ptr(), ld,
                             torch.cuda.current_stream().cuda_stream)
         assert torch.equal(stack[0, :, :d], X) and not stack[:, :, d:].any()  # nothing is written past a row
         return stack
 
-    both(n, run, 2 * copied)
+    both(n, run, copied)
 
 
 # widths on either side of a line, off 16, 8 and 4 bytes; rows that several to a line hold; one wide enough for column
