@@ -441,7 +441,8 @@ gp_status gp_set_hbm_budget_bytes(int64_t bytes);
  *                     chosen per plan as about nnz / 65536 within 64 .. 1024.  Read
  *                     by gp_plan_blocks.
  *   "column_tile"     feature columns per pass of the kernel, 0 = automatic.
- *   "persistent_blocks"  workgroups of the hop kernel (0 = as many as stay resident).
+ *   "persistent_blocks"  workgroups of the hop kernel (0 = as many as stay resident, and for long
+ *                     lists up to six times as many).
  *   "lc_tile_rows"       batch rows per work item of gp_lc_forward, at most: 32 or 64 (0 = by batch size: 16, 32 or
  *                     48, the tallest there is; models of few products 32 or 64).  Results do not depend on it.
  *   "column_slices"   column slices one pass is divided into (1 .. 16; 0 = automatic).

@@ -928,14 +928,18 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
         return per_cu * prop.multiProcessorCount;
     }();
     int64_t persist = a.persistent_blocks > 0 ? a.persistent_blocks : resident;
-    // Long implicit lists get several times as many workgroups as stay resident, so that most of the list is dealt out as
-    // workgroups finish: with one round of fixed shares the launch waits for the slowest compute unit.  Whole multiples
-    // (a last round that is nearly empty costs more than it gains: 1.25 rounds are 5 - 14 % slower than one), up to six,
-    // and two records per group left for the pipeline.  One / two / three / six rounds, us: three hops of 169,343 rows x 128
-    // fp32 columns 474 / 462 / 471 / 461, x 256 1135 / 1051 / 1040 / 1032; 507,001 x 128 bf16 1045 / 1029 / 1026 / 1029;
-    // ten filter hops of 169,343 x 64 892 / 899 / 867 / 860; 2,450,000 x 100 22600 / 22570 / 22850 / 22350.  Short lists lose
-    // by it, a group's first record waiting for memory three times over: four hops of 37,123 rows x 152 (42 thousand
-    // records, ten per group) 235 / 236 / 241 / 247; 74,000 x 152 520 / 520 / 523 / 528; 150,000 x 152 1251 / 1246 / 1231 / 1223.
+    // Long implicit lists (the LDS pass's other non-zeros and streamed blocks among them) get several times as many workgroups
+    // as stay resident, so that most of the list is dealt out as workgroups finish: with one round of fixed shares the launch
+    // waits for the slowest compute unit.  Whole multiples (a last round that is nearly empty costs more than it gains: 1.25
+    // rounds are 5 - 14 % slower than one), up to six, and two records per group left for the pipeline: four to six rounds.
+    // 193 stacks and filters of 60,000 to 1,500,000 rows of mean degree 4 to 50, 3 to 640 columns, are 1.8 % faster than by
+    // one round throughout, 17 % at best (500,000 x 256 fp32, mean degree 4, 1524 -> 1267 us); seven are 1 to 3 % slower
+    // (bf16 filters; fewer than 15 records per group).  One / two / three / four / six rounds, us: two hops of 170,000 x 128
+    // fp32 columns 329 / 323 / 321 / 318 / 317, of 500,000 x 128 bf16 569 / 556 / 560 / 559 / 556, of 500,000 x 256 with hubs
+    // from LDS 2672 / 2497 / 2377 / 2528 / 2456; four filter hops of 135,000 x 64 287 / 286 / 283 / 280 / 284, of 135,000 x 74
+    // bf16 (14 records per group, the worst) 354 / 357 / 358 / 359 / 365; ten of 169,343 x 64 892 / 899 / 867 / - / 860.
+    // Short lists lose by it, a group's first record waiting for memory three times over: four hops of 37,123 rows x 152 (42
+    // thousand records, ten per group) 235 / 236 / 241 / - / 247; 74,000 x 152 520 / 520 / 523 / - / 528.
     const int64_t per_group = chunks * 8 / resident;
     if (a.persistent_blocks <= 0 && !a.xcd_off && per_group >= 8 && a.num_segs >= kManyRecords) persist *= std::min<int64_t>(6, per_group / 2);
     persist = (persist + 7) / 8 * 8;

@@ -1,5 +1,7 @@
 """Hop launches of several rounds of workgroups (long implicit lists) against one round of as many as stay resident: how
 records are dealt out changes no sum, so the bits are the same."""
+import json
+
 import numpy as np
 import pytest
 import torch
@@ -8,21 +10,36 @@ import paper_2207_12000_amd as gp
 
 pytestmark = pytest.mark.gpu
 
+MOST_RESIDENT = 256 * 8  # workgroups of four wavefronts, at most eight wavefronts on a SIMD
 
-# (rows, columns, type, operator): record counts around two, three and six rounds, with a last round that is not full,
-# for groups of 8, 16 and 32 lanes, one and two column slices, weights and none
-@pytest.mark.parametrize("n,d,dtype,agg", [(270_001, 24, torch.float32, gp.GP_AGG_SYM), (450_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
-                                           (140_003, 128, torch.float32, gp.GP_AGG_SUM), (150_007, 47, torch.float32, gp.GP_AGG_SYM)])
-def test_rounds_change_no_bit(n, d, dtype, agg):
+
+def hop_grids(call, path):
+    """The workgroups of every hop launch that call() makes."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    p.export_chrome_trace(str(path))
+    events = json.loads(path.read_text())["traceEvents"]
+    return [e["args"]["grid"][0] for e in events if "gp_hop_segments" in e.get("name", "") and "grid" in e.get("args", {})]
+
+
+# (rows, columns, type, operator): four rounds and more (eight records per group) whatever the occupancy, with a last
+# round that is not full, for groups of 8, 16 and 32 lanes, weights and none, rows read where they lie and from copies
+@pytest.mark.parametrize("n,d,dtype,agg", [(530_001, 24, torch.float32, gp.GP_AGG_SYM), (530_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
+                                           (140_003, 128, torch.float32, gp.GP_AGG_SUM), (270_007, 47, torch.float32, gp.GP_AGG_SYM)])
+def test_rounds_change_no_bit(n, d, dtype, agg, tmp_path):
     rng = np.random.default_rng(n)
     src, dst = (rng.integers(0, n, 2 * n).astype(np.int32) for _ in range(2))
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
-    stacks = []
+    stacks, grids = [], []
     for blocks in (0, 512):
         gp.gp_set_option("persistent_blocks", blocks)
         try:
             with gp.gp_plan_blocks(src, dst, n, 1 << 19, gp.GP_SYMMETRISE) as plan:
                 stacks.append(gp.propagate_tensors(plan, X, agg, 2).view(torch.int16 if dtype == torch.bfloat16 else torch.int32).cpu())
+                grids.append(hop_grids(lambda: gp.propagate_tensors(plan, X, agg, 2), tmp_path / "trace.json"))
         finally:
             gp.gp_set_option("persistent_blocks", 0)
     assert torch.equal(*stacks)
+    assert len(grids[0]) == 2 and min(grids[0]) > MOST_RESIDENT and grids[1] == [512, 512]
