@@ -33,6 +33,14 @@ from __future__ import annotations
 import numpy as np
 
 
+def _product(Z, W):
+    """Z W, with the rows of Z filled up by zeros to a whole number of the tiles that BLAS libraries take rows in: they
+    may sum what is left over of a tile in another order (OpenBLAS without AVX-512 does), and the same row would
+    then have other last bits at another place of the batch."""
+    rows = -(-len(Z) // 48) * 48
+    return (np.concatenate([Z, np.zeros((rows - len(Z), Z.shape[1]))]) @ W)[:len(Z)]
+
+
 def lc_forward(stack, ids, gamma, weights):
     """H^LC for the rows `ids` (Appendix A, LC version of GPRGNN).
 
@@ -48,8 +56,8 @@ def lc_forward(stack, ids, gamma, weights):
     for k in range(len(gamma)):
         Z = np.asarray(stack[k][ids], dtype=np.float64)
         for W in Ws[:-1]:
-            Z = np.maximum(Z @ W, 0.0)
-        H += float(gamma[k]) * (Z @ Ws[-1])
+            Z = np.maximum(_product(Z, W), 0.0)
+        H += float(gamma[k]) * _product(Z, Ws[-1])
     return H
 
 
@@ -87,8 +95,8 @@ def lc_forward_branches(stack, ids, gamma, weights, depth, comb):
             continue
         Z = np.asarray(stack[k][ids], dtype=np.float64)
         for W in Ws[:depth[k] - 1]:
-            Z = np.maximum(Z @ W, 0.0)
-        parts.append(float(gamma[k]) * (Z @ Ws[depth[k] - 1]))
+            Z = np.maximum(_product(Z, W), 0.0)
+        parts.append(float(gamma[k]) * _product(Z, Ws[depth[k] - 1]))
     if comb == COMB_CONCAT:
         return np.concatenate(parts, axis=1)
     if comb == COMB_MAX:
