@@ -10,6 +10,26 @@ import paper_2207_12000_amd as gp
 
 pytestmark = pytest.mark.gpu
 
+
+# (rows, columns, type, operator): record counts around two, three and six rounds, with a last round that is not full,
+# for groups of 8, 16 and 32 lanes, one and two column slices, weights and none
+@pytest.mark.parametrize("n,d,dtype,agg", [(270_001, 24, torch.float32, gp.GP_AGG_SYM), (450_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
+                                           (140_003, 128, torch.float32, gp.GP_AGG_SUM), (150_007, 47, torch.float32, gp.GP_AGG_SYM)])
+def test_rounds_change_no_bit(n, d, dtype, agg):
+    rng = np.random.default_rng(n)
+    src, dst = (rng.integers(0, n, 2 * n).astype(np.int32) for _ in range(2))
+    X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
+    stacks = []
+    for blocks in (0, 512):
+        gp.gp_set_option("persistent_blocks", blocks)
+        try:
+            with gp.gp_plan_blocks(src, dst, n, 1 << 19, gp.GP_SYMMETRISE) as plan:
+                stacks.append(gp.propagate_tensors(plan, X, agg, 2).view(torch.int16 if dtype == torch.bfloat16 else torch.int32).cpu())
+        finally:
+            gp.gp_set_option("persistent_blocks", 0)
+    assert torch.equal(*stacks)
+
+
 MOST_RESIDENT = 256 * 8  # workgroups of four wavefronts, at most eight wavefronts on a SIMD
 
 
@@ -28,7 +48,7 @@ def hop_grids(call, path):
 # round that is not full, for groups of 8, 16 and 32 lanes, weights and none, rows read where they lie and from copies
 @pytest.mark.parametrize("n,d,dtype,agg", [(530_001, 24, torch.float32, gp.GP_AGG_SYM), (530_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
                                            (140_003, 128, torch.float32, gp.GP_AGG_SUM), (270_007, 47, torch.float32, gp.GP_AGG_SYM)])
-def test_rounds_change_no_bit(n, d, dtype, agg, tmp_path):
+def test_four_rounds_and_more_are_made(n, d, dtype, agg, tmp_path):
     rng = np.random.default_rng(n)
     src, dst = (rng.integers(0, n, 2 * n).astype(np.int32) for _ in range(2))
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()

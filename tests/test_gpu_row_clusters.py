@@ -24,8 +24,13 @@ def graph(kind):
     rng = np.random.default_rng(19)
     if kind == "lengths":                     # short, mid and big rows at their edges; many empty ones
         n = 20_000
-        src, dst = star_rows([1, 2, 63, 64, 65, 127, 511, 512, 513, 1024, 8191, 8192, 8193, 12_287, 12_288, 12_289, 16_385, 19_000], n, rng)
+        src, dst = star_rows([1, 2, 63, 64, 65, 127, 511, 512, 513, 1024, 8191, 8192, 8193, 16_385, 19_000], n, rng)
         more = rng.integers(0, n, (2, 3000))  # some rows whose labels move on
+        return n, np.concatenate([src, more[0]]), np.concatenate([dst, more[1]]), 0
+    if kind == "table":                       # a workgroup's table, filled to three quarters, and past it
+        n = 20_000
+        src, dst = star_rows([12_287, 12_288, 12_289, 16_383, 16_384], n, rng)
+        more = rng.integers(0, n, (2, 3000))
         return n, np.concatenate([src, more[0]]), np.concatenate([dst, more[1]]), 0
     if kind == "huge":                        # rows that count in memory, more than go side by side; labels that do and do not repeat
         n, lengths = 700_001, [700_001, 300_000] + [13_000] * 300
@@ -50,7 +55,7 @@ def graph(kind):
 
 
 @pytest.mark.parametrize("planner", [0, gp.GP_PLAN_ON_DEVICE])
-@pytest.mark.parametrize("kind", ["lengths", "ties", "communities", "one", "power law", "sparse", "huge"])
+@pytest.mark.parametrize("kind", ["lengths", "ties", "communities", "one", "power law", "sparse", "table", "huge"])
 def test_the_gpus_clusters_are_the_hosts(kind, planner):
     import torch
     n, src, dst, flags = graph(kind)
