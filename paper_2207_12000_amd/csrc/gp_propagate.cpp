@@ -890,7 +890,9 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         HopArgs cold = a;  // as it stands: implicit lists
         if ((st = attach_work_lists(plan, a, stream, may_allocate, &split, &lds, no_room)) != GP_OK) return st;
         const int64_t stride = line_stride((int64_t)d * es);
-        const double gain = k == 1 && may_allocate && !split && !lds && !a.xcd_off ? copy_gains(plan, d, es, ldo, stride, K) : 0.0;
+        // (rows of two or three elements in wider slots may touch fewer lines side by side too, but the instances that store
+        // rows twice take no vectors as short as theirs)
+        const double gain = k == 1 && d >= 4 && may_allocate && !split && !lds && !a.xcd_off ? copy_gains(plan, d, es, ldo, stride, K) : 0.0;
         if (gain > 0.0) {
             bool there = false;
             {

@@ -28,9 +28,9 @@ def both(n, run, copied):
     assert copies[0] - copies[1] == copied
 
 
-def hop_stack(n, d, dtype, agg, K, where, copied):
+def hop_stack(n, d, dtype, agg, K, where, copied, ld=None):
     dtype = getattr(torch, dtype)
-    ld = d + (d % 2 * 2 if where == "padded" else 0)  # an odd stride stays odd
+    ld = ld or d + (d % 2 * 2 if where == "padded" else 0)  # an odd stride stays odd
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
 
     def run(plan):
@@ -66,6 +66,14 @@ def test_hop_stack(n, d, dtype, agg, K, where):
                                        (60_000, 9, "bfloat16"), (40_000, 33, "float32"), (20_000, 47, "float32"), (60_000, 100, "bfloat16")])
 def test_rows_that_are_read_where_they_lie(n, d, dtype):
     hop_stack(n, d, dtype, gp.GP_AGG_SUM, 2, "tensor", False)
+
+
+# rows that save lines by leaving slots that are wider than they are: from four elements on, in the shortest vectors too
+@pytest.mark.parametrize("n,d,dtype,ld,copied", [(600_000, 2, "float32", 5, False), (600_000, 3, "float32", 5, False),
+                                                 (600_000, 4, "float32", 5, True), (2_800_000, 3, "bfloat16", 10, False),
+                                                 (1_200_000, 7, "bfloat16", 7, True)])
+def test_narrow_rows_in_wider_slots(n, d, dtype, ld, copied):
+    hop_stack(n, d, dtype, gp.GP_AGG_SUM, 2, "tensor", copied, ld)
 
 
 @pytest.mark.parametrize("n,d,dtype,copied", [(80_000, 20, "float32", False), (40_000, 63, "float32", True), (20_000, 47, "bfloat16", True),
