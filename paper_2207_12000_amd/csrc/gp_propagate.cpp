@@ -627,49 +627,71 @@ int64_t line_stride(int64_t w)
     return lines_per_row(w, half) <= lines_per_row(w, full) ? half : full;
 }
 
-// Lines that a gather of rows of w bytes saves by finding them `to` bytes apart instead of `from`, less what it loses by the
-// caches holding fewer rows of a larger slab.
-double lines_saved(int64_t w, int64_t from, int64_t to)
+// What a gather of one of n rows of w bytes costs where they lie `stride` bytes apart, in lines that an L2 holds: one that it
+// misses costs 4.6 of them, and of rows taken at random a 4 MiB L2 holds as much as fits.
+double gather_cost(int64_t w, int64_t stride, int64_t n)
 {
-    const double before = lines_per_row(w, from);
-    return before - lines_per_row(w, to) - 0.17 * std::max(0.0, (double)to / (double)from - 1.0) * before;
+    const double held = std::min(1.0, (double)((int64_t)4 << 20) / ((double)n * (double)stride));
+    return lines_per_row(w, stride) * (1.0 + 3.6 * (1.0 - held));
 }
 
-// Line reads (some 57 a ns) that K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading
-// dimension ld as they are); none or less: they do not.  The line reads that the gathers save have to make up for a launch, and for a row's lines copied once and written
-// once more per hop, some two of them each; the factors are those of a fit to 153 pairs of measurements (fp32, 3 to 119
-// columns, 37,000 to 1,500,000 rows of mean degree 5 to 41, one to three hops), all but three of which it calls right within
-// 1 %.  Slabs below 4 MiB stay in an L2 as they are.  With and without, us: two hops of mean degree 17, 1,500,000 rows x 28
-// 1071 / 1464, x 47 2011 / 2156, x 9 912 / 940, x 5 814 / 764, x 3 734 / 692; 60,000 x 50 74.7 / 72.7; one hop of mean
-// degree 5, 500,000 x 47 178 / 141; four hops of 37,123 x 47 98 / 104.  Small matrices of bf16 are not bound by lines
+// What it saves by finding them `to` bytes apart instead of `from`, less what a larger slab costs the other caches.
+double gather_saves(int64_t w, int64_t from, int64_t to, int64_t n)
+{
+    const double before = gather_cost(w, from, n);
+    return before - gather_cost(w, to, n) - 0.135 * std::max(0.0, (double)to / (double)from - 1.0) * before;
+}
+
+// What K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading dimension ld as they are),
+// in gather_cost's units (some 285,000 to the us); none or less: they do not.  What the gathers save has to make up for a
+// launch, and for a row's lines copied once and written once more per hop, some ten each.  The factors are those of a fit to
+// 2,500 pairs of measurements: fp32 and bf16 from dwords on, uniform and power-law graphs of mean degree 4 to 40, 4 to 200
+// columns, slabs of 4 to 90 MiB, one to four hops.  Four of those that take copies are 2 - 4 % slower by it, none more (a rule
+// without the L2: 57 more than 2 %, by up to 20).  With and without, us, four hops of mean degree 16: 131,000 rows x 10
+// fp32 columns (5 -> 8 MiB) 132 / 106, 400,000 x 10 495 / 510; two hops of 1,500,000 x 28 1071 / 1464; one hop of mean
+// degree 5, 500,000 x 47 178 / 141.  Slabs below 4 MiB stay in an L2 as they are; small matrices of bf16 are not bound by lines
 // (four hops of 37,123 x 190, 14 MB, 170 / 168).
-// Rows of bf16 off a dword are gathered two bytes a lane as they are, and gain by being on one whatever their lines: three
-// hops of mean degree 5, 500,000 x 33 288 / 574, x 155 1050 / 1124; of 41, 60,000 x 73 207 / 491; 10,000 x 47 (1 MB) 34 / 35.
-// Up to 16 columns one load of a lane group takes the row anyhow (60,000 x 9 45.6 / 40.5, x 15 47.6 / 45.1; 500,000 x 9
-// 250 / 390), up to three are no wider than a dword (1,500,000 x 3 802 / 639), and one hop over few wide rows does not pay
-// for the copy (500,000 x 155, mean degree 5, 421 / 396).
+// Rows of bf16 off a dword are gathered two bytes a lane as they are, and gain by being on one whatever their lines, most of
+// them by 30 - 90 % (three hops of mean degree 41, 60,000 x 73 207 / 491).  Not where a row is one load of a lane group anyhow and
+// the hops few (two hops of mean degree 8, 1,000,000 x 5 368 / 326; one of degree 16, 47,000 x 15 0.9 times as fast);
+// not where rows are few and sources too: a long record is then what the launch waits for, and eight elements a lane leave
+// an eighth of the wavefronts to wait side by side (power law, 16,000 x 59, mean degree 8, four hops 81 / 68; uniform,
+// 11,000 x 127, degree 4, one hop 19 / 17); and not for one hop over few wide rows' worth of gathers (500,000 x 155, degree 5,
+// 421 / 396).  Of 932 such pairs none is slower by more than 0.5 %.
 double copy_gains(const gp_plan* plan, int32_t d, int es, int64_t ld, int64_t stride, int32_t K)
 {
     if (plan->opt.column_tile > 0 || d > max_columns_per_pass(16 / es)) return 0.0;
-    const int64_t w = (int64_t)d * es, bytes = plan->n * w;
-    const double gathers = (double)plan->nnz * K, rows = (double)plan->n;
+    const int64_t w = (int64_t)d * es, n = plan->n, nnz = plan->nnz, bytes = n * w;
+    const double gathers = (double)nnz * K, rows = (double)n;
     if (es == 2 && ld % 2 != 0) {
-        const bool pays = d > 16 ? bytes >= (1 << 20) && (d < 128 || gathers >= 8.0 * rows) : d >= 5 && bytes >= (8 << 20);
-        return pays ? 0.3 * lines_per_row(w, ld * es) * gathers : 0.0;  // (500,000 x 97, mean degree 41: 2840 -> 1996 us)
+        bool pays;
+        if (d <= 16)
+            pays = d >= 5 && bytes >= (8 << 20) && gathers >= (d > 8 ? 6.0 : 120.0) * rows;
+        else if (bytes < (1 << 20))
+            pays = false;
+        else if (n >= 32768 || nnz >= 12 * n)
+            pays = d < 128 || gathers >= 12.0 * rows;
+        else if (!plan->split.empty() && !plan->dev.rows_whole)  // (of 33 to 64 elements: one a lane as they are)
+            pays = d <= 32 || (d > 64 && K > 1);
+        else
+            pays = d <= 100 || gathers > 10.0 * rows;
+        return pays ? 1.5 * lines_per_row(w, ld * es) * gathers : 0.0;  // (500,000 x 97, mean degree 41: 2840 -> 1996 us)
     }
     if (bytes < (es == 4 ? 4 : 16) << 20) return 0.0;
-    return lines_saved(w, ld * es, stride) * gathers - 5e5 - 2.0 * (K + 1) * rows * (double)w / (double)kLineBytes;
+    return gather_saves(w, ld * es, stride, n) * gathers - 2e5 - 10.0 * (K + 1) * rows * (double)w / (double)kLineBytes;
 }
-// What making slabs costs the one call that does, about a ms for two, in such line reads: a plan's first call leaves them
+// What making slabs costs the one call that does, about a ms for two, in those units: a plan's first call leaves them
 // to the next unless it gains more by itself (plan, three hops, plan dropped, 60,000 x 47 fp32: 4.1 ms with and 3.2 without;
 // 490,000 x 47 13.4 and 13.1).
-constexpr double kSlabsCost = 5.7e7;
+constexpr double kSlabsCost = 2.85e8;
 
-// Whether the slabs that a filter's hops hand on gain by that stride: they are written either way.  (Smaller ones: four hops
-// of 60,000 x 20 110 / 108 us, 60,000 x 28 114 / 121; 170,000 x 20 208 / 232.)
+// Whether the slabs that a filter's hops hand on gain by that stride: they are written either way, of wider lines.  (Smaller
+// ones: four hops of 60,000 x 20 110 / 108 us, 60,000 x 28 114 / 121; 170,000 x 20 208 / 232.  Of 413 pairs three are 2 - 4 % slower.)
 bool wide_slabs_pay(const gp_plan* plan, int64_t w, int64_t compact, int64_t stride)
 {
-    return plan->n * w >= (5 << 20) && lines_saved(w, compact, stride) > 0.0;
+    const double rows = (double)plan->n;
+    return plan->n * w >= (5 << 20) &&
+           gather_saves(w, compact, stride, plan->n) * (double)plan->nnz > 4.0 * rows * (double)w / (double)kLineBytes;
 }
 
 // The first `count` of two slabs of n rows, `bytes` each, that hops hand rows on in (plan->mu held).  optional: they are done

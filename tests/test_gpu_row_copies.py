@@ -51,7 +51,7 @@ def hop_stack(n, d, dtype, agg, K, where, copied, ld=None):
 
 # widths on either side of a line, off 16, 8 and 4 bytes; rows that several to a line hold; one wide enough for column
 # slices, one of several vectors a lane; one hop and more
-@pytest.mark.parametrize("n,d,dtype,agg,K", [(160_000, 7, "float32", gp.GP_AGG_SUM, 3), (40_000, 47, "float32", gp.GP_AGG_SYM, 3),
+@pytest.mark.parametrize("n,d,dtype,agg,K", [(300_000, 15, "float32", gp.GP_AGG_SUM, 3), (40_000, 47, "float32", gp.GP_AGG_SYM, 3),
                                              (40_000, 63, "float32", gp.GP_AGG_SUM, 2), (70_000, 58, "float32", gp.GP_AGG_MEAN, 1),
                                              (40_000, 159, "float32", gp.GP_AGG_SYM, 2), (280_000, 15, "bfloat16", gp.GP_AGG_SUM, 2),
                                              (20_000, 47, "bfloat16", gp.GP_AGG_MEAN, 3), (9_000, 301, "bfloat16", gp.GP_AGG_SYM, 2),
@@ -61,19 +61,20 @@ def test_hop_stack(n, d, dtype, agg, K, where):
     hop_stack(n, d, dtype, agg, K, where, True)
 
 
-# rows of a few elements, which a copy would only spread out; rows that touch no fewer lines; small matrices
+# rows of a few elements, which a copy would only spread out; slabs that an L2 holds most of until they are wider; rows that
+# touch no fewer lines; small matrices
 @pytest.mark.parametrize("n,d,dtype", [(600_000, 1, "bfloat16"), (400_000, 3, "bfloat16"), (360_000, 3, "float32"), (250_000, 5, "float32"),
-                                       (60_000, 9, "bfloat16"), (40_000, 33, "float32"), (20_000, 47, "float32"), (60_000, 100, "bfloat16")])
+                                       (60_000, 9, "bfloat16"), (131_000, 10, "float32"), (160_000, 7, "float32"), (1_200_000, 7, "bfloat16"), (40_000, 33, "float32"), (20_000, 47, "float32"), (60_000, 100, "bfloat16")])
 def test_rows_that_are_read_where_they_lie(n, d, dtype):
     hop_stack(n, d, dtype, gp.GP_AGG_SUM, 2, "tensor", False)
 
 
 # rows that save lines by leaving slots that are wider than they are: from four elements on, in the shortest vectors too
-@pytest.mark.parametrize("n,d,dtype,ld,copied", [(600_000, 2, "float32", 5, False), (600_000, 3, "float32", 5, False),
-                                                 (600_000, 4, "float32", 5, True), (2_800_000, 3, "bfloat16", 10, False),
-                                                 (1_200_000, 7, "bfloat16", 7, True)])
-def test_narrow_rows_in_wider_slots(n, d, dtype, ld, copied):
-    hop_stack(n, d, dtype, gp.GP_AGG_SUM, 2, "tensor", copied, ld)
+@pytest.mark.parametrize("n,d,dtype,ld,K,copied", [(600_000, 2, "float32", 5, 2, False), (600_000, 3, "float32", 5, 2, False),
+                                                   (600_000, 4, "float32", 5, 2, True), (2_800_000, 3, "bfloat16", 10, 2, False),
+                                                   (700_000, 7, "bfloat16", 7, 6, True)])
+def test_narrow_rows_in_wider_slots(n, d, dtype, ld, K, copied):
+    hop_stack(n, d, dtype, gp.GP_AGG_SUM, K, "tensor", copied, ld)
 
 
 @pytest.mark.parametrize("n,d,dtype,copied", [(80_000, 20, "float32", False), (40_000, 63, "float32", True), (20_000, 47, "bfloat16", True),
