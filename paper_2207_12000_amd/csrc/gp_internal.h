@@ -415,6 +415,7 @@ constexpr int kHopCtrlWords = 16;
 struct HopArgs {
     const Segment* segs;    // DEVICE
     int64_t num_segs;
+    int64_t nnz = 0;        // the records' non-zeros, where the caller knows them
     const int32_t* col;     // DEVICE; entry e of the sorted list is col[e - col_base]
     int64_t col_base;
     const float* edge_w;    // DEVICE: nullptr (weight 1), or an n-vector gathered by column id,

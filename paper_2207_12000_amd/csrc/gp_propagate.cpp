@@ -843,6 +843,7 @@ gp_status lds_hop(const gp_plan* plan, HopArgs& a, gp_agg agg, hipStream_t strea
     if (st != GP_OK) return st;
     a.segs = D.lds_cold;
     a.num_segs = h.num_pos;
+    a.nnz = 0;
     a.col = D.lds_col;
     if (a.edge_w) {  // weights by column id: the per-edge array follows the plan's column order
         a.edge_w = D.dinv_sqrt;
@@ -891,6 +892,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
         HopArgs a;
         a.segs = D.segs;
         a.num_segs = D.num_segs;
+        a.nnz = plan->nnz;
         a.col = D.col;
         a.col_base = 0;
         a.edge_w = edge_w;
@@ -952,6 +954,7 @@ gp_status resident_hops(const gp_plan* plan, const void* X, int64_t ldx, int32_t
             a.carry_ld = cold.carry_ld = D.split_carry_ld;
             cold.segs = D.split_cold;
             cold.num_segs = D.split_num_cold;
+            cold.nnz = 0;
             if (cold.num_segs > 0 && (st = hop_passes(cold, stream)) != GP_OK) return st;
         }
         if (lds) {
@@ -1029,6 +1032,7 @@ gp_status propagate_combine(const gp_plan* plan, const void* X, int64_t ldx, int
         HopArgs a;
         a.segs = D.segs;
         a.num_segs = D.num_segs;
+        a.nnz = plan->nnz;
         a.col = D.col;
         a.col_base = 0;
         a.edge_w = edge_w;

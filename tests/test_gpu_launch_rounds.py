@@ -44,13 +44,10 @@ def hop_grids(call, path):
     return [e["args"]["grid"][0] for e in events if "gp_hop_segments" in e.get("name", "") and "grid" in e.get("args", {})]
 
 
-# (rows, columns, type, operator): four rounds and more (eight records per group) whatever the occupancy, with a last
-# round that is not full, for groups of 8, 16 and 32 lanes, weights and none, rows read where they lie and from copies
-@pytest.mark.parametrize("n,d,dtype,agg", [(530_001, 24, torch.float32, gp.GP_AGG_SYM), (530_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
-                                           (140_003, 128, torch.float32, gp.GP_AGG_SUM), (270_007, 47, torch.float32, gp.GP_AGG_SYM)])
-def test_four_rounds_and_more_are_made(n, d, dtype, agg, tmp_path):
+def both_ways(n, pairs, d, dtype, agg, path):
+    """The stack with workgroups as the library has them and with 512, and the grids of the first's hop launches."""
     rng = np.random.default_rng(n)
-    src, dst = (rng.integers(0, n, 2 * n).astype(np.int32) for _ in range(2))
+    src, dst = (rng.integers(0, n, pairs).astype(np.int32) for _ in range(2))
     X = torch.randn(n, d, generator=torch.Generator().manual_seed(d)).to(dtype).cuda()
     stacks, grids = [], []
     for blocks in (0, 512):
@@ -58,8 +55,22 @@ def test_four_rounds_and_more_are_made(n, d, dtype, agg, tmp_path):
         try:
             with gp.gp_plan_blocks(src, dst, n, 1 << 19, gp.GP_SYMMETRISE) as plan:
                 stacks.append(gp.propagate_tensors(plan, X, agg, 2).view(torch.int16 if dtype == torch.bfloat16 else torch.int32).cpu())
-                grids.append(hop_grids(lambda: gp.propagate_tensors(plan, X, agg, 2), tmp_path / "trace.json"))
+                grids.append(hop_grids(lambda: gp.propagate_tensors(plan, X, agg, 2), path))
         finally:
             gp.gp_set_option("persistent_blocks", 0)
-    assert torch.equal(*stacks)
-    assert len(grids[0]) == 2 and min(grids[0]) > MOST_RESIDENT and grids[1] == [512, 512]
+    assert torch.equal(*stacks) and len(grids[0]) == 2 and grids[1] == [512, 512]
+    return grids[0]
+
+
+# (rows, columns, type, operator): four rounds and more (eight records per group, of twenty non-zeros) whatever the occupancy,
+# with a last round that is not full, for groups of 8, 16 and 32 lanes, weights and none, rows read where they lie and from copies
+@pytest.mark.parametrize("n,d,dtype,agg", [(530_001, 24, torch.float32, gp.GP_AGG_SYM), (530_003, 20, torch.bfloat16, gp.GP_AGG_MEAN),
+                                           (140_003, 128, torch.float32, gp.GP_AGG_SUM), (270_007, 47, torch.float32, gp.GP_AGG_SYM)])
+def test_four_rounds_and_more_are_made(n, d, dtype, agg, tmp_path):
+    assert min(both_ways(n, 10 * n, d, dtype, agg, tmp_path / "trace.json")) > MOST_RESIDENT
+
+
+# records of two to four non-zeros, and rows of 9 to 16 bf16 elements off a dword: one round
+@pytest.mark.parametrize("n,mean,d,dtype", [(600_001, 2, 16, torch.float32), (530_001, 4, 24, torch.bfloat16), (300_001, 16, 9, torch.bfloat16)])
+def test_short_records_get_one_round(n, mean, d, dtype, tmp_path):
+    assert max(both_ways(n, mean * n // 2, d, dtype, gp.GP_AGG_SUM, tmp_path / "trace.json")) <= MOST_RESIDENT
