@@ -940,10 +940,10 @@ gp_status launch_hop_t(const HopArgs& a, hipStream_t stream)
     // bf16 (14 records per group, the worst) 354 / 357 / 358 / 359 / 365; ten of 169,343 x 64 892 / 899 / 867 / - / 860.
     // Short lists lose by it, a group's first record waiting for memory three times over: four hops of 37,123 rows x 152 (42
     // thousand records, ten per group) 235 / 236 / 241 / - / 247; 74,000 x 152 520 / 520 / 523 / - / 528.
-    // So do short records, of fewer than 80 non-zeros per group together, and bf16 rows of 9 to 16 elements off a dword, one
-    // load of a group each (two hops of 291,000 x 9, mean degree 4, 76 / 87; 131,000 - 1,450,000 of them, degree 2 to 16, 1 - 15 %
-    // slower throughout; 2,600 pairs otherwise, 1 to 130 columns, with that line at most 4 % in classes of ten and more).  Wider rows
-    // off a dword gain 5 - 50 % whatever their degree.
+    // So do records of fewer than 80 non-zeros per group together (2,600 pairs, 131,000 to 1,450,000 rows of mean degree 2 to 16, 1 to
+    // 130 columns: below that line 2 - 5 % slower on average and 13 at worst, above it 1 - 5 % faster), and at any degree bf16 rows
+    // of 9 to 16 elements off a dword, one two-byte load of a group each (two hops of 291,000 x 9, mean degree 4, 76 / 87; 400 pairs 1 - 15 %
+    // slower).  Wider rows off a dword gain 5 - 50 % whatever their degree.
     const int64_t per_group = chunks * 8 / resident;
     const bool by_two_bytes = sizeof(T) == 2 && VEC == 1;
     const bool worth_rounds = by_two_bytes && G >= 16 ? G > 16 : a.nnz == 0 || per_group * a.nnz >= 80 * a.num_segs;

@@ -645,9 +645,9 @@ double gather_saves(int64_t w, int64_t from, int64_t to, int64_t n)
 // What K hops over rows of d elements gain by reading copies of them `stride` bytes apart (leading dimension ld as they are),
 // in gather_cost's units (some 285,000 to the us); none or less: they do not.  What the gathers save has to make up for a
 // launch, and for a row's lines copied once and written once more per hop, some ten each.  The factors are those of a fit to
-// 2,500 pairs of measurements: fp32 and bf16 from dwords on, uniform and power-law graphs of mean degree 4 to 40, 4 to 200
-// columns, slabs of 4 to 90 MiB, one to four hops.  Four of those that take copies are 2 - 4 % slower by it, none more (a rule
-// without the L2: 57 more than 2 %, by up to 20).  With and without, us, four hops of mean degree 16: 131,000 rows x 10
+// 3,036 pairs of measurements: fp32 and bf16 from dwords on, uniform and power-law graphs of mean degree 4 to 40, 4 to 200
+// columns, slabs of 1 to 90 MiB, one to four hops.  Eight of them are 2 - 4 % slower by the copies it makes, none more (by a rule
+// without the L2 63 are, by up to 20).  With and without, us, four hops of mean degree 16: 131,000 rows x 10
 // fp32 columns (5 -> 8 MiB) 132 / 106, 400,000 x 10 495 / 510; two hops of 1,500,000 x 28 1071 / 1464; one hop of mean
 // degree 5, 500,000 x 47 178 / 141.  Slabs below 4 MiB stay in an L2 as they are; small matrices of bf16 are not bound by lines
 // (four hops of 37,123 x 190, 14 MB, 170 / 168).
